@@ -573,7 +573,7 @@ pm_status ensure_phase_scratch(pm_mesh* m) {
   TRY(ensure(m, m->sflag, V));
   TRY(ensure(m, m->spos, V));
   TRY(ensure(m, m->spart, scan_partials_needed(V) + 2));
-  // staging for the rows past the register path (more than 32 candidates):
+  // staging for the rows past the wavefront path (more than 64 candidates):
   // 4 ids per candidate; a round that runs out is redone from a row rebuild
   // with twice the staging
   size_t stage = (size_t)(m->stage_scale * m->headroom / 3.0 * (4.0 * T + 4.0 * V)) +

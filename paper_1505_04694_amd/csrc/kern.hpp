@@ -232,7 +232,7 @@ struct Commit {
   // absorbs without reading its neighbours' records
   uint64_t* tk;
   int4* tgt;
-  int* stage;      // staging for rows past the register paths
+  int* stage;      // staging for rows past the wavefront path
   int64_t stage_cap;
   int* touched;    // small rounds: every row rebuilt, for the list-based selection (else null)
   int touched_cap;

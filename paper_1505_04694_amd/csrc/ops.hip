@@ -855,149 +855,45 @@ void flip_class(const Store& st, const int* list, int n, OpArgs a, Commit cm, in
 }
 
 // ---- deferred update: commit ------------------------------------------------------------------
-// Each claimed row is rebuilt once, by the owner's thread, from its candidate
+// Each claimed row is rebuilt once, by its owner's lane group, from its candidate
 // elements: the old NE(x), all of NE(w) for a neighbour w collapsed onto x,
 // and the two elements of every committed flip around x. NE(x) becomes the
 // sorted candidates that are live and hold x (the canonical order); NN(x) is
 // then the set of the other vertices of those elements.
 
 // the candidates of row x that are live and hold x (possibly repeated),
-// written to dst[k * stride] for k < lim; returns how many there are. A class
+// written to dst[k] when dst is given; returns how many there are. A class
 // holds one kind of operation: F, flips (records (epoch, t1, t2, 0)), else
 // collapses (records (epoch, -(u+1), ne_off, ne_cnt), the member's NE row).
-// Rows of up to kCandB entries are gathered level by level, each level's
-// loads issued together: NE(x), NN(x) and x's own record; then the elements
-// of NE(x) and the neighbours' records; then what those records name (an
-// absorbed NE row, then its elements; or each flip's two elements). Element
-// and record loads take index 0 for an empty slot, so that no load waits on
-// a branch. Longer rows go through the same steps B entries at a time.
-// Filtering here keeps the candidate count at the new row's size (a collapse
-// target's old row and the absorbed row share only the two elements that die).
-constexpr int kCandB = 8;  // row entries per batch (two 16-byte loads)
+// Only the general path takes this loop, one entry after another, so that the
+// commit kernels keep their registers for the lane groups.
 __device__ __forceinline__ bool keeps(const Elem& e, int x) { return e.w && holds(e, x); }
 
 template <bool F>
-__device__ __forceinline__ int row_candidates(const Store& st, const Commit& cm, int x, Hdr h, int* dst, int stride,
-                                              int lim) {
-  constexpr int B = kCandB;
+__device__ __forceinline__ int row_candidates(const Store& st, const Commit& cm, int x, Hdr h, int* dst) {
   int n = 0;
   auto put = [&](int t) {
-    if (n < lim) dst[n * stride] = t;
-    ++n;
-  };
-  // the elements t[0 .. B) (t < 0: none) that are live and hold x
-  auto put_live = [&](const int (&t)[B]) {
-    Elem e[B];
-#pragma unroll
-    for (int q = 0; q < B; ++q) e[q] = st.tri[max(t[q], 0)];
-#pragma unroll
-    for (int q = 0; q < B; ++q)
-      if (t[q] >= 0 && keeps(e[q], x)) put(t[q]);
-  };
-  // NE(w) of a neighbour w collapsed onto x
-  auto absorb = [&](int z, int cnt) {
-    for (int k0 = 0; k0 < cnt; k0 += B) {
-      int t[B];
-      row8(st.ne, z + k0, cnt - k0, t);
-      put_live(t);
+    if (keeps(st.tri[t], x)) {
+      if (dst) dst[n] = t;
+      ++n;
     }
   };
-  if (!F) {
-    // collapses onto x: their count (this epoch's, else none) and the last
-    // one's NE range
-    uint64_t tk = cm.tk[x];
-    int4 tg = cm.tgt[x];
-    int nt = (uint32_t)(tk >> 32) == (uint32_t)cm.epoch ? (int)(uint32_t)tk : 0;
-    if (h.w <= B && (nt == 0 || (nt == 1 && tg.z <= B))) {
-      // the entries of NE(x) and of the absorbed row side by side, then the
-      // elements of each
-      int t[B], u[B];
-      row8(st.ne, h.z, h.w, t);
-      row8(st.ne, tg.y, nt == 1 ? tg.z : 0, u);
-      put_live(t);
-      if (nt == 1) put_live(u);
-      return n;
-    }
-    absorb(h.z, h.w);
-    if (nt == 1) {
-      absorb(tg.y, tg.z);
-    } else if (nt > 1) {
-      // several members collapsed onto x: their ranges, from their records
-      for (int j = 0; j < h.y; ++j) {
-        int4 r = cm.ops[st.nn[h.x + j]];
-        if (r.x == cm.epoch && r.y == -x - 1) absorb(r.z, r.w);
+  // NE(x) (j < 0), then what each neighbour's record of this epoch hands over
+#pragma unroll 1
+  for (int j = -1; j < h.y; ++j) {
+    int o = h.z, c = h.w;
+    if (j >= 0) {
+      int4 r = cm.ops[st.nn[h.x + j]];
+      bool from = r.x == cm.epoch && (F ? r.y >= 0 : r.y == -x - 1);
+      if (F && from) {
+        put(r.y);
+        put(r.z);
       }
+      o = r.z;
+      c = from && !F ? r.w : 0;
     }
-    return n;
-  }
-  // flips: NE(x), and the two elements of a flip whose far vertex x is,
-  // from x's record; x the far vertex of several flips: the two elements of
-  // every committed flip around x (x's own and its neighbours'), four
-  // neighbour records at a time
-  uint64_t tkf = cm.tk[x];
-  int4 tgf = cm.tgt[x];
-  int ntf = (uint32_t)(tkf >> 32) == (uint32_t)cm.epoch ? (int)(uint32_t)tkf : 0;
-  if (ntf <= 1) {
-    int t[B], u[B];
-    row8(st.ne, h.z, h.w, t);
-#pragma unroll
-    for (int q = 0; q < B; ++q) u[q] = -1;
-    if (ntf == 1) {
-      u[0] = tgf.x;
-      u[1] = tgf.y;
-    }
-    put_live(t);
-    if (ntf == 1) put_live(u);
-    for (int k0 = B; k0 < h.w; k0 += B) {
-      row8(st.ne, h.z + k0, h.w - k0, t);
-      put_live(t);
-    }
-    return n;
-  }
-  int4 rx = cm.ops[x];
-  auto scan_flips = [&](const int (&w)[B]) {
-#pragma unroll
-    for (int q0 = 0; q0 < B; q0 += B / 2) {
-      int4 r[B / 2];
-#pragma unroll
-      for (int q = 0; q < B / 2; ++q) r[q] = cm.ops[max(w[q0 + q], 0)];
-      int f0[B / 2], f1[B / 2];
-#pragma unroll
-      for (int q = 0; q < B / 2; ++q) {
-        bool c = w[q0 + q] >= 0 && r[q].x == cm.epoch && r[q].y >= 0;
-        f0[q] = c ? r[q].y : -1;
-        f1[q] = c ? r[q].z : -1;
-      }
-      Elem e0[B / 2], e1[B / 2];
-#pragma unroll
-      for (int q = 0; q < B / 2; ++q) e0[q] = st.tri[max(f0[q], 0)];
-#pragma unroll
-      for (int q = 0; q < B / 2; ++q) e1[q] = st.tri[max(f1[q], 0)];
-#pragma unroll
-      for (int q = 0; q < B / 2; ++q) {
-        if (f0[q] >= 0 && keeps(e0[q], x)) put(f0[q]);
-        if (f1[q] >= 0 && keeps(e1[q], x)) put(f1[q]);
-      }
-    }
-  };
-  if (h.w <= B && h.y <= B) {
-    int t[B], w[B];
-    row8(st.ne, h.z, h.w, t);
-    row8(st.nn, h.x, h.y, w);
-    put_live(t);
-    scan_flips(w);
-  } else {
-    absorb(h.z, h.w);
-    for (int j0 = 0; j0 < h.y; j0 += B) {
-      int w[B];
-      row8(st.nn, h.x + j0, h.y - j0, w);
-      scan_flips(w);
-    }
-  }
-  if (rx.x == cm.epoch && rx.y >= 0) {
-    Elem a = st.tri[rx.y], b = st.tri[rx.z];
-    if (keeps(a, x)) put(rx.y);
-    if (keeps(b, x)) put(rx.z);
+#pragma unroll 1
+    for (int k = 0; k < c; ++k) put(st.ne[o + k]);
   }
   return n;
 }
@@ -1047,7 +943,7 @@ template <bool F>
 __device__ __forceinline__ void rebuild_staged(const Store& st, const Commit& cm, int x, int* ctr) {
   Hdr h = st.hdr[x];
   int2 cp = st.cap[x];
-  int tot = row_candidates<F>(st, cm, x, h, nullptr, 0, 0);
+  int tot = row_candidates<F>(st, cm, x, h, nullptr);
   int64_t need = 4 * (int64_t)tot + 4;
   int base = atomicAdd(&ctr[C_STAGE], (int)need);
   if ((int64_t)base + need > cm.stage_cap) {
@@ -1055,7 +951,7 @@ __device__ __forceinline__ void rebuild_staged(const Store& st, const Commit& cm
     return;
   }
   int* s = cm.stage + base;
-  row_candidates<F>(st, cm, x, h, s, 1, tot);
+  row_candidates<F>(st, cm, x, h, s);
   int m = tot;
   sort_unique(s, m);
   int* q = s + tot;
@@ -1074,224 +970,234 @@ __device__ __forceinline__ void rebuild_staged(const Store& st, const Commit& cm
   st.cap[x] = make_int2(nn_cap, ne_cap);
 }
 
-// the three vertex ids of element t (its live flag not loaded)
-__device__ __forceinline__ Elem tri_ids(const Store& st, int t) {
-  const int* p = (const int*)(st.tri + t);
-  return make_int4(p[0], p[1], p[2], 1);
+// lane l's value of another lane of its 16-lane row, rotated by K (1 .. 15)
+template <int K>
+__device__ __forceinline__ int ror16(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, 0x120 + K, 0xF, 0xF, false);
 }
-
-constexpr int kRegSmall = 16;  // rows up to this many candidates: the small register path
-constexpr int kRegRow = 32;    // up to this many: the large register path
-
-// wave-wide exclusive offsets into two counters, both atomics in flight together
-__device__ __forceinline__ int2 wave_add2(int* c0, int a0, int* c1, int a1) {
-  int lane = __lane_id();
-  int i0 = a0, i1 = a1;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int o0 = __shfl_up(i0, d), o1 = __shfl_up(i1, d);
-    if (lane >= d) {
-      i0 += o0;
-      i1 += o1;
+// f(o) with the value v of every other lane of this lane's group of G lanes
+// holding an item (lanes 0 .. n - 1; the others are passed or not, and hold a
+// value that f ignores). G = 16: rotations inside the row of lanes, one move
+// each; G = 64: one lane read per item, n the same for the whole wavefront.
+template <int G, int K = 1, class Fn>
+__device__ __forceinline__ void each_other(int v, int n, Fn&& f) {
+  if constexpr (G == 16) {
+    if constexpr (K < 16) {
+      f(ror16<K>(v));
+      each_other<G, K + 1>(v, n, f);
     }
+  } else {
+    n = __builtin_amdgcn_readfirstlane(n);
+    for (int k = 0; k < n; ++k) f(__builtin_amdgcn_readlane(v, k));
   }
-  int b0 = 0, b1 = 0;
-  if (lane == kWave - 1) {
-    if (i0 > 0) b0 = atomicAdd(c0, i0);
-    if (i1 > 0) b1 = atomicAdd(c1, i1);
-  }
-  b0 = __shfl(b0, kWave - 1);
-  b1 = __shfl(b1, kWave - 1);
-  return make_int2(b0 + i0 - a0, b1 + i1 - a1);
 }
 
-// Register path for rows of at most N candidates, staged in this thread's
-// LDS column (x < 0: idle lane). Every lane of the wavefront makes this call
-// together, so fresh pool space is handed out with one atomic per wavefront
-// and pool. NE(x) = the sorted, distinct candidates that are live and hold
-// x, written back to the column; NN(x) = the sorted "next" vertices of those
-// elements plus the one "previous" vertex that is no "next" (x on the
-// boundary). Returns true for a row whose elements do not form a disk or a
-// half-disk around x; such a row is left to the general path.
-template <int N, int S>
-__device__ __forceinline__ bool rebuild_reg(const Store& st, const Commit& cm, int x, Hdr h, int2 cp, int tot, int* col,
-                                            int* ctr) {
+// Rebuild row x on a group of G lanes (16, or a whole wavefront for the rows
+// that do not fit 16): x is the group's, negative for an idle group. Lane l
+// takes the l-th entry of the old NE(x) and of the row x absorbs, then those
+// two elements; the candidates that are live and hold x are packed to the
+// group's LDS slots (3 G ints: id, next vertex, previous vertex), one per
+// lane, and each lane counts the smaller ones for its place in the sorted
+// row. NE(x) = those ids; NN(x) = their "next" vertices plus the one
+// "previous" vertex that is no next (x on the boundary). An element reaches
+// a row twice only in a flip (once from NE(x), once from the record): the
+// record's is dropped.
+// A row that holds more than G of anything goes to the block's queue bq (G =
+// 16, each queued row then takes a wavefront), or to the general path; so do
+// rows whose elements form no disk or half-disk around x.
+// What bounds it: a chain of four dependent gathers (header and records;
+// row entries; elements; stores), about 19 cache lines a row.
+// One thread per row read the elements twice and wrote the rows entry by
+// entry, 36 lines a row, and sorted in registers (96 of them): the commits of
+// a 33 x 33 adaptation took 1.72 ms so and take 0.77, the member-driven ones
+// of the 2049 x 2049 step 34 us a launch and 17. The largest vertex-order
+// launches (1.3 million collapses) take 550 us either way.
+template <bool F, int G>
+__device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm, int x, int* slots, int* ctr, int* bq,
+                                              int* bqn, int& rows) {
+  int lane = __lane_id(), l = lane & (G - 1), gb = lane & ~(G - 1);
+  uint64_t gm = G == 64 ? ~0ull : (1ull << G) - 1ull;
+  uint64_t below = (1ull << l) - 1ull;
+  auto gballot = [&](bool p) { return (__ballot(p) >> gb) & gm; };
   bool act = x >= 0;
-  int m = 0;
-  {
-    int c[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      int t = INT_MAX;
-      if (act && k < tot) t = col[k * S];
-      c[k] = t;
-    }
-    bitonic<N>(c);
-    int prev = INT_MAX;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      int t = c[k];
-      if (t != INT_MAX && t != prev) col[(m++) * S] = t;
-      prev = t;
-    }
+  int xs = max(x, 0);
+  Hdr h = st.hdr[xs];
+  int2 cp = st.cap[xs];
+  uint64_t tk = cm.tk[xs];
+  int4 tg = cm.tgt[xs];
+  // members that hand something over to x in this epoch
+  int nt = (uint32_t)(tk >> 32) == (uint32_t)cm.epoch ? (int)(uint32_t)tk : 0;
+  bool fits = act && h.w <= G && (nt <= 1 || h.y <= G) && (F || nt != 1 || tg.z <= G);
+  int t0 = -1, t1 = -1;
+  if (fits && l < h.w) t0 = st.ne[h.z + l];
+  if (fits && nt == 1) {
+    if (F) t1 = l == 0 ? tg.x : (l == 1 ? tg.y : -1);
+    else if (l < tg.z) t1 = st.ne[tg.y + l];
   }
-  // next vertex of x in each element (and, for the small path, the previous
-  // one from the same load; the large path loads the elements again rather
-  // than hold both arrays)
-  constexpr bool kBoth = N <= kRegSmall;
-  int nx[N], pv[kBoth ? N : 1];
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    int t = k < m ? col[k * S] : -1;
-    Elem e = tri_ids(st, max(t, 0));
-    int sl = slot_of(e, x);
-    nx[k] = t >= 0 ? at(e, sl == 2 ? 0 : sl + 1) : INT_MAX;
-    if constexpr (kBoth) pv[k] = t >= 0 ? at(e, sl == 0 ? 2 : sl - 1) : -1;
-    // the large path keeps at most eight element loads in flight
-    if constexpr (!kBoth)
-      if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
-  }
-  bitonic<N>(nx);
-  // previous vertices that are no next (one for a boundary vertex; more:
-  // the elements form no disk or half-disk, and the general path decides)
-  int extra = INT_MAX, nextra = 0;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    if (k < m) {
-      int b;
-      if constexpr (kBoth) {
-        b = pv[k];
-      } else {
-        Elem e = tri_ids(st, col[k * S]);
-        int sl = slot_of(e, x);
-        b = at(e, sl == 0 ? 2 : sl - 1);
+  Elem e0 = st.tri[max(t0, 0)], e1 = st.tri[max(t1, 0)];
+  int n = 0;
+  auto add = [&](bool k, int t, const Elem& e) {
+    uint64_t b = gballot(k);
+    int pos = n + __popcll(b & below);
+    if (k && pos < G) {
+      int sl = slot_of(e, x);
+      slots[pos] = t;
+      slots[G + pos] = at(e, sl == 2 ? 0 : sl + 1);
+      slots[2 * G + pos] = at(e, sl == 0 ? 2 : sl - 1);
+    }
+    n += __popcll(b);
+  };
+  // a flip's element t (in lanes 0 and 1) that NE(x) holds already (every
+  // lane of the group makes this call: it votes)
+  auto known = [&](int t) {
+    int a = __shfl(t, gb), b = __shfl(t, gb + 1);
+    uint64_t ka = gballot(t0 >= 0 && t0 == a), kb = gballot(t0 >= 0 && t0 == b);
+    return l == 0 ? ka != 0 : kb != 0;
+  };
+  add(t0 >= 0 && keeps(e0, x), t0, e0);
+  if (nt == 1) {
+    bool old = F ? known(t1) : false;
+    add(t1 >= 0 && !old && keeps(e1, x), t1, e1);
+  } else if (nt > 1 && fits) {
+    // several members: from the neighbours' own records
+    int4 r = make_int4(0, 0, 0, 0);
+    if (l < h.y) r = cm.ops[st.nn[h.x + l]];
+    uint64_t from = gballot(l < h.y && r.x == cm.epoch && (F ? r.y >= 0 : r.y == -x - 1));
+    while (from) {
+      int q = gb + __ffsll((unsigned long long)from) - 1;
+      from &= from - 1;
+      int ry = __shfl(r.y, q), rz = __shfl(r.z, q), rw = __shfl(r.w, q);
+      int t = -1;
+      if (F) {
+        t = l == 0 ? ry : (l == 1 ? rz : -1);
+      } else if (rw > G) {
+        fits = false;
+        break;
+      } else if (l < rw) {
+        t = st.ne[rz + l];
       }
-      bool found = false;
-#pragma unroll
-      for (int q = 0; q < N; ++q) found |= nx[q] == b;
-      if (!found) {
-        extra = b;
-        ++nextra;
-      }
+      Elem e = st.tri[max(t, 0)];
+      bool old = F ? known(t) : false;
+      add(t >= 0 && !old && keeps(e, x), t, e);
     }
   }
-  bool odd = act && nextra > 1;
-  bool reg = act && !odd;
-  int nq = nextra;
-#pragma unroll
-  for (int k = 0; k < N; ++k) nq += nx[k] != INT_MAX;
+  fits = fits && n <= G;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  bool own = fits && l < n;
+  int id = own ? slots[l] : INT_MAX, nx = own ? slots[G + l] : INT_MAX, pv = own ? slots[2 * G + l] : -1;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  int nn_ = fits ? n : 0, rid = 0, rnx = 0;
+  bool found = false;
+  each_other<G>(id, nn_, [&](int o) { rid += o < id ? 1 : 0; });
+  each_other<G>(nx, nn_, [&](int o) {
+    rnx += o < nx ? 1 : 0;
+    found |= o == pv;
+  });
+  uint64_t lone = gballot(own && !found);
+  int nextra = __popcll(lone);
+  int ex = nextra ? __shfl(pv, gb + __ffsll((unsigned long long)lone) - 1) : INT_MAX;
+  int exat = __popcll(gballot(own && nx < ex));
+  bool reg = fits && nextra <= 1;
+  int nq = n + nextra;
+  if (own && ex < nx) ++rnx;
   // slots: in place when the row fits, else fresh pool space
-  int ne_off = h.z, ne_cap = cp.y, nn_off = h.x, nn_cap = cp.x;
-  int ne_need = reg && m > ne_cap ? grown_cap(m) : 0;
+  int ne_off = h.z, ne_cap = cp.y, nn_off = h.x, nn_cap = cp.x, lim_ne = n, lim_nn = nq;
+  int ne_need = reg && n > ne_cap ? grown_cap(n) : 0;
   int nn_need = reg && nq > nn_cap ? grown_cap(nq) : 0;
-  int2 at2 = wave_add2(&ctr[C_NE_TOP], ne_need, &ctr[C_NN_TOP], nn_need);
-  int lim_ne = m, lim_nn = nq;
-  if (ne_need) {
-    if ((int64_t)at2.x + ne_need > st.ne_pool) {
-      room_fail(ctr, E_NE_POOL, cm.epoch);
-      lim_ne = min(m, ne_cap);
-    } else {
-      ne_off = at2.x;
-      ne_cap = ne_need;
+  if (ne_need | nn_need) {
+    int o0 = 0, o1 = 0;
+    if (l == 0) {
+      if (ne_need) o0 = atomicAdd(&ctr[C_NE_TOP], ne_need);
+      if (nn_need) o1 = atomicAdd(&ctr[C_NN_TOP], nn_need);
+      atomicAdd(stripe_ptr(ctr, S_RELOC), (ne_need ? 1 : 0) + (nn_need ? 1 : 0));
     }
-  }
-  if (nn_need) {
-    if ((int64_t)at2.y + nn_need > st.nn_pool) {
-      room_fail(ctr, E_NN_POOL, cm.epoch);
-      lim_nn = min(nq, nn_cap);
-    } else {
-      nn_off = at2.y;
-      nn_cap = nn_need;
-    }
-  }
-  uint64_t rel = __ballot(ne_need > 0), rel2 = __ballot(nn_need > 0);
-  if (__lane_id() == 0 && (rel | rel2)) atomicAdd(stripe_ptr(ctr, S_RELOC), __popcll(rel) + __popcll(rel2));
-  if (reg) {
-    // NE(x) four entries per store (the slot holds a multiple of four; the
-    // entries past the row are padding)
-    for (int k = 0; k < lim_ne; k += 4)
-      *(int4*)(st.ne + ne_off + k) = make_int4(col[k * S], col[(k + 1) * S], col[(k + 2) * S], col[(k + 3) * S]);
-    int w = 0;
-    bool put = nextra == 0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      int v = nx[k];
-      if (v == INT_MAX) continue;
-      if (!put && extra < v) {
-        if (w < lim_nn) st.nn[nn_off + w] = extra;
-        ++w;
-        put = true;
+    o0 = __shfl(o0, gb);
+    o1 = __shfl(o1, gb);
+    // a pool that is used up: the row keeps its slot and is cut to it (the
+    // host rebuilds every row before the round goes on)
+    if (ne_need) {
+      if ((int64_t)o0 + ne_need > st.ne_pool) {
+        if (l == 0) room_fail(ctr, E_NE_POOL, cm.epoch);
+        lim_ne = min(n, ne_cap);
+      } else {
+        ne_off = o0;
+        ne_cap = ne_need;
       }
-      if (w < lim_nn) st.nn[nn_off + w] = v;
-      ++w;
     }
-    if (!put) {
-      if (w < lim_nn) st.nn[nn_off + w] = extra;
-      ++w;
+    if (nn_need) {
+      if ((int64_t)o1 + nn_need > st.nn_pool) {
+        if (l == 0) room_fail(ctr, E_NN_POOL, cm.epoch);
+        lim_nn = min(nq, nn_cap);
+      } else {
+        nn_off = o1;
+        nn_cap = nn_need;
+      }
     }
-    st.hdr[x] = make_int4(nn_off, lim_nn, ne_off, lim_ne);
-    st.cap[x] = make_int2(nn_cap, ne_cap);
   }
-  return odd;
-}
-
-// Rebuild row x (x < 0: idle lane); every lane of the wavefront makes this
-// call together. Rows of up to N candidates (staged in this thread's LDS
-// column: N slots, stride S) take the register path. Rows with more are
-// queued in the block's LDS queue bq when one is given (for the larger
-// register path after the small rows), else they and rows that are no disk
-// take the general path. A row's first visit (bq given) flags it for the
-// next round and, in small rounds, appends it to the list of rebuilt rows;
-// that append's atomic is in flight while the row is gathered.
-template <bool F, int N, int S>
-__device__ __forceinline__ void rebuild_row(const Store& st, const Commit& cm, int x, int* col, int* ctr, int* bq,
-                                            int* bqn) {
-  bool act = x >= 0;
-  bool first = bq != nullptr;
-  int tbase = 0, tincl = 0;
-  if (first && cm.touched) {
-    int lane = __lane_id();
-    tincl = act ? 1 : 0;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-      int o = __shfl_up(tincl, d);
-      if (lane >= d) tincl += o;
+  if (reg) {
+    if (own && rid < lim_ne) st.ne[ne_off + rid] = id;
+    if (own && rnx < lim_nn) st.nn[nn_off + rnx] = nx;
+    if (l == 0) {
+      if (nextra && exat < lim_nn) st.nn[nn_off + exat] = ex;
+      st.hdr[x] = make_int4(nn_off, lim_nn, ne_off, lim_ne);
+      st.cap[x] = make_int2(nn_cap, ne_cap);
+      ++rows;
     }
-    if (lane == kWave - 1 && tincl > 0) tbase = atomicAdd(&ctr[C_TOUCH], tincl);
-  }
-  int tot = 0;
-  Hdr h = make_int4(0, 0, 0, 0);
-  int2 cp = make_int2(0, 0);
-  if (act) {
-    h = st.hdr[x];
-    cp = st.cap[x];
-    tot = row_candidates<F>(st, cm, x, h, col, S, N);
-  }
-  bool reg = act && tot <= N;
-  bool later = false;
-  if (first && act && !reg) {
-    int slot = atomicAdd(bqn, 1);
+  } else if (act && l == 0) {
+    int slot = G == 16 && !fits ? atomicAdd(bqn, 1) : kBlock;
     if (slot < kBlock) {
       bq[slot] = x;
-      later = true;
+    } else {
+      rebuild_staged<F>(st, cm, x, ctr);
+      ++rows;
     }
   }
-  bool general = act && !reg && !later;
-  if (__ballot(reg)) general |= rebuild_reg<N, S>(st, cm, reg ? x : -1, h, cp, tot, col, ctr);
-  if (general) rebuild_staged<F>(st, cm, x, ctr);
-  if (first) {
-    if (act) cm.nxt[x] = 1;
-    if (cm.touched) {
-      int slot = __shfl(tbase, kWave - 1) + tincl - 1;
-      if (act && slot < cm.touched_cap) cm.touched[slot] = x;
-    }
+  if (G == 16 && act && l == 0) cm.nxt[x] = 1;  // a row's first visit flags it for the next round
+}
+
+// LDS of a block's row rebuilds
+struct RowLds {
+  int slots[3 * kBlock];  // 3 per lane: the candidates of the rows in flight
+  int bq[kBlock];         // rows of more than 16 of anything
+  int bqn;
+};
+// Rebuild the n rows row(0 .. n - 1) with the kBlock threads of the block, 16
+// lanes each (every thread makes this call; bqn is zero). In small rounds the
+// rows are listed for the next selection.
+template <bool F, class Row>
+__device__ __forceinline__ void rebuild_rows(const Store& st, const Commit& cm, int n, Row&& row, RowLds& L, int* ctr,
+                                             int& rows) {
+  constexpr int G = 16;
+  int tid = (int)threadIdx.x, g = tid / G;
+  if (cm.touched && n > 0) {
+    __shared__ int tb;
+    if (tid == 0) tb = atomicAdd(&ctr[C_TOUCH], n);
+    __syncthreads();
+    for (int i = tid; i < n; i += kBlock)
+      if (tb + i < cm.touched_cap) cm.touched[tb + i] = row(i);
+    __syncthreads();
   }
-  bool done = act && !later;  // a queued row is counted when it is rebuilt
-  uint64_t rows = __ballot(done);
+  for (int r0 = 0; r0 < n; r0 += kBlock / G)
+    rebuild_group<F, G>(st, cm, r0 + g < n ? row(r0 + g) : -1, L.slots + 3 * G * g, ctr, L.bq, &L.bqn, rows);
+}
+// the queued rows, one per wavefront
+template <bool F>
+__device__ __forceinline__ void rebuild_queued(const Store& st, const Commit& cm, RowLds& L, int* ctr, int& rows) {
+  __syncthreads();
+  int nbig = min(L.bqn, kBlock), wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  for (int b = wv; b < nbig; b += kBlock / kWave)
+    rebuild_group<F, kWave>(st, cm, L.bq[b], L.slots + 3 * kWave * wv, ctr, nullptr, nullptr, rows);
+}
+// the rows rebuilt by this wavefront, into the counters
+__device__ __forceinline__ void count_rows(int rows, int* ctr) {
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) rows += __shfl_xor(rows, d);
   if (__lane_id() == 0 && rows) {
     int* sp = stripe_ptr(ctr, 0);
-    atomicAdd(sp + S_ROWS, __popcll(rows));
-    atomicAdd(sp + S_PROWS, __popcll(rows));
+    atomicAdd(sp + S_ROWS, rows);
+    atomicAdd(sp + S_PROWS, rows);
   }
 }
 
@@ -1320,13 +1226,10 @@ __device__ __forceinline__ int block_scan(int x, int& excl, int* wsum) {
 // LDS of one commit block
 constexpr int kPairB = 8;  // neighbours per member taken per pair round (two 16-byte loads)
 struct CommitLds {
-  int col[kRegSmall * kBlock];  // candidate staging: kRegSmall per thread, or kRegRow for half the threads
+  RowLds rows;
   int q[kPairB * kBlock];       // rows queued in a pair round
-  int bq[kBlock];               // rows of more than kRegSmall candidates
-  int bqn;
   int wsum[kBlock / kWave];
 };
-static_assert(kRegSmall * kBlock == kRegRow * (kBlock / 2), "the large path stages in the same LDS");
 
 // Rebuild the rows claimed by the committed members list[base .. base + cnt)
 // (cnt <= kBlock), with all kBlock threads of the block. Each member has tpm
@@ -1334,7 +1237,7 @@ static_assert(kRegSmall * kBlock == kRegRow * (kBlock / 2), "the large path stag
 // each member's neighbours over its threads); a thread takes kPairB of its
 // member's neighbours per pair round (row entries, then owner keys, loaded
 // side by side). The rows a member owns are queued in LDS in block order and
-// rebuilt 256 at a time. For flips one more round queues the members' own
+// rebuilt, 16 lanes each. For flips one more round queues the members' own
 // rows, after the rounds that read the members' rows.
 template <bool F>
 __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restrict__ list, int base, int cnt,
@@ -1356,8 +1259,8 @@ __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restr
     }
   }
   uint64_t key = own_key(cm.epoch, v);
-  int* mycol = L.col + tid;
-  if (tid == 0) L.bqn = 0;
+  int rows = 0;
+  if (tid == 0) L.rows.bqn = 0;
   bool own_round = F;
   for (int j0 = sl * kPairB;; j0 += kPairB << lg) {
     bool pairs = __syncthreads_or(j0 < deg);
@@ -1387,17 +1290,10 @@ __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restr
     for (int q = 0; q < kPairB; ++q)
       if (y[q] >= 0 && k[q] == key) L.q[at++] = y[q];
     __syncthreads();
-    for (int r0 = 0; r0 < tot; r0 += kBlock)
-      rebuild_row<F, kRegSmall, kBlock>(st, cm, r0 + tid < tot ? L.q[r0 + tid] : -1, mycol, ctr, L.bq, &L.bqn);
+    rebuild_rows<F>(st, cm, tot, [&](int i) { return L.q[i]; }, L.rows, ctr, rows);
   }
-  // rows of more than kRegSmall candidates, half the block at a time
-  __syncthreads();
-  int nbig = min(L.bqn, kBlock);
-  constexpr int H = kBlock / 2;
-  for (int b0 = 0; b0 < nbig; b0 += H) {
-    int x = (tid < H && b0 + tid < nbig) ? L.bq[b0 + tid] : -1;
-    rebuild_row<F, kRegRow, H>(st, cm, x, L.col + (tid & (H - 1)), ctr, nullptr, nullptr);
-  }
+  rebuild_queued<F>(st, cm, L.rows, ctr, rows);
+  count_rows(rows, ctr);
   __syncthreads();  // the LDS is reused by the next chunk
 }
 
@@ -1415,8 +1311,8 @@ __global__ void __launch_bounds__(256, 5) k_commit(Store st, const int* __restri
 // The same rebuild in vertex order, for classes whose claimed rows cover a
 // good part of the mesh: a work-group scans `chunk` consecutive vertex slots
 // (at most kSweepMax), queues the rows claimed in this epoch in LDS in slot
-// order (a block-wide ordered compaction, so every lane of a rebuild pass has
-// a row), and rebuilds them kBlock at a time. Consecutive rows then read
+// order (a block-wide ordered compaction, so every lane group of a rebuild pass
+// has a row), and rebuilds them. Consecutive rows then read
 // nearby headers, capacities, owner keys and target records, and walk rows
 // and elements in the order they are laid out, where the member-driven form
 // above touches them in its members' neighbour order. Every row is still
@@ -1424,10 +1320,8 @@ __global__ void __launch_bounds__(256, 5) k_commit(Store st, const int* __restri
 constexpr int kSweepStep = kPairB * kBlock;  // slots scanned per block-wide pass
 constexpr int kSweepMax = 2 * kSweepStep;    // most slots per work-group (16-bit offsets in LDS)
 struct SweepLds {
-  int col[kRegSmall * kBlock];
+  RowLds rows;
   uint16_t q[kSweepMax];
-  int bq[kBlock];
-  int bqn;
   int wsum[kBlock / kWave];
 };
 static_assert(kSweepMax <= 65536, "slot offsets are 16-bit");
@@ -1466,18 +1360,12 @@ __global__ void __launch_bounds__(256, 5) k_commit_sweep(Store st, Commit cm, in
     qn += tot;
     __syncthreads();  // wsum is reused by the next scan
   }
-  if (tid == 0) L.bqn = 0;
+  if (tid == 0) L.rows.bqn = 0;
   __syncthreads();
-  for (int r0 = 0; r0 < qn; r0 += kBlock)
-    rebuild_row<F, kRegSmall, kBlock>(st, cm, r0 + tid < qn ? base + (int)L.q[r0 + tid] : -1, L.col + tid, ctr,
-                                      L.bq, &L.bqn);
-  __syncthreads();
-  int nbig = min(L.bqn, kBlock);
-  constexpr int H = kBlock / 2;
-  for (int b0 = 0; b0 < nbig; b0 += H) {
-    int y = (tid < H && b0 + tid < nbig) ? L.bq[b0 + tid] : -1;
-    rebuild_row<F, kRegRow, H>(st, cm, y, L.col + (tid & (H - 1)), ctr, nullptr, nullptr);
-  }
+  int rows = 0;
+  rebuild_rows<F>(st, cm, qn, [&](int i) { return base + (int)L.q[i]; }, L.rows, ctr, rows);
+  rebuild_queued<F>(st, cm, L.rows, ctr, rows);
+  count_rows(rows, ctr);
 }
 
 // Work-groups of `fn` (kBlock threads) resident on the current device at
@@ -1508,9 +1396,11 @@ void commit_sweep(const Store& st, Commit cm, bool flips, int* ctr, hipStream_t 
   if (st.V <= 0) return;
   int res = flips ? resident_blocks((const void*)&k_commit_sweep<true>, 0)
                   : resident_blocks((const void*)&k_commit_sweep<false>, 1);
-  // slots per work-group: a multiple of kBlock, at most kSweepMax
+  // slots per work-group: a multiple of 32, at most kSweepMax (on a mesh of
+  // 1,500 vertices 256 slots left a work-group 12 passes one after another,
+  // 15 us a launch; 32 slots: two, 7 us)
   int64_t per = ((int64_t)st.V + res - 1) / res;
-  int chunk = (int)std::min<int64_t>(kSweepMax, std::max<int64_t>(kBlock, (per + kBlock - 1) / kBlock * kBlock));
+  int chunk = (int)std::min<int64_t>(kSweepMax, std::max<int64_t>(32, (per + 31) / 32 * 32));
   int nb = (st.V + chunk - 1) / chunk;
   if (flips)
     k_commit_sweep<true><<<nb, kBlock, 0, s>>>(st, cm, chunk, ctr);
