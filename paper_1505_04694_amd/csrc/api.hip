@@ -74,7 +74,8 @@ struct pm_mesh {
   int sel_mark = 0;      // selection stamp, one per small round
   DBuf<int4> ops;        // commit: operation records
   DBuf<uint64_t> own;    // commit: row owner keys
-  DBuf<uint64_t> tk;     // commit: collapse-target counts
+  DBuf<int> dirty;       // commit in vertex order: the epoch that claimed a row last
+  DBuf<int> cnt;         // commit: hand-overs counted per row
   DBuf<int4> tgt;        // commit: collapse-target records
   int epoch = 0;         // commit epoch, one per class
   DBuf<double> qpart;
@@ -568,8 +569,9 @@ pm_status ensure_phase_scratch(pm_mesh* m) {
   TRY(ensure(m, m->touch, std::max(V, 65536)));
   TRY(ensure(m, m->seen, V, true));
   TRY(ensure(m, m->own, V, true));
-  TRY(ensure(m, m->tk, V, true));
-  TRY(ensure(m, m->tgt, V));
+  TRY(ensure(m, m->dirty, V, true));
+  TRY(ensure(m, m->cnt, V, true));
+  TRY(ensure(m, m->tgt, V, true));
   TRY(ensure(m, m->sflag, V));
   TRY(ensure(m, m->spos, V));
   TRY(ensure(m, m->spart, scan_partials_needed(V) + 2));
@@ -589,7 +591,9 @@ Commit commit_of(pm_mesh* m) {
   c.touched = nullptr;
   c.touched_cap = (int)std::min<size_t>(m->touch.n, INT32_MAX);
   c.own = m->own.p;
-  c.tk = m->tk.p;
+  c.by_member = 1;
+  c.dirty = m->dirty.p;
+  c.cnt = m->cnt.p;
   c.tgt = m->tgt.p;
   c.stage = m->stage.p;
   c.stage_cap = (int64_t)m->stage.n;
@@ -836,13 +840,15 @@ pm_status run_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind) {
 
 // One class of a round: the operation over its members, then the commit of
 // the rows they changed (one launch for a small class)
-void run_class(pm_mesh* m, int kind, const Classes& cl, int c, const OpArgs& a, const Commit& cm) {
+void run_class(pm_mesh* m, int kind, const Classes& cl, int c, const OpArgs& a, Commit cm) {
   const int* list = m->cls.p + cl.off[c];
   int n = cl.size[c];
   if (n <= kSmallClass && !m->tune.small_work) {
     timed(m, kind == 0 ? PM_K_COLLAPSE : PM_K_FLIP, n, [&] { class_small(m->st, list, n, a, cm, kind, m->ctr, m->s); });
     return;
   }
+  bool sweep = m->tune.commit_order == 2 || (m->tune.commit_order == 0 && (int64_t)n * 64 >= m->st.V);
+  cm.by_member = sweep ? 0 : 1;
   if (kind == 0)
     timed(m, PM_K_COLLAPSE, n, [&] { collapse_class(m->st, list, n, a, cm, m->ctr, op_lanes(m), m->s); });
   else
@@ -850,7 +856,6 @@ void run_class(pm_mesh* m, int kind, const Classes& cl, int c, const OpArgs& a, 
       if (op_lanes(m) == 1) flip_class(m->st, list, n, a, cm, m->ctr, m->s);
       else flip_class_g(m->st, list, n, a, cm, m->ctr, m->s);
     });
-  bool sweep = m->tune.commit_order == 2 || (m->tune.commit_order == 0 && (int64_t)n * 64 >= m->st.V);
   if (sweep) {
     timed(m, PM_K_COMMIT, 0, [&] { commit_sweep(m->st, cm, kind != 0, m->ctr, m->s); });
   } else {
@@ -1269,7 +1274,8 @@ pm_status pm_mesh_destroy(pm_mesh* m) {
   dfree(m, m->rw.p, m->rw.n);
   dfree(m, m->seeds.p, m->seeds.n);
   dfree(m, m->own.p, m->own.n);
-  dfree(m, m->tk.p, m->tk.n);
+  dfree(m, m->dirty.p, m->dirty.n);
+  dfree(m, m->cnt.p, m->cnt.n);
   dfree(m, m->tgt.p, m->tgt.n);
   dfree(m, m->ops.p, m->ops.n);
   prof_flush(m);

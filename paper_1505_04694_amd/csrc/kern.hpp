@@ -226,11 +226,18 @@ struct Commit {
   // onto u is (epoch, -(u+1), ne_off, ne_cnt) with the member's NE row, a
   // flip (epoch, t1, t2, 0) with its two elements
   int4* ops;
-  uint64_t* own;   // V: row owner key, maximised: (epoch << 32) | ~member
-  // V: collapses onto the vertex, (epoch << 32) | count, and the last one's
-  // (member, ne_off, ne_cnt, epoch): a collapse target finds the row it
-  // absorbs without reading its neighbours' records
-  uint64_t* tk;
+  // rows claimed by the class. by_member: own, V row owner keys, maximised:
+  // (epoch << 32) | ~member. Else dirty, V: the epoch that claimed the row
+  // last (a plain store: the vertex-order commit asks only whether).
+  int by_member;
+  uint64_t* own;
+  int* dirty;
+  // V: what members hand over to the vertex. cnt: how often any did, ever
+  // (atomic adds only: an atomic on a line that the same launch stores to
+  // doubled the collapse's time). tgt: the last one's (a, b, epoch) and the
+  // count at the row's last rebuild, so that a collapse target finds the row
+  // it absorbs without reading its neighbours' records
+  int* cnt;
   int4* tgt;
   int* stage;      // staging for rows past the wavefront path
   int64_t stage_cap;

@@ -607,24 +607,30 @@ void colour_out(const Store& st, const uint64_t* rw, int* out, hipStream_t s) {
 }
 
 // ---- deferred update: stamps and claims (Sec. 3.3) -------------------------------------------
-// A committed member stamps its operation and claims every row it changes;
-// the claim with the largest key (the smallest member id) wins the row.
+// A committed member stamps its operation and claims every row it changes.
+// Where the commit starts from the members, the claim with the largest key
+// (the smallest member id) wins the row: an atomic per row. Where it walks the
+// rows in vertex order, it needs no owner, only the mark: a plain store (the
+// largest collapse launch of the 2049 x 2049 step 560 -> 546 us with one
+// 32-bit atomic a member instead of eight 64-bit ones).
 __device__ __forceinline__ void claim_row(const Commit& cm, int x, int v) {
-  atomicMax((unsigned long long*)&cm.own[x], (unsigned long long)own_key(cm.epoch, v));
+  if (cm.by_member)
+    atomicMax((unsigned long long*)&cm.own[x], (unsigned long long)own_key(cm.epoch, v));
+  else
+    cm.dirty[x] = cm.epoch;
 }
 __device__ __forceinline__ void stamp(const Commit& cm, int v, int a, int b, int c) {
   cm.ops[v] = make_int4(cm.epoch, a, b, c);
 }
-// a record (a, b, c) for row u in this epoch: the count's epoch is raised
-// first (a count of an older epoch restarts at zero). A member v collapsing
-// onto u hands over its NE row: (v, ne_off, ne_cnt). A flip of the edge
-// (v, w) with far vertices a and b gives rows a and b its two elements
-// (lo, hi, -1); rows v and w only lose elements.
-__device__ __forceinline__ void mark_target(const Commit& cm, int u, int a, int b, int c) {
-  cm.tgt[u] = make_int4(a, b, c, cm.epoch);
-  unsigned long long e = (unsigned long long)(uint32_t)cm.epoch << 32;
-  atomicMax((unsigned long long*)&cm.tk[u], e);
-  atomicAdd((unsigned long long*)&cm.tk[u], 1ull);
+// a record (a, b) for row u in this epoch. A member v collapsing onto u hands
+// over its NE row: (ne_off, ne_cnt). A flip of the edge (v, w) with far
+// vertices a and b gives rows a and b its two elements (lo, hi); rows v and w
+// only lose elements. After a commit out of room the count at the last
+// rebuild may lag behind: the row then goes to its neighbours' own records
+// (two or more) or, without a record of this epoch, takes none.
+__device__ __forceinline__ void mark_target(const Commit& cm, int u, int a, int b) {
+  *(int3*)&cm.tgt[u] = make_int3(a, b, cm.epoch);
+  atomicAdd(&cm.cnt[u], 1);
 }
 
 // a member is deferred when a same-class active neighbour has a larger key
@@ -744,7 +750,7 @@ __device__ __forceinline__ int collapse_one(const Store& st, int v, const OpArgs
   }
   st.valive[v] = 0;
   stamp(cm, v, -(u + 1), h.z, h.w);
-  mark_target(cm, u, v, h.z, h.w);
+  mark_target(cm, u, h.z, h.w);
   for (int j = 0; j < h.y; ++j) claim_row(cm, st.nn[h.x + j], v);
   return 2;
 }
@@ -831,8 +837,8 @@ __device__ __forceinline__ int flip_one(const Store& st, int v, const OpArgs& a,
   st.tri[lo] = make_int4(tv.x, tv.y, tv.z, 1);
   st.tri[hi] = make_int4(tw.x, tw.y, tw.z, 1);
   stamp(cm, v, lo, hi, 0);
-  mark_target(cm, ba, lo, hi, -1);
-  mark_target(cm, bb, lo, hi, -1);
+  mark_target(cm, ba, lo, hi);
+  mark_target(cm, bb, lo, hi);
   claim_row(cm, v, v);
   claim_row(cm, bw, v);
   claim_row(cm, ba, v);
@@ -1023,16 +1029,16 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
   int xs = max(x, 0);
   Hdr h = st.hdr[xs];
   int2 cp = st.cap[xs];
-  uint64_t tk = cm.tk[xs];
   int4 tg = cm.tgt[xs];
+  int ct = cm.cnt[xs];
   // members that hand something over to x in this epoch
-  int nt = (uint32_t)(tk >> 32) == (uint32_t)cm.epoch ? (int)(uint32_t)tk : 0;
-  bool fits = act && h.w <= G && (nt <= 1 || h.y <= G) && (F || nt != 1 || tg.z <= G);
+  int nt = tg.z == cm.epoch ? ct - tg.w : 0;
+  bool fits = act && h.w <= G && (nt <= 1 || h.y <= G) && (F || nt != 1 || tg.y <= G);
   int t0 = -1, t1 = -1;
   if (fits && l < h.w) t0 = st.ne[h.z + l];
   if (fits && nt == 1) {
     if (F) t1 = l == 0 ? tg.x : (l == 1 ? tg.y : -1);
-    else if (l < tg.z) t1 = st.ne[tg.y + l];
+    else if (l < tg.y) t1 = st.ne[tg.x + l];
   }
   Elem e0 = st.tri[max(t0, 0)], e1 = st.tri[max(t1, 0)];
   int n = 0;
@@ -1142,7 +1148,8 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
     if (l == 0) {
       if (nextra && exat < lim_nn) st.nn[nn_off + exat] = ex;
       st.hdr[x] = make_int4(nn_off, lim_nn, ne_off, lim_ne);
-      st.cap[x] = make_int2(nn_cap, ne_cap);
+      if (ne_need | nn_need) st.cap[x] = make_int2(nn_cap, ne_cap);
+      if (ct != tg.w) cm.tgt[x].w = ct;
       ++rows;
     }
   } else if (act && l == 0) {
@@ -1151,6 +1158,7 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
       bq[slot] = x;
     } else {
       rebuild_staged<F>(st, cm, x, ctr);
+      cm.tgt[x].w = ct;
       ++rows;
     }
   }
@@ -1333,7 +1341,7 @@ __global__ void __launch_bounds__(256, 5) k_commit_sweep(Store st, Commit cm, in
   int tid = (int)threadIdx.x;
   int base = xcd_block() * chunk;
   int end = min(st.V, base + chunk);
-  // each pass: thread tid reads the owner keys of kPairB consecutive slots,
+  // each pass: thread tid reads the marks of kPairB consecutive slots,
   // all in flight together, and one block-wide scan places the claimed rows
   // in slot order
   int qn = 0;
@@ -1342,12 +1350,12 @@ __global__ void __launch_bounds__(256, 5) k_commit_sweep(Store st, Commit cm, in
     bool dirty[kPairB];
     int mine = 0;
     {
-      uint64_t k[kPairB];
+      int k[kPairB];
 #pragma unroll
-      for (int q = 0; q < kPairB; ++q) k[q] = first + q < end ? cm.own[first + q] : 0ull;
+      for (int q = 0; q < kPairB; ++q) k[q] = first + q < end ? cm.dirty[first + q] : -1;
 #pragma unroll
       for (int q = 0; q < kPairB; ++q) {
-        dirty[q] = first + q < end && (uint32_t)(k[q] >> 32) == (uint32_t)cm.epoch;
+        dirty[q] = first + q < end && k[q] == cm.epoch;
         mine += dirty[q] ? 1 : 0;
       }
     }
@@ -2150,7 +2158,7 @@ __device__ __forceinline__ int collapse_group(const Store& st, int v, Hdr h, con
   if (g.j == 0) {
     st.valive[v] = 0;
     stamp(cm, v, -(u + 1), h.z, h.w);
-    mark_target(cm, u, v, h.z, h.w);
+    mark_target(cm, u, h.z, h.w);
   }
   return 2;
 }
@@ -2296,8 +2304,8 @@ __device__ __forceinline__ int flip_group(const Store& st, int v, Hdr h, const O
     st.tri[lo] = make_int4(tv.x, tv.y, tv.z, 1);
     st.tri[hi] = make_int4(tw.x, tw.y, tw.z, 1);
     stamp(cm, v, lo, hi, 0);
-    mark_target(cm, av, lo, hi, -1);
-    mark_target(cm, bv, lo, hi, -1);
+    mark_target(cm, av, lo, hi);
+    mark_target(cm, bv, lo, hi);
     claim_row(cm, v, v);
     claim_row(cm, w, v);
     claim_row(cm, av, v);
