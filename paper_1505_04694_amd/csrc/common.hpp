@@ -36,6 +36,18 @@ constexpr int kWave = 64;
 constexpr double kK4R3 = 6.928203230275509;  // the double nearest 4 sqrt(3)
 constexpr double kK12R3 = 20.784609690826528;  // the double nearest 12 sqrt(3)
 
+// x / 3, rounded as the division rounds it: the quotient by the rounded third
+// is off by less than a unit in the last place, its residual is exact, and one
+// correction then rounds correctly (Markstein 1990). Where the residual is
+// zero or no number (zeros, infinities) the quotient stands. Six instructions
+// where the compiler's division takes eleven and a quarter-rate reciprocal.
+__device__ __forceinline__ double third(double x) {
+  const double y = 1.0 / 3.0;
+  double q = x * y;
+  double r = __builtin_fma(-3.0, q, x);
+  return fabs(r) > 0.0 ? __builtin_fma(r, y, q) : q;
+}
+
 // ---- metric geometry (Sec. 2.2) ---------------------------------------------
 
 // squared length of edge i-j in the mean tensor of its end points
@@ -59,9 +71,9 @@ __device__ __forceinline__ Geo make_geo(double2 p0, double2 p1, double2 p2, Met 
   g.x[0] = p0.x; g.y[0] = p0.y;
   g.x[1] = p1.x; g.y[1] = p1.y;
   g.x[2] = p2.x; g.y[2] = p2.y;
-  g.a = ((m0.a + m1.a) + m2.a) / 3.0;
-  g.b = ((m0.b + m1.b) + m2.b) / 3.0;
-  g.c = ((m0.c + m1.c) + m2.c) / 3.0;
+  g.a = third((m0.a + m1.a) + m2.a);
+  g.b = third((m0.b + m1.b) + m2.b);
+  g.c = third((m0.c + m1.c) + m2.c);
   return g;
 }
 
@@ -173,7 +185,7 @@ __device__ __forceinline__ VParts vparts(const Geo& g) {
 
 // G(P) = F(P / 3) / P^2 and dG/dP
 __device__ __forceinline__ void vas_size(double P, double& G, double& dG) {
-  double x = P / 3.0;
+  double x = third(P);
   bool below = x < 1.0;
   double mm = below ? x : 1.0 / x;
   double f = mm * (2.0 - mm);

@@ -1442,9 +1442,9 @@ __global__ void k_elem_metric(Store st, Met* __restrict__ out) {
     if (!e.w) continue;
     Met m0 = st.met[e.x], m1 = st.met[e.y], m2 = st.met[e.z];
     Met r;
-    r.a = ((m0.a + m1.a) + m2.a) / 3.0;
-    r.b = ((m0.b + m1.b) + m2.b) / 3.0;
-    r.c = ((m0.c + m1.c) + m2.c) / 3.0;
+    r.a = third((m0.a + m1.a) + m2.a);
+    r.b = third((m0.b + m1.b) + m2.b);
+    r.c = third((m0.c + m1.c) + m2.c);
     out[t] = r;
   }
 }
@@ -1761,25 +1761,74 @@ __device__ __forceinline__ Grp grp() {
 }
 __device__ __forceinline__ double gget(double v, int k, const Grp& g) { return __shfl(v, g.base + k); }
 __device__ __forceinline__ int gget(int v, int k, const Grp& g) { return __shfl(v, g.base + k); }
-// serial sum acc = ((init + v_0) + v_1) + ... over lanes 0..n-1
-__device__ __forceinline__ double gsum(double v, int n, const Grp& g) {
-  double acc = 0.0;
-#pragma unroll
-  for (int k = 0; k < kG; ++k) {
-    double t = gget(v, k, g);
-    if (k < n) acc = acc + t;
-  }
-  return acc;
+// Sums over a group's lanes in row order, acc = ((0 + v_0) + v_1) + ..., go
+// through LDS: every lane stores its terms (0 in a lane without one: adding it
+// changes nothing), then reads the group's terms of a sum back, 16 bytes at a
+// time. A shuffle of a double is two LDS instructions per term and lane.
+constexpr int kSumW = kWave + 2;  // stride of one sum's terms (offsets the banks of the sums)
+__device__ __forceinline__ void wave_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
-// serial "first or smaller" minimum over lanes 0..n-1
-__device__ __forceinline__ double gmin(double v, int n, const Grp& g) {
-  double mn = 0.0;
+// the group's terms at t (16-byte aligned), summed
+__device__ __forceinline__ double sum8(const double* t) {
+  const double2* p = (const double2*)t;
+  double2 a = p[0], b = p[1], c = p[2], d = p[3];
+  return (((((((0.0 + a.x) + a.y) + b.x) + b.y) + c.x) + c.y) + d.x) + d.y;
+}
+// one sum, in every lane of the group
+__device__ __forceinline__ double gsum(double v, const Grp& g, double* lds) {
+  lds[g.base + g.j] = v;
+  wave_lds();
+  double s = sum8(lds + g.base);
+  wave_lds();
+  return s;
+}
+// N sums side by side: lane c < N adds up the c-th (its return value)
+template <int N>
+__device__ __forceinline__ double gsum_lane(const double (&v)[N], const Grp& g, double* lds) {
 #pragma unroll
-  for (int k = 0; k < kG; ++k) {
-    double t = gget(v, k, g);
-    if (k < n && (k == 0 || t < mn)) mn = t;
+  for (int c = 0; c < N; ++c) lds[c * kSumW + g.base + g.j] = v[c];
+  wave_lds();
+  double s = sum8(lds + (g.j < N ? g.j : 0) * kSumW + g.base);
+  wave_lds();
+  return s;
+}
+// N sums, every one in every lane of the group
+template <int N>
+__device__ __forceinline__ void gsums(double (&v)[N], const Grp& g, double* lds) {
+  double s = gsum_lane<N>(v, g, lds);
+  lds[g.base + g.j] = s;
+  wave_lds();
+#pragma unroll
+  for (int c = 0; c < N; ++c) v[c] = lds[g.base + c];
+  wave_lds();
+}
+// a double moved inside each row of 16 lanes by a DPP control
+template <int C>
+__device__ __forceinline__ double dpp64(double v) {
+  int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), C, 0xF, 0xF, false);
+  int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), C, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+// serial "first or smaller" minimum over lanes 0..n-1: three exchanges across
+// the eight lanes. The serial loop starts from lane 0 and takes no value that
+// is no number after it, so such a value counts as infinite, and as the result
+// in lane 0.
+__device__ __forceinline__ double gmin(double v, int n, const Grp& g) {
+  double m = g.j < n && v == v ? v : INFINITY;
+  double o = dpp64<0xB1>(m);   // lanes 1 0 3 2
+  m = o < m ? o : m;
+  o = dpp64<0x4E>(m);          // lanes 2 3 0 1
+  m = o < m ? o : m;
+  o = dpp64<0x141>(m);         // lanes 7 6 5 4 3 2 1 0
+  m = o < m ? o : m;
+  uint64_t bad = __ballot(!(v == v));
+  if (bad) {
+    double f = __shfl(v, g.base);
+    if (!(f == f)) m = f;
   }
-  return mn;
+  return n > 0 ? m : 0.0;
 }
 __device__ __forceinline__ bool gany(bool p, const Grp& g) {
   uint64_t b = __ballot(p);
@@ -1819,9 +1868,9 @@ __device__ __forceinline__ PatchElem load_patch_elem(const Store& st, int t, con
     pe.c = m.c;
   } else {
     Met m0 = st.met[e.x], m1 = st.met[e.y], m2 = st.met[e.z];
-    pe.a = ((m0.a + m1.a) + m2.a) / 3.0;
-    pe.b = ((m0.b + m1.b) + m2.b) / 3.0;
-    pe.c = ((m0.c + m1.c) + m2.c) / 3.0;
+    pe.a = third((m0.a + m1.a) + m2.a);
+    pe.b = third((m0.b + m1.b) + m2.b);
+    pe.c = third((m0.c + m1.c) + m2.c);
   }
   pe.k = slot_of(e, v);
   return pe;
@@ -1856,12 +1905,13 @@ __device__ __forceinline__ double gpatch_min(const PatchElem& pe, bool own, doub
   return gmin(q2, nw, g);
 }
 
-__device__ __forceinline__ double gpatch_q(const PatchElem& pe, bool own, double2 p, int nw, const Grp& g, int qk) {
-  double q = own ? qval(patch_geo(pe, p), qk) : 0.0;
-  return gsum(q, nw, g);
+__device__ __forceinline__ double gpatch_q(const PatchElem& pe, bool own, double2 p, const Grp& g, int qk, double* lds) {
+  return gsum(own ? qval(patch_geo(pe, p), qk) : 0.0, g, lds);
 }
 
-__device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, const Grp& g) {
+// sums a smoothing step takes side by side
+constexpr int kSmoothSums = 5;
+__device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, const Grp& g, double* lds) {
   double2 pv = st.xy[v];
   Met mv = st.met[v];
   bool ownn = g.j < h.y, owne = g.j < h.w;
@@ -1884,24 +1934,10 @@ __device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, 
     double eb = (mv.b + mw.b) * 0.5;
     double ec = (mv.c + mw.c) * 0.5;
     double dx = pw.x - pv.x, dy = pw.y - pv.y;
-    // the five sums side by side, one lane's terms at a time (each sum keeps
-    // the serial rounding sequence; holding all forty shuffled terms at once
-    // would spill)
-    double fx = ea * dx + eb * dy, fy = eb * dx + ec * dy;
-    double Ga = 0.0, Gb = 0.0, Gc = 0.0, rx = 0.0, ry = 0.0;
-#pragma unroll
-    for (int k = 0; k < kG; ++k) {
-      double ta = gget(ea, k, g), tb = gget(eb, k, g), tc = gget(ec, k, g), tx = gget(fx, k, g),
-             ty = gget(fy, k, g);
-      if (k < h.y) {
-        Ga = Ga + ta;
-        Gb = Gb + tb;
-        Gc = Gc + tc;
-        rx = rx + tx;
-        ry = ry + ty;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    double t[5] = {ownn ? ea : 0.0, ownn ? eb : 0.0, ownn ? ec : 0.0, ownn ? ea * dx + eb * dy : 0.0,
+                   ownn ? eb * dx + ec * dy : 0.0};
+    gsums(t, g, lds);
+    double Ga = t[0], Gb = t[1], Gc = t[2], rx = t[3], ry = t[4];
     double det = Ga * Gc - Gb * Gb;
     p = make_double2(pv.x + (Gc * rx - Gb * ry) / det, pv.y + (Ga * ry - Gb * rx) / det);
     bool vo, vn;
@@ -1911,16 +1947,9 @@ __device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, 
   } else if (kind == 1) {
     double ex = 0.0, ey = 0.0;
     if (owne) qgrad_x(patch_geo(pe, pv), pe.k, st.qk, ex, ey);
-    double gx = 0.0, gy = 0.0;
-#pragma unroll
-    for (int k = 0; k < kG; ++k) {
-      double tx = gget(ex, k, g), ty = gget(ey, k, g);
-      if (k < h.w) {
-        gx = gx + tx;
-        gy = gy + ty;
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    double t[3] = {ex, ey, owne ? qval(patch_geo(pe, pv), st.qk) : 0.0};
+    gsums(t, g, lds);
+    double gx = t[0], gy = t[1], Qold = t[2];
     if (gx == 0.0 && gy == 0.0) return false;
     double ax = fabs(gx), ay = fabs(gy);
     double nrm = ax < ay ? ay : ax;
@@ -1929,7 +1958,6 @@ __device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, 
     double hh = gmin(hx < hy ? hy : hx, h.y, g);
     bool vo;
     double oldmin = gpatch_min(pe, owne, pv, h.w, g, st.qk, vo);
-    double Qold = gpatch_q(pe, owne, pv, h.w, g, st.qk);
     double step = hh;
     bool ok = false;
     for (int k = 1; k <= 4 && !ok; ++k) {
@@ -1938,7 +1966,7 @@ __device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, 
       bool vn;
       double newmin = gpatch_min(pe, owne, p, h.w, g, st.qk, vn);
       if (!vn || !(newmin >= oldmin)) continue;
-      if (!(gpatch_q(pe, owne, p, h.w, g, st.qk) > Qold)) continue;
+      if (!(gpatch_q(pe, owne, p, g, st.qk, lds) > Qold)) continue;
       ok = true;
     }
     if (!ok) return false;
@@ -2008,6 +2036,8 @@ __device__ __forceinline__ bool smooth_group(Store& st, int v, Hdr h, int kind, 
 template <int K, int QK>
 __global__ void __launch_bounds__(256, 4) k_smooth_g(Store st, const int* __restrict__ list, int n, int* ctr) {
   st.qk = QK;  // the functional as a constant: one instantiation per kind
+  __shared__ __align__(16) double terms[kBlock / kWave][kSmoothSums * kSumW];
+  double* lds = terms[threadIdx.x / kWave];
   Grp g = grp();
   int gid = (int)(((int64_t)xcd_block() * blockDim.x + threadIdx.x) / kG);
   int status = -1;
@@ -2018,7 +2048,7 @@ __global__ void __launch_bounds__(256, 4) k_smooth_g(Store st, const int* __rest
       if (g.j == 0)
         status = (K == 0 ? smooth_laplace(st, v) : (K == 1 ? smooth_gradient(st, v) : smooth_minmax(st, v))) ? 2 : 1;
     } else {
-      bool moved = smooth_group(st, v, h, K, g);
+      bool moved = smooth_group(st, v, h, K, g, lds);
       if (g.j == 0) status = moved ? 2 : 1;
     }
   }
@@ -2431,46 +2461,39 @@ void round_small(const Store& st, const int* cls, int ncol, OpArgs a, Commit cm,
 template <int QK>
 __global__ void __launch_bounds__(256) k_adjoint_g(Store st, double* __restrict__ dQdx, double* __restrict__ dQdM) {
   st.qk = QK;  // the functional as a constant: one instantiation per kind
+  __shared__ __align__(16) double terms[kBlock / kWave][5 * kSumW];
+  double* lds = terms[threadIdx.x / kWave];
   Grp g = grp();
   int v = (int)(((int64_t)xcd_block() * blockDim.x + threadIdx.x) / kG);
   if (v >= st.V) return;
   Hdr h = st.hdr[v];
-  double gx = 0.0, gy = 0.0, ga = 0.0, gb = 0.0, gc = 0.0;
+  double sum = 0.0;  // lane 0, 1: dQ/dx; 2, 3, 4: dQ/dM
   for (int c0 = 0; c0 < h.w; c0 += kG) {
-    int nw = min(kG, h.w - c0);
-    double ex = 0.0, ey = 0.0, da = 0.0, db = 0.0, dc = 0.0;
-    if (g.j < nw) {
+    double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (c0 + g.j < h.w) {
       Elem e = st.tri[st.ne[h.z + c0 + g.j]];
       Geo gg = geo_of(st, e);
-      qgrad_x(gg, slot_of(e, v), st.qk, ex, ey);
-      qgrad_m(gg, st.qk, da, db, dc);
-      da = da / 3.0;
-      db = db / 3.0;
-      dc = dc / 3.0;
+      qgrad_x(gg, slot_of(e, v), st.qk, t[0], t[1]);
+      qgrad_m(gg, st.qk, t[2], t[3], t[4]);
+      t[2] = third(t[2]);
+      t[3] = third(t[3]);
+      t[4] = third(t[4]);
     }
+    // terms past a row's first eight go on from its sum so far
+    if (c0 == 0) {
+      sum = gsum_lane<5>(t, g, lds);
+    } else {
 #pragma unroll
-    for (int k = 0; k < kG; ++k) {
-      double tx = gget(ex, k, g), ty = gget(ey, k, g), ta = gget(da, k, g), tb = gget(db, k, g),
-             tc = gget(dc, k, g);
-      if (k < nw) {
-        gx = gx + tx;
-        gy = gy + ty;
-        ga = ga + ta;
-        gb = gb + tb;
-        gc = gc + tc;
-      }
+      for (int c = 0; c < 5; ++c) lds[c * kSumW + g.base + g.j] = t[c];
+      wave_lds();
+      for (int k = 0; k < kG; ++k) sum = sum + lds[(g.j < 5 ? g.j : 0) * kSumW + g.base + k];
+      wave_lds();
     }
   }
-  if (g.j == 0) {
-    if (dQdx) {
-      dQdx[2 * v] = gx;
-      dQdx[2 * v + 1] = gy;
-    }
-    if (dQdM) {
-      dQdM[3 * v] = ga;
-      dQdM[3 * v + 1] = gb;
-      dQdM[3 * v + 2] = gc;
-    }
+  if (g.j < 2) {
+    if (dQdx) dQdx[2 * (int64_t)v + g.j] = sum;
+  } else if (g.j < 5) {
+    if (dQdM) dQdM[3 * (int64_t)v + g.j - 2] = sum;
   }
 }
 
