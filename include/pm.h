@@ -98,9 +98,8 @@ typedef struct {
                             always in vertex order                              */
   int32_t host_rounds;   /* 0: rounds whose list is coloured by one work-group
                             and whose classes have at most 32 members run
-                            device-driven (each kernel takes its sizes from
-                            device counters, the host reads back every four
-                            rounds); 2: the same, two rounds captured as a
+                            device-driven (one launch runs them one after
+                            another); 2: the same, the launch captured as a
                             graph that the handle keeps and replays while its
                             launch arguments are unchanged; 1: the host drives
                             every round                                         */

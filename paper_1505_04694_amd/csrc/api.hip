@@ -81,7 +81,6 @@ struct pm_mesh {
   DBuf<double> qpart;
   DBuf<double> upd;  // pm_mesh_update: the previous coordinates and metric
   DBuf<uint64_t> rw;  // round words (priority, active, colour) per vertex
-  DBuf<uint64_t> seeds;  // device-driven rounds: the stream seed of every round of the phase
   // mesh ranges (host mirror of Store::vbase/vused/tbase/tused)
   std::vector<int> vbase, vused, tbase, tused;
   int* ranges = nullptr;  // device: vbase[B+1], vused[B], tbase[B+1], tused[B]
@@ -911,55 +910,45 @@ pm_status recover_round(pm_mesh* m, int kind, const Classes& cl, std::vector<int
 }
 
 // Rounds r, r + 1, ... of a phase whose lists fit one work-group, driven by
-// the device: each kernel takes its sizes from the counters, so the host
-// issues rounds without reading anything back. Two rounds (list A -> B -> A)
-// are captured once as a graph, replayed twice per read-back. Round r's
+// the device: one launch runs them one after another, with one read-back
+// (host_rounds 2: the launch replayed from a graph). Round r's
 // classes must be coloured (counters and class lists set). Returns with the
 // round counter, list and length of where the chain stopped: the list empty,
 // the round cap, a list too long for one work-group (r_out's list, not
 // coloured), or a selection that declined (declined: round r_out ran, its
 // next list is not selected; the host selects over every slot, after
 // rebuilding the rows if a commit ran out of room).
+constexpr int kDevRounds = 64;  // rounds of one launch (then a read-back, and the next)
 pm_status device_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind, int phase, int max_rounds, int r,
                         int* r_out, int* n_out, bool* declined) {
   int mode = kind == 0 ? 1 : 2;
   double qmin2 = o->q_min * o->q_min;
-  std::vector<uint64_t> seeds(max_rounds + 1);
-  for (int k = 0; k <= max_rounds; ++k) seeds[k] = stream_seed(m->seed, make_ctx(o->sweep, phase, k));
-  TRY(ensure(m, m->seeds, seeds.size()));
-  HIPCHK(hipMemcpyAsync(m->seeds.p, seeds.data(), sizeof(uint64_t) * seeds.size(), hipMemcpyHostToDevice, m->s));
-  dev_rounds_start(m->ctr, r, m->epoch + 1, m->sel_mark, r >= max_rounds ? 1 : 0, m->s);
   int* L[2] = {m->listA.p, m->listB.p};
-  Round rd{0, m->rw.p, m->seeds.p};
+  Round rd{0, m->rw.p};
   OpArgs a{m->rw.p, 0, rd, o->L_low2, qmin2};
   Commit cm = commit_of(m);
   cm.touched = m->touch.p;
-  auto rounds = [&](hipStream_t q) {
-    for (int k = 0; k < 2; ++k) {
-      const int* A = L[k];
-      int* B = L[k ^ 1];
-      round_small(m->st, m->cls.p, -1, a, cm, kind, m->ctr, q);
-      clear_round_dev(A, m->ctr + C_LIST_B, m->rw.p, q);
-      select_small(m->st, mode, o->L_low2, A, -1, m->touch.p, cm.touched_cap, m->nxt.p, m->seen.p, 0, max_rounds, B,
-                   m->ctr, q);
-      colour_small(m->st, B, 0, m->ctr + C_LIST_B, rd, m->jpU0.p, m->jpU1.p, m->jpB.p, m->cls.p, m->ctr, q);
-    }
-  };
-  // the graph of two rounds is kept while its launch arguments stay the same
-  // (the same store layout, buffers and parameters; the seed table is read
-  // when it runs)
+  DevRounds dr{L[0], L[1], m->cls.p, m->jpU0.p, m->jpU1.p, m->jpB.p, m->seen.p, m->rw.p, m->seed,
+               o->sweep, phase, r & 1, max_rounds, kDevRounds, mode, 1, r, m->epoch + 1, m->sel_mark};
+  if (m->tune.host_rounds == 2) {
+    // a launch that is replayed starts from the counters
+    dev_rounds_start(m->ctr, r, m->epoch + 1, m->sel_mark, r >= max_rounds ? 1 : 0, m->s);
+    dr.start = dr.round = dr.epoch = dr.mark = 0;
+    cm.epoch = 0;
+  }
+  auto rounds = [&](hipStream_t q) { rounds_dev(m->st, dr, a, cm, kind, m->ctr, q); };
+  // the graph is kept while its launch arguments stay the same
+  // (the same store layout, buffers and parameters)
   hipGraphExec_t ge = nullptr;
   if (m->tune.host_rounds == 2) {
     std::string key;
     auto add = [&](const void* p, size_t n) { key.append((const char*)p, n); };
     add(&m->st, sizeof(Store));
-    add(L, sizeof(L));
     add(&a, sizeof(a));
     add(&cm, sizeof(cm));
-    int ints[4] = {kind, mode, max_rounds, 0};
-    add(ints, sizeof(ints));
-    void* ptrs[8] = {m->cls.p, m->ctr, m->nxt.p, m->seen.p, m->jpU0.p, m->jpU1.p, m->jpB.p, m->touch.p};
-    add(ptrs, sizeof(ptrs));
+    add(&dr, sizeof(dr));
+    add(&kind, sizeof(kind));
+    add(&m->ctr, sizeof(m->ctr));
     for (auto& g : m->dr_graphs)
       if (g.first == key) ge = g.second;
     if (!ge) {
@@ -974,11 +963,11 @@ pm_status device_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind,
   pm_status res = PM_OK;
   for (;;) {
     hipError_t e = hipSuccess;
-    for (int k = 0; k < 2 && e == hipSuccess; ++k)
-      timed(m, kind == 0 ? PM_K_COLLAPSE : PM_K_FLIP, 0, [&] {
-        if (ge) e = hipGraphLaunch(ge, m->s);
-        else rounds(m->s);
-      });
+    timed(m, kind == 0 ? PM_K_COLLAPSE : PM_K_FLIP, 0, [&] {
+      if (ge) e = hipGraphLaunch(ge, m->s);
+      else rounds(m->s);
+    });
+    dr.start = 0;
     if (e != hipSuccess) {
       res = fail(m, PM_E_DEVICE, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
       break;
@@ -1113,7 +1102,7 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
     if (small) {
       timed(m, PM_K_SELECT, nA, [&] {
         select_small(m->st, mode, o->L_low2, m->listA.p, nA, m->touch.p, cm.touched_cap, m->nxt.p, m->seen.p,
-                     ++m->sel_mark, max_rounds, m->listB.p, m->ctr, m->s);
+                     ++m->sel_mark, m->listB.p, m->ctr, m->s);
       });
       bool launch = r + 1 < max_rounds;
       if (launch) {
@@ -1272,7 +1261,6 @@ pm_status pm_mesh_destroy(pm_mesh* m) {
   dfree(m, m->qpart.p, m->qpart.n);
   dfree(m, m->upd.p, m->upd.n);
   dfree(m, m->rw.p, m->rw.n);
-  dfree(m, m->seeds.p, m->seeds.n);
   dfree(m, m->own.p, m->own.n);
   dfree(m, m->dirty.p, m->dirty.n);
   dfree(m, m->cnt.p, m->cnt.n);

@@ -211,9 +211,6 @@ __host__ __device__ __forceinline__ bool rw_beats(uint64_t rw_w, int w, uint64_t
 struct Round {
   uint64_t sseed;      // stream seed of this round's priorities
   uint64_t* rw;        // round words
-  // device-driven rounds: the stream seed of round r is seeds[r], r =
-  // ctr[C_DROUND] (null: sseed above)
-  const uint64_t* seeds = nullptr;
 };
 
 // Deferred update by pull: a committing member stamps its operation and
@@ -258,8 +255,6 @@ struct OpArgs {
 
 void set_flags(const int* list, int n, uint8_t* flag, uint8_t val, hipStream_t s);
 void clear_round(const int* list, int n, uint64_t* rw, hipStream_t s);
-// the same with the list length read from the device (*n_dev; nothing when <= 0)
-void clear_round_dev(const int* list, const int* n_dev, uint64_t* rw, hipStream_t s);
 // mode: 0 colour (active flags or all live), 1 coarsen, 2 swap, 3 smooth
 // selected vertices in ascending order, their count to ctr[C_LIST_B];
 // flag/pos: V ints, partial: scan scratch
@@ -289,11 +284,8 @@ void colour_out(const Store& st, const uint64_t* rw, int* out, hipStream_t s);
 // deferred ones carry the next-round flag) and the rows rebuilt, each vertex
 // once (stamp array `seen`, marker `mark`); writes the count to C_LIST_B, or
 // -1 when the rebuilt rows overflowed their list (then select over all slots)
-// nA < 0: device-driven round (length ctr[C_LIST_B], stamp ctr[C_DMARK] + 1;
-// at the end the round counter advances and C_DSTOP is raised when the list
-// is empty or max_rounds is reached; nothing runs while C_DSTOP is set)
 void select_small(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
-                  uint8_t* nxt, int* seen, int mark, int max_rounds, int* out, int* ctr, hipStream_t s);
+                  uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s);
 // lists up to kSmallColour entries: colouring and class lists in one block;
 // writes class sizes, offsets and count like class_lists, iterations to C_TOTAL
 constexpr int kSmallColour = 8192;
@@ -324,9 +316,20 @@ void class_small(const Store& st, const int* list, int n, OpArgs a, Commit cm, i
 // all ncol classes of a round (every one of at most kSmallClass members) in one
 // block: class c with epoch cm.epoch + c, size and offset from ctr[C_HIST + c],
 // ctr[C_OFF + c] (a.cls is ignored)
-// ncol < 0: device-driven round (ncol = ctr[C_NCOL], epochs from C_DEPOCH,
-// nothing while C_DSTOP is set)
 void round_small(const Store& st, const int* cls, int ncol, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s);
+
+// Device-driven rounds in one launch (see k_rounds_dev). The list of round r is
+// L0 where r and par have the same parity. start: the counters begin at round,
+// epoch and mark (else they go on from where they are). Priorities are drawn
+// from (seed, sweep, phase, round).
+struct DevRounds {
+  int *L0, *L1, *cls, *W0, *W1, *WB, *seen;
+  uint64_t* rw;
+  uint64_t seed;
+  int sweep, phase, par, max_rounds, budget, mode;
+  int start, round, epoch, mark;
+};
+void rounds_dev(const Store& st, const DevRounds& d, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s);
 
 void quality_sum(const Store& st, double* psum, double* pmin, int nparts, double* out2, hipStream_t s);
 void quality_adjoint(const Store& st, double* dQdx, double* dQdM, hipStream_t s);

@@ -30,14 +30,6 @@ __global__ void k_clear_round(const int* __restrict__ list, int n, uint64_t* __r
 void clear_round(const int* list, int n, uint64_t* rw, hipStream_t s) {
   if (n > 0) k_clear_round<<<grid_for(n), kBlock, 0, s>>>(list, n, rw);
 }
-__global__ void k_clear_round_dev(const int* __restrict__ list, const int* n_dev, uint64_t* __restrict__ rw) {
-  int n = *n_dev;
-  for (int i = gtid(); i < n; i += gstride()) rw[list[i]] = 0;
-}
-void clear_round_dev(const int* list, const int* n_dev, uint64_t* rw, hipStream_t s) {
-  k_clear_round_dev<<<grid_for(kSmallColour), kBlock, 0, s>>>(list, n_dev, rw);
-}
-
 // ---- flags and lists -----------------------------------------------------------------
 __global__ void k_set_flags(const int* __restrict__ list, int n, uint8_t* __restrict__ flag, uint8_t val) {
   for (int i = gtid(); i < n; i += gstride()) flag[list[i]] = val;
@@ -451,152 +443,156 @@ void class_lists(const int* A, int n, const uint64_t* rw, int* ctr, int* out, in
 // launch. Classes come out in no particular order; the members of a class
 // are an independent set, so their order does not change any result.
 constexpr int kSmallThreads = 1024;
-__global__ void __launch_bounds__(kSmallThreads) k_colour_small(Store st, const int* __restrict__ A, int n,
-                                                              const int* n_dev, Round rd, int* W0, int* W1, int* WB,
-                                                              int* __restrict__ out, int* ctr) {
-  __shared__ int nwait, hist[256], cur[256];
+struct ColourLds {
+  int nwait, ncol;
+  int hist[256], cur[256];
+  int wsum[4];
+};
+// The n vertices of A, by the NT threads of the block. Returns the size of
+// the largest class, and the number of iterations in *its (-1: given up).
+// The class offsets are a scan by 256 threads: one thread adding them up one
+// after another took 8 us, half of the colouring of some hundred vertices.
+template <int NT>
+__device__ __forceinline__ int colour_body(const Store& st, const int* A, int n, const Round& rd, int* W0,
+                                           int* W1, int* WB, int* out, int* ctr, ColourLds& L, int* its) {
   int tid = (int)threadIdx.x;
-  if (n_dev) {
-    // the list length from the device (a colouring launched ahead of the
-    // read-back); a list this kernel does not take is reported as -1 colours
-    // a device-driven chain that has stopped leaves the counters as they
-    // are (they describe the round that ran last)
-    if (rd.seeds && ctr[C_DSTOP]) return;
-    n = *n_dev;
-    if (n < 0 || n > kSmallColour) {
-      __syncthreads();
-      if (tid == 0) {
-        ctr[C_NCOL] = -1;
-        if (rd.seeds) ctr[C_DSTOP] = 1;  // a device-driven chain ends here
-      }
-      return;
-    }
-  }
-  if (rd.seeds) rd.sseed = rd.seeds[ctr[C_DROUND]];
-  for (int i = tid; i < n; i += kSmallThreads) {
+  for (int i = tid; i < n; i += NT) {
     int v = A[i];
     uint64_t prio = key_of(st, rd, v) >> 32;
     rd.rw[v] = (prio << 32) | kRwAct | 0xFFull;
   }
-  if (tid < 256) hist[tid] = 0;
+  if (tid < 256) L.hist[tid] = 0;
+  if (tid == 0) L.ncol = 0;
   __syncthreads();
   const int* in = A;
   int nw = n, it = 0, visited = 0;
   while (nw > 0) {
-    if (tid == 0) nwait = 0;
+    if (tid == 0) L.nwait = 0;
     __syncthreads();
     int* wout = (it & 1) ? W1 : W0;
     const int* bin = WB + ((it & 1) ? 0 : kSmallColour);  // blockers beside the entries read
     int* bout = WB + ((it & 1) ? kSmallColour : 0);
-    for (int i = tid; i < nw; i += kSmallThreads) {
+    for (int i = tid; i < nw; i += NT) {
       int v = in[i];
       int bl = it > 0 ? bin[i] : -1;
       if (!jp_try(st, v, rd, ctr, bl)) {
-        int k = atomicAdd(&nwait, 1);
+        int k = atomicAdd(&L.nwait, 1);
         wout[k] = v;
         bout[k] = bl;
       }
     }
     __syncthreads();
     visited += nw;
-    nw = nwait;
+    nw = L.nwait;
     in = wout;
     ++it;
     __syncthreads();
     if (it > 4 * kMaxColours + n) {  // cannot happen: the largest waiting key is always ready
       if (tid == 0) atomicOr(&ctr[C_ERR], E_COLOURS);
-      return;
+      *its = -1;
+      return 0;
     }
   }
-  for (int i = tid; i < n; i += kSmallThreads) atomicAdd(&hist[(int)(rd.rw[A[i]] & 0xFF)], 1);
+  for (int i = tid; i < n; i += NT) atomicAdd(&L.hist[(int)(rd.rw[A[i]] & 0xFF)], 1);
   __syncthreads();
+  int h = tid < 256 ? L.hist[tid] : 0, incl = h, lane = __lane_id();
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    int o = __shfl_up(incl, d);
+    if (lane >= d) incl += o;
+  }
+  if (tid < 256 && lane == kWave - 1) L.wsum[tid / kWave] = incl;
+  if (h) atomicMax(&L.ncol, tid + 1);
+  int big = h;
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) big = max(big, __shfl_xor(big, d));
+  __syncthreads();
+  if (tid < 256) {
+    int o = incl - h;
+    for (int w = 0; w < tid / kWave; ++w) o += L.wsum[w];
+    L.cur[tid] = o;
+    ctr[C_OFF + tid] = o;
+    ctr[C_HIST + tid] = h;
+  }
   if (tid == 0) {
-    int o = 0, ncol = 0;
-    for (int c = 0; c < 256; ++c) {
-      cur[c] = o;
-      ctr[C_OFF + c] = o;
-      ctr[C_HIST + c] = hist[c];
-      o += hist[c];
-      if (hist[c]) ncol = c + 1;
-    }
-    ctr[C_NCOL] = ncol;
+    L.nwait = 0;
+    ctr[C_NCOL] = L.ncol;
     ctr[C_JP] = 0;
     ctr[C_TOUCH] = 0;
     ctr[C_TOTAL] = it;
     atomicAdd(ctr + C_STRIPE + S_PJP, visited);
-    if (rd.seeds) {
-      // a device-driven chain takes rounds whose classes all fit one block's
-      // pass; a larger class ends it here, coloured, for the host to run
-      // (and count)
-      bool big = false;
-      for (int c = 0; c < ncol; ++c) big |= hist[c] > kSmallClass;
-      if (big) {
-        ctr[C_DSTOP] = 1;
-      } else {
-        ctr[C_ACC_COL] += n;
-        ctr[C_ACC_NCOL] += ncol;
-        ctr[C_ACC_IT] += it;
-      }
-    }
   }
   __syncthreads();
-  for (int i = tid; i < n; i += kSmallThreads) {
+  if (tid < 256 && lane == 0) atomicMax(&L.nwait, big);
+  for (int i = tid; i < n; i += NT) {
     int v = A[i];
-    out[atomicAdd(&cur[(int)(rd.rw[v] & 0xFF)], 1)] = v;
+    out[atomicAdd(&L.cur[(int)(rd.rw[v] & 0xFF)], 1)] = v;
   }
+  __syncthreads();
+  *its = it;
+  return L.nwait;
+}
+
+__global__ void __launch_bounds__(kSmallThreads) k_colour_small(Store st, const int* __restrict__ A, int n,
+                                                              const int* n_dev, Round rd, int* W0, int* W1, int* WB,
+                                                              int* __restrict__ out, int* ctr) {
+  __shared__ ColourLds L;
+  if (n_dev) {
+    // the list length from the device (a colouring launched ahead of the
+    // read-back); a list this kernel does not take is reported as -1 colours
+    n = *n_dev;
+    if (n < 0 || n > kSmallColour) {
+      if (threadIdx.x == 0) ctr[C_NCOL] = -1;
+      return;
+    }
+  }
+  int its;
+  colour_body<kSmallThreads>(st, A, n, rd, W0, W1, WB, out, ctr, L, &its);
 }
 void colour_small(const Store& st, const int* A, int n, const int* n_dev, Round rd, int* W0, int* W1, int* WB,
                   int* out, int* ctr, hipStream_t s) {
   k_colour_small<<<1, kSmallThreads, 0, s>>>(st, A, n, n_dev, rd, W0, W1, WB, out, ctr);
 }
 
+// The vertices to act on next, from the members A and the rows rebuilt, each
+// once; returns their number (every thread of the block makes this call).
+template <int NT>
+__device__ __forceinline__ int select_body(const Store& st, int mode, double L_low2, const int* A, int nA,
+                                           const int* touched, int nt, uint8_t* nxt, int* seen, int mark, int* out,
+                                           int* cnt) {
+  if (threadIdx.x == 0) *cnt = 0;
+  __syncthreads();
+  for (int i = (int)threadIdx.x; i < nA + nt; i += NT) {
+    int x = i < nA ? A[i] : touched[i - nA];
+    if (!nxt[x] || atomicMax(&seen[x], mark) >= mark) continue;
+    nxt[x] = 0;
+    if (want(st, x, mode, L_low2, nullptr)) out[atomicAdd(cnt, 1)] = x;
+  }
+  __syncthreads();
+  int n = *cnt;
+  __syncthreads();
+  return n;
+}
+
 __global__ void __launch_bounds__(kSmallThreads) k_select_small(Store st, int mode, double L_low2,
                                                                const int* __restrict__ A, int nA,
                                                                const int* __restrict__ touched, int cap,
                                                                uint8_t* __restrict__ nxt, int* __restrict__ seen,
-                                                               int mark, int max_rounds, int* __restrict__ out,
-                                                               int* ctr) {
+                                                               int mark, int* __restrict__ out, int* ctr) {
   __shared__ int cnt;
-  bool dev = nA < 0;
-  if (dev) {
-    if (ctr[C_DSTOP]) return;
-    nA = ctr[C_LIST_B];
-    mark = ctr[C_DMARK] + 1;
-  }
   int nt = ctr[C_TOUCH];
   if (nt > cap || room_failed(ctr)) {
     // the host selects over every slot (and rebuilds the rows first after a
     // commit that ran out of room)
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      ctr[C_LIST_B] = -1;
-      if (dev) ctr[C_DSTOP] = 1;
-    }
+    if (threadIdx.x == 0) ctr[C_LIST_B] = -1;
     return;
   }
-  if (threadIdx.x == 0) cnt = 0;
-  __syncthreads();
-  for (int i = (int)threadIdx.x; i < nA + nt; i += kSmallThreads) {
-    int x = i < nA ? A[i] : touched[i - nA];
-    if (!nxt[x] || atomicMax(&seen[x], mark) >= mark) continue;
-    nxt[x] = 0;
-    if (want(st, x, mode, L_low2, nullptr)) out[atomicAdd(&cnt, 1)] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    ctr[C_LIST_B] = cnt;
-    if (dev) {
-      int r = ctr[C_DROUND] + 1;
-      ctr[C_DROUND] = r;
-      ctr[C_DMARK] = mark;
-      if (cnt == 0 || r >= max_rounds) ctr[C_DSTOP] = 1;
-    }
-  }
+  int n = select_body<kSmallThreads>(st, mode, L_low2, A, nA, touched, nt, nxt, seen, mark, out, &cnt);
+  if (threadIdx.x == 0) ctr[C_LIST_B] = n;
 }
 void select_small(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
-                  uint8_t* nxt, int* seen, int mark, int max_rounds, int* out, int* ctr, hipStream_t s) {
-  k_select_small<<<1, kSmallThreads, 0, s>>>(st, mode, L_low2, A, nA, touched, cap, nxt, seen, mark, max_rounds,
-                                             out, ctr);
+                  uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s) {
+  k_select_small<<<1, kSmallThreads, 0, s>>>(st, mode, L_low2, A, nA, touched, cap, nxt, seen, mark, out, ctr);
 }
 
 __global__ void k_colour_out(int V, const uint64_t* __restrict__ rw, int* __restrict__ out) {
@@ -1165,37 +1161,38 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
   if (G == 16 && act && l == 0) cm.nxt[x] = 1;  // a row's first visit flags it for the next round
 }
 
-// LDS of a block's row rebuilds
+// LDS of a block's row rebuilds (NT threads)
+template <int NT>
 struct RowLds {
-  int slots[3 * kBlock];  // 3 per lane: the candidates of the rows in flight
+  int slots[3 * NT];      // 3 per lane: the candidates of the rows in flight
   int bq[kBlock];         // rows of more than 16 of anything
   int bqn;
 };
-// Rebuild the n rows row(0 .. n - 1) with the kBlock threads of the block, 16
+// Rebuild the n rows row(0 .. n - 1) with the NT threads of the block, 16
 // lanes each (every thread makes this call; bqn is zero). In small rounds the
 // rows are listed for the next selection.
-template <bool F, class Row>
-__device__ __forceinline__ void rebuild_rows(const Store& st, const Commit& cm, int n, Row&& row, RowLds& L, int* ctr,
-                                             int& rows) {
+template <bool F, int NT, class Row>
+__device__ __forceinline__ void rebuild_rows(const Store& st, const Commit& cm, int n, Row&& row, RowLds<NT>& L,
+                                             int* ctr, int& rows) {
   constexpr int G = 16;
   int tid = (int)threadIdx.x, g = tid / G;
   if (cm.touched && n > 0) {
     __shared__ int tb;
     if (tid == 0) tb = atomicAdd(&ctr[C_TOUCH], n);
     __syncthreads();
-    for (int i = tid; i < n; i += kBlock)
+    for (int i = tid; i < n; i += NT)
       if (tb + i < cm.touched_cap) cm.touched[tb + i] = row(i);
     __syncthreads();
   }
-  for (int r0 = 0; r0 < n; r0 += kBlock / G)
+  for (int r0 = 0; r0 < n; r0 += NT / G)
     rebuild_group<F, G>(st, cm, r0 + g < n ? row(r0 + g) : -1, L.slots + 3 * G * g, ctr, L.bq, &L.bqn, rows);
 }
 // the queued rows, one per wavefront
-template <bool F>
-__device__ __forceinline__ void rebuild_queued(const Store& st, const Commit& cm, RowLds& L, int* ctr, int& rows) {
+template <bool F, int NT>
+__device__ __forceinline__ void rebuild_queued(const Store& st, const Commit& cm, RowLds<NT>& L, int* ctr, int& rows) {
   __syncthreads();
   int nbig = min(L.bqn, kBlock), wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  for (int b = wv; b < nbig; b += kBlock / kWave)
+  for (int b = wv; b < nbig; b += NT / kWave)
     rebuild_group<F, kWave>(st, cm, L.bq[b], L.slots + 3 * kWave * wv, ctr, nullptr, nullptr, rows);
 }
 // the rows rebuilt by this wavefront, into the counters
@@ -1210,6 +1207,7 @@ __device__ __forceinline__ void count_rows(int rows, int* ctr) {
 }
 
 // block-wide exclusive scan of one int per thread; returns the block total
+template <int NT>
 __device__ __forceinline__ int block_scan(int x, int& excl, int* wsum) {
   int lane = __lane_id(), wv = (int)threadIdx.x / kWave;
   int incl = x;
@@ -1222,7 +1220,7 @@ __device__ __forceinline__ int block_scan(int x, int& excl, int* wsum) {
   __syncthreads();
   int before = 0, total = 0;
 #pragma unroll
-  for (int q = 0; q < kBlock / kWave; ++q) {
+  for (int q = 0; q < NT / kWave; ++q) {
     int c = wsum[q];
     total += c;
     if (q < wv) before += c;
@@ -1233,26 +1231,27 @@ __device__ __forceinline__ int block_scan(int x, int& excl, int* wsum) {
 
 // LDS of one commit block
 constexpr int kPairB = 8;  // neighbours per member taken per pair round (two 16-byte loads)
+template <int NT>
 struct CommitLds {
-  RowLds rows;
-  int q[kPairB * kBlock];       // rows queued in a pair round
-  int wsum[kBlock / kWave];
+  RowLds<NT> rows;
+  int q[kPairB * NT];       // rows queued in a pair round
+  int wsum[NT / kWave];
 };
 
 // Rebuild the rows claimed by the committed members list[base .. base + cnt)
-// (cnt <= kBlock), with all kBlock threads of the block. Each member has tpm
+// (cnt <= NT), with all NT threads of the block. Each member has tpm
 // threads (a power of two: as many as fit, so a block of few members spreads
 // each member's neighbours over its threads); a thread takes kPairB of its
 // member's neighbours per pair round (row entries, then owner keys, loaded
 // side by side). The rows a member owns are queued in LDS in block order and
 // rebuilt, 16 lanes each. For flips one more round queues the members' own
 // rows, after the rounds that read the members' rows.
-template <bool F>
+template <bool F, int NT>
 __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restrict__ list, int base, int cnt,
-                                             const Commit& cm, int* ctr, CommitLds& L) {
+                                             const Commit& cm, int* ctr, CommitLds<NT>& L) {
   int tid = (int)threadIdx.x;
   int lg = 0;
-  while ((cnt << (lg + 1)) <= kBlock) ++lg;
+  while ((cnt << (lg + 1)) <= NT) ++lg;
   int mi = tid >> lg, sl = tid & ((1 << lg) - 1);
   int v = -1, deg = 0, off = 0;
   bool com = false;
@@ -1293,14 +1292,14 @@ __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restr
 #pragma unroll
     for (int q = 0; q < kPairB; ++q) mine += (y[q] >= 0 && k[q] == key) ? 1 : 0;
     int at;
-    int tot = block_scan(mine, at, L.wsum);
+    int tot = block_scan<NT>(mine, at, L.wsum);
 #pragma unroll
     for (int q = 0; q < kPairB; ++q)
       if (y[q] >= 0 && k[q] == key) L.q[at++] = y[q];
     __syncthreads();
-    rebuild_rows<F>(st, cm, tot, [&](int i) { return L.q[i]; }, L.rows, ctr, rows);
+    rebuild_rows<F, NT>(st, cm, tot, [&](int i) { return L.q[i]; }, L.rows, ctr, rows);
   }
-  rebuild_queued<F>(st, cm, L.rows, ctr, rows);
+  rebuild_queued<F, NT>(st, cm, L.rows, ctr, rows);
   count_rows(rows, ctr);
   __syncthreads();  // the LDS is reused by the next chunk
 }
@@ -1310,10 +1309,10 @@ __device__ __forceinline__ void commit_chunk(const Store& st, const int* __restr
 template <bool F>
 __global__ void __launch_bounds__(256, 5) k_commit(Store st, const int* __restrict__ list, int n, int mpb, Commit cm,
                                                 int* ctr) {
-  __shared__ CommitLds L;
+  __shared__ CommitLds<kBlock> L;
   if (room_failed_block(ctr)) return;  // other blocks may set it meanwhile: one answer per block
   int base = xcd_block() * mpb;
-  commit_chunk<F>(st, list, base, min(mpb, n - base), cm, ctr, L);
+  commit_chunk<F, kBlock>(st, list, base, min(mpb, n - base), cm, ctr, L);
 }
 
 // The same rebuild in vertex order, for classes whose claimed rows cover a
@@ -1328,7 +1327,7 @@ __global__ void __launch_bounds__(256, 5) k_commit(Store st, const int* __restri
 constexpr int kSweepStep = kPairB * kBlock;  // slots scanned per block-wide pass
 constexpr int kSweepMax = 2 * kSweepStep;    // most slots per work-group (16-bit offsets in LDS)
 struct SweepLds {
-  RowLds rows;
+  RowLds<kBlock> rows;
   uint16_t q[kSweepMax];
   int wsum[kBlock / kWave];
 };
@@ -1360,7 +1359,7 @@ __global__ void __launch_bounds__(256, 5) k_commit_sweep(Store st, Commit cm, in
       }
     }
     int at;
-    int tot = block_scan(mine, at, L.wsum);
+    int tot = block_scan<kBlock>(mine, at, L.wsum);
     at += qn;
 #pragma unroll
     for (int q = 0; q < kPairB; ++q)
@@ -1371,8 +1370,8 @@ __global__ void __launch_bounds__(256, 5) k_commit_sweep(Store st, Commit cm, in
   if (tid == 0) L.rows.bqn = 0;
   __syncthreads();
   int rows = 0;
-  rebuild_rows<F>(st, cm, qn, [&](int i) { return base + (int)L.q[i]; }, L.rows, ctr, rows);
-  rebuild_queued<F>(st, cm, L.rows, ctr, rows);
+  rebuild_rows<F, kBlock>(st, cm, qn, [&](int i) { return base + (int)L.q[i]; }, L.rows, ctr, rows);
+  rebuild_queued<F, kBlock>(st, cm, L.rows, ctr, rows);
   count_rows(rows, ctr);
 }
 
@@ -2373,13 +2372,15 @@ void flip_class_g(const Store& st, const int* list, int n, OpArgs a, Commit cm, 
 // A small class in one block: the operation (collapse or flips on groups of
 // kGC lanes per member), a block barrier, then the commit of the same
 // members. Every thread reaches every barrier.
+constexpr int kClassThreads = 512;
 template <bool F>
-__device__ __forceinline__ void class_body(const Store& st, const int* __restrict__ list, int n, const OpArgs& a,
-                                           const Commit& cm, int* ctr, CommitLds& L) {
+__device__ __forceinline__ void class_body(const Store& st, const int* list, int n, const OpArgs& a,
+                                           const Commit& cm, int* ctr, CommitLds<kClassThreads>& L) {
+  constexpr int NT = kClassThreads;
   int tid = (int)threadIdx.x;
   if (tid == 0) ctr[C_STAGE] = 0;  // the commit's fallback staging
   Grp g = grp_of<kGC>();
-  for (int p0 = 0; p0 < n; p0 += kBlock / kGC) {
+  for (int p0 = 0; p0 < n; p0 += NT / kGC) {
     int gid = p0 + tid / kGC;
     int status = -1;
     if (gid < n) {
@@ -2395,51 +2396,34 @@ __device__ __forceinline__ void class_body(const Store& st, const int* __restric
     count_status(status, ctr);
   }
   __syncthreads();
-  for (int base = 0; base < n; base += kBlock) commit_chunk<F>(st, list, base, min(kBlock, n - base), cm, ctr, L);
+  for (int base = 0; base < n; base += NT) commit_chunk<F, NT>(st, list, base, min(NT, n - base), cm, ctr, L);
 }
 
 // one small class, one launch instead of two
 template <bool F, int QK>
-__global__ void __launch_bounds__(256) k_class_small(Store st, const int* __restrict__ list, int n, OpArgs a,
-                                                     Commit cm, int* ctr) {
+__global__ void __launch_bounds__(kClassThreads) k_class_small(Store st, const int* __restrict__ list, int n, OpArgs a,
+                                                               Commit cm, int* ctr) {
   st.qk = QK;  // the functional as a constant: one instantiation per kind
-  __shared__ CommitLds L;
+  __shared__ CommitLds<kClassThreads> L;
   if (room_failed_block(ctr)) return;
   class_body<F>(st, list, n, a, cm, ctr, L);
 }
 void class_small(const Store& st, const int* list, int n, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s) {
   if (n <= 0) return;
-  if (kind)
-    (st.qk ? k_class_small<true, 1> : k_class_small<true, 0>)<<<1, kBlock, 0, s>>>(st, list, n, a, cm, ctr);
-  else
-    (st.qk ? k_class_small<false, 1> : k_class_small<false, 0>)<<<1, kBlock, 0, s>>>(st, list, n, a, cm, ctr);
+  auto k = kind ? (st.qk ? k_class_small<true, 1> : k_class_small<true, 0>)
+                : (st.qk ? k_class_small<false, 1> : k_class_small<false, 0>);
+  k<<<1, kClassThreads, 0, s>>>(st, list, n, a, cm, ctr);
 }
 
 // Every class of a round in one block, one after the other (a round whose
-// classes are all small): class c takes epoch cm.epoch + c and its size and
-// offset from the colouring's counters. One launch per round instead of one
-// per class, and the block's caches stay warm from class to class.
-template <bool F, int QK>
-__global__ void __launch_bounds__(256) k_round_small(Store st, const int* __restrict__ cls, int ncol, OpArgs a,
-                                                     Commit cm, int* ctr) {
-  st.qk = QK;  // the functional as a constant: one instantiation per kind
-  __shared__ CommitLds L;
-  int epoch0 = cm.epoch;
-  bool dev = ncol < 0;
-  if (dev) {
-    if (ctr[C_DSTOP]) return;
-    ncol = ctr[C_NCOL];
-    epoch0 = ctr[C_DEPOCH];
-    __syncthreads();  // every thread has read the counters before they change
-    if (threadIdx.x == 0) {
-      ctr[C_DEPOCH0] = epoch0;
-      ctr[C_DEPOCH] = epoch0 + max(ncol, 0);
-    }
-  }
+// classes are all small): class c takes epoch epoch0 + c and its size and
+// offset from the colouring's counters. Returns false when a commit ran out
+// of room: the host rebuilds the rows and runs the remaining classes.
+template <bool F>
+__device__ __forceinline__ bool round_body(const Store& st, const int* cls, int ncol, int epoch0,
+                                           const OpArgs& a, const Commit& cm, int* ctr, CommitLds<kClassThreads>& L) {
   for (int c = 0; c < ncol; ++c) {
-    // a commit of this block may have run out of room: stop, the host
-    // rebuilds the rows and runs the remaining classes
-    if (room_failed_block(ctr)) return;
+    if (room_failed_block(ctr)) return false;
     int n = ctr[C_HIST + c], off = ctr[C_OFF + c];
     if (n == 0) continue;
     Commit cc = cm;
@@ -2448,13 +2432,119 @@ __global__ void __launch_bounds__(256) k_round_small(Store st, const int* __rest
     ac.cls = c;
     class_body<F>(st, cls + off, n, ac, cc, ctr, L);
   }
+  return !room_failed_block(ctr);
+}
+
+// One launch per round instead of one per class, and the block's caches stay
+// warm from class to class.
+template <bool F, int QK>
+__global__ void __launch_bounds__(kClassThreads) k_round_small(Store st, const int* __restrict__ cls, int ncol, OpArgs a,
+                                                               Commit cm, int* ctr) {
+  st.qk = QK;  // the functional as a constant: one instantiation per kind
+  __shared__ CommitLds<kClassThreads> L;
+  round_body<F>(st, cls, ncol, cm.epoch, a, cm, ctr, L);
 }
 void round_small(const Store& st, const int* cls, int ncol, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s) {
   if (ncol == 0) return;
-  if (kind)
-    (st.qk ? k_round_small<true, 1> : k_round_small<true, 0>)<<<1, kBlock, 0, s>>>(st, cls, ncol, a, cm, ctr);
-  else
-    (st.qk ? k_round_small<false, 1> : k_round_small<false, 0>)<<<1, kBlock, 0, s>>>(st, cls, ncol, a, cm, ctr);
+  auto k = kind ? (st.qk ? k_round_small<true, 1> : k_round_small<true, 0>)
+                : (st.qk ? k_round_small<false, 1> : k_round_small<false, 0>);
+  k<<<1, kClassThreads, 0, s>>>(st, cls, ncol, a, cm, ctr);
+}
+
+// Rounds driven by the device: from the coloured round ctr[C_DROUND] on, one
+// block runs a round's classes, clears its round words, selects the next
+// list (from list A into list B, then the other way round) and colours it,
+// and goes on until the list is empty, the round cap or the launch's budget of
+// rounds is reached, a selection declines (C_LIST_B = -1), or a list or class
+// is too large for one block (the list is then uncoloured, C_NCOL = -1, or
+// coloured and left to the host). With four launches a round (classes, round
+// words, selection, colouring) the 64 such rounds of a 33 x 33 adaptation took
+// 256 launches and 1.2 ms of kernels; in 16 launches they take 0.59 ms. 512
+// threads: 32 members or rows at a time, against 16 with 256 (the flips' 165
+// registers leave no room for 1024).
+// LDS: the classes' and the colouring's are never in use together.
+template <bool F, int QK>
+__global__ void __launch_bounds__(kClassThreads) k_rounds_dev(Store st, DevRounds d, OpArgs a, Commit cm, int* ctr) {
+  st.qk = QK;  // the functional as a constant: one instantiation per kind
+  constexpr int NT = kClassThreads;
+  __shared__ union {
+    CommitLds<NT> commit;
+    ColourLds colour;
+  } L;
+  __shared__ int cnt;
+  int tid = (int)threadIdx.x;
+  int r = ctr[C_DROUND], stop = ctr[C_DSTOP], epoch = ctr[C_DEPOCH], epoch0 = ctr[C_DEPOCH0], mark = ctr[C_DMARK];
+  int n = ctr[C_LIST_B], ncol = ctr[C_NCOL];
+  int acc_col = ctr[C_ACC_COL], acc_ncol = ctr[C_ACC_NCOL], acc_it = ctr[C_ACC_IT];
+  if (d.start) {
+    r = d.round;
+    epoch = epoch0 = d.epoch;
+    mark = d.mark;
+    stop = r >= d.max_rounds ? 1 : 0;
+    acc_col = acc_ncol = acc_it = 0;
+  }
+  __syncthreads();  // every thread has read the counters before they change
+  for (int k = 0; k < d.budget && !stop; ++k) {
+    const int* A = (r ^ d.par) & 1 ? d.L1 : d.L0;
+    int* B = (r ^ d.par) & 1 ? d.L0 : d.L1;
+    epoch0 = epoch;
+    epoch += ncol;
+    bool room = round_body<F>(st, d.cls, ncol, epoch0, a, cm, ctr, L.commit);
+    for (int i = tid; i < n; i += NT) d.rw[A[i]] = 0;
+    int nt = __hip_atomic_load(&ctr[C_TOUCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!room || nt > cm.touched_cap) {
+      n = -1;
+      stop = 1;
+      break;
+    }
+    n = select_body<NT>(st, d.mode, a.L_low2, A, n, cm.touched, nt, cm.nxt, d.seen, ++mark, B, &cnt);
+    ++r;
+    if (n == 0 || r >= d.max_rounds) {
+      ncol = 0;
+      stop = 1;
+      break;
+    }
+    if (n > kSmallColour) {
+      ncol = -1;
+      stop = 1;
+      break;
+    }
+    Round rd{stream_seed(d.seed, make_ctx(d.sweep, d.phase, r)), d.rw};
+    int its;
+    int big = colour_body<NT>(st, B, n, rd, d.W0, d.W1, d.WB, d.cls, ctr, L.colour, &its);
+    ncol = L.colour.ncol;
+    __syncthreads();
+    if (its < 0) {
+      stop = 1;
+      break;
+    }
+    if (big > kSmallClass) {
+      // the host runs this round, coloured as it is (and counts it)
+      stop = 1;
+      break;
+    }
+    acc_col += n;
+    acc_ncol += ncol;
+    acc_it += its;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    ctr[C_DROUND] = r;
+    ctr[C_DEPOCH] = epoch;
+    ctr[C_DEPOCH0] = epoch0;
+    ctr[C_DMARK] = mark;
+    ctr[C_DSTOP] = stop;
+    ctr[C_LIST_B] = n;
+    ctr[C_NCOL] = ncol;
+    ctr[C_ACC_COL] = acc_col;
+    ctr[C_ACC_NCOL] = acc_ncol;
+    ctr[C_ACC_IT] = acc_it;
+  }
+}
+void rounds_dev(const Store& st, const DevRounds& d, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s) {
+  auto k = kind ? (st.qk ? k_rounds_dev<true, 1> : k_rounds_dev<true, 0>)
+                : (st.qk ? k_rounds_dev<false, 1> : k_rounds_dev<false, 0>);
+  k<<<1, kClassThreads, 0, s>>>(st, d, a, cm, ctr);
 }
 
 // ---- adjoint with lane groups ---------------------------------------------------------------------
