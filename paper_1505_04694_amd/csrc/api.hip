@@ -78,6 +78,7 @@ struct pm_mesh {
   DBuf<int> cnt;         // commit: hand-overs counted per row
   DBuf<int4> tgt;        // commit: collapse-target records
   int epoch = 0;         // commit epoch, one per class
+  DBuf<JpRec> jprec;  // small colourings: predecessor records
   DBuf<double> qpart;
   DBuf<double> upd;  // pm_mesh_update: the previous coordinates and metric
   DBuf<uint64_t> rw;  // round words (priority, active, colour) per vertex
@@ -558,10 +559,10 @@ pm_status ensure_phase_scratch(pm_mesh* m) {
   TRY(ensure(m, m->listA, V));
   TRY(ensure(m, m->listB, V));
   TRY(ensure(m, m->jpU0, ((size_t)V + kJpChunk - 1) / kJpChunk * kJpChunk));
-  TRY(ensure(m, m->jpB, std::max(((size_t)V + kJpChunk - 1) / kJpChunk * kJpChunk, 2 * (size_t)kSmallColour)));
-  // chunk counts of the chunked JP, or the second waiting list of the small colouring
-  TRY(ensure(m, m->jpU1, std::max((size_t)V / kJpChunk + 1, (size_t)std::min(V, kSmallColour))));
+  TRY(ensure(m, m->jpB, ((size_t)V + kJpChunk - 1) / kJpChunk * kJpChunk));
+  TRY(ensure(m, m->jpU1, (size_t)V / kBlock + 1));  // chunk counts of the chunked JP
   TRY(ensure(m, m->cls, V));
+  TRY(ensure(m, m->jprec, (size_t)std::min(V, kSmallColour)));
   TRY(ensure(m, m->rw, V, true));
   TRY(ensure(m, m->nxt, V, true));
   TRY(ensure(m, m->ops, V, true));
@@ -611,6 +612,7 @@ struct Classes {
 // and are launched in batches between read-backs of the count still waiting;
 // a launch past the end of the work finds only empty chunks.
 constexpr int kJpBatch = 4;
+constexpr int kFinish = 2048;
 
 // the classes of a one-block colouring, from the host copy of the counters
 void small_classes(pm_mesh* m, Classes& out) {
@@ -625,7 +627,7 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
   if (n == 0) return PM_OK;
   if (n <= kSmallColour && !m->tune.small_work) {
     timed(m, PM_K_JP, 0,
-          [&] { colour_small(m->st, A, n, nullptr, rd, m->jpU0.p, m->jpU1.p, m->jpB.p, m->cls.p, m->ctr, m->s); });
+          [&] { colour_small(m->st, A, n, nullptr, n, rd, m->jprec.p, m->cls.p, m->ctr, m->s); });
     TRY(read_ctr(m, 0, C_NCOL + 1));
     TRY(check_err(m, true));
     small_classes(m, out);
@@ -637,16 +639,25 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
   TRY(ensure(m, m->spart, scan_partials_needed(256 * nb) + 2));
   jp_init(m->st, A, n, rd, m->s);
   stripe_zero(m->ctr, S_JPL, 8, m->s);
+  bool finish = !m->tune.small_work;
   int it = 0;
   for (;;) {
     // first batch: as many iterations as the last colouring needed, so that
     // most colourings need one read-back; the class lists are cut before
     // that read-back, which then also returns them (cut again if the
     // colouring was not finished)
-    int batch = it == 0 ? std::min(std::max(m->jp_last, kJpBatch), 64) : kJpBatch;
+    // (with the one-block finish: until few enough wait for it)
+    int batch = it == 0 ? std::min(std::max(m->jp_last, finish ? 1 : kJpBatch), 64) : kJpBatch;
     for (int b = 0; b < batch; ++b, ++it)
       timed(m, PM_K_JP, 0,
             [&] { jp_chunk(m->st, A, n, m->jpU0.p, m->jpB.p, m->jpU1.p, it == 0, rd, m->ctr, it, m->s); });
+    if (finish) {
+      // what every iteration of the last eight left, then the rest
+      stripe_sum(m->ctr, S_JPL, 8, C_JPL, m->s);
+      timed(m, PM_K_JP, 0, [&] {
+        jp_finish(m->st, n, m->jpU0.p, m->jpU1.p, rd, m->jprec.p, m->cls.p, m->ctr, it - 1, m->s);
+      });
+    }
     stripe_sum(m->ctr, S_JPL + ((it - 1) & 7), 1, C_JP, m->s);
     m->class_seq = m->class_seq >= 0x3FFFFFFF ? 1 : m->class_seq + 1;
     class_lists(A, n, rd.rw, m->ctr, m->cls.p, m->ctab.p, m->ctabs.p, m->spart.p,
@@ -662,7 +673,14 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
     TRY(read_ctr(m, 0, C_NCOL + 1));
   }
   out.jp_iters = it;
+  // the iterations to run before the finish next time: until no more than
+  // kFinish wait (the counts of the last seven are there; a further iteration
+  // takes 7 us, solving 8,000 vertices 60 and 2,000 vertices 15); without the
+  // finish, all
   m->jp_last = it;
+  if (finish)
+    while (m->jp_last > 1 && it - m->jp_last < 6 && m->hctr[C_JPL + ((m->jp_last - 2) & 7)] <= kFinish) --m->jp_last;
+  if (finish && m->jp_last == it && m->hctr[C_JPL + ((it - 1) & 7)] > kFinish) ++m->jp_last;
   TRY(check_err(m, true));
   out.ncol = std::max(m->hctr[C_NCOL], 0);
   out.size.assign(m->hctr + C_HIST, m->hctr + C_HIST + out.ncol);
@@ -903,7 +921,7 @@ pm_status recover_round(pm_mesh* m, int kind, const Classes& cl, std::vector<int
       run_class(m, kind, cl, c, a, cm);
     }
     HIPCHK(hipStreamSynchronize(m->s));  // the offsets' host copy is a local vector
-    clear_round(m->cls.p, listA_n, m->rw.p, m->s);
+    clear_round(m->cls.p, listA_n, m->rw.p, nullptr, m->s);
     TRY(read_ctr(m, 0, kRoundCtrs));
     class_epoch = ep;
   }
@@ -928,7 +946,7 @@ pm_status device_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind,
   OpArgs a{m->rw.p, 0, rd, o->L_low2, qmin2};
   Commit cm = commit_of(m);
   cm.touched = m->touch.p;
-  DevRounds dr{L[0], L[1], m->cls.p, m->jpU0.p, m->jpU1.p, m->jpB.p, m->seen.p, m->rw.p, m->seed,
+  DevRounds dr{L[0], L[1], m->cls.p, m->seen.p, m->rw.p, m->seed,
                o->sweep, phase, r & 1, max_rounds, kDevRounds, mode, 1, r, m->epoch + 1, m->sel_mark};
   if (m->tune.host_rounds == 2) {
     // a launch that is replayed starts from the counters
@@ -1097,19 +1115,18 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
       OpArgs a{m->rw.p, c, rd, o->L_low2, qmin2};
       run_class(m, kind, cl, c, a, cm);
     }
-    clear_round(m->listA.p, nA, m->rw.p, m->s);
+    clear_round(m->listA.p, nA, m->rw.p, m->ctr + C_LIST_B, m->s);
     bool listed = false;
     if (small) {
       timed(m, PM_K_SELECT, nA, [&] {
-        select_small(m->st, mode, o->L_low2, m->listA.p, nA, m->touch.p, cm.touched_cap, m->nxt.p, m->seen.p,
-                     ++m->sel_mark, m->listB.p, m->ctr, m->s);
+        select_list(m->st, mode, o->L_low2, m->listA.p, nA, m->touch.p, cm.touched_cap, m->nxt.p, m->seen.p,
+                    ++m->sel_mark, m->listB.p, m->ctr, m->s);
       });
       bool launch = r + 1 < max_rounds;
       if (launch) {
         Round rn{stream_seed(m->seed, make_ctx(o->sweep, phase, r + 1)), m->rw.p};
         timed(m, PM_K_JP, 0, [&] {
-          colour_small(m->st, m->listB.p, 0, m->ctr + C_LIST_B, rn, m->jpU0.p, m->jpU1.p, m->jpB.p, m->cls.p,
-                       m->ctr, m->s);
+          colour_small(m->st, m->listB.p, 0, m->ctr + C_LIST_B, nA, rn, m->jprec.p, m->cls.p, m->ctr, m->s);
         });
       }
       TRY(read_ctr(m, 0, launch ? C_NCOL + 1 : kRoundCtrs));
@@ -1258,6 +1275,7 @@ pm_status pm_mesh_destroy(pm_mesh* m) {
   dfree(m, m->emet.p, m->emet.n);
   dfree(m, m->vr.p, m->vr.n);
   for (auto* b : ub) dfree(m, b->p, b->n);
+  dfree(m, m->jprec.p, m->jprec.n);
   dfree(m, m->qpart.p, m->qpart.n);
   dfree(m, m->upd.p, m->upd.n);
   dfree(m, m->rw.p, m->rw.n);
@@ -1446,7 +1464,7 @@ pm_status pm_colour(pm_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* co
     HIPCHK(hipMemcpyAsync(colour_out, m->vt0.p, sizeof(int) * st.V,
                           mem_kind == PM_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, m->s));
   }
-  clear_round(m->listA.p, n, m->rw.p, m->s);
+  clear_round(m->listA.p, n, m->rw.p, nullptr, m->s);
   return sync(m);
 }
 
@@ -1526,7 +1544,7 @@ pm_status pm_smooth(pm_mesh* m, const pm_options* o, pm_stats* st) {
       });
   }
   m->st.emet = nullptr;
-  clear_round(m->listA.p, n, m->rw.p, m->s);
+  clear_round(m->listA.p, n, m->rw.p, nullptr, m->s);
   TRY(stats_read(m, st));
   st->v[0] = o->smooth_sweeps;
   st->v[7] = 1;

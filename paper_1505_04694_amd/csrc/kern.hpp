@@ -38,6 +38,8 @@ enum Ctr {
   C_ACC_COL = 24,   // vertices coloured, colours and colouring iterations of the rounds run
   C_ACC_NCOL = 25,
   C_ACC_IT = 26,
+  C_JPN = 31,       // length of the list the one-block finish takes (-1: too many wait)
+  C_JPL = 32,       // 32..39: JP vertices left by iteration modulo 8, before the one-block finish
   C_HIST = 64,      // 64..319: colour histogram (class sizes)
   C_OFF = 320,      // 320..575: class offsets
   C_CUR = 576,      // 576..831: class cursors
@@ -254,7 +256,8 @@ struct OpArgs {
 };
 
 void set_flags(const int* list, int n, uint8_t* flag, uint8_t val, hipStream_t s);
-void clear_round(const int* list, int n, uint64_t* rw, hipStream_t s);
+// zero (or null): an int set to 0
+void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s);
 // mode: 0 colour (active flags or all live), 1 coarsen, 2 swap, 3 smooth
 // selected vertices in ascending order, their count to ctr[C_LIST_B];
 // flag/pos: V ints, partial: scan scratch
@@ -265,13 +268,23 @@ void jp_init(const Store& st, const int* A, int n, Round rd, hipStream_t s);
 // off[c], the device copy of the class offsets) as their colouring set them
 void restore_round(const Store& st, const int* cls, int n, const int* off, int ncol, Round rd, hipStream_t s);
 void dev_rounds_start(int* ctr, int r, int epoch, int mark, int stop, hipStream_t s);
-// One JP iteration over a chunked list: chunk k of kJpChunk slots holds cnt[k]
-// vertices at W[k * kJpChunk ...]; the first iteration reads the n entries of
+// One JP iteration over a chunked list: chunk k of c slots (c = 256, or 512
+// for more than kJpShort vertices) holds cnt[k]
+// vertices at W[k * c ...]; the first iteration reads the n entries of
 // A instead. Waiting vertices are compacted in place, in order, per chunk.
-constexpr int kJpChunk = 512;
+constexpr int kJpChunk = 512, kJpShort = 1 << 19;
 // WB holds, beside each waiting vertex, the neighbour that blocked it
 void jp_chunk(const Store& st, const int* A, int n, int* W, int* WB, int* cnt, bool first, Round rd, int* ctr,
               int it, hipStream_t s);
+// a vertex's predecessors in a small colouring (see ops.hip)
+struct JpRec {
+  uint64_t lo, hi, used;
+  int cnt, pad;
+};
+// what jp_chunk's iteration it left waiting, when that is not more than a small
+// colouring; recs, list: kSmallColour entries of scratch
+void jp_finish(const Store& st, int n, const int* W, const int* cnt, Round rd, JpRec* recs, int* list, int* ctr, int it,
+               hipStream_t s);
 // stable class lists; tab/tabscan: 256 * ceil(n/256) ints each. cm (4,
 // kClassNarrow or 256): the colours the table holds; a list with a colour of
 // cm or more reports C_NCOL = -2 and is to be cut again with cm = 256. seq: a
@@ -284,16 +297,19 @@ void colour_out(const Store& st, const uint64_t* rw, int* out, hipStream_t s);
 // deferred ones carry the next-round flag) and the rows rebuilt, each vertex
 // once (stamp array `seen`, marker `mark`); writes the count to C_LIST_B, or
 // -1 when the rebuilt rows overflowed their list (then select over all slots)
-void select_small(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
-                  uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s);
+void select_list(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
+                 uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s);
 // lists up to kSmallColour entries: colouring and class lists in one block;
 // writes class sizes, offsets and count like class_lists, iterations to C_TOTAL
 constexpr int kSmallColour = 8192;
-// WB: 2 * kSmallColour ints for the blockers of the waiting lists
 // n_dev: when given, the list length is read there instead (n ignored), and a
 // length outside [0, kSmallColour] leaves the list uncoloured with C_NCOL = -1
-void colour_small(const Store& st, const int* A, int n, const int* n_dev, Round rd, int* W0, int* W1, int* WB,
-                  int* out, int* ctr, hipStream_t s);
+// n_about: the length it is expected to have (one launch up to kOneBlock, else
+// three: with a limit of 512 the lists of a 33 x 33 adaptation took 19 us of
+// kernels a colouring instead of 22, but the launches more than that); recs: kSmallColour entries of scratch
+constexpr int kOneBlock = 2048;
+void colour_small(const Store& st, const int* A, int n, const int* n_dev, int n_about, Round rd, JpRec* recs, int* out,
+                  int* ctr, hipStream_t s);
 
 // lanes per member: 1 (one thread), 8 or 16
 void collapse_class(const Store& st, const int* list, int n, OpArgs a, Commit cm, int* ctr, int lanes,
@@ -323,7 +339,7 @@ void round_small(const Store& st, const int* cls, int ncol, OpArgs a, Commit cm,
 // epoch and mark (else they go on from where they are). Priorities are drawn
 // from (seed, sweep, phase, round).
 struct DevRounds {
-  int *L0, *L1, *cls, *W0, *W1, *WB, *seen;
+  int *L0, *L1, *cls, *seen;
   uint64_t* rw;
   uint64_t seed;
   int sweep, phase, par, max_rounds, budget, mode;

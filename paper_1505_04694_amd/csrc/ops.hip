@@ -24,11 +24,12 @@ __device__ __forceinline__ uint64_t key_of(const Store& st, const Round& rd, int
 }
 __device__ __forceinline__ void rw_put(uint64_t* rw, int v, uint64_t x) { ((volatile uint64_t*)rw)[v] = x; }
 
-__global__ void k_clear_round(const int* __restrict__ list, int n, uint64_t* __restrict__ rw) {
+__global__ void k_clear_round(const int* __restrict__ list, int n, uint64_t* __restrict__ rw, int* zero) {
+  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
   for (int i = gtid(); i < n; i += gstride()) rw[list[i]] = 0;
 }
-void clear_round(const int* list, int n, uint64_t* rw, hipStream_t s) {
-  if (n > 0) k_clear_round<<<grid_for(n), kBlock, 0, s>>>(list, n, rw);
+void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s) {
+  if (n > 0) k_clear_round<<<grid_for(n), kBlock, 0, s>>>(list, n, rw, zero);
 }
 // ---- flags and lists -----------------------------------------------------------------
 __global__ void k_set_flags(const int* __restrict__ list, int n, uint8_t* __restrict__ flag, uint8_t val) {
@@ -150,15 +151,19 @@ void restore_round(const Store& st, const int* cls, int n, const int* off, int n
 // every colour set before it is visible; a colour set during the launch may
 // read as unset, which only makes v wait (priorities and active bits do not
 // change during the colouring), and the vertex of largest key still waiting
-// is ready at every launch, so each chunked launch makes progress. The
-// one-block colouring runs to completion in one launch: its iterations are
-// separated by block barriers, and a work-group's waves share one CU's
-// vector L1, which the CU's own stores write through, so every iteration
-// sees the colours of the ones before it (its loop is bounded regardless).
+// is ready at every launch, so each chunked launch makes progress.
+// LIVE: round words change under the loop that calls this (solve_items), so
+// they are read as atomics of the work-group.
+template <bool LIVE>
+__device__ __forceinline__ uint64_t rw_get(const uint64_t* rw, int v) {
+  if constexpr (LIVE) return __hip_atomic_load(rw + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return rw[v];
+}
+template <bool LIVE = false>
 __device__ bool jp_try(const Store& st, int v, const Round& rd, int* ctr, int& blocker) {
   constexpr int B = 8;  // neighbours fetched side by side
   const uint64_t* rw = rd.rw;
-  if (blocker >= 0 && (rw[blocker] & 0xFF) == 0xFF) return false;
+  if (!LIVE && blocker >= 0 && (rw[blocker] & 0xFF) == 0xFF) return false;
   uint64_t rv = rw[v];
   Hdr h = st.hdr[v];
   uint64_t used = 0;
@@ -168,7 +173,7 @@ __device__ bool jp_try(const Store& st, int v, const Round& rd, int* ctr, int& b
     uint64_t x[B];
     row8(st.nn, h.x + j0, h.y - j0, w);
 #pragma unroll
-    for (int q = 0; q < B; ++q) x[q] = w[q] >= 0 ? rw[w[q]] : 0ull;
+    for (int q = 0; q < B; ++q) x[q] = w[q] >= 0 ? rw_get<LIVE>(rw, w[q]) : 0ull;
     int wait = -1;
 #pragma unroll
     for (int q = 0; q < B; ++q) {
@@ -193,7 +198,7 @@ __device__ bool jp_try(const Store& st, int v, const Round& rd, int* ctr, int& b
       bool taken = false;
       for (int j = 0; j < h.y && !taken; ++j) {
         int w = st.nn[h.x + j];
-        uint64_t x = rw[w];
+        uint64_t x = rw_get<LIVE>(rw, w);
         if (!(x & kRwAct) || !rw_beats(x, w, rv, v)) continue;
         taken = (int)(x & 0xFF) == c;
       }
@@ -209,38 +214,39 @@ __device__ bool jp_try(const Store& st, int v, const Round& rd, int* ctr, int& b
   return true;
 }
 
-// One block per chunk; each thread takes kJpItems entries (item r of thread
+// One block per chunk; each thread takes R entries (item r of thread
 // t is entry r * kBlock + t). The waiting vertices are packed to the front of
 // the chunk in their old order: every read happens before the block barrier,
 // every write after it, so the compaction can run in place. One atomic per
 // chunk (on a stripe) counts what is left.
-constexpr int kJpItems = kJpChunk / kBlock;
 constexpr int kJpLocal = 3;  // passes per launch over a chunk that makes progress
+template <int R>
 __global__ void __launch_bounds__(256) k_jp_chunk(Store st, const int* __restrict__ A, int n, int* W, int* WB,
                                                   int* __restrict__ cnt, int first, Round rd, int* ctr, int slot,
                                                   int next_slot) {
-  __shared__ int wtot[kJpItems][kBlock / kWave];
+  constexpr int kChunk = R * kBlock;
+  __shared__ int wtot[R][kBlock / kWave];
   int kb = xcd_block();
   if (blockIdx.x == 0 && threadIdx.x < kStripes) ctr[C_STRIPE + threadIdx.x * kStripeW + next_slot] = 0;
-  int m = first ? min(kJpChunk, n - kb * kJpChunk) : cnt[kb];
+  int m = first ? min(kChunk, n - kb * kChunk) : cnt[kb];
   if (m <= 0) {
     if (first && threadIdx.x == 0) cnt[kb] = 0;
     return;
   }
-  const int* in = (first ? A : W) + (size_t)kb * kJpChunk;
-  const int* inb = WB + (size_t)kb * kJpChunk;
-  int vv[kJpItems], bl[kJpItems];
+  const int* in = (first ? A : W) + (size_t)kb * kChunk;
+  const int* inb = WB + (size_t)kb * kChunk;
+  int vv[R], bl[R];
 #pragma unroll
-  for (int r = 0; r < kJpItems; ++r) {
+  for (int r = 0; r < R; ++r) {
     int i = r * kBlock + (int)threadIdx.x;
     vv[r] = i < m ? in[i] : -1;
     bl[r] = (i < m && !first) ? inb[i] : -1;
   }
-  bool keep[kJpItems];
+  bool keep[R];
   int tries = 0;  // this thread's vertex visits, for the profile's unit count
   bool moved = false;
 #pragma unroll
-  for (int r = 0; r < kJpItems; ++r) {
+  for (int r = 0; r < R; ++r) {
     keep[r] = vv[r] >= 0 && !jp_try(st, vv[r], rd, ctr, bl[r]);
     moved |= vv[r] >= 0 && !keep[r];
     tries += vv[r] >= 0 ? 1 : 0;
@@ -250,11 +256,11 @@ __global__ void __launch_bounds__(256) k_jp_chunk(Store st, const int* __restric
   for (int pass = 1; pass < kJpLocal; ++pass) {
     bool waiting = false;
 #pragma unroll
-    for (int r = 0; r < kJpItems; ++r) waiting |= keep[r];
+    for (int r = 0; r < R; ++r) waiting |= keep[r];
     if (!__syncthreads_or(moved && waiting)) break;
     moved = false;
 #pragma unroll
-    for (int r = 0; r < kJpItems; ++r)
+    for (int r = 0; r < R; ++r)
       if (keep[r]) {
         ++tries;
         keep[r] = !jp_try(st, vv[r], rd, ctr, bl[r]);
@@ -264,17 +270,17 @@ __global__ void __launch_bounds__(256) k_jp_chunk(Store st, const int* __restric
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) tries += __shfl_xor(tries, d);
   int lane = __lane_id(), wv = (int)threadIdx.x / kWave;
-  uint64_t bal[kJpItems];
+  uint64_t bal[R];
 #pragma unroll
-  for (int r = 0; r < kJpItems; ++r) {
+  for (int r = 0; r < R; ++r) {
     bal[r] = __ballot(keep[r]);
     if (lane == 0) wtot[r][wv] = __popcll(bal[r]);
   }
   __syncthreads();
-  int base = 0, pos[kJpItems];
+  int base = 0, pos[R];
   uint64_t below = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int r = 0; r < kJpItems; ++r) {
+  for (int r = 0; r < R; ++r) {
     int before = 0, row = 0;
 #pragma unroll
     for (int q = 0; q < kBlock / kWave; ++q) {
@@ -285,10 +291,10 @@ __global__ void __launch_bounds__(256) k_jp_chunk(Store st, const int* __restric
     pos[r] = base + before + __popcll(bal[r] & below);
     base += row;
   }
-  int* out = W + (size_t)kb * kJpChunk;
-  int* outb = WB + (size_t)kb * kJpChunk;
+  int* out = W + (size_t)kb * kChunk;
+  int* outb = WB + (size_t)kb * kChunk;
 #pragma unroll
-  for (int r = 0; r < kJpItems; ++r)
+  for (int r = 0; r < R; ++r)
     if (keep[r]) {
       out[pos[r]] = vv[r];
       outb[pos[r]] = bl[r];
@@ -301,12 +307,18 @@ __global__ void __launch_bounds__(256) k_jp_chunk(Store st, const int* __restric
   if (lane == 0 && tries) atomicAdd(stripe_ptr(ctr, S_PJP), tries);
 }
 
+// Entries per chunk: 512 for long lists (a chunk resolves chains of neighbours
+// inside it, and the launch is bound by the rows' line look-ups on full CUs),
+// 256 for lists whose blocks are then all resident at once (66,000 vertices are
+// 130 blocks of 512 on 256 CUs, each CU bound by its own look-ups).
+int jp_chunk_of(int n) { return n <= kJpShort ? kBlock : 2 * kBlock; }
+
 void jp_chunk(const Store& st, const int* A, int n, int* W, int* WB, int* cnt, bool first, Round rd, int* ctr,
               int it, hipStream_t s) {
-  int nch = (n + kJpChunk - 1) / kJpChunk;
-  if (nch > 0)
-    k_jp_chunk<<<nch, kBlock, 0, s>>>(st, A, n, W, WB, cnt, first ? 1 : 0, rd, ctr, S_JPL + (it & 7),
-                                       S_JPL + ((it + 1) & 7));
+  int chunk = jp_chunk_of(n), nch = (n + chunk - 1) / chunk;
+  if (nch <= 0) return;
+  auto k = chunk == kBlock ? k_jp_chunk<1> : k_jp_chunk<2>;
+  k<<<nch, kBlock, 0, s>>>(st, A, n, W, WB, cnt, first ? 1 : 0, rd, ctr, S_JPL + (it & 7), S_JPL + ((it + 1) & 7));
 }
 
 // ---- striped counters --------------------------------------------------------------------------
@@ -443,57 +455,154 @@ void class_lists(const int* A, int n, const uint64_t* rw, int* ctr, int* out, in
 // launch. Classes come out in no particular order; the members of a class
 // are an independent set, so their order does not change any result.
 constexpr int kSmallThreads = 1024;
-struct ColourLds {
-  int nwait, ncol;
-  int hist[256], cur[256];
-  int wsum[4];
+// A list of at most kSmallColour vertices is coloured by one block in LDS. Its
+// round words carry each vertex's place in the list (bits 9 ..), one scan of a
+// vertex's row then gives its record: the colours of the neighbours before it
+// that are coloured already, and the places of up to eight that are not. From
+// there on a vertex only follows its predecessors' colours, bytes in LDS.
+// Scanning rows is eleven line look-ups a vertex, which one CU does at about
+// one a clock: re-scanning every waiting row per iteration took 31 us for 1,500
+// vertices, this 22 (19 scanned by many blocks). Lists of more than kOneBlock are scanned by as many blocks as they
+// fill (k_jp_pred, into JpRec records), so that only the solving is one
+// block's.
+constexpr int kPlaceBit = 9;
+static_assert(kSmallColour <= 1 << 16, "places are 16-bit");
+struct Preds {
+  uint64_t lo, hi;  // places, 16 bits each, in row order
+  uint64_t used;    // colours taken, below 64
+  int cnt;          // places; -1: more than eight, or a colour past 63 (then jp_try)
 };
-// The n vertices of A, by the NT threads of the block. Returns the size of
-// the largest class, and the number of iterations in *its (-1: given up).
-// The class offsets are a scan by 256 threads: one thread adding them up one
-// after another took 8 us, half of the colouring of some hundred vertices.
-template <int NT>
-__device__ __forceinline__ int colour_body(const Store& st, const int* A, int n, const Round& rd, int* W0,
-                                           int* W1, int* WB, int* out, int* ctr, ColourLds& L, int* its) {
-  int tid = (int)threadIdx.x;
-  for (int i = tid; i < n; i += NT) {
-    int v = A[i];
-    uint64_t prio = key_of(st, rd, v) >> 32;
-    rd.rw[v] = (prio << 32) | kRwAct | 0xFFull;
-  }
-  if (tid < 256) L.hist[tid] = 0;
-  if (tid == 0) L.ncol = 0;
-  __syncthreads();
-  const int* in = A;
-  int nw = n, it = 0, visited = 0;
-  while (nw > 0) {
-    if (tid == 0) L.nwait = 0;
-    __syncthreads();
-    int* wout = (it & 1) ? W1 : W0;
-    const int* bin = WB + ((it & 1) ? 0 : kSmallColour);  // blockers beside the entries read
-    int* bout = WB + ((it & 1) ? kSmallColour : 0);
-    for (int i = tid; i < nw; i += NT) {
-      int v = in[i];
-      int bl = it > 0 ? bin[i] : -1;
-      if (!jp_try(st, v, rd, ctr, bl)) {
-        int k = atomicAdd(&L.nwait, 1);
-        wout[k] = v;
-        bout[k] = bl;
+__device__ __forceinline__ Preds preds_of(const Store& st, int v, const Round& rd) {
+  constexpr int B = 8;
+  uint64_t rv = rd.rw[v];
+  Hdr h = st.hdr[v];
+  Preds p{0, 0, 0, 0};
+  bool big = false;
+  for (int j0 = 0; j0 < h.y; j0 += B) {
+    int w[B];
+    uint64_t x[B];
+    row8(st.nn, h.x + j0, h.y - j0, w);
+#pragma unroll
+    for (int q = 0; q < B; ++q) x[q] = w[q] >= 0 ? rd.rw[w[q]] : 0ull;
+#pragma unroll
+    for (int q = 0; q < B; ++q) {
+      if (!(x[q] & kRwAct) || !rw_beats(x[q], w[q], rv, v)) continue;
+      int c = (int)(x[q] & 0xFF);
+      if (c == 0xFF) {
+        if (p.cnt >= 8) big = true;
+        uint64_t at = (x[q] >> kPlaceBit) & 0xFFFF;
+        if (p.cnt < 4) p.lo |= at << (16 * p.cnt);
+        else p.hi |= at << (16 * (p.cnt & 3));
+        ++p.cnt;
+      } else if (c < 64) {
+        p.used |= 1ull << c;
+      } else {
+        big = true;
       }
     }
-    __syncthreads();
-    visited += nw;
-    nw = L.nwait;
-    in = wout;
-    ++it;
-    __syncthreads();
-    if (it > 4 * kMaxColours + n) {  // cannot happen: the largest waiting key is always ready
-      if (tid == 0) atomicOr(&ctr[C_ERR], E_COLOURS);
-      *its = -1;
-      return 0;
+  }
+  if (big) p.cnt = -1;
+  return p;
+}
+
+// Colours the list A (n <= K * NT vertices) from its predecessor records, each
+// thread K of them (recs: their records, else one scan each). col: a byte per
+// place, 0xFF at the start. No barriers: every thread goes round its own
+// vertices until all have a colour; the waiting one of largest key is always
+// ready, so the passes end (they are bounded all the same). What bounds it: the
+// longest chain of waiting vertices, an LDS round trip per link. Adds the
+// visits to *visits, raises *its to the passes of a thread.
+constexpr int kMaxPasses = 1 << 20;
+template <int NT, int K>
+__device__ __forceinline__ void solve_items(const Store& st, const int* A, int n, const JpRec* recs, const Round& rd,
+                                            volatile uint8_t* col, int* ctr, int* its, int* visits) {
+  int tid = (int)threadIdx.x;
+  Preds p[K];
+  uint32_t todo = 0, far = 0;  // far: the vertices that jp_try colours
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    int i = tid + k * NT;
+    p[k] = Preds{0, 0, 0, 0};
+    if (i >= n) continue;
+    todo |= 1u << k;
+    if (recs) {
+      JpRec r = recs[i];
+      p[k] = Preds{r.lo, r.hi, r.used, r.cnt};
+    } else {
+      p[k] = preds_of(st, A[i], rd);
+    }
+    if (p[k].cnt < 0) far |= 1u << k;
+  }
+  if (!recs) __syncthreads();  // every row is scanned before a colour is stored
+  int pass = 0, mine = __popc(todo);
+  for (; todo && pass < kMaxPasses; ++pass) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!((todo & ~far) >> k & 1)) continue;
+      Preds& q = p[k];
+      while (q.cnt > 0) {
+        int y = col[q.lo & 0xFFFF];
+        if (y == 0xFF) break;
+        if (y < 64) q.used |= 1ull << y;
+        else far |= 1u << k;
+        q.lo = q.lo >> 16 | q.hi << 48;
+        q.hi >>= 16;
+        --q.cnt;
+      }
+      if (q.cnt > 0) continue;
+      if (!~q.used) far |= 1u << k;
+      if (far >> k & 1) continue;
+      int c = __ffsll((unsigned long long)~q.used) - 1, i = tid + k * NT;
+      col[i] = (uint8_t)c;
+      // the low half of the round word: the priority stays
+      ((volatile uint32_t*)rd.rw)[2 * (int64_t)A[i]] = (uint32_t)kRwAct | (uint32_t)c;
+      todo &= ~(1u << k);
+    }
+    uint32_t slow = todo & far;
+    while (slow) {
+      int k = __ffs((int)slow) - 1, i = tid + k * NT, b = -1;
+      slow &= slow - 1;
+      if (!jp_try<true>(st, A[i], rd, ctr, b)) continue;
+      col[i] = (uint8_t)(rw_get<true>(rd.rw, A[i]) & 0xFF);
+      todo &= ~(1u << k);
     }
   }
-  for (int i = tid; i < n; i += NT) atomicAdd(&L.hist[(int)(rd.rw[A[i]] & 0xFF)], 1);
+  if (pass) {
+    atomicMax(its, pass);
+    atomicAdd(visits, mine);
+  }
+  if (todo) atomicOr(&ctr[C_ERR], E_COLOURS);  // cannot happen
+}
+
+struct ColourLds {
+  int big, ncol, its, visits;
+  int hist[256], cur[256];
+  int wsum[4];
+  uint8_t col[kSmallColour];
+};
+// The n <= K * NT vertices of A, by the NT threads of the block; recs: their
+// records, with the round words set, or null (both made here). Returns the
+// size of the largest class; L.its: the most passes of a thread.
+// The class offsets are a scan by 256 threads: one thread adding them up one
+// after another took 8 us, half of the colouring of some hundred vertices.
+template <int NT, int K>
+__device__ __forceinline__ int colour_body(const Store& st, const int* A, int n, const JpRec* recs, const Round& rd,
+                                           int* out, int* ctr, ColourLds& L) {
+  int tid = (int)threadIdx.x;
+  for (int i = tid; i < n; i += NT) {
+    if (!recs) {
+      int v = A[i];
+      uint64_t prio = key_of(st, rd, v) >> 32;
+      rd.rw[v] = (prio << 32) | ((uint64_t)i << kPlaceBit) | kRwAct | 0xFFull;
+    }
+    L.col[i] = 0xFF;
+  }
+  if (tid < 256) L.hist[tid] = 0;
+  if (tid == 0) L.ncol = L.its = L.visits = L.big = 0;
+  __syncthreads();
+  solve_items<NT, K>(st, A, n, recs, rd, L.col, ctr, &L.its, &L.visits);
+  __syncthreads();
+  for (int i = tid; i < n; i += NT) atomicAdd(&L.hist[L.col[i]], 1);
   __syncthreads();
   int h = tid < 256 ? L.hist[tid] : 0, incl = h, lane = __lane_id();
 #pragma unroll
@@ -515,43 +624,137 @@ __device__ __forceinline__ int colour_body(const Store& st, const int* A, int n,
     ctr[C_HIST + tid] = h;
   }
   if (tid == 0) {
-    L.nwait = 0;
     ctr[C_NCOL] = L.ncol;
     ctr[C_JP] = 0;
     ctr[C_TOUCH] = 0;
-    ctr[C_TOTAL] = it;
-    atomicAdd(ctr + C_STRIPE + S_PJP, visited);
+    ctr[C_TOTAL] = L.its;
+    atomicAdd(ctr + C_STRIPE + S_PJP, L.visits);
   }
   __syncthreads();
-  if (tid < 256 && lane == 0) atomicMax(&L.nwait, big);
-  for (int i = tid; i < n; i += NT) {
-    int v = A[i];
-    out[atomicAdd(&L.cur[(int)(rd.rw[v] & 0xFF)], 1)] = v;
-  }
+  if (tid < 256 && lane == 0) atomicMax(&L.big, big);
+  for (int i = tid; i < n; i += NT) out[atomicAdd(&L.cur[L.col[i]], 1)] = A[i];
   __syncthreads();
-  *its = it;
-  return L.nwait;
+  return L.big;
 }
 
-__global__ void __launch_bounds__(kSmallThreads) k_colour_small(Store st, const int* __restrict__ A, int n,
-                                                              const int* n_dev, Round rd, int* W0, int* W1, int* WB,
-                                                              int* __restrict__ out, int* ctr) {
-  __shared__ ColourLds L;
-  if (n_dev) {
-    // the list length from the device (a colouring launched ahead of the
-    // read-back); a list this kernel does not take is reported as -1 colours
-    n = *n_dev;
-    if (n < 0 || n > kSmallColour) {
-      if (threadIdx.x == 0) ctr[C_NCOL] = -1;
-      return;
-    }
-  }
-  int its;
-  colour_body<kSmallThreads>(st, A, n, rd, W0, W1, WB, out, ctr, L, &its);
+// the list length, or -1 for one that the small colouring does not take
+__device__ __forceinline__ int small_length(int n, const int* n_dev) {
+  if (n_dev) n = *n_dev;
+  return n < 0 || n > kSmallColour ? -1 : n;
 }
-void colour_small(const Store& st, const int* A, int n, const int* n_dev, Round rd, int* W0, int* W1, int* WB,
-                  int* out, int* ctr, hipStream_t s) {
-  k_colour_small<<<1, kSmallThreads, 0, s>>>(st, A, n, n_dev, rd, W0, W1, WB, out, ctr);
+__global__ void k_jp_place(Store st, const int* __restrict__ A, int n, const int* n_dev, Round rd) {
+  n = small_length(n, n_dev);
+  for (int i = gtid(); i < n; i += gstride()) {
+    int v = A[i];
+    uint64_t prio = key_of(st, rd, v) >> 32;
+    rd.rw[v] = (prio << 32) | ((uint64_t)i << kPlaceBit) | kRwAct | 0xFFull;
+  }
+}
+__global__ void k_jp_pred(Store st, const int* __restrict__ A, int n, const int* n_dev, Round rd,
+                          JpRec* __restrict__ recs) {
+  n = small_length(n, n_dev);
+  for (int i = gtid(); i < n; i += gstride()) {
+    Preds p = preds_of(st, A[i], rd);
+    recs[i] = JpRec{p.lo, p.hi, p.used, p.cnt, 0};
+  }
+}
+__global__ void __launch_bounds__(kSmallThreads) k_colour_small(Store st, const int* A, int n, const int* n_dev, Round rd,
+                                                              const JpRec* recs, int* out, int* ctr) {
+  __shared__ ColourLds L;
+  // the list length may come from the device (a colouring launched ahead of
+  // the read-back); a list this kernel does not take is reported as -1 colours
+  n = small_length(n, n_dev);
+  if (n < 0) {
+    if (threadIdx.x == 0) ctr[C_NCOL] = -1;
+    return;
+  }
+  if (n <= 2 * kSmallThreads) (void)colour_body<kSmallThreads, 2>(st, A, n, recs, rd, out, ctr, L);
+  else (void)colour_body<kSmallThreads, kSmallColour / kSmallThreads>(st, A, n, recs, rd, out, ctr, L);
+}
+void colour_small(const Store& st, const int* A, int n, const int* n_dev, int n_about, Round rd, JpRec* recs, int* out,
+                  int* ctr, hipStream_t s) {
+  bool one = n_about <= kOneBlock;
+  if (!one) {
+    int nb = grid_for(n_dev ? kSmallColour : n);
+    k_jp_place<<<nb, kBlock, 0, s>>>(st, A, n, n_dev, rd);
+    k_jp_pred<<<nb, kBlock, 0, s>>>(st, A, n, n_dev, rd, recs);
+  }
+  k_colour_small<<<1, kSmallThreads, 0, s>>>(st, A, n, n_dev, rd, one ? nullptr : recs, out, ctr);
+}
+
+// The rest of a chunked colouring, when the launch that counted its waiting
+// vertices in `slot` left no more than kSmallColour (else nothing happens and
+// *nleft is -1): gathered into `list` with their places, then scanned by many
+// blocks and solved by one. A launch of the chunked form takes 7 us however few
+// wait, and the last five to ten of a colouring have a tenth of the list.
+__global__ void __launch_bounds__(kSmallThreads) k_jp_gather(const int* __restrict__ W, const int* __restrict__ cnt, int nch,
+                                                           int chunk, Round rd, int* list, int* ctr, int slot, int* nleft) {
+  constexpr int NT = kSmallThreads;
+  __shared__ int offs[NT], wsum[NT / kWave], left;
+  int tid = (int)threadIdx.x, lane = __lane_id(), wv = tid / kWave;
+  if (tid < kStripes) {
+    int* sp = ctr + C_STRIPE + tid * kStripeW + slot;
+    int x = *sp;
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    if (tid == 0) {
+      left = x;
+      *nleft = x <= kSmallColour ? x : -1;
+    }
+    if (x <= kSmallColour) *sp = 0;
+  }
+  __syncthreads();
+  int n = left;
+  if (n == 0 || n > kSmallColour) return;
+  // thread t's chunks are [t * per, (t + 1) * per); offs: the entries before them
+  int per = (nch + NT - 1) / NT, sum = 0;
+  for (int c = tid * per; c < min(nch, (tid + 1) * per); ++c) sum += cnt[c];
+  int incl = sum;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    int o = __shfl_up(incl, d);
+    if (lane >= d) incl += o;
+  }
+  if (lane == kWave - 1) wsum[wv] = incl;
+  __syncthreads();
+  int before = incl - sum;
+  for (int w = 0; w < wv; ++w) before += wsum[w];
+  offs[tid] = before;
+  __syncthreads();
+  for (int i = tid; i < n; i += NT) {
+    int t = 0;  // the last thread whose entries start at or before i
+#pragma unroll
+    for (int b = NT / 2; b > 0; b >>= 1)
+      if (offs[t + b] <= i) t += b;
+    int k = i - offs[t], c = t * per;
+    while (k >= cnt[c]) k -= cnt[c++];
+    int v = W[(size_t)c * chunk + k];
+    list[i] = v;
+    rw_put(rd.rw, v, rd.rw[v] | ((uint64_t)i << kPlaceBit));
+  }
+}
+__global__ void __launch_bounds__(kSmallThreads) k_jp_solve(Store st, const int* A, const int* nleft, Round rd,
+                                                          const JpRec* recs, int* ctr) {
+  __shared__ uint8_t col[kSmallColour];
+  __shared__ int its, visits;
+  int n = *nleft;
+  if (n <= 0) return;
+  for (int i = (int)threadIdx.x; i < n; i += kSmallThreads) col[i] = 0xFF;
+  if (threadIdx.x == 0) its = visits = 0;
+  __syncthreads();
+  if (n <= 2 * kSmallThreads) solve_items<kSmallThreads, 2>(st, A, n, recs, rd, col, ctr, &its, &visits);
+  else solve_items<kSmallThreads, kSmallColour / kSmallThreads>(st, A, n, recs, rd, col, ctr, &its, &visits);
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(ctr + C_STRIPE + S_PJP, visits);
+}
+void jp_finish(const Store& st, int n, const int* W, const int* cnt, Round rd, JpRec* recs, int* list, int* ctr, int it,
+               hipStream_t s) {
+  int chunk = jp_chunk_of(n), nch = (n + chunk - 1) / chunk;
+  if (nch <= 0) return;
+  int* nleft = ctr + C_JPN;
+  k_jp_gather<<<1, kSmallThreads, 0, s>>>(W, cnt, nch, chunk, rd, list, ctr, S_JPL + (it & 7), nleft);
+  k_jp_pred<<<grid_for(kSmallColour), kBlock, 0, s>>>(st, list, 0, nleft, rd, recs);
+  k_jp_solve<<<1, kSmallThreads, 0, s>>>(st, list, nleft, rd, recs, ctr);
 }
 
 // The vertices to act on next, from the members A and the rows rebuilt, each
@@ -574,25 +777,30 @@ __device__ __forceinline__ int select_body(const Store& st, int mode, double L_l
   return n;
 }
 
-__global__ void __launch_bounds__(kSmallThreads) k_select_small(Store st, int mode, double L_low2,
-                                                               const int* __restrict__ A, int nA,
-                                                               const int* __restrict__ touched, int cap,
-                                                               uint8_t* __restrict__ nxt, int* __restrict__ seen,
-                                                               int mark, int* __restrict__ out, int* ctr) {
-  __shared__ int cnt;
+// The same on a grid: a list of some thousand vertices took one block up to
+// 60 us. ctr[C_LIST_B] is 0 at the start (clear_round), or -1 at the end when
+// the host has to select over every slot (and rebuild the rows first after a
+// commit that ran out of room).
+__global__ void k_select_list(Store st, int mode, double L_low2, const int* __restrict__ A, int nA,
+                              const int* __restrict__ touched, int cap, uint8_t* __restrict__ nxt,
+                              int* __restrict__ seen, int mark, int* __restrict__ out, int* ctr) {
   int nt = ctr[C_TOUCH];
   if (nt > cap || room_failed(ctr)) {
-    // the host selects over every slot (and rebuilds the rows first after a
-    // commit that ran out of room)
-    if (threadIdx.x == 0) ctr[C_LIST_B] = -1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctr[C_LIST_B] = -1;
     return;
   }
-  int n = select_body<kSmallThreads>(st, mode, L_low2, A, nA, touched, nt, nxt, seen, mark, out, &cnt);
-  if (threadIdx.x == 0) ctr[C_LIST_B] = n;
+  for (int i = gtid(); i < nA + nt; i += gstride()) {
+    int x = i < nA ? A[i] : touched[i - nA];
+    if (!nxt[x] || atomicMax(&seen[x], mark) >= mark) continue;
+    nxt[x] = 0;
+    if (want(st, x, mode, L_low2, nullptr)) out[wave_append_slot(&ctr[C_LIST_B])] = x;
+  }
 }
-void select_small(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
-                  uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s) {
-  k_select_small<<<1, kSmallThreads, 0, s>>>(st, mode, L_low2, A, nA, touched, cap, nxt, seen, mark, out, ctr);
+void select_list(const Store& st, int mode, double L_low2, const int* A, int nA, const int* touched, int cap,
+                 uint8_t* nxt, int* seen, int mark, int* out, int* ctr, hipStream_t s) {
+  // the rows rebuilt are about five times the members
+  k_select_list<<<grid_for(6 * (int64_t)nA, 256), kBlock, 0, s>>>(st, mode, L_low2, A, nA, touched, cap, nxt, seen, mark,
+                                                                  out, ctr);
 }
 
 __global__ void k_colour_out(int V, const uint64_t* __restrict__ rw, int* __restrict__ out) {
@@ -2463,6 +2671,7 @@ void round_small(const Store& st, const int* cls, int ncol, OpArgs a, Commit cm,
 // threads: 32 members or rows at a time, against 16 with 256 (the flips' 165
 // registers leave no room for 1024).
 // LDS: the classes' and the colouring's are never in use together.
+constexpr int kDevItems = 2;  // vertices a thread colours, at most
 template <bool F, int QK>
 __global__ void __launch_bounds__(kClassThreads) k_rounds_dev(Store st, DevRounds d, OpArgs a, Commit cm, int* ctr) {
   st.qk = QK;  // the functional as a constant: one instantiation per kind
@@ -2504,20 +2713,16 @@ __global__ void __launch_bounds__(kClassThreads) k_rounds_dev(Store st, DevRound
       stop = 1;
       break;
     }
-    if (n > kSmallColour) {
+    if (n > kDevItems * NT) {
       ncol = -1;
       stop = 1;
       break;
     }
     Round rd{stream_seed(d.seed, make_ctx(d.sweep, d.phase, r)), d.rw};
-    int its;
-    int big = colour_body<NT>(st, B, n, rd, d.W0, d.W1, d.WB, d.cls, ctr, L.colour, &its);
+    int big = colour_body<NT, kDevItems>(st, B, n, nullptr, rd, d.cls, ctr, L.colour);
     ncol = L.colour.ncol;
+    int its = L.colour.its;
     __syncthreads();
-    if (its < 0) {
-      stop = 1;
-      break;
-    }
     if (big > kSmallClass) {
       // the host runs this round, coloured as it is (and counts it)
       stop = 1;
