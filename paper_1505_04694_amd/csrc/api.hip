@@ -11,6 +11,7 @@
 #include <unordered_map>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <string>
 #include <vector>
 
@@ -61,6 +62,7 @@ struct pm_mesh {
   int* hctr = nullptr;  // pinned mirror
   double* hq = nullptr; // pinned doubles
   int* haux = nullptr;   // pinned ints for small read-backs (upper half: staged uploads)
+  Mail mail;             // the pinned block's
   hipEvent_t up_ev = nullptr;  // the last staged upload's copy
   // scratch
   DBuf<int> listA, listB, jpU0, jpU1, cls, vt0, vt1, vt2, vt3, vt4, tt0, tt1, tt2, partial, mid;
@@ -80,7 +82,8 @@ struct pm_mesh {
   int epoch = 0;         // commit epoch, one per class
   DBuf<JpRec> jprec;  // small colourings: predecessor records
   DBuf<double> qpart;
-  DBuf<double> upd;  // pm_mesh_update: the previous coordinates and metric
+  DBuf<double2> upx;  // pm_mesh_update: where new coordinates and metrics are checked
+  DBuf<Met> upm;
   DBuf<uint64_t> rw;  // round words (priority, active, colour) per vertex
   // mesh ranges (host mirror of Store::vbase/vused/tbase/tused)
   std::vector<int> vbase, vused, tbase, tused;
@@ -231,34 +234,21 @@ pm_status dalloc(pm_mesh* m, T** p, size_t n) {
   m->peak_bytes = std::max(m->peak_bytes, m->cur_bytes);
   return PM_OK;
 }
-// Pinned host blocks (the counter mirror and the quality read-back) are kept
-// in a process-wide free list: pinning memory is a slow driver call.
-constexpr int kAuxInts = 16384;  // pinned room for small read-backs beside the counters
-constexpr size_t kPinnedBytes = C_COUNT * sizeof(int) + 64 * sizeof(double) + kAuxInts * sizeof(int);
-std::mutex g_pinned_mu;
-std::vector<void*> g_pinned_free;
+// the handle's pinned block: the counter mirror, 64 doubles, and kAuxInts ints
+constexpr int kAuxInts = 16384;
+static_assert(C_COUNT * sizeof(int) + 64 * sizeof(double) + kAuxInts * sizeof(int) < kPinnedBytes, "pinned block");
 bool pinned_get(pm_mesh* m) {
-  void* p = nullptr;
-  {
-    std::lock_guard<std::mutex> lk(g_pinned_mu);
-    if (!g_pinned_free.empty()) {
-      p = g_pinned_free.back();
-      g_pinned_free.pop_back();
-    }
-  }
-  if (!p && hipHostMalloc(&p, kPinnedBytes, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
+  void* p = pinned_take();
+  if (!p) return false;
   m->hctr = (int*)p;
   m->hq = (double*)((char*)p + C_COUNT * sizeof(int));
   m->haux = (int*)((char*)p + C_COUNT * sizeof(int) + 64 * sizeof(double));
+  m->mail = mail_of(p);
   return true;
 }
 void pinned_put(pm_mesh* m) {
   if (!m->hctr) return;
-  std::lock_guard<std::mutex> lk(g_pinned_mu);
-  g_pinned_free.push_back(m->hctr);
+  pinned_give(m->hctr);
   m->hctr = nullptr;
   m->hq = nullptr;
   m->haux = nullptr;
@@ -345,10 +335,12 @@ void prof_flush(pm_mesh* m) {
 // epoch of a commit that ran out of room
 constexpr int kRoundCtrs = C_FAILEP + 1;
 
-// copy device counters [lo, lo+n) to the pinned mirror and wait
+// device counters [lo, lo+n) into the pinned mirror; waits for them (and so
+// for all work issued before). Timed launches need the stream synchronised.
 pm_status read_ctr(pm_mesh* m, int lo, int n) {
-  HIPCHK(hipMemcpyAsync(m->hctr + lo, m->ctr + lo, n * sizeof(int), hipMemcpyDeviceToHost, m->s));
-  HIPCHK(hipStreamSynchronize(m->s));
+  mail_send(m->mail, m->ctr + lo, n, m->hctr + lo, m->s);
+  HIPCHK(mail_wait(m->mail, m->s));
+  if (m->prof.mask) HIPCHK(hipStreamSynchronize(m->s));
   return PM_OK;
 }
 
@@ -405,18 +397,16 @@ pm_status grow_vertices(pm_mesh* m, int need) {
   TRY(dalloc(m, &va, nc));
   TRY(dalloc(m, &hdr, nc));
   TRY(dalloc(m, &cap, nc));
-  HIPCHK(hipMemsetAsync(va, 0, nc, m->s));
-  HIPCHK(hipMemsetAsync(hdr, 0, sizeof(Hdr) * (size_t)nc, m->s));
-  HIPCHK(hipMemsetAsync(cap, 0, sizeof(int2) * (size_t)nc, m->s));
-  if (s.V > 0) {
-    HIPCHK(hipMemcpyAsync(xy, s.xy, sizeof(double2) * s.V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(met, s.met, sizeof(Met) * s.V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(tag, s.tag, s.V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(va, s.valive, s.V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(hdr, s.hdr, sizeof(Hdr) * s.V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(cap, s.cap, sizeof(int2) * s.V, hipMemcpyDeviceToDevice, m->s));
-  }
-  HIPCHK(hipStreamSynchronize(m->s));
+  // one launch; the old blocks go back to this stream's cache, where only later
+  // work can take them
+  Store to = s;
+  to.xy = xy;
+  to.met = met;
+  to.tag = tag;
+  to.valive = va;
+  to.hdr = hdr;
+  to.cap = cap;
+  copy_vertices(s, to, nc, m->s);
   dfree(m, s.xy, s.Vcap);
   dfree(m, s.met, s.Vcap);
   dfree(m, s.tag, s.Vcap);
@@ -439,9 +429,7 @@ pm_status grow_elements(pm_mesh* m, int need) {
   int nc = std::max(need, s.Tcap + s.Tcap / 2);
   Elem* tri;
   TRY(dalloc(m, &tri, nc));
-  HIPCHK(hipMemsetAsync(tri, 0, sizeof(Elem) * (size_t)nc, m->s));
-  if (s.T > 0) HIPCHK(hipMemcpyAsync(tri, s.tri, sizeof(Elem) * s.T, hipMemcpyDeviceToDevice, m->s));
-  HIPCHK(hipStreamSynchronize(m->s));
+  copy_elements(s, tri, nc, m->s);
   dfree(m, s.tri, s.Tcap);
   s.tri = tri;
   s.Tcap = nc;
@@ -458,7 +446,9 @@ pm_status upload_ranges(pm_mesh* m) {
   all.insert(all.end(), m->tbase.begin(), m->tbase.end());
   all.insert(all.end(), m->tused.begin(), m->tused.end());
   if (!m->ranges) TRY(dalloc(m, &m->ranges, all.size()));
-  if (all.size() <= (size_t)kAuxInts / 2) {
+  if (B == 1) {
+    set_ranges(m->ranges, m->vused[0], m->tused[0], st.V, st.T, m->s);
+  } else if (all.size() <= (size_t)kAuxInts / 2) {
     // staged in the upper half of the pinned ints and copied in stream
     // order; the previous upload's copy has finished before the stage is
     // rewritten
@@ -487,6 +477,8 @@ pm_status single_ranges(pm_mesh* m) {
   m->tused = {m->st.T};
   return upload_ranges(m);
 }
+
+constexpr int64_t kSmallPool = 1 << 24;  // entries: 64 MB a pool
 
 // (Re)build every adjacency row from the element list into fresh pools.
 // check: read the error bits back at the end (else they stay set for the
@@ -520,13 +512,15 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
     build_finish(st, m->ctr, m->s);
     return check ? check_err(m) : PM_OK;
   }
-  TRY(read_ctr(m, C_NN_TOP, 2));
-  int64_t nn_used = m->hctr[C_NN_TOP], ne_used = m->hctr[C_NE_TOP];
+  // small pools are simply sized by the bound (about twice what the rows need),
+  // which saves the read-back
+  bool small = m->headroom >= 3.0 && room <= (double)kSmallPool;
+  if (!small) TRY(read_ctr(m, C_NN_TOP, 2));
+  int64_t nn_used = small ? (int64_t)bound : m->hctr[C_NN_TOP], ne_used = small ? (int64_t)bound : m->hctr[C_NE_TOP];
   int64_t nn_need = (int64_t)(m->headroom * (double)nn_used + extra);
   int64_t ne_need = (int64_t)(m->headroom * (double)ne_used + extra);
   if (nn_need > INT32_MAX || ne_need > INT32_MAX) return fail(m, PM_E_NOMEM, "adjacency pool beyond 2^31 entries");
   if (st.nn_pool < nn_need || st.ne_pool < ne_need) {
-    TRY(sync(m));
     dfree(m, st.nn, st.nn_pool);
     dfree(m, st.ne, st.ne_pool);
     st.nn_pool = st.ne_pool = 0;
@@ -637,8 +631,7 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
   TRY(ensure(m, m->ctab, 256 * (size_t)nb + 256));
   TRY(ensure(m, m->ctabs, 256 * (size_t)nb + 256));
   TRY(ensure(m, m->spart, scan_partials_needed(256 * nb) + 2));
-  jp_init(m->st, A, n, rd, m->s);
-  stripe_zero(m->ctr, S_JPL, 8, m->s);
+  jp_init(m->st, A, n, rd, m->ctr, m->s);
   bool finish = !m->tune.small_work;
   int it = 0;
   for (;;) {
@@ -652,13 +645,12 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
       timed(m, PM_K_JP, 0,
             [&] { jp_chunk(m->st, A, n, m->jpU0.p, m->jpB.p, m->jpU1.p, it == 0, rd, m->ctr, it, m->s); });
     if (finish) {
-      // what every iteration of the last eight left, then the rest
-      stripe_sum(m->ctr, S_JPL, 8, C_JPL, m->s);
+      // what every iteration of the last eight left (C_JPL), then the rest
       timed(m, PM_K_JP, 0, [&] {
         jp_finish(m->st, n, m->jpU0.p, m->jpU1.p, rd, m->jprec.p, m->cls.p, m->ctr, it - 1, m->s);
       });
     }
-    stripe_sum(m->ctr, S_JPL + ((it - 1) & 7), 1, C_JP, m->s);
+    else stripe_sum(m->ctr, S_JPL + ((it - 1) & 7), 1, C_JP, m->s);
     m->class_seq = m->class_seq >= 0x3FFFFFFF ? 1 : m->class_seq + 1;
     class_lists(A, n, rd.rw, m->ctr, m->cls.p, m->ctab.p, m->ctabs.p, m->spart.p,
                 m->tune.class_colours ? m->tune.class_colours : kClassNarrow, m->class_seq, m->s);
@@ -688,11 +680,14 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
   return PM_OK;
 }
 
-void stats_zero(pm_mesh* m) { stripe_zero(m->ctr, S_EVAL, 6, m->s); }
+void stats_zero(pm_mesh* m) { phase_start(m->ctr, m->s); }
 
 pm_status stats_read(pm_mesh* m, pm_stats* st) {
-  stripe_sum(m->ctr, S_EVAL, 6, C_EVAL, m->s);
-  TRY(read_ctr(m, C_EVAL, 6));
+  // summed straight into the pinned mirror
+  mail_next(m->mail);
+  stripe_mail(m->ctr, S_EVAL, 6, m->hctr + C_EVAL, m->mail, m->s);
+  HIPCHK(mail_wait(m->mail, m->s));
+  if (m->prof.mask) HIPCHK(hipStreamSynchronize(m->s));
   prof_flush(m);
   if (st) {
     st->v[2] += m->hctr[C_EVAL];
@@ -707,6 +702,39 @@ pm_status stats_read(pm_mesh* m, pm_stats* st) {
 
 // headroom a batched mesh keeps after its used slots (refinement grows into it)
 int headroom(int used) { return std::max(used / 2, 64); }
+
+// A single mesh: the scans in vt1 and tt1 are the new ids, their totals the new
+// sizes. When every slot is live the renumbering is the identity, and the rows
+// stay.
+pm_status compact_one(pm_mesh* m) {
+  Store& st = m->st;
+  TRY(read_ctr(m, 0, C_TOTAL2 + 1));
+  int nV = m->hctr[C_TOTAL], nT = m->hctr[C_TOTAL2];
+  if (nV == st.V && nT == st.T) return check_err(m, true);
+  Store to = st;
+  TRY(dalloc(m, &to.xy, st.Vcap));
+  TRY(dalloc(m, &to.met, st.Vcap));
+  TRY(dalloc(m, &to.tag, st.Vcap));
+  TRY(dalloc(m, &to.valive, st.Vcap));
+  TRY(dalloc(m, &to.tri, st.Tcap));
+  compact_vertices(st, m->vt1.p, to.xy, to.met, to.tag, to.valive, m->s);
+  compact_elements(st, m->vt1.p, m->tt1.p, to.tri, m->s);
+  clear_tail(to, nV, nT, m->s);
+  dfree(m, st.xy, st.Vcap);
+  dfree(m, st.met, st.Vcap);
+  dfree(m, st.tag, st.Vcap);
+  dfree(m, st.valive, st.Vcap);
+  dfree(m, st.tri, st.Tcap);
+  st = to;
+  st.V = nV;
+  st.T = nT;
+  m->vbase = {0, nV};
+  m->vused = {nV};
+  m->tbase = {0, nT};
+  m->tused = {nT};
+  TRY(upload_ranges(m));
+  return build_rows(m);
+}
 
 // Stable renumbering of live vertices and elements. A single mesh is packed
 // densely; the meshes of a batch are packed into consecutive ranges with
@@ -726,6 +754,7 @@ pm_status compact(pm_mesh* m, const std::vector<int>* extra_v = nullptr, const s
   scan_excl(m->vt0.p, m->vt1.p, V, m->ctr + C_TOTAL, m->partial.p, m->s);
   flag_live_elements(st, m->tt0.p, m->s);
   scan_excl(m->tt0.p, m->tt1.p, T, m->ctr + C_TOTAL2, m->partial.p, m->s);
+  if (B == 1) return compact_one(m);
   range_sums(m->vt1.p, m->vt0.p, st.vbase, st.vused, B, m->rtmp.p, m->s);
   range_sums(m->tt1.p, m->tt0.p, st.tbase, st.tused, B, m->rtmp.p + B, m->s);
   std::vector<int> live(2 * B);
@@ -1019,8 +1048,6 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
   int phase = kind == 0 ? PH_COARSEN : PH_SWAP;
   double qmin2 = o->q_min * o->q_min;
   stats_zero(m);
-  set_int(m->ctr + C_LIST_B, 0, m->s);
-  set_int(m->ctr + C_FAILEP, INT_MAX, m->s);
   timed(m, PM_K_SELECT, m->st.V,
         [&] { select_vertices(m->st, mode, o->L_low2, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p,
                           m->spos.p, m->spart.p, m->s); });
@@ -1082,7 +1109,6 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
         Round rdd{stream_seed(m->seed, make_ctx(o->sweep, phase, rr)), m->rw.p};
         TRY(recover_round(m, kind, dc, dep, rdd, o, n_rr));
       }
-      set_int(m->ctr + C_LIST_B, 0, m->s);
       timed(m, PM_K_SELECT, m->st.V, [&] {
         select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spos.p,
                         m->spart.p, m->s);
@@ -1137,7 +1163,6 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
       }
     }
     auto select_all = [&]() -> pm_status {
-      set_int(m->ctr + C_LIST_B, 0, m->s);
       timed(m, PM_K_SELECT, m->st.V, [&] {
         select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spos.p,
                         m->spart.p, m->s);
@@ -1232,6 +1257,61 @@ hipError_t block_alloc(hipStream_t s, void** p, size_t bytes) {
 void block_free(void* p) {
   if (p && cache_put(p) == 0) (void)hipFree(p);
 }
+
+static std::mutex g_pinned_mu;
+static std::vector<void*> g_pinned_free;
+void* pinned_take() {
+  void* p = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    if (!g_pinned_free.empty()) {
+      p = g_pinned_free.back();
+      g_pinned_free.pop_back();
+      return p;
+    }
+  }
+  // coherent: the host sees a kernel's stores while later work still runs
+  if (hipHostMalloc(&p, kPinnedBytes, hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  memset(p, 0, kPinnedBytes);
+  return p;
+}
+void pinned_give(void* p) {
+  if (!p) return;
+  std::lock_guard<std::mutex> lk(g_pinned_mu);
+  g_pinned_free.push_back(p);
+}
+
+Mail mail_of(void* block) {
+  Mail b;
+  b.at = (volatile int*)((char*)block + kPinnedBytes - sizeof(int));
+  b.no = *b.at;
+  return b;
+}
+static __global__ void k_mail(const int* __restrict__ src, int n, int* dst, int* at, int no) {
+  for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) dst[i] = src[i];
+  mail_post(at, no);
+}
+void mail_next(Mail& b) { b.no = b.no == INT_MAX ? 1 : b.no + 1; }
+void mail_send(Mail& b, const int* src, int n, int* dst, hipStream_t s) {
+  mail_next(b);
+  k_mail<<<1, kBlock, 0, s>>>(src, n, dst, (int*)b.at, b.no);
+}
+hipError_t mail_wait(const Mail& b, hipStream_t s) {
+  for (int64_t k = 1;; ++k) {
+    if (__atomic_load_n(b.at, __ATOMIC_ACQUIRE) == b.no) return hipSuccess;
+    __builtin_ia32_pause();
+    if (k % 16384 == 0) {  // a fraction of a millisecond: has the stream failed?
+      hipError_t e = hipStreamQuery(s);
+      if (e == hipSuccess) return __atomic_load_n(b.at, __ATOMIC_ACQUIRE) == b.no ? hipSuccess : hipErrorUnknown;
+      if (e != hipErrorNotReady) return e;
+      (void)hipGetLastError();
+      if (k > (1 << 20)) std::this_thread::yield();
+    }
+  }
+}
 }  // namespace pm
 
 extern "C" {
@@ -1277,7 +1357,8 @@ pm_status pm_mesh_destroy(pm_mesh* m) {
   for (auto* b : ub) dfree(m, b->p, b->n);
   dfree(m, m->jprec.p, m->jprec.n);
   dfree(m, m->qpart.p, m->qpart.n);
-  dfree(m, m->upd.p, m->upd.n);
+  dfree(m, m->upx.p, m->upx.n);
+  dfree(m, m->upm.p, m->upm.n);
   dfree(m, m->rw.p, m->rw.n);
   dfree(m, m->own.p, m->own.n);
   dfree(m, m->dirty.p, m->dirty.n);
@@ -1450,7 +1531,6 @@ pm_status pm_colour(pm_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* co
                           mem_kind == PM_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, m->s));
     act_in = m->u8tmp.p;
   }
-  set_int(m->ctr + C_LIST_B, 0, m->s);
   select_vertices(st, 0, 0.0, act_in, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spos.p, m->spart.p,
                   m->s);
   TRY(read_ctr(m, C_LIST_B, 1));
@@ -1500,7 +1580,6 @@ pm_status pm_smooth(pm_mesh* m, const pm_options* o, pm_stats* st) {
   TRY(ensure_phase_scratch(m));
   m->tune = o->tune;
   stats_zero(m);
-  set_int(m->ctr + C_LIST_B, 0, m->s);
   select_vertices(m->st, 3, 0.0, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spos.p,
                   m->spart.p, m->s);
   TRY(read_ctr(m, C_LIST_B, 1));
@@ -1585,17 +1664,21 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
     scan_excl(m->vt0.p, m->vt1.p, V0, m->ctr + C_TOTAL, m->partial.p, m->s);
     refine_count(s, o->L_up2, m->tt0.p, m->s);
     scan_excl(m->tt0.p, m->tt1.p, T0, m->ctr + C_TOTAL2, m->partial.p, m->s);
-    range_sums(m->vt1.p, m->vt0.p, s.vbase, s.vused, B, m->rtmp.p, m->s);
-    range_sums(m->tt1.p, m->tt0.p, s.tbase, s.tused, B, m->rtmp.p + B, m->s);
-    // per-mesh needs, totals and tested edges come back in one wait
     std::vector<int> need(2 * B);
     bool aux = 2 * B <= kAuxInts;
-    HIPCHK(hipMemcpyAsync(aux ? m->haux : need.data(), m->rtmp.p, sizeof(int) * 2 * B, hipMemcpyDeviceToHost, m->s));
+    if (B > 1) {
+      // per-mesh needs come back with the totals
+      range_sums(m->vt1.p, m->vt0.p, s.vbase, s.vused, B, m->rtmp.p, m->s);
+      range_sums(m->tt1.p, m->tt0.p, s.tbase, s.tused, B, m->rtmp.p + B, m->s);
+      HIPCHK(hipMemcpyAsync(aux ? m->haux : need.data(), m->rtmp.p, sizeof(int) * 2 * B, hipMemcpyDeviceToHost, m->s));
+    }
     stripe_sum(m->ctr, S_EDGES, 1, C_EDGES, m->s);
     TRY(read_ctr(m, 0, C_JP));
+    if (B > 1) TRY(sync(m));
     TRY(check_err(m, true));  // also the last row build's
-    if (aux) std::copy(m->haux, m->haux + 2 * B, need.begin());
     int nv = m->hctr[C_TOTAL], nt = m->hctr[C_TOTAL2];
+    if (B == 1) need = {nv, nt};
+    else if (aux) std::copy(m->haux, m->haux + 2 * B, need.begin());
     int edges = m->hctr[C_EDGES];
     if (nv == 0) {
       st->v[6] += edges;
@@ -1671,11 +1754,13 @@ pm_status pm_quality(pm_mesh* m, double* Q, double* qmin, double* dQdx, double* 
   TRY(ensure(m, m->qpart, 2 * (size_t)nparts + 2));
   if (Q || qmin) {
     timed(m, PM_K_QUALITY, m->st.T,
-          [&] { quality_sum(m->st, m->qpart.p, m->qpart.p + nparts, nparts, m->qpart.p + 2 * nparts, m->s); });
-    HIPCHK(hipMemcpyAsync(m->hq, m->qpart.p + 2 * nparts, 2 * sizeof(double), hipMemcpyDeviceToHost, m->s));
+          [&] { mail_next(m->mail); quality_sum(m->st, m->qpart.p, m->qpart.p + nparts, nparts, m->hq, m->mail, m->s); });
   }
   if (dQdx || dQdM) timed(m, PM_K_ADJOINT, m->st.V, [&] { quality_adjoint(m->st, dQdx, dQdM, m->s); });
-  TRY(sync(m));
+  // scalars alone come by mail; gradients are complete when the call returns,
+  // for any stream
+  if (dQdx || dQdM || m->prof.mask || !(Q || qmin)) TRY(sync(m));
+  else HIPCHK(mail_wait(m->mail, m->s));
   prof_flush(m);
   if (Q) *Q = m->hq[0];
   if (qmin) *qmin = m->hq[1];
@@ -1753,25 +1838,28 @@ pm_status pm_mesh_update(pm_mesh* m, const double* xy, const double* metric, int
   Store& st = m->st;
   size_t V = (size_t)st.V;
   hipMemcpyKind k = mem_kind == PM_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
-  // the old values, kept until the new ones pass the checks
-  TRY(ensure(m, m->upd, 5 * V));
-  double2* old_xy = (double2*)m->upd.p;
-  Met* old_met = (Met*)(m->upd.p + 2 * V);
+  // the new values are checked in blocks of their own, which then take the
+  // place of the old ones; a refused update leaves the mesh untouched
+  Store nst = st;
   if (xy) {
-    HIPCHK(hipMemcpyAsync(old_xy, st.xy, sizeof(double2) * V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(st.xy, xy, sizeof(double2) * V, k, m->s));
+    TRY(ensure(m, m->upx, (size_t)st.Vcap));
+    nst.xy = m->upx.p;
+    HIPCHK(hipMemcpyAsync(nst.xy, xy, sizeof(double2) * V, k, m->s));
   }
   if (metric) {
-    HIPCHK(hipMemcpyAsync(old_met, st.met, sizeof(Met) * V, hipMemcpyDeviceToDevice, m->s));
-    HIPCHK(hipMemcpyAsync(st.met, metric, sizeof(Met) * V, k, m->s));
+    TRY(ensure(m, m->upm, (size_t)st.Vcap));
+    nst.met = m->upm.p;
+    HIPCHK(hipMemcpyAsync(nst.met, metric, sizeof(Met) * V, k, m->s));
   }
-  k_validate(st, m->ctr, m->s);
-  pm_status r = check_err(m);
-  if (r != PM_OK) {
-    if (xy) HIPCHK(hipMemcpyAsync(st.xy, old_xy, sizeof(double2) * V, hipMemcpyDeviceToDevice, m->s));
-    if (metric) HIPCHK(hipMemcpyAsync(st.met, old_met, sizeof(Met) * V, hipMemcpyDeviceToDevice, m->s));
-    TRY(sync(m));
-    return r;
+  k_validate(nst, m->ctr, m->s);
+  TRY(check_err(m));
+  if (xy) {
+    std::swap(st.xy, m->upx.p);
+    m->upx.n = (size_t)st.Vcap;
+  }
+  if (metric) {
+    std::swap(st.met, m->upm.p);
+    m->upm.n = (size_t)st.Vcap;
   }
   ++m->topo;  // the per-element tensors smoothing keeps follow the metric
   return PM_OK;
@@ -1788,8 +1876,8 @@ pm_status pm_quality_noalloc(pm_mesh* m, double* Q, double* qmin, double* dQdx, 
     return fail(m, PM_E_ARG, "pm_quality_noalloc: call it with the handle's device current");
   double* ps = m->scratch;
   if (Q || qmin) {
-    quality_sum(m->st, ps, ps + nparts, nparts, ps + 2 * nparts, m->s);
-    HIPCHK(hipMemcpyAsync(m->hq, ps + 2 * nparts, 2 * sizeof(double), hipMemcpyDeviceToHost, m->s));
+    mail_next(m->mail);
+    quality_sum(m->st, ps, ps + nparts, nparts, m->hq, m->mail, m->s);
   }
   if (dQdx || dQdM) quality_adjoint(m->st, dQdx, dQdM, m->s);
   HIPCHK(hipStreamSynchronize(m->s));

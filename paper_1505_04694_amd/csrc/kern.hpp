@@ -5,6 +5,7 @@
 
 #include <string>
 
+#include "blocks.hpp"
 #include "common.hpp"
 
 namespace pm {
@@ -66,6 +67,10 @@ __device__ __forceinline__ int* stripe_ptr(int* ctr, int slot) {
   return ctr + C_STRIPE + w * kStripeW + slot;
 }
 void stripe_zero(int* ctr, int slot, int nslots, hipStream_t s);
+// the statistics cleared, no commit out of room
+void phase_start(int* ctr, hipStream_t s);
+// sums over stripes into pinned host memory, delivered as mail b (numbered by the caller)
+void stripe_mail(const int* ctr, int slot, int nslots, int* dst, const Mail& b, hipStream_t s);
 // ctr[dst + k] = sum over stripes of slot + k, k < nslots
 void stripe_sum(int* ctr, int slot, int nslots, int dst, hipStream_t s);
 constexpr int kMaxColours = 255;  // colour 0xFF marks "uncoloured"
@@ -161,6 +166,14 @@ int scan_partials_needed(int n);
 void zero_ints(int* p, int n, hipStream_t s);
 void fill_u8(uint8_t* p, int n, uint8_t v, hipStream_t s);
 void set_int(int* p, int v, hipStream_t s);
+// the vertex arrays of `from` into those of `to`, which hold n slots (free ones
+// dead, with empty rows); the elements likewise
+void copy_vertices(const Store& from, const Store& to, int n, hipStream_t s);
+void copy_elements(const Store& from, Elem* to, int n, hipStream_t s);
+// dead slots from V and T to the capacities
+void clear_tail(const Store& st, int V, int T, hipStream_t s);
+// the ranges of a single mesh
+void set_ranges(int* ranges, int vused, int tused, int V, int T, hipStream_t s);
 void tri_in(const int* tri3, int T, Elem* tri, hipStream_t s);
 void xy_in(const double* xy, int V, double2* out, hipStream_t s);
 void tags_from_xy(const double2* xy, int V, uint8_t* tag, hipStream_t s);
@@ -263,7 +276,8 @@ void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s)
 // flag/pos: V ints, partial: scan scratch
 void select_vertices(const Store& st, int mode, double L_low2, const uint8_t* active, uint8_t* nxt, int* out,
                      int* ctr, int* flag, int* pos, int* partial, hipStream_t s);
-void jp_init(const Store& st, const int* A, int n, Round rd, hipStream_t s);
+// (also clears the counts of waiting vertices)
+void jp_init(const Store& st, const int* A, int n, Round rd, int* ctr, hipStream_t s);
 // round words of the n vertices of the class lists cls (class c starts at
 // off[c], the device copy of the class offsets) as their colouring set them
 void restore_round(const Store& st, const int* cls, int n, const int* off, int ncol, Round rd, hipStream_t s);
@@ -347,7 +361,8 @@ struct DevRounds {
 };
 void rounds_dev(const Store& st, const DevRounds& d, OpArgs a, Commit cm, int kind, int* ctr, hipStream_t s);
 
-void quality_sum(const Store& st, double* psum, double* pmin, int nparts, double* out2, hipStream_t s);
+// Q and qmin to out2 (pinned host memory), delivered as mail b (numbered by the caller)
+void quality_sum(const Store& st, double* psum, double* pmin, int nparts, double* out2, const Mail& b, hipStream_t s);
 void quality_adjoint(const Store& st, double* dQdx, double* dQdM, hipStream_t s);
 void quality_per_mesh(const Store& st, double* out, hipStream_t s);
 void element_metrics(const Store& st, Met* out, hipStream_t s);

@@ -1435,6 +1435,7 @@ struct pm3_mesh {
   int64_t nncap = 0, necap = 0;
   int* ctr = nullptr;   // device counters
   int* hctr = nullptr;  // pinned mirror
+  pm::Mail mail;        // its block's
   // scratch
   int *cnt = nullptr, *off = nullptr, *cur = nullptr, *flag = nullptr, *scan = nullptr, *partial = nullptr;
   int *A = nullptr, *cls = nullptr, *col = nullptr, *blk = nullptr, *mark = nullptr,
@@ -1499,8 +1500,9 @@ void dfree3(T*& p) {
 }
 
 pm_status read_ctr(pm3_mesh* m) {
-  H3(hipMemcpyAsync(m->hctr, m->ctr, sizeof(int) * K_COUNT, hipMemcpyDeviceToHost, m->s));
-  H3(hipStreamSynchronize(m->s));
+  pm::mail_send(m->mail, m->ctr, K_COUNT, m->hctr, m->s);
+  H3(hipGetLastError());
+  H3(pm::mail_wait(m->mail, m->s));
   return PM_OK;
 }
 
@@ -1564,9 +1566,7 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
 // after read_ctr)
 pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
   pm::scan_excl(in, out, n, m->ctr + K_TOTAL, m->partial, m->s);
-  H3(hipGetLastError());
-  H3(hipMemcpyAsync(m->hctr, m->ctr, sizeof(int) * K_COUNT, hipMemcpyDeviceToHost, m->s));
-  H3(hipStreamSynchronize(m->s));
+  T3(read_ctr(m));
   *total = m->hctr[K_TOTAL];
   return PM_OK;
 }
@@ -1675,8 +1675,8 @@ pm_status class_lists(pm3_mesh* m, int n, int ncol, std::vector<int>& off, std::
   k_class_place<<<std::max(1, (n + kB - 1) / kB), kB, 0, m->s>>>(m->A, n, m->col, ncol, m->coff,
                                                                    m->ccount + kMaxColours, m->cls);
   H3(hipGetLastError());
-  H3(hipMemcpyAsync(m->hctr + K_COUNT, m->ccount, sizeof(int) * ncol, hipMemcpyDeviceToHost, m->s));
-  H3(hipStreamSynchronize(m->s));
+  pm::mail_send(m->mail, m->ccount, ncol, m->hctr + K_COUNT, m->s);
+  H3(pm::mail_wait(m->mail, m->s));
   size.assign(ncol, 0);
   off.assign(ncol + 1, 0);
   for (int c = 0; c < ncol; ++c) {
@@ -1759,10 +1759,11 @@ pm_status pm3_mesh_create(const pm3_mesh_desc* d, const pm_options* o, void* str
   };
   int V = (int)d->V, T = (int)d->T;
   if (pm::block_alloc(m->s, (void**)&m->ctr, sizeof(int) * K_COUNT) != hipSuccess ||
-      hipHostMalloc((void**)&m->hctr, sizeof(int) * (K_COUNT + 2 * kMaxColours), hipHostMallocDefault) != hipSuccess) {
+      !(m->hctr = (int*)pm::pinned_take())) {
     (void)hipGetLastError();
     return bail(PM_E_NOMEM);
   }
+  m->mail = pm::mail_of(m->hctr);
   if (reserve(m, V, T) != PM_OK) return bail(PM_E_NOMEM);
   Store3& st = m->st;
   st.V = V;
@@ -1822,7 +1823,7 @@ pm_status pm3_mesh_destroy(pm3_mesh* m) {
   dfree3(m->rows);
   dfree3(m->rec);
   dfree3(m->tops);
-  if (m->hctr) (void)hipHostFree(m->hctr);
+  pm::pinned_give(m->hctr);
   delete m;
   return PM_OK;
 }

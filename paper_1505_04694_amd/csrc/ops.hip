@@ -95,15 +95,17 @@ void select_vertices(const Store& st, int mode, double L_low2, const uint8_t* ac
 }
 
 // ---- Jones-Plassmann colouring (Sec. 3.2) ------------------------------------------------
-__global__ void k_jp_init(Store st, const int* __restrict__ A, int n, Round rd) {
+__global__ void k_jp_init(Store st, const int* __restrict__ A, int n, Round rd, int* ctr) {
+  if (blockIdx.x == 0 && threadIdx.x < kStripes)
+    for (int k = 0; k < 8; ++k) ctr[C_STRIPE + threadIdx.x * kStripeW + S_JPL + k] = 0;
   for (int i = gtid(); i < n; i += gstride()) {
     int v = A[i];
     uint64_t prio = key_of(st, rd, v) >> 32;
     rd.rw[v] = (prio << 32) | kRwAct | 0xFFull;
   }
 }
-void jp_init(const Store& st, const int* A, int n, Round rd, hipStream_t s) {
-  if (n > 0) k_jp_init<<<grid_for(n), kBlock, 0, s>>>(st, A, n, rd);
+void jp_init(const Store& st, const int* A, int n, Round rd, int* ctr, hipStream_t s) {
+  if (n > 0) k_jp_init<<<grid_for(n), kBlock, 0, s>>>(st, A, n, rd, ctr);
 }
 
 // start of device-driven rounds: round r, next epoch, last stamp; the
@@ -337,6 +339,23 @@ __global__ void k_stripe_sum(int* ctr, int slot, int nslots, int dst) {
     for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
     if (w == 0) ctr[dst + k] = x;
   }
+}
+__global__ void k_phase_start(int* ctr) {
+  for (int k = 0; k < 6; ++k) ctr[C_STRIPE + threadIdx.x * kStripeW + S_EVAL + k] = 0;
+  if (threadIdx.x == 0) ctr[C_FAILEP] = INT_MAX;
+}
+void phase_start(int* ctr, hipStream_t s) { k_phase_start<<<1, kStripes, 0, s>>>(ctr); }
+__global__ void k_stripe_mail(const int* ctr, int slot, int nslots, int* dst, int* at, int no) {
+  for (int k = 0; k < nslots; ++k) {
+    int x = ctr[C_STRIPE + threadIdx.x * kStripeW + slot + k];
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    if (threadIdx.x == 0) dst[k] = x;
+  }
+  mail_post(at, no);
+}
+void stripe_mail(const int* ctr, int slot, int nslots, int* dst, const Mail& b, hipStream_t s) {
+  k_stripe_mail<<<1, kStripes, 0, s>>>(ctr, slot, nslots, dst, (int*)b.at, b.no);
 }
 void stripe_sum(int* ctr, int slot, int nslots, int dst, hipStream_t s) {
   static_assert(kStripes == kWave, "one lane per stripe");
@@ -692,16 +711,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_jp_gather(const int* __restri
   constexpr int NT = kSmallThreads;
   __shared__ int offs[NT], wsum[NT / kWave], left;
   int tid = (int)threadIdx.x, lane = __lane_id(), wv = tid / kWave;
-  if (tid < kStripes) {
-    int* sp = ctr + C_STRIPE + tid * kStripeW + slot;
-    int x = *sp;
+  // wavefront w adds up what the iterations w modulo 8 left
+  if (wv < 8) {
+    int x = ctr[C_STRIPE + lane * kStripeW + S_JPL + wv];
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
-    if (tid == 0) {
+    if (lane == 0) ctr[C_JPL + wv] = x;
+    if (S_JPL + wv == slot && lane == 0) {
       left = x;
       *nleft = x <= kSmallColour ? x : -1;
+      ctr[C_JP] = x <= kSmallColour ? 0 : x;
     }
-    if (x <= kSmallColour) *sp = 0;
   }
   __syncthreads();
   int n = left;
@@ -2824,7 +2844,7 @@ __global__ void k_quality(Store st, double* __restrict__ psum, double* __restric
   }
 }
 __global__ void k_quality_final(const double* __restrict__ psum, const double* __restrict__ pmin, int np,
-                                double* __restrict__ out) {
+                                double* __restrict__ out, int* at, int no) {
   __shared__ double ls[QB], lm[QB];
   double s = 0.0, mn = INFINITY;
   for (int i = threadIdx.x; i < np; i += QB) {
@@ -2846,6 +2866,7 @@ __global__ void k_quality_final(const double* __restrict__ psum, const double* _
     out[0] = ls[0];
     out[1] = lm[0];
   }
+  mail_post(at, no);
 }
 // one block per mesh of a batch: Q and qmin of each mesh's element range
 template <int QK>
@@ -2882,9 +2903,9 @@ void quality_per_mesh(const Store& st, double* out, hipStream_t s) {
   (st.qk ? k_quality_mesh<1> : k_quality_mesh<0>)<<<st.B, QB, 0, s>>>(st, out);
 }
 
-void quality_sum(const Store& st, double* psum, double* pmin, int nparts, double* out2, hipStream_t s) {
+void quality_sum(const Store& st, double* psum, double* pmin, int nparts, double* out2, const Mail& b, hipStream_t s) {
   (st.qk ? k_quality<1> : k_quality<0>)<<<nparts, QB, 0, s>>>(st, psum, pmin);
-  k_quality_final<<<1, QB, 0, s>>>(psum, pmin, nparts, out2);
+  k_quality_final<<<1, QB, 0, s>>>(psum, pmin, nparts, out2, (int*)b.at, b.no);
 }
 
 void quality_adjoint(const Store& st, double* dQdx, double* dQdM, hipStream_t s) {

@@ -5,6 +5,8 @@
 // elements (Sec. 3.1: per-vertex adjacency lists). Every row is a sorted id
 // set stored in a slack-padded slot of its pool, so the commit can grow it in
 // place; a row that outgrows its slot moves to the pool's bump region.
+#include <algorithm>
+
 #include "kern.hpp"
 
 namespace pm {
@@ -776,6 +778,47 @@ void fill_u8(uint8_t* p, int n, uint8_t v, hipStream_t s) {
 }
 __global__ void k_set_int(int* p, int v) { *p = v; }
 void set_int(int* p, int v, hipStream_t s) { k_set_int<<<1, 1, 0, s>>>(p, v); }
+
+__global__ void k_copy_vertices(Store a, Store b, int n) {
+  for (int v = gtid(); v < n; v += gstride()) {
+    bool old = v < a.V;
+    if (old) {
+      b.xy[v] = a.xy[v];
+      b.met[v] = a.met[v];
+      b.tag[v] = a.tag[v];
+    }
+    b.valive[v] = old ? a.valive[v] : 0;
+    b.hdr[v] = old ? a.hdr[v] : make_int4(0, 0, 0, 0);
+    b.cap[v] = old ? a.cap[v] : make_int2(0, 0);
+  }
+}
+void copy_vertices(const Store& from, const Store& to, int n, hipStream_t s) {
+  k_copy_vertices<<<grid_for(n), kBlock, 0, s>>>(from, to, n);
+}
+__global__ void k_copy_elements(const Elem* __restrict__ a, int T, Elem* __restrict__ b, int n) {
+  for (int t = gtid(); t < n; t += gstride()) b[t] = t < T ? a[t] : make_int4(0, 0, 0, 0);
+}
+void copy_elements(const Store& from, Elem* to, int n, hipStream_t s) {
+  k_copy_elements<<<grid_for(n), kBlock, 0, s>>>(from.tri, from.T, to, n);
+}
+__global__ void k_clear_tail(Store st, int V, int T) {
+  for (int v = V + gtid(); v < st.Vcap; v += gstride()) st.valive[v] = 0;
+  for (int t = T + gtid(); t < st.Tcap; t += gstride()) st.tri[t] = make_int4(0, 0, 0, 0);
+}
+void clear_tail(const Store& st, int V, int T, hipStream_t s) {
+  k_clear_tail<<<grid_for(std::max(st.Vcap - V, st.Tcap - T)), kBlock, 0, s>>>(st, V, T);
+}
+__global__ void k_set_ranges(int* r, int vused, int tused, int V, int T) {
+  r[0] = 0;
+  r[1] = V;
+  r[2] = vused;
+  r[3] = 0;
+  r[4] = T;
+  r[5] = tused;
+}
+void set_ranges(int* ranges, int vused, int tused, int V, int T, hipStream_t s) {
+  k_set_ranges<<<1, 1, 0, s>>>(ranges, vused, tused, V, T);
+}
 
 // input triangles (T x 3) to stored elements: rotated smallest-id first, live
 __global__ void k_tri_in(const int* __restrict__ tri3, int T, Elem* __restrict__ tri) {
