@@ -18,6 +18,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/pm3.h"
@@ -48,12 +49,25 @@ enum {
   K_COMMIT = 5,     // collapses / accepted moves
   K_EDGES = 6,      // edges tested by refinement
   K_TOTAL = 7,      // scan total
-  K_CCOMMIT = 8,    // collapses of the class in progress (gates its row commit)
+  K_CCOMMIT = 8,    // 1: the class in progress collapsed something (gates its row commit)
   K_ROOM = 9,       // a row commit ran out of room (pool stripe full, or a row past the wavefront form)
   K_ROOMEP = 10,    // the epoch of the class whose commit ran out of room
   K_NROWS = 11,     // rows stamped by the class in progress (the length of its row list)
-  K_COUNT = 16
+  K_WAIT = 12,      // vertices left to the one-block end of a colouring
+  K_COUNT = 16,
+  K_CLASS = K_COUNT,                    // class sizes, cursors and offsets, kMaxColours each
+  K_STRIPE = K_CLASS + 3 * kMaxColours, // kStripes lines of striped counts
+  K_ALL = K_STRIPE + 64 * 32
 };
+// Counts that every wavefront adds to are striped over 64 lines and summed by
+// the read-back: adds to one line take about 10 ns each, one after another (the
+// four counts of the largest collapse launches, 58,000 wavefronts, took most of
+// their 1.5 ms).
+constexpr int kStripes = 64, kStripeW = 32;
+enum { S_COLOURED, S_EVAL, S_DEFER, S_COMMIT, S_EDGES, S_SLOTS };
+__device__ __forceinline__ int counter_of(int slot) {
+  return slot == S_COLOURED ? K_COLOURED : slot == S_EVAL ? K_EVAL : slot == S_DEFER ? K_DEFER : slot == S_COMMIT ? K_COMMIT : K_EDGES;
+}
 enum { E_MESH = 1, E_METRIC = 2, E_COLOURS = 4, E_LEAVES = 8 };
 
 struct Met6 {
@@ -180,8 +194,36 @@ __device__ __forceinline__ double qual(const Geo3& g) {
 
 __device__ __forceinline__ bool tag_ok(const Store3& st, int v, int u) { return (st.tag[v] & ~st.tag[u]) == 0; }
 
-__device__ __forceinline__ void stripe_add(int* ctr, int slot, int x) {
-  if (x) atomicAdd(&ctr[slot], x);
+// the sum of x over the wavefront (every lane calls it) to a striped count
+__device__ __forceinline__ void count_add(int* ctr, int slot, int x) {
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
+  int w = (int)((blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) & (kStripes - 1));
+  if (__lane_id() == 0 && x) atomicAdd(&ctr[K_STRIPE + w * kStripeW + slot], x);
+}
+// counters zero, and no stripe holds anything
+__device__ __forceinline__ void zero_counters(int* ctr) {
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x < K_COUNT) ctr[threadIdx.x] = 0;
+  if (threadIdx.x < kStripes)
+    for (int k = 0; k < S_SLOTS; ++k) ctr[K_STRIPE + threadIdx.x * kStripeW + k] = 0;
+}
+__global__ void k_zero_ctr(int* ctr) { zero_counters(ctr); }
+// the counters (and `more` class sizes behind them) to the host, striped counts
+// summed (256 threads)
+__global__ void k_mail3(const int* ctr, int more, int* dst, int* at, int no) {
+  int tid = (int)threadIdx.x;
+  for (int i = tid; i < K_COUNT + more; i += (int)blockDim.x) {
+    bool striped = i == K_COLOURED || i == K_EVAL || i == K_DEFER || i == K_COMMIT || i == K_EDGES;
+    if (!striped) dst[i] = ctr[i];
+  }
+  for (int k = tid / kWave; k < S_SLOTS; k += (int)blockDim.x / kWave) {
+    int x = ctr[K_STRIPE + (tid & (kWave - 1)) * kStripeW + k];
+#pragma unroll
+    for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    if ((tid & (kWave - 1)) == 0) dst[counter_of(k)] = x;
+  }
+  pm::mail_post(at, no);
 }
 
 // ---- input, validation ------------------------------------------------------------------
@@ -654,29 +696,110 @@ __global__ void k_tops_init(int* tops, int64_t base, int64_t per) {
 }
 
 // ---- colouring (Sec. 3.2) -----------------------------------------------------------------
-// One Jones-Plassmann iteration `it`: a waiting vertex takes the first colour
-// free among its coloured neighbours once every active neighbour with a
-// larger key was coloured in an earlier iteration. A colour is stored with
-// its iteration, (it << 8) | colour, and a neighbour coloured in this same
-// iteration counts as waiting, so the result does not depend on the order in
-// which the threads run: the greedy first-fit colouring in descending key
-// order. k_jp_strip leaves the colours alone once the colouring is done. A
-// vertex that has to wait remembers the neighbour it waits for (blk) and
-// reads its row again only once that neighbour has a colour. Counts go to
-// the counters once per wavefront.
-__device__ __forceinline__ bool coloured_before(int cw, int it) { return cw >= 0 && (cw >> 8) < it; }
+// A vertex takes the first colour free among the active neighbours of larger
+// key, once all of those have one: the greedy first-fit colouring in descending
+// key order, whatever the order in which threads run. One scan of its row gives
+// a vertex's record, the neighbours it waits for; from there on it follows their
+// colours one after another. Re-reading the row of every waiting vertex in every
+// iteration (14 neighbours, each two look-ups and a hash) took 78 us an iteration
+// for the long lists of a mesh of 250,000 vertices.
 
-// one visit of a waiting vertex v in iteration it: its colour (returned),
-// or -1 while a neighbour it has to wait for has none
-__device__ __forceinline__ int jp_visit(const Store3& st, int v, const uint8_t* __restrict__ act, int* col, int* blk,
-                                        int it, uint64_t sseed, int* ctr) {
-  int b = blk[v];
-  if (b >= 0 && !coloured_before(col[b], it)) return -1;
-  uint64_t kv = vkey(sseed, (uint32_t)v);
+// Lists of at most kSolve vertices, and what is left of a longer one once no
+// more than that wait, are coloured by one work-group in LDS, without barriers:
+// a record then holds places in the list (blk), 16 bits each (one work-group
+// iterating over the rows took 80 us for some hundred vertices).
+constexpr int kSolve = 2048, kSolveThreads = 1024, kPreds = 32;
+struct Rec3 {
+  uint64_t places[kPreds / 4];  // 16 bits each
+  uint64_t used;                // colours taken, below 64
+  int cnt;                      // places; -1: more than kPreds, or a colour past 63
+  int pad;
+};
+// of a long list: the neighbours themselves, and how many have been followed
+struct RecL {
+  int ids[kPreds];
+  uint64_t used;
+  int cnt, pos;  // cnt: as above (pos: the neighbour it waits for, or -1); -2: the vertex has its colour
+};
+
+// the list's vertices active, each with its place
+__global__ void k_place(const int* __restrict__ A, int n, uint8_t* act, int* blk) {
+  for (int i = gtid(); i < n; i += gstride()) {
+    act[A[i]] = 1;
+    blk[A[i]] = i;
+  }
+}
+// the vertices of A without a colour: their list, their places, their number
+__global__ void k_waiting(const int* __restrict__ A, int n, const int* __restrict__ col, int* out, int* blk, int* ctr) {
+  for (int i = gtid(); i < n; i += gstride()) {
+    int v = A[i];
+    if (col[v] >= 0) continue;
+    int k = pm::wave_append_slot(&ctr[K_WAIT]);
+    if (k < kSolve) {  // the host has counted them
+      out[k] = v;
+      blk[v] = k;
+    }
+  }
+}
+// eight lanes a vertex, each every eighth entry of its row; a lane's places go
+// behind the lower lanes' (their order does not matter)
+template <class R>
+__global__ void k_pred(Store3 st, const int* __restrict__ A, int n, const uint8_t* __restrict__ act,
+                       const int* __restrict__ col, const int* __restrict__ blk, uint64_t sseed, R* recs) {
+  constexpr bool kLong = std::is_same<R, RecL>::value;
+  constexpr int G = 8;
+  int lane = __lane_id(), l = lane & (G - 1), gb = lane & ~(G - 1);
+  for (int i = gtid() / G; i < n; i += gstride() / G) {
+    int v = A[i];
+    uint64_t kv = vkey(sseed, (uint32_t)v), used = 0;
+    int4 h = st.hdr[v];
+    int cnt = 0;
+    bool big = false;
+    for (int j0 = 0; j0 < h.y; j0 += G) {
+      int j = j0 + l, place = -1;
+      if (j < h.y) {
+        int w = st.nn[h.x + j], cw = col[w];
+        if (act[w] && vkey(sseed, (uint32_t)w) > kv) {
+          if (cw < 0) place = kLong ? w : blk[w];
+          else if ((cw & 0xFF) < 64) used |= 1ull << (cw & 0xFF);
+          else big = true;
+        }
+      }
+      uint32_t has = (uint32_t)(__ballot(place >= 0) >> gb) & 0xFFu;
+      int at = cnt + __popc(has & ((1u << l) - 1u));
+      if (place >= 0 && at < kPreds) {
+        if constexpr (kLong) recs[i].ids[at] = place;
+        else ((uint16_t*)recs[i].places)[at] = (uint16_t)place;
+      }
+      cnt += __popc(has);
+    }
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) {
+      uint32_t lo = (uint32_t)used, hi = (uint32_t)(used >> 32);
+      lo |= (uint32_t)__shfl_xor((int)lo, d);
+      hi |= (uint32_t)__shfl_xor((int)hi, d);
+      used = (uint64_t)hi << 32 | lo;
+    }
+    big = ((__ballot(big) >> gb) & 0xFFu) != 0;
+    if (l == 0) {
+      recs[i].used = used;
+      recs[i].cnt = big || cnt > kPreds ? -1 : cnt;
+      if constexpr (kLong) recs[i].pos = big || cnt > kPreds ? -1 : 0;
+    }
+  }
+}
+
+__device__ __forceinline__ int colour_of(const int* col, int w) {
+  return __hip_atomic_load(col + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// the visit of a vertex whose record did not hold everything: its colour, or -1
+// while a neighbour before it has none (blocker: that neighbour, asked first the
+// next time). Eight neighbours at a time, their loads in flight together.
+__device__ __forceinline__ int far_visit(const Store3& st, int v, const uint8_t* act, const int* col, uint64_t sseed,
+                                         int& blocker, int* ctr) {
+  if (blocker >= 0 && colour_of(col, blocker) < 0) return -1;
+  uint64_t kv = vkey(sseed, (uint32_t)v), used[kMaxColours / 64] = {0, 0, 0, 0};
   int4 h = st.hdr[v];
-  uint64_t used[kMaxColours / 64] = {0, 0, 0, 0};
-  // eight neighbours at a time: their ids, then their colours and activity
-  // flags, all in flight together; taken in row order as a serial loop
   constexpr int B = 8;
   for (int j0 = 0; j0 < h.y; j0 += B) {
     int w[B], cw[B];
@@ -685,109 +808,205 @@ __device__ __forceinline__ int jp_visit(const Store3& st, int v, const uint8_t* 
     for (int q = 0; q < B; ++q) w[q] = j0 + q < h.y ? st.nn[h.x + j0 + q] : -1;
 #pragma unroll
     for (int q = 0; q < B; ++q) {
-      cw[q] = w[q] >= 0 ? col[w[q]] : -1;
+      cw[q] = w[q] >= 0 ? colour_of(col, w[q]) : -1;
       aw[q] = w[q] >= 0 ? act[w[q]] : 0;
     }
 #pragma unroll
     for (int q = 0; q < B; ++q) {
-      if (w[q] < 0) continue;
-      if (coloured_before(cw[q], it)) {
-        int c = cw[q] & 0xFF;
-        used[c >> 6] |= 1ull << (c & 63);
-      } else if (aw[q] && vkey(sseed, (uint32_t)w[q]) > kv) {
-        blk[v] = w[q];
+      if (!aw[q] || vkey(sseed, (uint32_t)w[q]) < kv) continue;
+      if (cw[q] < 0) {
+        blocker = w[q];
         return -1;
       }
+#pragma unroll
+      for (int u = 0; u < kMaxColours / 64; ++u)
+        if (cw[q] >> 6 == u) used[u] |= 1ull << (cw[q] & 63);
     }
   }
   int c = -1;
-  for (int q = 0; q < kMaxColours / 64 && c < 0; ++q)
-    if (~used[q]) c = q * 64 + __ffsll((long long)~used[q]) - 1;
+#pragma unroll
+  for (int q = 0; q < kMaxColours / 64; ++q)
+    if (c < 0 && ~used[q]) c = q * 64 + __ffsll((long long)~used[q]) - 1;
   if (c < 0) {
     atomicOr(&ctr[K_ERR], E_COLOURS);
     c = kMaxColours - 1;
   }
-  col[v] = (it << 8) | c;
   return c;
 }
 
-// a wavefront's counts: vertices coloured and colours used
-__device__ __forceinline__ void jp_counts(int coloured, int ncol, int* ctr) {
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) {
-    coloured += __shfl_xor(coloured, d);
-    ncol = max(ncol, __shfl_xor(ncol, d));
-  }
-  if (__lane_id() == 0 && coloured > 0) {
-    atomicAdd(&ctr[K_COLOURED], coloured);
-    atomicMax(&ctr[K_NCOL], ncol);
-  }
-}
-
-__global__ void k_jp(Store3 st, const int* __restrict__ A, int n, const uint8_t* __restrict__ act, int* col,
-                     int* blk, int it, uint64_t sseed, int* ctr) {
+// One iteration over a long list: every waiting vertex follows the neighbours it
+// waits for as far as they have colours, kLocal times over (colours stored by
+// the work-group itself are seen at once, others at the next launch). Counts go
+// to the counters once per wavefront.
+constexpr int kLocal = 3;
+__global__ void __launch_bounds__(256) k_follow(Store3 st, const int* __restrict__ A, int n, const uint8_t* act, int* col,
+                                               uint64_t sseed, RecL* recs, int* ctr) {
   int coloured = 0, ncol = 0;
   for (int i = gtid(); i < n; i += gstride()) {
-    int v = A[i];
-    if (col[v] >= 0) continue;
-    int c = jp_visit(st, v, act, col, blk, it, sseed, ctr);
+    RecL& r = recs[i];
+    int cnt = r.cnt, pos = r.pos, was = pos;
+    if (cnt == -2) continue;
+    uint64_t used = r.used;
+    int v = A[i], c = -1;
+    for (int p = 0; p < kLocal && c < 0; ++p) {
+      while (pos < cnt) {
+        int y = colour_of(col, r.ids[pos]);
+        if (y < 0) break;
+        if (y >= 64) {
+          cnt = pos = -1;
+          break;
+        }
+        used |= 1ull << y;
+        ++pos;
+      }
+      if (cnt >= 0 && pos == cnt) {
+        if (~used) c = __ffsll((long long)~used) - 1;
+        else cnt = pos = -1;
+      }
+      // (its blocker in pos)
+      if (cnt < 0) c = far_visit(st, v, act, col, sseed, pos, ctr);
+    }
     if (c >= 0) {
+      ((volatile int*)col)[v] = c;
+      r.cnt = -2;
       ++coloured;
       ncol = max(ncol, c + 1);
-    }
-  }
-  jp_counts(coloured, ncol, ctr);
-}
-
-// Lists of at most kJpOne vertices (one per thread): one work-group runs the
-// same iterations to completion, separated by block barriers instead of
-// launches (at most n + 8 of them, as the host allows one launch each). The
-// work-group's waves share one CU's vector L1, which their stores write
-// through, so every iteration sees the colours of the ones before it.
-constexpr int kJpOne = 1024;
-constexpr int kJpOneThreads = 1024;
-__global__ void __launch_bounds__(kJpOneThreads) k_jp_one(Store3 st, const int* __restrict__ A, int n,
-                                                          const uint8_t* __restrict__ act, int* col, int* blk,
-                                                          uint64_t sseed, int* ctr) {
-  int coloured = 0, ncol = 0;
-  for (int it = 0; it <= n + 8; ++it) {
-    bool waiting = false;
-    for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x) {
-      int v = A[i];
-      if (col[v] >= 0) continue;
-      int c = jp_visit(st, v, act, col, blk, it, sseed, ctr);
-      if (c >= 0) {
-        ++coloured;
-        ncol = max(ncol, c + 1);
-      } else {
-        waiting = true;
+    } else {
+      if (cnt < 0) r.cnt = cnt;
+      if (pos != was) {
+        r.used = used;
+        r.pos = pos;
       }
     }
-    if (!__syncthreads_or(waiting)) break;
   }
-  jp_counts(coloured, ncol, ctr);
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) ncol = max(ncol, __shfl_xor(ncol, d));
+  count_add(ctr, S_COLOURED, coloured);
+  // (a stale count only costs the add)
+  if (__lane_id() == 0 && ncol > ctr[K_NCOL]) atomicMax(&ctr[K_NCOL], ncol);
 }
 
-__global__ void k_jp_strip(const int* __restrict__ A, int n, int* col) {
-  for (int i = gtid(); i < n; i += gstride()) {
-    int v = A[i];
-    if (col[v] >= 0) col[v] &= 0xFF;
+// Colours the list A (n <= K * kSolveThreads) from its records, K vertices a
+// thread, each thread going round its own until all have a colour. The waiting
+// vertex of largest key is always ready, so the passes end (they are bounded
+// all the same). The places are held in registers: what bounds it is the longest
+// chain of waiting vertices, an LDS round trip per link.
+constexpr int kMaxPasses = 1 << 20;
+template <int K>
+__device__ __forceinline__ void solve3(const Store3& st, const int* A, int n, const Rec3* recs, const uint8_t* act,
+                                       int* col, uint64_t sseed, volatile uint16_t* cl, int* ctr) {
+  constexpr int NT = kSolveThreads, W = kPreds / 4;
+  int tid = (int)threadIdx.x;
+  uint64_t cur[K][W], used[K];
+  int pos[K], cnt[K];
+  uint32_t todo = 0, far = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    int i = tid + k * NT;
+    used[k] = 0;
+    pos[k] = cnt[k] = 0;
+#pragma unroll
+    for (int q = 0; q < W; ++q) cur[k][q] = 0;
+    if (i >= n) continue;
+    todo |= 1u << k;
+    const Rec3& r = recs[i];
+    cnt[k] = r.cnt;
+    used[k] = r.used;
+#pragma unroll
+    for (int q = 0; q < W; ++q) cur[k][q] = r.places[q];
+    if (r.cnt < 0) far |= 1u << k;
   }
+  for (int p = 0; todo && p < kMaxPasses; ++p) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!((todo & ~far) >> k & 1)) continue;
+      int i = tid + k * NT;
+      while (pos[k] < cnt[k]) {
+        int y = cl[cur[k][0] & 0xFFFF];
+        if (y == 0xFFFF) break;
+        if (y < 64) used[k] |= 1ull << y;
+        else far |= 1u << k;
+        ++pos[k];
+        cur[k][0] >>= 16;
+        if ((pos[k] & 3) == 0) {
+#pragma unroll
+          for (int q = 0; q + 1 < W; ++q) cur[k][q] = cur[k][q + 1];
+        }
+      }
+      if (pos[k] < cnt[k]) continue;
+      if (!~used[k]) far |= 1u << k;
+      if (far >> k & 1) continue;
+      int c = __ffsll((long long)~used[k]) - 1;
+      cl[i] = (uint16_t)c;
+      ((volatile int*)col)[A[i]] = c;
+      todo &= ~(1u << k);
+    }
+    uint32_t slow = todo & far;
+    while (slow) {
+      int k = __ffs((int)slow) - 1, i = tid + k * NT;
+      slow &= slow - 1;
+      int b = -1, c = far_visit(st, A[i], act, col, sseed, b, ctr);
+      if (c < 0) continue;
+      cl[i] = (uint16_t)c;
+      ((volatile int*)col)[A[i]] = c;
+      todo &= ~(1u << k);
+    }
+  }
+  if (todo) atomicOr(&ctr[K_ERR], E_COLOURS);  // cannot happen
+}
+
+// cnt, off, cls: also the class sizes, offsets and lists (a list coloured here
+// as a whole), or null
+__global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A, int n, const Rec3* recs,
+                                                       const uint8_t* act, int* col, uint64_t sseed, int* ctr, int* cnt,
+                                                       int* off, int* cls) {
+  __shared__ uint16_t cl[kSolve];
+  __shared__ int hist[kMaxColours], cur[kMaxColours], wsum[4], ncol;
+  int tid = (int)threadIdx.x;
+  for (int i = tid; i < n; i += kSolveThreads) cl[i] = 0xFFFF;
+  if (tid < kMaxColours) hist[tid] = 0;
+  if (tid == 0) ncol = 0;
+  __syncthreads();
+  if (n <= kSolveThreads) solve3<1>(st, A, n, recs, act, col, sseed, cl, ctr);
+  else solve3<kSolve / kSolveThreads>(st, A, n, recs, act, col, sseed, cl, ctr);
+  __syncthreads();
+  for (int i = tid; i < n; i += kSolveThreads) atomicAdd(&hist[cl[i]], 1);
+  __syncthreads();
+  int h = tid < kMaxColours ? hist[tid] : 0, incl = h, lane = __lane_id();
+  if (h) atomicMax(&ncol, tid + 1);
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    int o = __shfl_up(incl, d);
+    if (lane >= d) incl += o;
+  }
+  if (tid < kMaxColours && lane == kWave - 1) wsum[tid / kWave] = incl;
+  __syncthreads();
+  if (tid == 0) {
+    atomicAdd(&ctr[K_STRIPE + S_COLOURED], n);
+    atomicMax(&ctr[K_NCOL], ncol);
+  }
+  if (!cls) return;
+  if (tid < kMaxColours) {
+    int o = incl - h;
+    for (int w = 0; w < tid / kWave; ++w) o += wsum[w];
+    cur[tid] = o;
+    off[tid] = o;
+    cnt[tid] = h;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += kSolveThreads) cls[atomicAdd(&cur[cl[i]], 1)] = A[i];
 }
 
 __global__ void k_fill_int(int* p, int n, int x) {
   for (int i = gtid(); i < n; i += gstride()) p[i] = x;
 }
 
-__global__ void k_set_act(const int* __restrict__ A, int n, uint8_t* act, uint8_t x) {
-  for (int i = gtid(); i < n; i += gstride()) act[A[i]] = x;
-}
-
-// the list's vertices active, with no neighbour to wait for yet
-__global__ void k_jp_init(const int* __restrict__ A, int n, uint8_t* act, int* blk) {
-  for (int i = gtid(); i < n; i += gstride()) {
-    act[A[i]] = 1;
-    blk[A[i]] = -1;
+// no colours, no active vertices, counters zero
+__global__ void k_colour_start(int* col, uint8_t* act, int V, int* ctr) {
+  zero_counters(ctr);
+  for (int v = gtid(); v < V; v += gstride()) {
+    col[v] = -1;
+    act[v] = 0;
   }
 }
 
@@ -1054,14 +1273,10 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
     cm = 1;
   }
   if (j0 != 0) ev = df = cm = 0;
-  // one add per wavefront and counter
-  uint64_t me = __ballot(ev), md = __ballot(df), mc = __ballot(cm);
-  if (__lane_id() == 0) {
-    stripe_add(ctr, K_EVAL, __popcll(me));
-    stripe_add(ctr, K_DEFER, __popcll(md));
-    stripe_add(ctr, K_COMMIT, __popcll(mc));
-    stripe_add(ctr, K_CCOMMIT, __popcll(mc));
-  }
+  count_add(ctr, S_EVAL, ev);
+  count_add(ctr, S_DEFER, df);
+  count_add(ctr, S_COMMIT, cm);
+  if (cm) ctr[K_CCOMMIT] = 1;
 }
 
 // stable renumbering of live vertices and elements (a monotone map keeps the
@@ -1112,7 +1327,7 @@ __global__ void k_mark(Store3 st, double L_up2, int* mark, int* cnt, int* ctr) {
     }
     cnt[v] = c;
   }
-  stripe_add(ctr, K_EDGES, edges);
+  count_add(ctr, S_EDGES, edges);
 }
 
 // new vertex ids V0 + (rank of the edge in (min id, max id) order); the
@@ -1345,8 +1560,8 @@ __global__ void __launch_bounds__(256) k_smooth(Store3 st, const int* __restrict
       ++cm;
     }
   }
-  stripe_add(ctr, K_EVAL, ev);
-  stripe_add(ctr, K_COMMIT, cm);
+  count_add(ctr, S_EVAL, ev);
+  count_add(ctr, S_COMMIT, cm);
 }
 
 // ---- quality ----------------------------------------------------------------------------------------
@@ -1433,13 +1648,16 @@ struct pm3_mesh {
   Store3 st;
   int Vcap = 0, Tcap = 0;
   int64_t nncap = 0, necap = 0;
-  int* ctr = nullptr;   // device counters
+  int* ctr = nullptr;   // device counters, then class sizes, cursors and offsets (kMaxColours each)
   int* hctr = nullptr;  // pinned mirror
   pm::Mail mail;        // its block's
   // scratch
   int *cnt = nullptr, *off = nullptr, *cur = nullptr, *flag = nullptr, *scan = nullptr, *partial = nullptr;
   int *A = nullptr, *cls = nullptr, *col = nullptr, *blk = nullptr, *mark = nullptr,
-      *tcnt = nullptr, *tscan = nullptr, *ccount = nullptr, *coff = nullptr;
+      *tcnt = nullptr, *tscan = nullptr;
+  Rec3* recs = nullptr;  // one-block colourings: predecessor records
+  RecL* recl = nullptr;  // long colourings', lcap of them
+  int lcap = 0;
   uint8_t *act = nullptr, *nxt = nullptr;
   double* qbuf = nullptr;
   int scap = 0, tscap = 0, pcap = 0;
@@ -1499,15 +1717,17 @@ void dfree3(T*& p) {
   p = nullptr;
 }
 
-pm_status read_ctr(pm3_mesh* m) {
-  pm::mail_send(m->mail, m->ctr, K_COUNT, m->hctr, m->s);
+// the counters, and `more` class sizes behind them
+pm_status read_ctr(pm3_mesh* m, int more = 0) {
+  pm::mail_next(m->mail);
+  k_mail3<<<1, kB, 0, m->s>>>(m->ctr, more, m->hctr, (int*)m->mail.at, m->mail.no);
   H3(hipGetLastError());
   H3(pm::mail_wait(m->mail, m->s));
   return PM_OK;
 }
 
 pm_status zero_ctr(pm3_mesh* m) {
-  k_fill_int<<<1, kB, 0, m->s>>>(m->ctr, K_COUNT, 0);
+  k_zero_ctr<<<1, kB, 0, m->s>>>(m->ctr);
   H3(hipGetLastError());
   return PM_OK;
 }
@@ -1625,58 +1845,76 @@ pm_status select_list(pm3_mesh* m, int mode, double L_low2, int* n) {
 }
 
 // Jones-Plassmann colouring of the list A[0, n); col holds the colours
-// (-1 elsewhere); returns the colour count
-pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, int* ncol) {
+// (-1 elsewhere); returns the colour count. A short list comes with its class
+// lists (*listed: m->cls, and the sizes in the counters' mirror)
+pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, int* ncol, bool* listed) {
   Store3& st = m->st;
   uint64_t sseed = stream_seed(m->seed, ctx);
-  k_fill_int<<<grid(st.V), kB, 0, m->s>>>(m->col, st.V, -1);
-  k_fill_u8<<<grid(st.V), kB, 0, m->s>>>(m->act, st.V, 0);
-  k_jp_init<<<grid(n), kB, 0, m->s>>>(m->A, n, m->act, m->blk);
-  T3(zero_ctr(m));
+  *listed = false;
+  *ncol = 0;
+  if (!m->recs) T3(dgrow(m, &m->recs, 0, kSolve, false));
+  k_colour_start<<<grid(st.V), kB, 0, m->s>>>(m->col, m->act, st.V, m->ctr);
+  if (n == 0) return PM_OK;
+  int* cnt = m->ctr + K_CLASS;
+  // the records' lanes: eight a vertex
+  auto solve = [&](const int* A, int k, bool whole) {
+    k_pred<<<grid(8 * (int64_t)k), kB, 0, m->s>>>(st, A, k, m->act, m->col, m->blk, sseed, m->recs);
+    k_solve<<<1, kSolveThreads, 0, m->s>>>(st, A, k, m->recs, m->act, m->col, sseed, m->ctr, cnt, cnt + kMaxColours,
+                                         whole ? m->cls : nullptr);
+  };
   int done = 0;
-  if (n > 0 && n <= kJpOne) {
-    k_jp_one<<<1, kJpOneThreads, 0, m->s>>>(st, m->A, n, m->act, m->col, m->blk, sseed, m->ctr);
+  k_place<<<grid(n), kB, 0, m->s>>>(m->A, n, m->act, m->blk);
+  if (n <= kSolve) {
+    solve(m->A, n, true);
     H3(hipGetLastError());
-    T3(read_ctr(m));
-    if (m->hctr[K_ERR] & E_COLOURS) return fail3(m, PM_E_DEVICE, "more than 256 colours");
-    if (m->hctr[K_COLOURED] != n) return fail3(m, PM_E_DEVICE, "colouring made no progress");
-    done = n;
+    T3(read_ctr(m, kMaxColours));
+    *listed = true;
+    done = m->hctr[K_COLOURED];
+  } else {
+    if (n > m->lcap) {
+      T3(dgrow(m, &m->recl, m->lcap, m->Vcap, false));
+      m->lcap = m->Vcap;
+    }
+    k_pred<<<grid(8 * (int64_t)n), kB, 0, m->s>>>(st, m->A, n, m->act, m->col, m->blk, sseed, m->recl);
   }
-  // iterations in batches of kJpBatch between read-backs (an iteration after
-  // the last vertex has its colour changes nothing)
+  // iterations in batches of kJpBatch between read-backs, until few enough
+  // vertices wait for the one-block end
   constexpr int kJpBatch = 4;
   for (int it = 0; done < n;) {
-    // the stamp keeps 23 bits of the iteration
-    if (it > n + 8 || it + kJpBatch >= (1 << 23)) return fail3(m, PM_E_DEVICE, "colouring made no progress");
+    if (*listed || it > n + 8) return fail3(m, PM_E_DEVICE, "colouring made no progress");
     for (int b = 0; b < kJpBatch; ++b, ++it)
-      k_jp<<<grid(n), kB, 0, m->s>>>(st, m->A, n, m->act, m->col, m->blk, it, sseed, m->ctr);
+      k_follow<<<grid(n), kB, 0, m->s>>>(st, m->A, n, m->act, m->col, sseed, m->recl, m->ctr);
     H3(hipGetLastError());
     T3(read_ctr(m));
     if (m->hctr[K_ERR] & E_COLOURS) return fail3(m, PM_E_DEVICE, "more than 256 colours");
     done = m->hctr[K_COLOURED];
+    if (done < n && n - done <= kSolve) {
+      k_waiting<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, m->cls, m->blk, m->ctr);
+      solve(m->cls, n - done, false);
+      H3(hipGetLastError());
+      T3(read_ctr(m));
+      done = m->hctr[K_COLOURED];
+      if (done < n) return fail3(m, PM_E_DEVICE, "colouring made no progress");
+    }
   }
-  if (n > 0) k_jp_strip<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col);
-  H3(hipGetLastError());
-  *ncol = n > 0 ? m->hctr[K_NCOL] : 0;
+  if (m->hctr[K_ERR] & E_COLOURS) return fail3(m, PM_E_DEVICE, "more than 256 colours");
+  *ncol = m->hctr[K_NCOL];
   return PM_OK;
 }
 
 // class lists of the coloured list: m->cls, offsets and sizes on the host
-pm_status class_lists(pm3_mesh* m, int n, int ncol, std::vector<int>& off, std::vector<int>& size) {
-  if (!m->ccount) {
-    T3(dgrow(m, &m->ccount, 0, 2 * kMaxColours, false));
-    T3(dgrow(m, &m->coff, 0, kMaxColours, false));
-  }
+pm_status class_lists(pm3_mesh* m, int n, int ncol, bool listed, std::vector<int>& off, std::vector<int>& size) {
   // sizes, offsets and placement on the device; one read-back of the sizes
   // (the host computes the same offsets from them)
-  k_fill_int<<<1, 2 * kMaxColours, 0, m->s>>>(m->ccount, 2 * kMaxColours, 0);
-  k_class_count<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, ncol, m->ccount);
-  k_class_offsets<<<1, kMaxColours, 0, m->s>>>(m->ccount, ncol, m->coff);
-  k_class_place<<<std::max(1, (n + kB - 1) / kB), kB, 0, m->s>>>(m->A, n, m->col, ncol, m->coff,
-                                                                   m->ccount + kMaxColours, m->cls);
-  H3(hipGetLastError());
-  pm::mail_send(m->mail, m->ccount, ncol, m->hctr + K_COUNT, m->s);
-  H3(pm::mail_wait(m->mail, m->s));
+  int *cnt = m->ctr + K_CLASS, *place = cnt + kMaxColours, *coff = place + kMaxColours;
+  if (!listed && n > 0) {
+    k_fill_int<<<1, 2 * kMaxColours, 0, m->s>>>(cnt, 2 * kMaxColours, 0);
+    k_class_count<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, ncol, cnt);
+    k_class_offsets<<<1, kMaxColours, 0, m->s>>>(cnt, ncol, coff);
+    k_class_place<<<std::max(1, (n + kB - 1) / kB), kB, 0, m->s>>>(m->A, n, m->col, ncol, coff, place, m->cls);
+    H3(hipGetLastError());
+    T3(read_ctr(m, kMaxColours));
+  }
   size.assign(ncol, 0);
   off.assign(ncol + 1, 0);
   for (int c = 0; c < ncol; ++c) {
@@ -1758,7 +1996,7 @@ pm_status pm3_mesh_create(const pm3_mesh_desc* d, const pm_options* o, void* str
     return s;
   };
   int V = (int)d->V, T = (int)d->T;
-  if (pm::block_alloc(m->s, (void**)&m->ctr, sizeof(int) * K_COUNT) != hipSuccess ||
+  if (pm::block_alloc(m->s, (void**)&m->ctr, sizeof(int) * K_ALL) != hipSuccess ||
       !(m->hctr = (int*)pm::pinned_take())) {
     (void)hipGetLastError();
     return bail(PM_E_NOMEM);
@@ -1813,8 +2051,10 @@ pm_status pm3_mesh_destroy(pm3_mesh* m) {
   dfree3(st.nn);
   dfree3(st.ne);
   for (int** p : {&m->cnt, &m->off, &m->cur, &m->flag, &m->scan, &m->partial, &m->A, &m->cls, &m->col,
-                  &m->blk, &m->mark, &m->tcnt, &m->tscan, &m->ccount, &m->coff, &m->ctr})
+                  &m->blk, &m->mark, &m->tcnt, &m->tscan, &m->ctr})
     dfree3(*p);
+  dfree3(m->recs);
+  dfree3(m->recl);
   dfree3(m->act);
   dfree3(m->nxt);
   dfree3(m->qbuf);
@@ -1931,7 +2171,8 @@ pm_status pm3_colour(pm3_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* 
     n = total;
   }
   int ncol = 0;
-  T3(colour_list(m, n, ctx, &ncol));
+  bool listed;
+  T3(colour_list(m, n, ctx, &ncol, &listed));
   if (ncolours) *ncolours = ncol;
   if (colour_out) {
     H3(hipMemcpyAsync(colour_out, m->col, sizeof(int) * st.V, hipMemcpyDeviceToHost, m->s));
@@ -1955,10 +2196,11 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
     uint32_t ctx = make_ctx(o->sweep, PH3_COARSEN, r);
     uint64_t sseed = stream_seed(m->seed, ctx);
     int ncol = 0;
-    T3(colour_list(m, n, ctx, &ncol));
+    bool lists;
+    T3(colour_list(m, n, ctx, &ncol, &lists));
     sv[PM_S_COLOURED] += n;
     sv[PM_S_COLOURS] += ncol;
-    T3(class_lists(m, n, ncol, off, size));
+    T3(class_lists(m, n, ncol, lists, off, size));
     // the colouring zeroed the counters: the round's stats accumulate on the
     // device and come back with the next list's length. Each class: the
     // collapses, then the commit of the rows they changed. A commit that runs
@@ -2061,11 +2303,12 @@ pm_status pm3_smooth(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   int n = 0;
   T3(select_list(m, 2, 0.0, &n));
   int ncol = 0;
-  T3(colour_list(m, n, make_ctx(o->sweep, PH3_SMOOTH, 0), &ncol));
+  bool lists;
+  T3(colour_list(m, n, make_ctx(o->sweep, PH3_SMOOTH, 0), &ncol, &lists));
   sv[PM_S_COLOURED] += n;
   sv[PM_S_COLOURS] += ncol;
   std::vector<int> off, size;
-  T3(class_lists(m, n, ncol, off, size));
+  T3(class_lists(m, n, ncol, lists, off, size));
   T3(zero_ctr(m));
   for (int s = 0; s < o->smooth_sweeps; ++s)
     for (int c = 0; c < ncol; ++c)
