@@ -444,6 +444,70 @@ __device__ __forceinline__ void room3(int* ctr, int epoch) {
   atomicOr(&ctr[K_ROOM], 1);
 }
 
+// The two rows of a vertex with at most kWave elements and kWave neighbours, by
+// one wavefront: lane l < m holds the l-th element id and its other three
+// vertices. A lane's place in NE is the number of smaller ids, one lane read and
+// compare per element; the other vertices go through a hash table in LDS, which
+// leaves each once, and are placed the same way. Sorting networks over the 64
+// lanes with four and eight slots each took some 700 exchanges a row, whatever
+// its length (24 elements and 14 neighbours on average).
+// False (nothing decided) when an id comes twice or there are more neighbours.
+struct StarLds {
+  int hash[256];
+  int list[kWave];
+  int4 kept[kWave];
+};
+__device__ __forceinline__ void star_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ bool star_rows(int m, int id, const int (&oth)[3], StarLds& L, int& rid, int& u, int& val,
+                                          int& rnn) {
+  int lane = __lane_id();
+  bool has = lane < m;
+  m = __builtin_amdgcn_readfirstlane(m);
+  rid = 0;
+  bool twice = false;
+  for (int k = 0; k < m; ++k) {
+    int o = __builtin_amdgcn_readlane(id, k);
+    rid += o < id ? 1 : 0;
+    twice |= o == id && k != lane;
+  }
+  *(int4*)(L.hash + 4 * lane) = make_int4(-1, -1, -1, -1);
+  star_sync();
+  u = 0;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    bool fresh = false;
+    if (has) {
+      uint32_t at = ((uint32_t)oth[q] * 2654435761u) >> 24;
+      for (;;) {  // at most 3 kWave = 192 different vertices: a slot is free
+        int old = atomicCAS(&L.hash[at], -1, oth[q]);
+        fresh = old == -1;
+        if (fresh || old == oth[q]) break;
+        at = (at + 1) & 255u;
+      }
+    }
+    uint64_t b = __ballot(fresh);
+    int pos = u + __popcll(b & ((1ull << lane) - 1ull));
+    if (fresh && pos < kWave) L.list[pos] = oth[q];
+    u += __popcll(b);
+  }
+  if (__ballot(has && twice) || u > kWave) return false;
+  star_sync();
+  u = __builtin_amdgcn_readfirstlane(u);
+  val = lane < u ? L.list[lane] : INT_MAX;
+  rnn = 0;
+  for (int k = 0; k < u; ++k) rnn += __builtin_amdgcn_readlane(val, k) < val ? 1 : 0;
+  star_sync();
+  return true;
+}
+__device__ __forceinline__ void others_of(const int4& e, int x, int (&o)[3]) {
+  o[0] = e.x == x ? e.y : e.x;
+  o[1] = e.x == x || e.y == x ? e.z : e.y;
+  o[2] = e.w == x ? e.z : e.w;
+}
+
 // Row x from its candidates, RC slots per lane: NE(x) (slot o, count n)
 // followed by the rows of the absorbed members (za[j], counts ca[j], j <
 // nab), at most RC kWave candidates in all. RN = 2 RC slots per lane hold
@@ -551,9 +615,75 @@ __device__ __forceinline__ bool put_row3(const Store3& st, int x, int o, int n, 
   return true;
 }
 
+// Row x (slot o, count n, room for capx) from the candidates of put_row3 when
+// every list of them fits the lanes. 1: written; 0: not (more than kWave of
+// something); -1: its stripe is full.
+__device__ __forceinline__ int star_commit(const Store3& st, int x, int o, int n, int capx, const int (&za)[kAbsMax],
+                                           const int (&ca)[kAbsMax], int nab, int* tops, int64_t base, int64_t per,
+                                           StarLds& L) {
+  int lane = __lane_id();
+  if (n > kWave) return 0;
+  int m = 0;
+  bool fits = true;
+  auto keep = [&](int t, const int4& e, bool alive) {
+    bool k = t >= 0 && alive && has4(e, x);
+    uint64_t b = __ballot(k);
+    int pos = m + __popcll(b & ((1ull << lane) - 1ull));
+    if (k && pos < kWave) {
+      int q[3];
+      others_of(e, x, q);
+      L.kept[pos] = make_int4(t, q[0], q[1], q[2]);
+    }
+    m += __popcll(b);
+  };
+  // NE(x) and the first absorbed row together, then the others
+  int t0 = lane < n ? st.ne[o + lane] : -1, t1 = -1;
+  if (nab > 0) {
+    fits = ca[0] <= kWave;
+    if (fits && lane < ca[0]) t1 = st.ne[za[0] + lane];
+  }
+  int4 e0 = st.tet[max(t0, 0)], e1 = st.tet[max(t1, 0)];
+  bool a0 = st.talive[max(t0, 0)] != 0, a1 = st.talive[max(t1, 0)] != 0;
+  keep(t0, e0, a0);
+  if (nab > 0) keep(t1, e1, a1);
+  for (int j = 1; j < nab; ++j) {
+    if (ca[j] > kWave) {
+      fits = false;
+      break;
+    }
+    int t = lane < ca[j] ? st.ne[za[j] + lane] : -1;
+    int4 e = st.tet[max(t, 0)];
+    keep(t, e, st.talive[max(t, 0)] != 0);
+  }
+  if (!fits || m > kWave) return 0;
+  star_sync();
+  int4 mine = lane < m ? L.kept[lane] : make_int4(INT_MAX, -1, -1, -1);
+  int oth[3] = {mine.y, mine.z, mine.w};
+  int rid, u, val, rnn;
+  if (!star_rows(m, mine.x, oth, L, rid, u, val, rnn)) return 0;
+  int off = o, cap = capx;
+  if (m > capx) {
+    int need = 2 * m;
+    int sidx = x % kTopStripes;
+    int got = 0;
+    if (lane == 0) got = atomicAdd(&tops[sidx * kTopStride], need);
+    got = __shfl(got, 0);
+    if ((int64_t)got + need > base + (int64_t)(sidx + 1) * per) return -1;
+    off = got;
+    cap = need;
+  }
+  if (lane < m) st.ne[off + rid] = mine.x;
+  if (lane < u) st.nn[3 * (int64_t)off + rnn] = val;
+  if (lane == 0) {
+    st.hdr[x] = make_int4(3 * off, u, off, m);
+    st.cap[x] = cap;
+  }
+  return 1;
+}
+
 // one stamped row (every lane of the wavefront)
 __device__ __forceinline__ void commit_row3(const Store3& st, int x, int epoch, const int2* __restrict__ rec,
-                                            int* tops, int64_t base, int64_t per, int* ctr) {
+                                            int* tops, int64_t base, int64_t per, int* ctr, StarLds& L) {
   int lane = __lane_id();
   int4 h = st.hdr[x];
   int capx = st.cap[x];
@@ -592,9 +722,13 @@ __device__ __forceinline__ void commit_row3(const Store3& st, int x, int epoch, 
       }
     }
   }
-  // the smaller form when every candidate could be kept in it
+  // lane counts where they fit; else the smaller network when every candidate
+  // could be kept in it, else the larger
   bool ok = false;
-  if (nab <= kAbsMax && tot <= 2 * kWave)
+  int star = nab <= kAbsMax ? star_commit(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per, L) : 0;
+  if (star != 0)
+    ok = star > 0;
+  else if (nab <= kAbsMax && tot <= 2 * kWave)
     ok = put_row3<4, 8>(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per);
   else if (nab <= kAbsMax && tot <= 8 * kWave)
     ok = put_row3<8, 16>(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per);
@@ -611,6 +745,7 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
                                                  const int2* __restrict__ rec, int* tops, int64_t base,
                                                  int64_t per, int* ctr) {
   if (ctr[K_CCOMMIT] == 0 || ctr[K_ROOM]) return;
+  __shared__ __align__(16) StarLds L[kB / kWave];
   int lane = __lane_id();
   int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
@@ -622,7 +757,7 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
     while (dm) {
       int l = __ffsll((unsigned long long)dm) - 1;
       dm &= dm - 1;
-      commit_row3(st, c0 + l, epoch, rec, tops, base, per, ctr);
+      commit_row3(st, c0 + l, epoch, rec, tops, base, per, ctr, L[threadIdx.x / kWave]);
     }
   }
 }
@@ -631,10 +766,11 @@ __global__ void __launch_bounds__(256) k_commit3_list(Store3 st, int epoch, cons
                                                       const int2* __restrict__ rec, int* tops, int64_t base,
                                                       int64_t per, int* ctr) {
   if (ctr[K_CCOMMIT] == 0 || ctr[K_ROOM]) return;
+  __shared__ __align__(16) StarLds L[kB / kWave];
   int n = ctr[K_NROWS];
   int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
-  for (int i = wid; i < n; i += nw) commit_row3(st, rows[i], epoch, rec, tops, base, per, ctr);
+  for (int i = wid; i < n; i += nw) commit_row3(st, rows[i], epoch, rec, tops, base, per, ctr, L[threadIdx.x / kWave]);
 }
 
 // the start of a class: its collapse count and its row list emptied
@@ -654,6 +790,7 @@ __global__ void k_class_start(int* ctr) {
 // before it. Rows of more than kWave elements take the serial form on the
 // wavefront's first lane.
 __global__ void __launch_bounds__(256) k_rows_finish(Store3 st, const int* __restrict__ off, const int* __restrict__ cnt) {
+  __shared__ __align__(16) StarLds L[kB / kWave];
   int lane = __lane_id();
   int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
@@ -669,6 +806,17 @@ __global__ void __launch_bounds__(256) k_rows_finish(Store3 st, const int* __res
     bool has = lane < n;
     int t = has ? st.ne[o + lane] : INT_MAX;
     int4 e = st.tet[has ? t : 0];
+    int oth[3], rid, u0, val, rnn;
+    others_of(e, v, oth);
+    if (star_rows(n, t, oth, L[threadIdx.x / kWave], rid, u0, val, rnn)) {
+      if (has) st.ne[o + rid] = t;
+      if (lane < u0) st.nn[3 * (int64_t)o + rnn] = val;
+      if (lane == 0) {
+        st.hdr[v] = make_int4(3 * o, u0, o, n);
+        st.cap[v] = n;
+      }
+      continue;
+    }
     int a[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};
     if (has) {
       int id[4] = {e.x, e.y, e.z, e.w};
