@@ -1246,25 +1246,75 @@ __global__ void k_compact_list(const int* __restrict__ flag, const int* __restri
 // ---- coarsening (Sec. 2.4.1) -------------------------------------------------------------------
 
 
+// a vertex's position and metric, held by a lane
+struct Vtx {
+  double x, y, z;
+  Met6 m;
+};
+__device__ __forceinline__ Vtx vtx(const Store3& st, int v) {
+  double4 p = st.xyz[v];
+  return Vtx{p.x, p.y, p.z, st.met[v]};
+}
+__device__ __forceinline__ double lane_of(double v, int k) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), k), __builtin_amdgcn_readlane(__double2loint(v), k));
+}
+__device__ __forceinline__ Vtx lane_of(const Vtx& v, int k) {
+  return Vtx{lane_of(v.x, k), lane_of(v.y, k), lane_of(v.z, k),
+             Met6{lane_of(v.m.a00, k), lane_of(v.m.a01, k), lane_of(v.m.a02, k), lane_of(v.m.a11, k),
+                  lane_of(v.m.a12, k), lane_of(v.m.a22, k)}};
+}
+__device__ __forceinline__ Vtx pick(bool c, const Vtx& a, const Vtx& b) {
+  return Vtx{c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z,
+             Met6{c ? a.m.a00 : b.m.a00, c ? a.m.a01 : b.m.a01, c ? a.m.a02 : b.m.a02, c ? a.m.a11 : b.m.a11,
+                  c ? a.m.a12 : b.m.a12, c ? a.m.a22 : b.m.a22}};
+}
+// The geometry of the element (u, o0, o1, o2) in canonical order, o0 the
+// smallest of the three: u first if it is smaller still; else o0, then the
+// smallest of the other three, which the orientation has in the cycle (u, o2, o1).
+__device__ __forceinline__ Geo3 star_geo(int u, const Vtx& pu, const int (&o)[3], const Vtx (&p)[3]) {
+  bool A = u < o[0], B = !A && u < o[1] && u < o[2], C = !A && !B && o[1] < o[2];
+  // A: u o0 o1 o2   B: o0 u o2 o1   C: o0 o1 u o2   D: o0 o2 o1 u
+  Vtx q0 = pick(A, pu, p[0]);
+  Vtx q1 = pick(A, p[0], pick(B, pu, pick(C, p[1], p[2])));
+  Vtx q2 = pick(B, p[2], pick(C, pu, p[1]));
+  Vtx q3 = pick(B, p[1], pick(A || C, p[2], pu));
+  Geo3 g;
+  g.p[0] = make_double4(q0.x, q0.y, q0.z, 0.0);
+  g.p[1] = make_double4(q1.x, q1.y, q1.z, 0.0);
+  g.p[2] = make_double4(q2.x, q2.y, q2.z, 0.0);
+  g.p[3] = make_double4(q3.x, q3.y, q3.z, 0.0);
+  g.m = Met6{(((q0.m.a00 + q1.m.a00) + q2.m.a00) + q3.m.a00) / 4.0, (((q0.m.a01 + q1.m.a01) + q2.m.a01) + q3.m.a01) / 4.0,
+             (((q0.m.a02 + q1.m.a02) + q2.m.a02) + q3.m.a02) / 4.0, (((q0.m.a11 + q1.m.a11) + q2.m.a11) + q3.m.a11) / 4.0,
+             (((q0.m.a12 + q1.m.a12) + q2.m.a12) + q3.m.a12) / 4.0, (((q0.m.a22 + q1.m.a22) + q2.m.a22) + q3.m.a22) / 4.0};
+  return g;
+}
+// element e's other vertices, in an order with v before them that keeps its
+// orientation, the smallest first
+__device__ __forceinline__ void star_others(const int4& e, int v, int (&o)[3]) {
+  int a, b, c;
+  if (e.x == v) { a = e.y; b = e.z; c = e.w; }
+  else if (e.y == v) { a = e.x; b = e.w; c = e.z; }
+  else if (e.z == v) { a = e.w; b = e.x; c = e.y; }
+  else { a = e.z; b = e.y; c = e.x; }
+  bool bf = b < a && b < c, cf = c < a && c < b;
+  o[0] = bf ? b : (cf ? c : a);
+  o[1] = bf ? c : (cf ? a : b);
+  o[2] = bf ? a : (cf ? b : c);
+}
+
 // One class: re-validation against the current graph, then each kept
 // member's collapse, evaluated and applied (members are pairwise
 // non-adjacent, so no member reads what another writes). A member runs on a
-// group of kL lanes: lane j takes the row entries j, j + kL, ..., so a
-// member's neighbours and elements are gathered side by side; the group
-// combines its lanes' answers (any beaten, the smallest candidate pair, every
-// re-pointed element valid), which are exact, so the decisions are those of a
-// serial loop over the rows.
-// 32 lanes: rows of 40-70 elements after refinement leave 16 lanes two to
-// five elements each per candidate test (psi3 204 -> 192 ms); 8 lanes took 244.
-constexpr int kL = 32;
-
-__device__ __forceinline__ bool grp_any(bool p) {
-  uint64_t b = __ballot(p);
-  int base = __lane_id() & ~(kL - 1);
-  constexpr uint64_t mask = kL >= kWave ? ~0ull : ((1ull << kL) - 1);
-  return ((b >> base) & mask) != 0;
-}
-
+// wavefront: lane l holds its l-th neighbour and its l-th element with the
+// positions and metrics of that element's other vertices, all gathered once.
+// The candidates (neighbours by a short legal edge) are ordered by (L^2, u) by
+// counting, and each is tried on registers alone: its data goes from its lane
+// to all, and every lane evaluates its re-pointed element. Rows longer than the
+// wavefront go on with further loads.
+// With 32 lanes a member and the elements' four vertices gathered again for
+// every candidate (21 loads a lane), a class of some hundred members took 30 us,
+// most of it in candidates that fail: late rounds try every short edge of
+// vertices that the quality bound keeps.
 __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restrict__ list, int n,
                                                   const int* __restrict__ col, int c, uint64_t sseed, double L_low2,
                                                   double qmin3, uint8_t* nxt, int epoch, int* own, int* rows,
@@ -1272,88 +1322,88 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
   // an earlier class's row commit ran out of room: the host rebuilds the
   // rows and runs this class again
   if (ctr[K_ROOM]) return;
-  int j0 = __lane_id() & (kL - 1);
-  int gid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kL);
-  bool act = gid < n;
-  int v = act ? list[gid] : 0;
-  int4 h = act ? st.hdr[v] : make_int4(0, 0, 0, 0);
+  int lane = __lane_id();
+  int gid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
+  if (gid >= n) return;
+  int v = __builtin_amdgcn_readfirstlane(list[gid]);
+  int4 h = st.hdr[v];
+  int nn = __builtin_amdgcn_readfirstlane(h.y), ne = __builtin_amdgcn_readfirstlane(h.w);
   uint64_t kv = vkey(sseed, (uint32_t)v);
-  // one pass over the row: re-validation, and each neighbour's metric
-  // length kept for the candidate search (rows of up to kC * kL entries;
-  // INFINITY marks a neighbour that is no candidate)
-  constexpr int kC = 2;
-  int cu[kC];
-  double cL[kC];
-#pragma unroll
-  for (int q = 0; q < kC; ++q) {
-    cu[q] = -1;
-    cL[q] = INFINITY;
+  // level by level: row entries; neighbours and elements; the elements' vertices
+  int w = lane < nn ? st.nn[h.x + lane] : -1, t = lane < ne ? st.ne[h.z + lane] : -1;
+  int ws = max(w, 0);
+  Vtx pv = vtx(st, v), pw = vtx(st, ws);
+  int cw = col[ws], tv = st.tag[v], tw = st.tag[ws];
+  int4 e = st.tet[max(t, 0)];
+  bool beat = w >= 0 && cw == c && vkey(sseed, (uint32_t)w) > kv;
+  for (int j = kWave + lane; j < nn; j += kWave) {
+    int y = st.nn[h.x + j];
+    beat = beat || (col[y] == c && vkey(sseed, (uint32_t)y) > kv);
   }
-  bool b = false;
-  for (int jb = 0, q = 0; jb < h.y; jb += kL, ++q) {
-    int j = jb + j0;
-    if (j < h.y) {
-      int w = st.nn[h.x + j];
-      b = b || (col[w] == c && vkey(sseed, (uint32_t)w) > kv);
-#pragma unroll
-      for (int r = 0; r < kC; ++r)
-        if (r == q) {
-          cu[r] = w;
-          if (tag_ok(st, v, w)) {
-            double L = len2(st, v, w);
-            if (L < L_low2) cL[r] = L;
-          }
-        }
+  if (__ballot(beat)) {
+    if (lane == 0) {
+      nxt[v] = 1;
+      atomicAdd(&ctr[K_STRIPE + (gid & (kStripes - 1)) * kStripeW + S_DEFER], 1);
     }
+    return;
   }
-  bool cached = h.y <= kC * kL;
-  bool beaten = grp_any(b);
-  int ev = 0, df = 0, cm = 0;
-  if (act && beaten) {
-    if (j0 == 0) nxt[v] = 1;
-    df = 1;
+  auto length = [&](const Vtx& p) {
+    return qform(edge_met(pv.m, p.m), p.x - pv.x, p.y - pv.y, p.z - pv.z);
+  };
+  double L = INFINITY;
+  if (w >= 0 && (tv & ~tw) == 0) {
+    double l = length(pw);
+    if (l < L_low2) L = l;
   }
-  int target = -1;
-  if (act && !beaten) {
-    ev = 1;
-    // candidates in ascending (L^2, u): each step takes the smallest pair
-    // above the previous one
-    double pL = -1.0;
-    int pu = -1;
-    for (;;) {
+  bool cand = L < L_low2;
+  bool longer = nn > kWave;  // some candidates are not held by lanes
+  // a held candidate's place in the order
+  int rank = 0;
+  uint64_t cb = __ballot(cand);
+  int nc = __popcll(cb);
+  for (uint64_t b = cb; b; b &= b - 1) {
+    int k = __ffsll((unsigned long long)b) - 1;
+    double Lk = lane_of(L, k);
+    int wk = __builtin_amdgcn_readlane(w, k);
+    rank += Lk < L || (Lk == L && wk < w) ? 1 : 0;
+  }
+  int o[3] = {-1, -1, -1};
+  Vtx p[3];
+  if (nc > 0 || longer) {
+    if (t >= 0) star_others(e, v, o);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) p[q] = vtx(st, max(o[q], 0));
+  }
+  int target = -1, next = 0;
+  double pL = -1.0;
+  int pu = -1;
+  for (;;) {
+    // the next candidate: from the lanes, or past pL, pu among all
+    Vtx du = pw;
+    int u = -1;
+    if (!longer) {
+      if (next >= nc) break;
+      int k = __ffsll((unsigned long long)__ballot(cand && rank == next)) - 1;
+      ++next;
+      u = __builtin_amdgcn_readlane(w, k);
+      du = lane_of(pw, k);
+    } else {
       double bL = 0.0;
       int bu = -1;
-      if (cached) {
-#pragma unroll
-        for (int q = 0; q < kC; ++q) {
-          double L = cL[q];
-          int u = cu[q];
-          if (u < 0 || !(L < L_low2)) continue;
-          bool after = L > pL || (L == pL && u > pu);
-          bool before = bu < 0 || L < bL || (L == bL && u < bu);
-          if (after && before) {
-            bL = L;
-            bu = u;
-          }
-        }
-      } else {
-        for (int jb = 0; jb < h.y; jb += kL) {
-          int j = jb + j0;
-          if (j >= h.y) continue;
-          int u = st.nn[h.x + j];
-          if (!tag_ok(st, v, u)) continue;
-          double L = len2(st, v, u);
-          if (!(L < L_low2)) continue;
-          bool after = L > pL || (L == pL && u > pu);
-          bool before = bu < 0 || L < bL || (L == bL && u < bu);
-          if (after && before) {
-            bL = L;
-            bu = u;
-          }
+      for (int j = lane; j < nn; j += kWave) {
+        int y = st.nn[h.x + j];
+        if (!tag_ok(st, v, y)) continue;
+        double l = length(vtx(st, y));
+        if (!(l < L_low2)) continue;
+        bool after = l > pL || (l == pL && y > pu);
+        bool before = bu < 0 || l < bL || (l == bL && y < bu);
+        if (after && before) {
+          bL = l;
+          bu = y;
         }
       }
 #pragma unroll
-      for (int d = kL / 2; d > 0; d >>= 1) {
+      for (int d = kWave / 2; d > 0; d >>= 1) {
         double oL = __shfl_xor(bL, d);
         int ou = __shfl_xor(bu, d);
         if (ou >= 0 && (bu < 0 || oL < bL || (oL == bL && ou < bu))) {
@@ -1361,70 +1411,72 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
           bu = ou;
         }
       }
-      if (bu < 0) break;
-      bool bad = false;
-      for (int kb = 0; kb < h.w; kb += kL) {
-        int k = kb + j0;
-        if (k >= h.w) continue;
-        int4 e = st.tet[st.ne[h.z + k]];
-        if (has4(e, bu)) continue;
-        Geo3 g = geo(st, canon4(replace4(e, v, bu)), -1, make_double4(0, 0, 0, 0));
-        if (!(vol6(g) > 0.0) || !(qual3(g) >= qmin3)) bad = true;
-      }
-      if (!grp_any(bad)) {
-        target = bu;
-        break;
-      }
+      u = __builtin_amdgcn_readfirstlane(bu);
+      if (u < 0) break;
       pL = bL;
-      pu = bu;
+      pu = u;
+      du = vtx(st, u);
+    }
+    bool bad = false;
+    if (t >= 0 && o[0] != u && o[1] != u && o[2] != u) {
+      Geo3 g = star_geo(u, du, o, p);
+      bad = !(vol6(g) > 0.0) || !(qual3(g) >= qmin3);
+    }
+    if (__ballot(bad)) continue;
+    for (int k = kWave + lane; k < ne; k += kWave) {
+      int4 f = st.tet[st.ne[h.z + k]];
+      if (has4(f, u)) continue;
+      Geo3 g = geo(st, canon4(replace4(f, v, u)), -1, make_double4(0, 0, 0, 0));
+      bad = bad || !(vol6(g) > 0.0) || !(qual3(g) >= qmin3);
+    }
+    if (!__ballot(bad)) {
+      target = u;
+      break;
     }
   }
-  if (target >= 0) {
-    for (int kb = 0; kb < h.w; kb += kL) {
-      int k = kb + j0;
-      if (k >= h.w) continue;
-      int t = st.ne[h.z + k];
-      int4 e = st.tet[t];
-      if (has4(e, target))
-        st.talive[t] = 0;
-      else
-        st.tet[t] = canon4(replace4(e, v, target));
-    }
-    // the changed rows (every neighbour's, the target's among them) for the
-    // row commit, stamped with the class epoch; with a row list (rows given)
-    // the first stamp of a row in this class also appends it to the list
-    // (one add per wavefront); and the member's target
-    for (int jb = 0; jb < h.y; jb += kL) {
-      int j = jb + j0;
-      int w = -1;
-      bool fresh = false;
-      if (j < h.y) {
-        w = st.nn[h.x + j];
-        nxt[w] = 1;
-        if (rows)
-          fresh = atomicExch(&own[w], epoch) != epoch;
-        else
-          own[w] = epoch;
-      }
-      if (rows) {
-        uint64_t on = __ballot(true), fb = __ballot(fresh);
-        int lead = __ffsll((unsigned long long)on) - 1, at = 0;
-        if (__lane_id() == lead && fb) at = atomicAdd(&ctr[K_NROWS], __popcll(fb));
-        at = __shfl(at, lead);
-        if (fresh) rows[at + __popcll(fb & ((1ull << __lane_id()) - 1ull))] = w;
-      }
-    }
-    if (j0 == 0) {
+  int stripe = K_STRIPE + (gid & (kStripes - 1)) * kStripeW;
+  if (lane == 0) {
+    atomicAdd(&ctr[stripe + S_EVAL], 1);
+    if (target >= 0) {
+      atomicAdd(&ctr[stripe + S_COMMIT], 1);
+      ctr[K_CCOMMIT] = 1;
       st.valive[v] = 0;
       rec[v] = make_int2(epoch, target);
     }
-    cm = 1;
   }
-  if (j0 != 0) ev = df = cm = 0;
-  count_add(ctr, S_EVAL, ev);
-  count_add(ctr, S_DEFER, df);
-  count_add(ctr, S_COMMIT, cm);
-  if (cm) ctr[K_CCOMMIT] = 1;
+  if (target < 0) return;
+  for (int k = lane; k < ne; k += kWave) {
+    int tk = st.ne[h.z + k];
+    int4 f = st.tet[tk];
+    if (has4(f, target))
+      st.talive[tk] = 0;
+    else
+      st.tet[tk] = canon4(replace4(f, v, target));
+  }
+  // the changed rows (every neighbour's, the target's among them) for the
+  // row commit, stamped with the class epoch; with a row list (rows given)
+  // the first stamp of a row in this class also appends it to the list
+  // (one add per wavefront)
+  for (int jb = 0; jb < nn; jb += kWave) {
+    int j = jb + lane;
+    int y = -1;
+    bool fresh = false;
+    if (j < nn) {
+      y = st.nn[h.x + j];
+      nxt[y] = 1;
+      if (rows)
+        fresh = atomicExch(&own[y], epoch) != epoch;
+      else
+        own[y] = epoch;
+    }
+    if (rows) {
+      uint64_t fb = __ballot(fresh);
+      int at = 0;
+      if (lane == 0 && fb) at = atomicAdd(&ctr[K_NROWS], __popcll(fb));
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (fresh) rows[at + __popcll(fb & ((1ull << lane) - 1ull))] = y;
+    }
+  }
 }
 
 // stable renumbering of live vertices and elements (a monotone map keeps the
@@ -2367,7 +2419,7 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
         // give, at most one grid's worth), else vertex order
         int64_t reach = (int64_t)size[c] * 16;
         bool listed = reach * 8 <= st.V;
-        int nb = (int)(((int64_t)size[c] * kL + kB - 1) / kB);
+        int nb = (int)(((int64_t)size[c] * kWave + kB - 1) / kB);
         k_collapse<<<nb, kB, 0, m->s>>>(st, m->cls + off[c], size[c], m->col, c, sseed, o->L_low2, qmin3,
                                          m->nxt, ep, m->own, listed ? m->rows : nullptr, m->rec, m->ctr);
         if (listed)
