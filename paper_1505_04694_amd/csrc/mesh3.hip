@@ -49,11 +49,13 @@ enum {
   K_COMMIT = 5,     // collapses / accepted moves
   K_EDGES = 6,      // edges tested by refinement
   K_TOTAL = 7,      // scan total
-  K_CCOMMIT = 8,    // 1: the class in progress collapsed something (gates its row commit)
-  K_ROOM = 9,       // a row commit ran out of room (pool stripe full, or a row past the wavefront form)
-  K_ROOMEP = 10,    // the epoch of the class whose commit ran out of room
-  K_NROWS = 11,     // rows stamped by the class in progress (the length of its row list)
-  K_WAIT = 12,      // vertices left to the one-block end of a colouring
+  K_ROOM = 8,       // a row commit ran out of room (pool stripe full, or a row past the wavefront form)
+  K_ROOMEP = 9,     // the epoch of the class whose commit ran out of room
+  K_WAIT = 10,      // vertices left to the one-block end of a colouring
+  // by the parity of a class's epoch (its commit clears the other's):
+  K_CCOMMIT = 11,   // 11, 12: 1: the class collapsed something (gates its row commit)
+  K_NROWS = 13,     // 13, 14: rows stamped by the class (the length of its row list)
+  K_LIST = 15,      // length of the list selected last
   K_COUNT = 16,
   K_CLASS = K_COUNT,                    // class sizes, cursors and offsets, kMaxColours each
   K_STRIPE = K_CLASS + 3 * kMaxColours, // kStripes lines of striped counts
@@ -202,13 +204,17 @@ __device__ __forceinline__ void count_add(int* ctr, int slot, int x) {
   if (__lane_id() == 0 && x) atomicAdd(&ctr[K_STRIPE + w * kStripeW + slot], x);
 }
 // counters zero, and no stripe holds anything
-__device__ __forceinline__ void zero_counters(int* ctr) {
-  if (blockIdx.x != 0) return;
+__global__ void k_zero_ctr(int* ctr) {
   if (threadIdx.x < K_COUNT) ctr[threadIdx.x] = 0;
   if (threadIdx.x < kStripes)
     for (int k = 0; k < S_SLOTS; ++k) ctr[K_STRIPE + threadIdx.x * kStripeW + k] = 0;
 }
-__global__ void k_zero_ctr(int* ctr) { zero_counters(ctr); }
+// a colouring's counts zero
+__device__ __forceinline__ void zero_colouring(int* ctr) {
+  if (blockIdx.x != 0) return;
+  if (threadIdx.x == 0) ctr[K_ERR] = ctr[K_NCOL] = ctr[K_WAIT] = 0;
+  if (threadIdx.x < kStripes) ctr[K_STRIPE + threadIdx.x * kStripeW + S_COLOURED] = 0;
+}
 // the counters (and `more` class sizes behind them) to the host, striped counts
 // summed (256 threads)
 __global__ void k_mail3(const int* ctr, int more, int* dst, int* at, int no) {
@@ -735,6 +741,15 @@ __device__ __forceinline__ void commit_row3(const Store3& st, int x, int epoch, 
   if (!ok && lane == 0) room3(ctr, epoch);
 }
 
+// whether the class has rows to commit; the next class's counts start at zero
+__device__ __forceinline__ bool class_committed(int* ctr, int epoch) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctr[K_CCOMMIT + (~epoch & 1)] = 0;
+    ctr[K_NROWS + (~epoch & 1)] = 0;
+  }
+  return ctr[K_CCOMMIT + (epoch & 1)] != 0 && ctr[K_ROOM] == 0;
+}
+
 // Two launch shapes rebuild the same rows, each once. Vertex order (large
 // classes): each wavefront takes a range of vertex slots, reads their stamps
 // a wavefront at a time and rebuilds the stamped rows in turn, so
@@ -744,7 +759,7 @@ __device__ __forceinline__ void commit_row3(const Store3& st, int x, int epoch, 
 __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int* __restrict__ own,
                                                  const int2* __restrict__ rec, int* tops, int64_t base,
                                                  int64_t per, int* ctr) {
-  if (ctr[K_CCOMMIT] == 0 || ctr[K_ROOM]) return;
+  if (!class_committed(ctr, epoch)) return;
   __shared__ __align__(16) StarLds L[kB / kWave];
   int lane = __lane_id();
   int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
@@ -765,20 +780,12 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
 __global__ void __launch_bounds__(256) k_commit3_list(Store3 st, int epoch, const int* __restrict__ rows,
                                                       const int2* __restrict__ rec, int* tops, int64_t base,
                                                       int64_t per, int* ctr) {
-  if (ctr[K_CCOMMIT] == 0 || ctr[K_ROOM]) return;
+  if (!class_committed(ctr, epoch)) return;
   __shared__ __align__(16) StarLds L[kB / kWave];
-  int n = ctr[K_NROWS];
+  int n = ctr[K_NROWS + (epoch & 1)];
   int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
   for (int i = wid; i < n; i += nw) commit_row3(st, rows[i], epoch, rec, tops, base, per, ctr, L[threadIdx.x / kWave]);
-}
-
-// the start of a class: its collapse count and its row list emptied
-__global__ void k_class_start(int* ctr) {
-  if (threadIdx.x == 0) {
-    ctr[K_CCOMMIT] = 0;
-    ctr[K_NROWS] = 0;
-  }
 }
 
 // Sorted rows from the element lists gathered in build order: NE(v) sorted;
@@ -870,8 +877,39 @@ struct RecL {
   int cnt, pos;  // cnt: as above (pos: the neighbour it waits for, or -1); -2: the vertex has its colour
 };
 
+// no colours, no active vertices
+__global__ void k_colour_start(int* col, uint8_t* act, int V, int* ctr) {
+  zero_colouring(ctr);
+  for (int v = gtid(); v < V; v += gstride()) {
+    col[v] = -1;
+    act[v] = 0;
+  }
+}
+
+// the same for the list's vertices alone, after its last class (and no list)
+__global__ void k_unlist(const int* __restrict__ A, int n, int* col, uint8_t* act, int* ctr) {
+  zero_colouring(ctr);
+  if (blockIdx.x == 0 && threadIdx.x == 0) ctr[K_LIST] = 0;
+  for (int i = gtid(); i < n; i += gstride()) {
+    col[A[i]] = -1;
+    act[A[i]] = 0;
+  }
+}
+// the colours of a list again from its classes
+__global__ void k_recolour(const int* __restrict__ cls, int n, int c, int* col) {
+  for (int i = gtid(); i < n; i += gstride()) col[cls[i]] = c;
+}
+// a list's length: given, or (colouring ahead of the read-back) the device's,
+// 0 when it is too long for one block
+__device__ __forceinline__ int list_length(int n, const int* n_dev) {
+  if (!n_dev) return n;
+  n = *n_dev;
+  return n > kSolve ? 0 : n;
+}
+
 // the list's vertices active, each with its place
-__global__ void k_place(const int* __restrict__ A, int n, uint8_t* act, int* blk) {
+__global__ void k_place(const int* __restrict__ A, int n, const int* n_dev, uint8_t* act, int* blk) {
+  n = list_length(n, n_dev);
   for (int i = gtid(); i < n; i += gstride()) {
     act[A[i]] = 1;
     blk[A[i]] = i;
@@ -892,8 +930,9 @@ __global__ void k_waiting(const int* __restrict__ A, int n, const int* __restric
 // eight lanes a vertex, each every eighth entry of its row; a lane's places go
 // behind the lower lanes' (their order does not matter)
 template <class R>
-__global__ void k_pred(Store3 st, const int* __restrict__ A, int n, const uint8_t* __restrict__ act,
+__global__ void k_pred(Store3 st, const int* __restrict__ A, int n, const int* n_dev, const uint8_t* __restrict__ act,
                        const int* __restrict__ col, const int* __restrict__ blk, uint64_t sseed, R* recs) {
+  n = list_length(n, n_dev);
   constexpr bool kLong = std::is_same<R, RecL>::value;
   constexpr int G = 8;
   int lane = __lane_id(), l = lane & (G - 1), gb = lane & ~(G - 1);
@@ -1105,12 +1144,14 @@ __device__ __forceinline__ void solve3(const Store3& st, const int* A, int n, co
 
 // cnt, off, cls: also the class sizes, offsets and lists (a list coloured here
 // as a whole), or null
-__global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A, int n, const Rec3* recs,
-                                                       const uint8_t* act, int* col, uint64_t sseed, int* ctr, int* cnt,
+__global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A, int n, const int* n_dev,
+                                                       const Rec3* recs, const uint8_t* act, int* col, uint64_t sseed, int* ctr, int* cnt,
                                                        int* off, int* cls) {
   __shared__ uint16_t cl[kSolve];
   __shared__ int hist[kMaxColours], cur[kMaxColours], wsum[4], ncol;
   int tid = (int)threadIdx.x;
+  n = list_length(n, n_dev);
+  if (n <= 0) return;
   for (int i = tid; i < n; i += kSolveThreads) cl[i] = 0xFFFF;
   if (tid < kMaxColours) hist[tid] = 0;
   if (tid == 0) ncol = 0;
@@ -1147,15 +1188,6 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A
 
 __global__ void k_fill_int(int* p, int n, int x) {
   for (int i = gtid(); i < n; i += gstride()) p[i] = x;
-}
-
-// no colours, no active vertices, counters zero
-__global__ void k_colour_start(int* col, uint8_t* act, int V, int* ctr) {
-  zero_counters(ctr);
-  for (int v = gtid(); v < V; v += gstride()) {
-    col[v] = -1;
-    act[v] = 0;
-  }
 }
 
 // Class sizes: a histogram of the block's list entries in LDS, then one
@@ -1222,19 +1254,34 @@ __device__ __forceinline__ bool has_candidate(const Store3& st, int v, double L_
 }
 
 // mode 0: live vertices with a candidate; 1: flagged ones (flags cleared);
-// 2: live interior vertices
-__global__ void k_select(Store3 st, int mode, double L_low2, uint8_t* nxt, int* flag) {
-  for (int v = gtid(); v < st.V; v += gstride()) {
-    bool on = st.valive[v] != 0;
-    if (mode == 1) {
+// 2: live interior vertices. Their list and its length (ctr[K_LIST], 0 at the
+// start): every pass of a work-group over 256 vertices appends what it selects
+// with one add. After a commit that ran out of room mode 1 selects nothing and
+// leaves the flags for the selection that follows the rebuild.
+__global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_low2, uint8_t* nxt, int* out, int* ctr) {
+  __shared__ int wsum[kB / kWave], base;
+  if (mode == 1 && ctr[K_ROOM]) return;
+  int lane = __lane_id(), wv = (int)threadIdx.x / kWave;
+  for (int v0 = (int)blockIdx.x * kB; v0 < st.V; v0 += (int)gridDim.x * kB) {
+    int v = v0 + (int)threadIdx.x;
+    bool on = v < st.V && st.valive[v] != 0;
+    if (mode == 1 && v < st.V) {
       on = on && nxt[v];
       nxt[v] = 0;
     }
-    if (mode == 2)
-      on = on && st.tag[v] == 0;
-    else
-      on = on && has_candidate(st, v, L_low2);
-    flag[v] = on ? 1 : 0;
+    if (on) on = mode == 2 ? st.tag[v] == 0 : has_candidate(st, v, L_low2);
+    uint64_t b = __ballot(on);
+    if (lane == 0) wsum[wv] = __popcll(b);
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < kB / kWave; ++q) {
+      if (q < wv) before += wsum[q];
+      total += wsum[q];
+    }
+    if (threadIdx.x == 0) base = total ? atomicAdd(&ctr[K_LIST], total) : 0;
+    __syncthreads();
+    if (on) out[base + before + __popcll(b & ((1ull << lane) - 1ull))] = v;
   }
 }
 
@@ -1439,7 +1486,7 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
     atomicAdd(&ctr[stripe + S_EVAL], 1);
     if (target >= 0) {
       atomicAdd(&ctr[stripe + S_COMMIT], 1);
-      ctr[K_CCOMMIT] = 1;
+      ctr[K_CCOMMIT + (epoch & 1)] = 1;
       st.valive[v] = 0;
       rec[v] = make_int2(epoch, target);
     }
@@ -1472,7 +1519,7 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
     if (rows) {
       uint64_t fb = __ballot(fresh);
       int at = 0;
-      if (lane == 0 && fb) at = atomicAdd(&ctr[K_NROWS], __popcll(fb));
+      if (lane == 0 && fb) at = atomicAdd(&ctr[K_NROWS + (epoch & 1)], __popcll(fb));
       at = __builtin_amdgcn_readfirstlane(at);
       if (fresh) rows[at + __popcll(fb & ((1ull << lane) - 1ull))] = y;
     }
@@ -1853,7 +1900,7 @@ struct pm3_mesh {
   pm::Mail mail;        // its block's
   // scratch
   int *cnt = nullptr, *off = nullptr, *cur = nullptr, *flag = nullptr, *scan = nullptr, *partial = nullptr;
-  int *A = nullptr, *cls = nullptr, *col = nullptr, *blk = nullptr, *mark = nullptr,
+  int *A = nullptr, *B = nullptr, *cls = nullptr, *col = nullptr, *blk = nullptr, *mark = nullptr,
       *tcnt = nullptr, *tscan = nullptr;
   Rec3* recs = nullptr;  // one-block colourings: predecessor records
   RecL* recl = nullptr;  // long colourings', lcap of them
@@ -1950,6 +1997,7 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
     T3(dgrow(m, &m->flag, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->scan, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->A, m->Vcap, nc, true));
+    T3(dgrow(m, &m->B, m->Vcap, nc, false));
     T3(dgrow(m, &m->cls, m->Vcap, nc, true));
     T3(dgrow(m, &m->col, m->Vcap, nc, true));
     T3(dgrow(m, &m->blk, m->Vcap, nc, true));
@@ -2032,41 +2080,42 @@ pm_status build_rows(pm3_mesh* m) {
   return PM_OK;
 }
 
-// list of the vertices selected by mode (ascending); returns its length
+// list of the vertices selected by mode, in m->A; returns its length
 pm_status select_list(pm3_mesh* m, int mode, double L_low2, int* n) {
-  Store3& st = m->st;
-  k_select<<<grid(st.V), kB, 0, m->s>>>(st, mode, L_low2, m->nxt, m->flag);
-  int total = 0;
-  T3(scan_total(m, m->flag, m->scan, st.V, &total));
-  k_compact_list<<<grid(st.V), kB, 0, m->s>>>(m->flag, m->scan, st.V, m->A);
+  k_unlist<<<1, kB, 0, m->s>>>(nullptr, 0, m->col, m->act, m->ctr);
+  k_select<<<grid(m->st.V), kB, 0, m->s>>>(m->st, mode, L_low2, m->nxt, m->A, m->ctr);
+  T3(read_ctr(m));
+  *n = m->hctr[K_LIST];
+  return PM_OK;
+}
+
+// A list of at most kSolve vertices coloured and cut into classes (n_dev: its
+// length from the device; n is then the most it can be)
+pm_status solve_list(pm3_mesh* m, const int* A, int n, const int* n_dev, uint64_t sseed, bool whole) {
+  int* cnt = m->ctr + K_CLASS;
+  k_pred<<<grid(8 * (int64_t)n), kB, 0, m->s>>>(m->st, A, n, n_dev, m->act, m->col, m->blk, sseed, m->recs);
+  k_solve<<<1, kSolveThreads, 0, m->s>>>(m->st, A, n, n_dev, m->recs, m->act, m->col, sseed, m->ctr, cnt,
+                                       cnt + kMaxColours, whole ? m->cls : nullptr);
   H3(hipGetLastError());
-  *n = total;
   return PM_OK;
 }
 
 // Jones-Plassmann colouring of the list A[0, n); col holds the colours
 // (-1 elsewhere); returns the colour count. A short list comes with its class
-// lists (*listed: m->cls, and the sizes in the counters' mirror)
-pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, int* ncol, bool* listed) {
+// lists (*listed: m->cls, and the sizes in the counters' mirror). clean: no
+// vertex has a colour or is active, the colouring's counts are zero
+pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, bool clean, int* ncol, bool* listed) {
   Store3& st = m->st;
   uint64_t sseed = stream_seed(m->seed, ctx);
   *listed = false;
   *ncol = 0;
   if (!m->recs) T3(dgrow(m, &m->recs, 0, kSolve, false));
-  k_colour_start<<<grid(st.V), kB, 0, m->s>>>(m->col, m->act, st.V, m->ctr);
+  if (!clean) k_colour_start<<<grid(st.V), kB, 0, m->s>>>(m->col, m->act, st.V, m->ctr);
   if (n == 0) return PM_OK;
-  int* cnt = m->ctr + K_CLASS;
-  // the records' lanes: eight a vertex
-  auto solve = [&](const int* A, int k, bool whole) {
-    k_pred<<<grid(8 * (int64_t)k), kB, 0, m->s>>>(st, A, k, m->act, m->col, m->blk, sseed, m->recs);
-    k_solve<<<1, kSolveThreads, 0, m->s>>>(st, A, k, m->recs, m->act, m->col, sseed, m->ctr, cnt, cnt + kMaxColours,
-                                         whole ? m->cls : nullptr);
-  };
   int done = 0;
-  k_place<<<grid(n), kB, 0, m->s>>>(m->A, n, m->act, m->blk);
+  k_place<<<grid(n), kB, 0, m->s>>>(m->A, n, nullptr, m->act, m->blk);
   if (n <= kSolve) {
-    solve(m->A, n, true);
-    H3(hipGetLastError());
+    T3(solve_list(m, m->A, n, nullptr, sseed, true));
     T3(read_ctr(m, kMaxColours));
     *listed = true;
     done = m->hctr[K_COLOURED];
@@ -2075,7 +2124,7 @@ pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, int* ncol, bool* listed)
       T3(dgrow(m, &m->recl, m->lcap, m->Vcap, false));
       m->lcap = m->Vcap;
     }
-    k_pred<<<grid(8 * (int64_t)n), kB, 0, m->s>>>(st, m->A, n, m->act, m->col, m->blk, sseed, m->recl);
+    k_pred<<<grid(8 * (int64_t)n), kB, 0, m->s>>>(st, m->A, n, nullptr, m->act, m->col, m->blk, sseed, m->recl);
   }
   // iterations in batches of kJpBatch between read-backs, until few enough
   // vertices wait for the one-block end
@@ -2090,8 +2139,7 @@ pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, int* ncol, bool* listed)
     done = m->hctr[K_COLOURED];
     if (done < n && n - done <= kSolve) {
       k_waiting<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, m->cls, m->blk, m->ctr);
-      solve(m->cls, n - done, false);
-      H3(hipGetLastError());
+      T3(solve_list(m, m->cls, n - done, nullptr, sseed, false));
       T3(read_ctr(m));
       done = m->hctr[K_COLOURED];
       if (done < n) return fail3(m, PM_E_DEVICE, "colouring made no progress");
@@ -2250,7 +2298,7 @@ pm_status pm3_mesh_destroy(pm3_mesh* m) {
   dfree3(st.hdr);
   dfree3(st.nn);
   dfree3(st.ne);
-  for (int** p : {&m->cnt, &m->off, &m->cur, &m->flag, &m->scan, &m->partial, &m->A, &m->cls, &m->col,
+  for (int** p : {&m->cnt, &m->off, &m->cur, &m->flag, &m->scan, &m->partial, &m->A, &m->B, &m->cls, &m->col,
                   &m->blk, &m->mark, &m->tcnt, &m->tscan, &m->ctr})
     dfree3(*p);
   dfree3(m->recs);
@@ -2372,7 +2420,7 @@ pm_status pm3_colour(pm3_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* 
   }
   int ncol = 0;
   bool listed;
-  T3(colour_list(m, n, ctx, &ncol, &listed));
+  T3(colour_list(m, n, ctx, false, &ncol, &listed));
   if (ncolours) *ncolours = ncol;
   if (colour_out) {
     H3(hipMemcpyAsync(colour_out, m->col, sizeof(int) * st.V, hipMemcpyDeviceToHost, m->s));
@@ -2387,25 +2435,26 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   Store3& st = m->st;
   int64_t sv[16] = {};
   double qmin3 = (o->q_min * o->q_min) * o->q_min;
-  int n = 0;
+  int n = 0, ncol = 0;
+  bool lists = false;
+  T3(zero_ctr(m));
   T3(select_list(m, 0, o->L_low2, &n));
   k_fill_u8<<<grid(st.V), kB, 0, m->s>>>(m->nxt, st.V, 0);
   int r = 0;
+  auto ctx_of = [&](int round) { return make_ctx(o->sweep, PH3_COARSEN, round); };
+  if (n > 0 && r < o->coarsen_rounds) T3(colour_list(m, n, ctx_of(0), false, &ncol, &lists));
   std::vector<int> off, size;
   while (n > 0 && r < o->coarsen_rounds) {
-    uint32_t ctx = make_ctx(o->sweep, PH3_COARSEN, r);
-    uint64_t sseed = stream_seed(m->seed, ctx);
-    int ncol = 0;
-    bool lists;
-    T3(colour_list(m, n, ctx, &ncol, &lists));
+    uint64_t sseed = stream_seed(m->seed, ctx_of(r));
     sv[PM_S_COLOURED] += n;
     sv[PM_S_COLOURS] += ncol;
     T3(class_lists(m, n, ncol, lists, off, size));
-    // the colouring zeroed the counters: the round's stats accumulate on the
-    // device and come back with the next list's length. Each class: the
+    // The phase's stats accumulate on the device. Each class: the
     // collapses, then the commit of the rows they changed. A commit that runs
     // out of room makes the round's later classes stand down; the host then
     // rebuilds every row from the elements and runs those classes again.
+    // The next list is selected, and coloured if one block takes it, before the
+    // round's one read-back.
     std::vector<int> class_epoch(ncol, -1);
     int c0 = 0;
     for (;;) {
@@ -2413,7 +2462,6 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
         if (size[c] == 0) continue;
         int ep = ++m->epoch;
         class_epoch[c] = ep;
-        k_class_start<<<1, kWave, 0, m->s>>>(m->ctr);
         // the row list while the class can stamp at most about an eighth of
         // the rows (a wavefront for about every row a member's neighbours
         // give, at most one grid's worth), else vertex order
@@ -2430,8 +2478,17 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
                                                                    m->top_per, m->ctr);
         H3(hipGetLastError());
       }
-      T3(read_ctr(m));
+      k_unlist<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, m->act, m->ctr);
+      k_select<<<grid(st.V), kB, 0, m->s>>>(st, 1, o->L_low2, m->nxt, m->B, m->ctr);
+      if (r + 1 < o->coarsen_rounds) {
+        const int* len = m->ctr + K_LIST;
+        k_place<<<grid(kSolve), kB, 0, m->s>>>(m->B, kSolve, len, m->act, m->blk);
+        T3(solve_list(m, m->B, kSolve, len, stream_seed(m->seed, ctx_of(r + 1)), true));
+      }
+      T3(read_ctr(m, kMaxColours));
+      if (m->hctr[K_ERR] & E_COLOURS) return fail3(m, PM_E_DEVICE, "more than 256 colours");
       if (!m->hctr[K_ROOM]) break;
+      // (nothing was selected: the classes and their lists are as they were)
       int failed = -1;
       for (int c = 0; c < ncol; ++c)
         if (class_epoch[c] == m->hctr[K_ROOMEP]) failed = c;
@@ -2439,12 +2496,21 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
       T3(build_rows(m));
       ++sv[13];
       c0 = failed + 1;
+      for (int c = 0; c < ncol; ++c)
+        if (size[c] > 0) k_recolour<<<grid(size[c]), kB, 0, m->s>>>(m->cls + off[c], size[c], c, m->col);
+      k_fill_int<<<1, kWave, 0, m->s>>>(m->ctr + K_CCOMMIT, 4, 0);
     }
-    T3(select_list(m, 1, o->L_low2, &n));  // its read-back returns the round's counters too
-    sv[PM_S_EVALUATED] += m->hctr[K_EVAL];
-    sv[PM_S_DEFERRED] += m->hctr[K_DEFER];
-    sv[PM_S_COMMITTED] += m->hctr[K_COMMIT];
+    std::swap(m->A, m->B);
+    n = m->hctr[K_LIST];
     ++r;
+    lists = n <= kSolve;
+    ncol = m->hctr[K_NCOL];
+    sv[PM_S_EVALUATED] = m->hctr[K_EVAL];
+    sv[PM_S_DEFERRED] = m->hctr[K_DEFER];
+    sv[PM_S_COMMITTED] = m->hctr[K_COMMIT];
+    if (lists && r < o->coarsen_rounds && m->hctr[K_COLOURED] != n)
+      return fail3(m, PM_E_DEVICE, "colouring made no progress");
+    if (!lists && r < o->coarsen_rounds) T3(colour_list(m, n, ctx_of(r), true, &ncol, &lists));
   }
   sv[PM_S_ROUNDS] = r;
   sv[PM_S_CONVERGED] = n == 0 ? 1 : 0;
@@ -2504,7 +2570,7 @@ pm_status pm3_smooth(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   T3(select_list(m, 2, 0.0, &n));
   int ncol = 0;
   bool lists;
-  T3(colour_list(m, n, make_ctx(o->sweep, PH3_SMOOTH, 0), &ncol, &lists));
+  T3(colour_list(m, n, make_ctx(o->sweep, PH3_SMOOTH, 0), false, &ncol, &lists));
   sv[PM_S_COLOURED] += n;
   sv[PM_S_COLOURS] += ncol;
   std::vector<int> off, size;
