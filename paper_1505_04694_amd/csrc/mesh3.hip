@@ -1244,13 +1244,20 @@ __global__ void k_class_place(const int* __restrict__ A, int n, const int* __res
 
 // ---- selection of active vertices ------------------------------------------------------------
 
+// whether v (held by the 16 lanes of a group, -1: none) has a short edge it may
+// collapse along; lane l takes every 16th neighbour
+constexpr int kVL = 16;
 __device__ __forceinline__ bool has_candidate(const Store3& st, int v, double L_low2) {
-  int4 h = st.hdr[v];
-  for (int j = 0; j < h.y; ++j) {
-    int u = st.nn[h.x + j];
-    if (tag_ok(st, v, u) && len2(st, v, u) < L_low2) return true;
+  int lane = __lane_id(), l = lane & (kVL - 1), gb = lane & ~(kVL - 1);
+  bool any = false;
+  if (v >= 0) {
+    int4 h = st.hdr[v];
+    for (int j = l; j < h.y && !any; j += kVL) {
+      int u = st.nn[h.x + j];
+      any = tag_ok(st, v, u) && len2(st, v, u) < L_low2;
+    }
   }
-  return false;
+  return (__ballot(any) >> gb & 0xFFFFull) != 0;
 }
 
 // mode 0: live vertices with a candidate; 1: flagged ones (flags cleared);
@@ -1259,29 +1266,54 @@ __device__ __forceinline__ bool has_candidate(const Store3& st, int v, double L_
 // with one add. After a commit that ran out of room mode 1 selects nothing and
 // leaves the flags for the selection that follows the rebuild.
 __global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_low2, uint8_t* nxt, int* out, int* ctr) {
-  __shared__ int wsum[kB / kWave], base;
+  __shared__ int wsum[kB / kWave], base, q[kB];
   if (mode == 1 && ctr[K_ROOM]) return;
-  int lane = __lane_id(), wv = (int)threadIdx.x / kWave;
+  int tid = (int)threadIdx.x, lane = __lane_id(), wv = tid / kWave;
+  uint64_t below = (1ull << lane) - 1ull;
+  // the place of a thread that is `on` among those of the work-group
+  auto place = [&](bool on, int& total) {
+    uint64_t b = __ballot(on);
+    if (lane == 0) wsum[wv] = __popcll(b);
+    __syncthreads();
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < kB / kWave; ++k) {
+      if (k < wv) before += wsum[k];
+      total += wsum[k];
+    }
+    __syncthreads();
+    return before + __popcll(b & below);
+  };
   for (int v0 = (int)blockIdx.x * kB; v0 < st.V; v0 += (int)gridDim.x * kB) {
-    int v = v0 + (int)threadIdx.x;
+    int v = v0 + tid, total;
     bool on = v < st.V && st.valive[v] != 0;
     if (mode == 1 && v < st.V) {
       on = on && nxt[v];
       nxt[v] = 0;
     }
-    if (on) on = mode == 2 ? st.tag[v] == 0 : has_candidate(st, v, L_low2);
-    uint64_t b = __ballot(on);
-    if (lane == 0) wsum[wv] = __popcll(b);
-    __syncthreads();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int q = 0; q < kB / kWave; ++q) {
-      if (q < wv) before += wsum[q];
-      total += wsum[q];
+    if (mode == 2) on = on && st.tag[v] == 0;
+    int at = place(on, total);
+    if (mode != 2) {
+      // those come first that are to be tested, 16 lanes each (one thread went
+      // along a row of 14 neighbours load after load: 20 us for a few vertices;
+      // the launch now takes 9 us)
+      if (on) q[at] = v;
+      __syncthreads();
+      for (int i0 = 0; i0 < total; i0 += kB / kVL) {
+        int i = i0 + tid / kVL, x = i < total ? q[i] : -1;
+        bool c = has_candidate(st, x, L_low2);
+        if ((tid & (kVL - 1)) == 0 && i < total && !c) q[i] = -1;
+      }
+      __syncthreads();
+      v = tid < total ? q[tid] : -1;
+      on = v >= 0;
+      at = place(on, total);
     }
-    if (threadIdx.x == 0) base = total ? atomicAdd(&ctr[K_LIST], total) : 0;
+    if (tid == 0) base = total ? atomicAdd(&ctr[K_LIST], total) : 0;
     __syncthreads();
-    if (on) out[base + before + __popcll(b & ((1ull << lane) - 1ull))] = v;
+    if (on) out[base + at] = v;
+    __syncthreads();
   }
 }
 
@@ -1557,42 +1589,49 @@ __global__ void k_fill_u8(uint8_t* p, int n, uint8_t x) {
 // ---- refinement (Sec. 2.4.2) ---------------------------------------------------------------------
 
 // marks the long edges (v, w), w > v, per NN entry; counts them per vertex
+// kVL lanes a vertex, lane l every kVL-th neighbour: one thread along a row
+// took 41 us on a mesh of 5,600 vertices, however few it had; this takes 6 us
 __global__ void k_mark(Store3 st, double L_up2, int* mark, int* cnt, int* ctr) {
+  int lane = __lane_id(), l = lane & (kVL - 1), gb = lane & ~(kVL - 1);
   int edges = 0;
-  for (int v = gtid(); v < st.V; v += gstride()) {
+  for (int v = gtid() / kVL; v < st.V; v += gstride() / kVL) {
     int4 h = st.hdr[v];
     int c = 0;
-    for (int j = 0; j < h.y; ++j) {
-      int w = st.nn[h.x + j];
-      int m = 0;
-      if (w > v) {
-        ++edges;
-        m = len2(st, v, w) > L_up2 ? 1 : 0;
+    for (int j0 = 0; j0 < h.y; j0 += kVL) {
+      int j = j0 + l;
+      bool m = false;
+      if (j < h.y) {
+        int w = st.nn[h.x + j];
+        if (w > v) {
+          ++edges;
+          m = len2(st, v, w) > L_up2;
+        }
+        mark[h.x + j] = m ? 1 : 0;
       }
-      mark[h.x + j] = m;
-      c += m;
+      c += __popcll(__ballot(m) >> gb & 0xFFFFull);
     }
-    cnt[v] = c;
+    if (l == 0) cnt[v] = c;
   }
   count_add(ctr, S_EDGES, edges);
 }
-
-// new vertex ids V0 + (rank of the edge in (min id, max id) order); the
-// midpoint, the edge-mean metric and the AND of the end tags
+// new vertices on the marked edges (a, b > a), in (a, b) order; the mark
+// becomes the new vertex's id
 __global__ void k_mint(Store3 st, int V0, const int* __restrict__ vscan, int* mark) {
-  for (int v = gtid(); v < V0; v += gstride()) {
+  int lane = __lane_id(), l = lane & (kVL - 1), gb = lane & ~(kVL - 1);
+  for (int v = gtid() / kVL; v < V0; v += gstride() / kVL) {
     int4 h = st.hdr[v];
-    int k = vscan[v];
-    for (int j = 0; j < h.y; ++j) {
-      if (!mark[h.x + j]) {
-        mark[h.x + j] = -1;
-        continue;
-      }
+    int first = V0 + vscan[v];
+    for (int j0 = 0; j0 < h.y; j0 += kVL) {
+      int j = j0 + l;
+      bool m = j < h.y && mark[h.x + j] != 0;
+      uint64_t b = __ballot(m) >> gb & 0xFFFFull;
+      int id = first + __popcll(b & ((1ull << l) - 1ull));
+      first += __popcll(b);
+      if (j < h.y) mark[h.x + j] = m ? id : -1;
+      if (!m) continue;
       int w = st.nn[h.x + j];
-      int id = V0 + k++;
-      mark[h.x + j] = id;
-      double4 a = st.xyz[v], b = st.xyz[w];
-      st.xyz[id] = make_double4((a.x + b.x) * 0.5, (a.y + b.y) * 0.5, (a.z + b.z) * 0.5, 0.0);
+      double4 a = st.xyz[v], p = st.xyz[w];
+      st.xyz[id] = make_double4((a.x + p.x) * 0.5, (a.y + p.y) * 0.5, (a.z + p.z) * 0.5, 0.0);
       st.met[id] = edge_met(st.met[v], st.met[w]);
       st.tag[id] = st.tag[v] & st.tag[w];
       st.valive[id] = 1;
@@ -1624,22 +1663,40 @@ __device__ __forceinline__ int mid_of(const Store3& st, const int* mark, int a, 
   return -1;
 }
 
-// the element's split edges in the global order
-__device__ int own_splits(const Store3& st, const int* mark, int4 e, Split* s) {
+// The element's split edges in the global order, in s (a column of the work-
+// group's LDS). An edge is split when its length says so, the same test that
+// marked it; only those are looked up in a row, and only where their midpoints
+// are wanted (mark).
+constexpr int kSplitThreads = 64;
+struct SplitLds {
+  Split s[6][kSplitThreads];
+  int4 piece[8][kSplitThreads];
+  int from[8][kSplitThreads];
+};
+__device__ __forceinline__ int own_splits(const Store3& st, const int* mark, int4 e, double L_up2, SplitLds& S) {
+  int c = (int)threadIdx.x, n = 0;
   int id[4] = {e.x, e.y, e.z, e.w};
-  int n = 0;
+  double4 p[4];
+  Met6 m[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    p[i] = st.xyz[id[i]];
+    m[i] = st.met[id[i]];
+  }
+#pragma unroll
   for (int i = 0; i < 4; ++i)
+#pragma unroll
     for (int j = i + 1; j < 4; ++j) {
+      double L = qform(edge_met(m[i], m[j]), p[j].x - p[i].x, p[j].y - p[i].y, p[j].z - p[i].z);
+      if (!(L > L_up2)) continue;
       int a = min(id[i], id[j]), b = max(id[i], id[j]);
-      int m = mid_of(st, mark, a, b);
-      if (m < 0) continue;
-      Split x{a, b, m, len2(st, a, b)};
+      Split x{a, b, mark ? mid_of(st, mark, a, b) : 0, L};
       int k = n++;
-      while (k > 0 && split_before(x, s[k - 1])) {
-        s[k] = s[k - 1];
+      while (k > 0 && split_before(x, S.s[k - 1][c])) {
+        S.s[k][c] = S.s[k - 1][c];
         --k;
       }
-      s[k] = x;
+      S.s[k][c] = x;
     }
   return n;
 }
@@ -1650,18 +1707,17 @@ __device__ int own_splits(const Store3& st, const int* mark, int4 e, Split* s) {
 // lies inside its parent. count_only: returns the number of leaves; else
 // writes them (the first into slot t, the rest from base).
 constexpr int kMaxLeaves = 64;
-__device__ int bisect(Store3 st, const Split* s, int ns, int4 e, bool count_only, int t, int base) {
-  int4 stk_t[8];
-  int stk_k[8];
+__device__ __forceinline__ int bisect(const Store3& st, int ns, int4 e, bool count_only, int t, int base, SplitLds& S) {
+  int col = (int)threadIdx.x;
   int top = 0;
-  stk_t[0] = e;
-  stk_k[0] = 0;
+  S.piece[0][col] = e;
+  S.from[0][col] = 0;
   int leaves = 0;
   while (top >= 0) {
-    int4 x = stk_t[top];
-    int k = stk_k[top];
+    int4 x = S.piece[top][col];
+    int k = S.from[top][col];
     --top;
-    while (k < ns && !(has4(x, s[k].a) && has4(x, s[k].b))) ++k;
+    while (k < ns && !(has4(x, S.s[k][col].a) && has4(x, S.s[k][col].b))) ++k;
     if (k == ns) {
       if (!count_only) {
         int slot = leaves == 0 ? t : base + leaves - 1;
@@ -1671,28 +1727,32 @@ __device__ int bisect(Store3 st, const Split* s, int ns, int4 e, bool count_only
       ++leaves;
       continue;
     }
-    int4 ca = replace4(x, s[k].b, s[k].mid);  // keeps a
-    int4 cb = replace4(x, s[k].a, s[k].mid);  // keeps b
+    // (when counting, a number no vertex has stands for the midpoint: it is in
+    // no other split edge)
+    Split sp = S.s[k][col];
+    int mid = count_only ? -1 - k : sp.mid;
+    int4 ca = replace4(x, sp.b, mid);  // keeps a
+    int4 cb = replace4(x, sp.a, mid);  // keeps b
     // depth first, child a first: push b, then a
     ++top;
-    stk_t[top] = cb;
-    stk_k[top] = k + 1;
+    S.piece[top][col] = cb;
+    S.from[top][col] = k + 1;
     ++top;
-    stk_t[top] = ca;
-    stk_k[top] = k + 1;
+    S.piece[top][col] = ca;
+    S.from[top][col] = k + 1;
   }
   return leaves;
 }
 
-__global__ void k_split_count(Store3 st, int T0, const int* __restrict__ mark, int* tcnt, int* ctr) {
+__global__ void __launch_bounds__(kSplitThreads) k_split_count(Store3 st, int T0, double L_up2, int* tcnt, int* ctr) {
+  __shared__ SplitLds S;
   for (int t = gtid(); t < T0; t += gstride()) {
     int c = 0;
     if (st.talive[t]) {
-      Split s[6];
       int4 e = st.tet[t];
-      int ns = own_splits(st, mark, e, s);
+      int ns = own_splits(st, nullptr, e, L_up2, S);
       if (ns > 0) {
-        int l = bisect(st, s, ns, e, true, t, 0);
+        int l = bisect(st, ns, e, true, t, 0, S);
         if (l > kMaxLeaves) atomicOr(&ctr[K_ERR], E_LEAVES);
         c = l - 1;
       }
@@ -1700,14 +1760,14 @@ __global__ void k_split_count(Store3 st, int T0, const int* __restrict__ mark, i
     tcnt[t] = c;
   }
 }
-
-__global__ void k_split_write(Store3 st, int T0, const int* __restrict__ mark, const int* __restrict__ tscan) {
+__global__ void __launch_bounds__(kSplitThreads) k_split_write(Store3 st, int T0, double L_up2, const int* __restrict__ mark,
+                                                             const int* __restrict__ tscan) {
+  __shared__ SplitLds S;
   for (int t = gtid(); t < T0; t += gstride()) {
     if (!st.talive[t]) continue;
-    Split s[6];
     int4 e = st.tet[t];
-    int ns = own_splits(st, mark, e, s);
-    if (ns > 0) bisect(st, s, ns, e, false, t, T0 + tscan[t]);
+    int ns = own_splits(st, mark, e, L_up2, S);
+    if (ns > 0) bisect(st, ns, e, false, t, T0 + tscan[t], S);
   }
 }
 
@@ -1839,16 +1899,31 @@ __global__ void k_quality(Store3 st, double* psum, double* pmin) {
   }
 }
 
-__global__ void k_quality_final(const double* __restrict__ psum, const double* __restrict__ pmin, int n,
-                                double* out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// (one thread adding up the 1,024 sums took 73 us)
+__global__ void k_quality_final(const double* __restrict__ psum, const double* __restrict__ pmin, int n, double* out,
+                                int* at, int no) {
+  __shared__ double ls[QB], lm[QB];
+  int tid = (int)threadIdx.x;
   double s = 0.0, mn = INFINITY;
-  for (int i = 0; i < n; ++i) {
+  for (int i = tid; i < n; i += QB) {
     s = s + psum[i];
     mn = fmin(mn, pmin[i]);
   }
-  out[0] = s;
-  out[1] = mn;
+  ls[tid] = s;
+  lm[tid] = mn;
+  __syncthreads();
+  for (int k = QB / 2; k > 0; k >>= 1) {
+    if (tid < k) {
+      ls[tid] = ls[tid] + ls[tid + k];
+      lm[tid] = fmin(lm[tid], lm[tid + k]);
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    out[0] = ls[0];
+    out[1] = lm[0];
+  }
+  pm::mail_post(at, no);
 }
 
 __global__ void k_export(Store3 st, double* xyz, int* tet, double* met) {
@@ -2530,7 +2605,7 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   for (; p < o->refine_passes; ++p) {
     int V0 = st.V, T0 = st.T;
     T3(zero_ctr(m));
-    k_mark<<<grid(V0), kB, 0, m->s>>>(st, o->L_up2, m->mark, m->cnt, m->ctr);
+    k_mark<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, o->L_up2, m->mark, m->cnt, m->ctr);
     int nv = 0;
     T3(scan_total(m, m->cnt, m->scan, V0, &nv));
     sv[PM_S_EDGES] += m->hctr[K_EDGES];
@@ -2539,14 +2614,14 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
       break;
     }
     T3(reserve(m, V0 + nv, T0));
-    k_mint<<<grid(V0), kB, 0, m->s>>>(st, V0, m->scan, m->mark);
+    k_mint<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, V0, m->scan, m->mark);
     st.V = V0 + nv;
-    k_split_count<<<grid(T0), kB, 0, m->s>>>(st, T0, m->mark, m->tcnt, m->ctr);
+    k_split_count<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->tcnt, m->ctr);
     int nt = 0;
     T3(scan_total(m, m->tcnt, m->tscan, T0, &nt));
     if (m->hctr[K_ERR] & E_LEAVES) return fail3(m, PM_E_DEVICE, "an element split into too many pieces");
     T3(reserve(m, V0 + nv, T0 + nt));
-    k_split_write<<<grid(T0), kB, 0, m->s>>>(st, T0, m->mark, m->tscan);
+    k_split_write<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->mark, m->tscan);
     st.T = T0 + nt;
     H3(hipGetLastError());
     sv[PM_S_NEWV] += nv;
@@ -2592,12 +2667,14 @@ pm_status pm3_smooth(pm3_mesh* m, const pm_options* o, pm_stats* out) {
 pm_status pm3_quality(pm3_mesh* m, double* Q, double* qmin) {
   if (!m) return PM_E_ARG;
   constexpr int NB = 1024;
-  if (!m->qbuf) T3(dgrow(m, &m->qbuf, 0, 2 * NB + 2, false));
+  if (!m->qbuf) T3(dgrow(m, &m->qbuf, 0, 2 * NB, false));
   k_quality<<<NB, QB, 0, m->s>>>(m->st, m->qbuf, m->qbuf + NB);
-  k_quality_final<<<1, 64, 0, m->s>>>(m->qbuf, m->qbuf + NB, NB, m->qbuf + 2 * NB);
-  double h[2];
-  H3(hipMemcpyAsync(h, m->qbuf + 2 * NB, sizeof(double) * 2, hipMemcpyDeviceToHost, m->s));
-  H3(hipStreamSynchronize(m->s));
+  double* h = (double*)(m->hctr + 1024);  // in the pinned block, past the counters and class sizes
+  static_assert(K_COUNT + kMaxColours <= 1024, "the counters' mirror");
+  pm::mail_next(m->mail);
+  k_quality_final<<<1, QB, 0, m->s>>>(m->qbuf, m->qbuf + NB, NB, h, (int*)m->mail.at, m->mail.no);
+  H3(hipGetLastError());
+  H3(pm::mail_wait(m->mail, m->s));
   if (Q) *Q = h[0];
   if (qmin) *qmin = h[1];
   return PM_OK;
