@@ -150,12 +150,13 @@ __device__ __forceinline__ int4 canon4(int4 t) {
   return r;
 }
 
-// element t's geometry; vertex ov, if present, placed at q
-__device__ __forceinline__ Geo3 geo(const Store3& st, int4 t, int ov, double4 q) {
+// element t's geometry
+__device__ __forceinline__ Geo3 geo(const Store3& st, int4 t) {
   Geo3 g;
-  int id[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) g.p[k] = id[k] == ov ? q : st.xyz[id[k]];
+  g.p[0] = st.xyz[t.x];
+  g.p[1] = st.xyz[t.y];
+  g.p[2] = st.xyz[t.z];
+  g.p[3] = st.xyz[t.w];
   Met6 a = st.met[t.x], b = st.met[t.y], c = st.met[t.z], d = st.met[t.w];
   g.m = Met6{(((a.a00 + b.a00) + c.a00) + d.a00) / 4.0, (((a.a01 + b.a01) + c.a01) + d.a01) / 4.0,
              (((a.a02 + b.a02) + c.a02) + d.a02) / 4.0, (((a.a11 + b.a11) + c.a11) + d.a11) / 4.0,
@@ -274,7 +275,7 @@ __global__ void k_tags(Store3 st) {
 __global__ void k_orient(Store3 st, int* ctr) {
   for (int t = gtid(); t < st.T; t += gstride()) {
     int4 e = st.tet[t];
-    if (!(vol6(geo(st, e, -1, make_double4(0, 0, 0, 0))) > 0.0)) atomicOr(&ctr[K_ERR], E_MESH);
+    if (!(vol6(geo(st, e)) > 0.0)) atomicOr(&ctr[K_ERR], E_MESH);
   }
 }
 
@@ -1505,7 +1506,7 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
     for (int k = kWave + lane; k < ne; k += kWave) {
       int4 f = st.tet[st.ne[h.z + k]];
       if (has4(f, u)) continue;
-      Geo3 g = geo(st, canon4(replace4(f, v, u)), -1, make_double4(0, 0, 0, 0));
+      Geo3 g = geo(st, canon4(replace4(f, v, u)));
       bad = bad || !(vol6(g) > 0.0) || !(qual3(g) >= qmin3);
     }
     if (!__ballot(bad)) {
@@ -1773,32 +1774,54 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Store3 st, int T0
 
 // ---- smoothing (Sec. 2.4.4) -------------------------------------------------------------------------
 
-// One class of Laplacian moves with kSL lanes per member: lane j takes the
-// row entries j, j + kSL, ... . The group adds the neighbour terms in row
-// order by shuffles, so each sum is the serial loop's; each lane gathers an
-// element's geometry once for its old and its moved quality; the patch
-// minima fold as the serial loop folds them (the first element's value
-// taken as it is, later ones only when smaller, so a NaN counts only as the
-// first), and the moved patch's validity is a group AND.
-constexpr int kSL = 8;
+// One class of Laplacian moves, a wavefront per member: a lane per neighbour for
+// the terms of the sums, then a lane per element for its old and its moved
+// quality. The terms lie in LDS and nine lanes add one sum each in row order, so
+// each is the serial loop's; the minima fold as the serial loop folds them.
+// What bounds a class is one member's chain of loads (header, row, vertices,
+// element, its vertices), so the width goes into a member: with 8 lanes each,
+// going along a row in steps of 8, a class of the 11^3 mesh took 47 us; this
+// takes 9 us (and 47 us in place of 77 us on the 29^3 one, with thousands of
+// members).
+// the serial loop's minimum over the wavefront (lane 0 holds the first value, a
+// lane without any infinity): a value that is no number counts only as the first
+__device__ __forceinline__ double wave_min(double v) {
+  double m = v == v ? v : INFINITY;
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) {
+    double o = __shfl_xor(m, d);
+    m = o < m ? o : m;
+  }
+  double f = lane_of(v, 0);
+  return f == f ? m : f;
+}
+
+__device__ __forceinline__ double4 pick(bool c, double4 a, double4 b) {
+  return make_double4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, 0.0);
+}
+
 __global__ void __launch_bounds__(256) k_smooth(Store3 st, const int* __restrict__ list, int n, int* ctr) {
+  __shared__ double terms[kB / kWave][9][kWave + 2];
+  auto& T = terms[threadIdx.x / kWave];
   int lane = __lane_id();
-  int j0 = lane & (kSL - 1), base = lane & ~(kSL - 1);
-  int64_t ng = (int64_t)gridDim.x * blockDim.x / kSL;
+  int nw = (int)(gridDim.x * (blockDim.x / kWave));
   int ev = 0, cm = 0;
-  // every branch below is uniform over a group (its member's data)
-  for (int64_t gi = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kSL; gi < n; gi += ng) {
-    int v = list[gi];
+  for (int i = (int)(blockIdx.x * (blockDim.x / kWave)) + (int)threadIdx.x / kWave; i < n; i += nw) {
+    int v = __builtin_amdgcn_readfirstlane(list[i]);
     int4 h = st.hdr[v];
+    int nn = __builtin_amdgcn_readfirstlane(h.y), ne = __builtin_amdgcn_readfirstlane(h.w);
     double4 pv = st.xyz[v];
     Met6 mv = st.met[v];
-    Met6 G{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    double rx = 0.0, ry = 0.0, rz = 0.0;
-    for (int jb = 0; jb < h.y; jb += kSL) {
-      int j = jb + j0;
+    // the neighbours' terms, and this lane's element, side by side
+    int t = lane < ne ? st.ne[h.z + lane] : -1;
+    int4 t4 = st.tet[max(t, 0)];
+    // lane c < 9 adds up the c-th sum in row order
+    double sum = 0.0;
+    for (int jb = 0; jb < nn; jb += kWave) {
+      int j = jb + lane;
       Met6 e{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
       double tx = 0.0, ty = 0.0, tz = 0.0;
-      if (j < h.y) {
+      if (j < nn) {
         int w = st.nn[h.x + j];
         e = edge_met(mv, st.met[w]);
         double4 pw = st.xyz[w];
@@ -1807,26 +1830,23 @@ __global__ void __launch_bounds__(256) k_smooth(Store3 st, const int* __restrict
         ty = (e.a01 * dx + e.a11 * dy) + e.a12 * dz;
         tz = (e.a02 * dx + e.a12 * dy) + e.a22 * dz;
       }
-      int cnt = min(kSL, h.y - jb);
-#pragma unroll
-      for (int k = 0; k < kSL; ++k) {
-        int src = base + k;
-        double s00 = __shfl(e.a00, src), s01 = __shfl(e.a01, src), s02 = __shfl(e.a02, src);
-        double s11 = __shfl(e.a11, src), s12 = __shfl(e.a12, src), s22 = __shfl(e.a22, src);
-        double sx = __shfl(tx, src), sy = __shfl(ty, src), sz = __shfl(tz, src);
-        if (k < cnt) {
-          G.a00 = G.a00 + s00;
-          G.a01 = G.a01 + s01;
-          G.a02 = G.a02 + s02;
-          G.a11 = G.a11 + s11;
-          G.a12 = G.a12 + s12;
-          G.a22 = G.a22 + s22;
-          rx = rx + sx;
-          ry = ry + sy;
-          rz = rz + sz;
-        }
-      }
+      T[0][lane] = e.a00;
+      T[1][lane] = e.a01;
+      T[2][lane] = e.a02;
+      T[3][lane] = e.a11;
+      T[4][lane] = e.a12;
+      T[5][lane] = e.a22;
+      T[6][lane] = tx;
+      T[7][lane] = ty;
+      T[8][lane] = tz;
+      star_sync();
+      const double* mine = T[lane < 9 ? lane : 0];
+      int cnt = min(kWave, nn - jb);
+      for (int q = 0; q < cnt; ++q) sum = sum + mine[q];
+      star_sync();
     }
+    Met6 G{lane_of(sum, 0), lane_of(sum, 1), lane_of(sum, 2), lane_of(sum, 3), lane_of(sum, 4), lane_of(sum, 5)};
+    double rx = lane_of(sum, 6), ry = lane_of(sum, 7), rz = lane_of(sum, 8);
     double det = det3(G);
     double c00 = G.a11 * G.a22 - G.a12 * G.a12, c01 = G.a02 * G.a12 - G.a01 * G.a22,
            c02 = G.a01 * G.a12 - G.a02 * G.a11, c11 = G.a00 * G.a22 - G.a02 * G.a02,
@@ -1834,35 +1854,25 @@ __global__ void __launch_bounds__(256) k_smooth(Store3 st, const int* __restrict
     double4 p = make_double4(pv.x + ((c00 * rx + c01 * ry) + c02 * rz) / det,
                              pv.y + ((c01 * rx + c11 * ry) + c12 * rz) / det,
                              pv.z + ((c02 * rx + c12 * ry) + c22 * rz) / det, 0.0);
-    if (j0 == 0) ++ev;
-    bool vn = true;
+    if (lane == 0) ++ev;
+    bool bad = false;
     double mo = INFINITY, mn = INFINITY;
-    for (int kb = 0; kb < h.w; kb += kSL) {
-      int k = kb + j0;
-      if (k >= h.w) continue;
-      int4 t = st.tet[st.ne[h.z + k]];
-      Geo3 go = geo(st, t, v, pv);
+    for (int k = lane; k < ne; k += kWave) {
+      if (k != lane) t4 = st.tet[st.ne[h.z + k]];
+      Geo3 go = geo(st, t4);
       Geo3 gn = go;
-      int id[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (id[q] == v) gn.p[q] = p;
-      if (!(vol6(gn) > 0.0)) vn = false;
+      gn.p[0] = pick(t4.x == v, p, go.p[0]);
+      gn.p[1] = pick(t4.y == v, p, go.p[1]);
+      gn.p[2] = pick(t4.z == v, p, go.p[2]);
+      gn.p[3] = pick(t4.w == v, p, go.p[3]);
+      if (!(vol6(gn) > 0.0)) bad = true;
       double qo = qual3(go), qn = qual3(gn);
       if (k == 0 || qo < mo) mo = qo;
       if (k == 0 || qn < mn) mn = qn;
     }
-    uint64_t gm = ((1ull << kSL) - 1ull) << base;
-    vn = (__ballot(!vn) & gm) == 0;
-    double oldmin = __shfl(mo, base), newmin = __shfl(mn, base);
-#pragma unroll
-    for (int k = 1; k < kSL; ++k) {
-      double a = __shfl(mo, base + k), b = __shfl(mn, base + k);
-      if (a < oldmin) oldmin = a;
-      if (b < newmin) newmin = b;
-    }
-    if (!(vn && newmin >= oldmin)) continue;
-    if (j0 == 0) {
+    double oldmin = wave_min(mo), newmin = wave_min(mn);
+    if (__ballot(bad) || !(newmin >= oldmin)) continue;
+    if (lane == 0) {
       st.xyz[v] = p;
       ++cm;
     }
@@ -1879,7 +1889,7 @@ __global__ void k_quality(Store3 st, double* psum, double* pmin) {
   double s = 0.0, mn = INFINITY;
   for (int t = gtid(); t < st.T; t += gstride()) {
     if (!st.talive[t]) continue;
-    double q = qual(geo(st, st.tet[t], -1, make_double4(0, 0, 0, 0)));
+    double q = qual(geo(st, st.tet[t]));
     s = s + q;
     mn = fmin(mn, q);
   }
@@ -2653,7 +2663,7 @@ pm_status pm3_smooth(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   T3(zero_ctr(m));
   for (int s = 0; s < o->smooth_sweeps; ++s)
     for (int c = 0; c < ncol; ++c)
-      if (size[c] > 0) k_smooth<<<grid((int64_t)size[c] * kSL), kB, 0, m->s>>>(st, m->cls + off[c], size[c], m->ctr);
+      if (size[c] > 0) k_smooth<<<grid((int64_t)size[c] * kWave), kB, 0, m->s>>>(st, m->cls + off[c], size[c], m->ctr);
   H3(hipGetLastError());
   T3(read_ctr(m));
   sv[PM_S_EVALUATED] = m->hctr[K_EVAL];
