@@ -281,27 +281,26 @@ __global__ void k_orient(Store3 st, int* ctr) {
 
 // ---- rows from the element list ----------------------------------------------------------
 
-__global__ void k_ne_count(Store3 st, int* cnt) {
+// how many elements a vertex has; an element's place among its vertices' ones is
+// what the adds return, so that the filling needs none (on
+// average over the builds of the 29^3 planar-front adaptation, up to 3.4 million
+// elements: count 182 and fill 206 us with adds in both, now 197 and 31)
+__global__ void __launch_bounds__(256) k_ne_count(Store3 st, int* cnt, int4* __restrict__ rank) {
   for (int t = gtid(); t < st.T; t += gstride()) {
     if (!st.talive[t]) continue;
     int4 e = st.tet[t];
-    atomicAdd(&cnt[e.x], 1);
-    atomicAdd(&cnt[e.y], 1);
-    atomicAdd(&cnt[e.z], 1);
-    atomicAdd(&cnt[e.w], 1);
+    rank[t] = make_int4(atomicAdd(&cnt[e.x], 1), atomicAdd(&cnt[e.y], 1), atomicAdd(&cnt[e.z], 1),
+                        atomicAdd(&cnt[e.w], 1));
   }
 }
-
-__global__ void k_ne_fill(Store3 st, const int* __restrict__ off, int* cur) {
+__global__ void __launch_bounds__(256) k_ne_fill(Store3 st, const int* __restrict__ off, const int4* __restrict__ rank) {
   for (int t = gtid(); t < st.T; t += gstride()) {
     if (!st.talive[t]) continue;
-    int4 e = st.tet[t];
-    int id[4] = {e.x, e.y, e.z, e.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      int pos = atomicAdd(&cur[id[k]], 1);
-      st.ne[off[id[k]] + pos] = t;
-    }
+    int4 e = st.tet[t], k = rank[t];
+    st.ne[off[e.x] + k.x] = t;
+    st.ne[off[e.y] + k.y] = t;
+    st.ne[off[e.z] + k.z] = t;
+    st.ne[off[e.w] + k.w] = t;
   }
 }
 
@@ -347,89 +346,6 @@ __device__ void rows_finish_serial(const Store3& st, int v, int o, int n) {
   st.cap[v] = n;
 }
 
-// Bitonic sorting networks across a wavefront, ascending. sort_lanes: one
-// value per lane (value i on lane i). sort_lanes_r<R>: R per lane (value i on
-// lane i / R, register i % R); pairs R or more apart are exchanged by
-// shuffles, nearer ones inside a lane. lanes_at<R>: each lane's value of
-// index i (its own i) from the R-per-lane layout.
-__device__ __forceinline__ int sort_lanes(int a) {
-  int lane = __lane_id();
-#pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1)
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      int o = __shfl_xor(a, j);
-      bool up = (lane & k) == 0, lo = (lane & j) == 0;
-      a = lo == up ? min(a, o) : max(a, o);
-    }
-  return a;
-}
-template <int R>
-__device__ __forceinline__ void sort_lanes_r(int (&a)[R]) {
-  int lane = __lane_id();
-#pragma unroll
-  for (int k = 2; k <= R * kWave; k <<= 1)
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      if (j >= R) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i = R * lane + r;
-          int o = __shfl_xor(a[r], j / R);
-          bool up = (i & k) == 0, lo = (i & j) == 0;
-          a[r] = lo == up ? min(a[r], o) : max(a[r], o);
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          if (r & j) continue;
-          int r2 = r | j, i = R * lane + r;
-          bool up = (i & k) == 0;
-          int x = a[r], y = a[r2];
-          a[r] = up ? min(x, y) : max(x, y);
-          a[r2] = up ? max(x, y) : min(x, y);
-        }
-      }
-    }
-}
-template <int R>
-__device__ __forceinline__ int lanes_at(const int (&a)[R], int i) {
-  int src = i / R, q = i % R, out = INT_MAX;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    int x = __shfl(a[r], src);
-    if (r == q) out = x;
-  }
-  return out;
-}
-
-// Sorted distinct values of the R-per-lane layout `a` (sorted, INT_MAX for
-// none) written to dst[0, u) where dst is the same on every lane; returns u.
-template <int R>
-__device__ __forceinline__ int put_distinct(const int (&a)[R], int* dst) {
-  int lane = __lane_id();
-  int before = __shfl_up(a[R - 1], 1);
-  bool keep[R];
-  int mine = 0;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    int prev = r > 0 ? a[r - 1] : (lane > 0 ? before : INT_MIN);
-    keep[r] = a[r] != INT_MAX && a[r] != prev;
-    mine += keep[r] ? 1 : 0;
-  }
-  int incl = mine;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int x = __shfl_up(incl, d);
-    if (lane >= d) incl += x;
-  }
-  int pos = incl - mine;
-#pragma unroll
-  for (int r = 0; r < R; ++r)
-    if (keep[r]) dst[pos++] = a[r];
-  return __shfl(incl, kWave - 1);
-}
-
 // ---- row commit after a collapse class ---------------------------------------------------------
 // The collapse kernel stamps every row its members change with the class
 // epoch (own) and records each committed member's target (rec). One
@@ -439,10 +355,9 @@ __device__ __forceinline__ int put_distinct(const int (&a)[R], int* dst) {
 // NN(x) = the sorted distinct other vertices of those elements. The row is
 // written in place when it fits its slot, else in fresh space from one of
 // kTopStripes bump pointers (a stripe per row id modulo the count, each with
-// its own range of the pool). Rows past this form (NE above 4 kWave, an
-// absorbed row above 2 kWave, more than two absorbed rows) and a full stripe
-// set the room counter instead; the later classes of the round then stand
-// down and the host rebuilds every row before it runs them again.
+// its own range of the pool). A row of more than kRowMax elements and a full
+// stripe set the room counter instead; the later classes of the round then
+// stand down and the host rebuilds every row before it runs them again.
 constexpr int kTopStripes = 64;
 constexpr int kTopStride = 16;  // ints between two stripes' bump pointers
 
@@ -451,50 +366,74 @@ __device__ __forceinline__ void room3(int* ctr, int epoch) {
   atomicOr(&ctr[K_ROOM], 1);
 }
 
-// The two rows of a vertex with at most kWave elements and kWave neighbours, by
-// one wavefront: lane l < m holds the l-th element id and its other three
-// vertices. A lane's place in NE is the number of smaller ids, one lane read and
-// compare per element; the other vertices go through a hash table in LDS, which
-// leaves each once, and are placed the same way. Sorting networks over the 64
-// lanes with four and eight slots each took some 700 exchanges a row, whatever
-// its length (24 elements and 14 neighbours on average).
-// False (nothing decided) when an id comes twice or there are more neighbours.
+// The two rows of a vertex are made by one wavefront. With at most kWave
+// elements and neighbours (24 and 14 on average) lane l < m holds the l-th
+// element id and its other three vertices. A lane's place in NE is the number of
+// smaller ids, one lane read and compare per element, or its lane where the ids
+// come sorted; the other vertices go through a hash table in LDS, which leaves
+// each once, and are placed the same way. Longer rows, to kRowMax elements, do
+// the same with everything in LDS. The rate of vector instructions bounds these
+// kernels: sorting networks over the 64 lanes with four and eight slots each took
+// some 700 exchanges a row, whatever its length, and kept for the long rows alone
+// they still cost the others their registers and some 200 spilled scalars. Over
+// the 53 large classes of the 29^3 planar-front coarsening a commit took 135 us
+// on average with them and takes 101 us without; a build of all rows 341 and 230.
+constexpr int kRowMax = 4 * kWave;
 struct StarLds {
   int hash[256];
   int list[kWave];
   int4 kept[kWave];
 };
+union RowLds {
+  StarLds s;
+  struct {
+    int hash[1024];
+    int list[3 * kRowMax];
+    int id[kRowMax];
+  } w;
+};
 __device__ __forceinline__ void star_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
-__device__ __forceinline__ bool star_rows(int m, int id, const int (&oth)[3], StarLds& L, int& rid, int& u, int& val,
-                                          int& rnn) {
+// whether x was not in the table yet; at most 3/4 of it come in, so a slot is free
+template <int BITS>
+__device__ __forceinline__ bool hash_in(int* hash, int x) {
+  uint32_t at = ((uint32_t)x * 2654435761u) >> (32 - BITS);
+  for (;;) {
+    int old = atomicCAS(&hash[at], -1, x);
+    if (old == -1) return true;
+    if (old == x) return false;
+    at = (at + 1) & ((1u << BITS) - 1u);
+  }
+}
+// False (nothing decided) when an id comes twice or there are more neighbours.
+__device__ __forceinline__ bool star_rows(int m, int id, const int (&oth)[3], bool sorted, StarLds& L, int& rid, int& u,
+                                          int& val, int& rnn) {
   int lane = __lane_id();
   bool has = lane < m;
   m = __builtin_amdgcn_readfirstlane(m);
-  rid = 0;
+  rid = lane;
   bool twice = false;
-  for (int k = 0; k < m; ++k) {
-    int o = __builtin_amdgcn_readlane(id, k);
-    rid += o < id ? 1 : 0;
-    twice |= o == id && k != lane;
+  if (!sorted) {
+    rid = 0;
+    int same = 0;
+    for (int k = 0; k < m; k += 4) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {  // lanes from m on hold INT_MAX
+        int o = __builtin_amdgcn_readlane(id, k + q);
+        rid += o < id ? 1 : 0;
+        same += o == id ? 1 : 0;
+      }
+    }
+    twice = same > 1;
   }
   *(int4*)(L.hash + 4 * lane) = make_int4(-1, -1, -1, -1);
   star_sync();
   u = 0;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    bool fresh = false;
-    if (has) {
-      uint32_t at = ((uint32_t)oth[q] * 2654435761u) >> 24;
-      for (;;) {  // at most 3 kWave = 192 different vertices: a slot is free
-        int old = atomicCAS(&L.hash[at], -1, oth[q]);
-        fresh = old == -1;
-        if (fresh || old == oth[q]) break;
-        at = (at + 1) & 255u;
-      }
-    }
+    bool fresh = has && hash_in<8>(L.hash, oth[q]);
     uint64_t b = __ballot(fresh);
     int pos = u + __popcll(b & ((1ull << lane) - 1ull));
     if (fresh && pos < kWave) L.list[pos] = oth[q];
@@ -505,7 +444,10 @@ __device__ __forceinline__ bool star_rows(int m, int id, const int (&oth)[3], St
   u = __builtin_amdgcn_readfirstlane(u);
   val = lane < u ? L.list[lane] : INT_MAX;
   rnn = 0;
-  for (int k = 0; k < u; ++k) rnn += __builtin_amdgcn_readlane(val, k) < val ? 1 : 0;
+  for (int k = 0; k < u; k += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rnn += __builtin_amdgcn_readlane(val, k + q) < val ? 1 : 0;
+  }
   star_sync();
   return true;
 }
@@ -515,231 +457,171 @@ __device__ __forceinline__ void others_of(const int4& e, int x, int (&o)[3]) {
   o[2] = e.w == x ? e.z : e.w;
 }
 
-// Row x from its candidates, RC slots per lane: NE(x) (slot o, count n)
-// followed by the rows of the absorbed members (za[j], counts ca[j], j <
-// nab), at most RC kWave candidates in all. RN = 2 RC slots per lane hold
-// the NN candidates. Writes the row in place when it holds at most capx
-// entries, else in fresh space of x's stripe (tops given), and returns
-// false, having written nothing, when the row has more than RN/4 kWave
-// entries or the stripe is full. Every lane of the wavefront makes this call.
-constexpr int kAbsMax = 8;  // absorbed rows a row commit takes
-template <int RC, int RN>
-__device__ __forceinline__ bool put_row3(const Store3& st, int x, int o, int n, int capx, const int (&za)[kAbsMax],
-                                         const int (&ca)[kAbsMax], int nab, int* tops, int64_t base, int64_t per) {
-  static_assert(RN == 2 * RC, "three other vertices per element, four slots each");
-  int lane = __lane_id();
-  int a[RC];
-#pragma unroll
-  for (int r = 0; r < RC; ++r) {
-    // candidate idx of the list NE(x), then the absorbed rows in turn
-    int idx = r * kWave + lane;
-    int src = -1;
-    if (idx < n) {
-      src = o + idx;
-    } else {
-      int q = idx - n;
-      for (int j = 0; j < nab; ++j) {
-        if (q < ca[j]) {
-          src = za[j] + q;
-          break;
-        }
-        q -= ca[j];
-      }
-    }
-    a[r] = src >= 0 ? st.ne[src] : -1;
-  }
-  {
-    int4 e[RC];
-    uint8_t al[RC];
-#pragma unroll
-    for (int r = 0; r < RC; ++r) {
-      e[r] = st.tet[max(a[r], 0)];
-      al[r] = st.talive[max(a[r], 0)];
-    }
-#pragma unroll
-    for (int r = 0; r < RC; ++r) a[r] = a[r] >= 0 && al[r] && has4(e[r], x) ? a[r] : INT_MAX;
-  }
-  sort_lanes_r<RC>(a);
-  // repeats out, then sorted again: the distinct entries come first
-  {
-    int before = __shfl_up(a[RC - 1], 1);
-    bool dup[RC];
-#pragma unroll
-    for (int r = 0; r < RC; ++r) {
-      int prev = r > 0 ? a[r - 1] : (lane > 0 ? before : INT_MIN);
-      dup[r] = a[r] != INT_MAX && a[r] == prev;
-    }
-#pragma unroll
-    for (int r = 0; r < RC; ++r)
-      if (dup[r]) a[r] = INT_MAX;
-  }
-  sort_lanes_r<RC>(a);
-  int m = 0;
-#pragma unroll
-  for (int r = 0; r < RC; ++r) m += a[r] != INT_MAX ? 1 : 0;
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) m += __shfl_xor(m, d);
-  constexpr int K = RN / 4;  // elements per lane
-  if (m > K * kWave) return false;
-  int el[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) el[k] = lanes_at<RC>(a, lane + k * kWave);
-  // the slot: in place, else fresh space from the row's stripe
-  int off = o, cap = capx;
-  if (m > capx) {
-    int need = 2 * m;
-    int sidx = x % kTopStripes;
-    int got = 0;
-    if (lane == 0) got = atomicAdd(&tops[sidx * kTopStride], need);
-    got = __shfl(got, 0);
-    if ((int64_t)got + need > base + (int64_t)(sidx + 1) * per) return false;
-    off = got;
-    cap = need;
-  }
-#pragma unroll
-  for (int k = 0; k < K; ++k)
-    if (lane + k * kWave < m) st.ne[off + k * kWave + lane] = el[k];
-  // NN: the other three vertices of each element, four slots per element
-  int b[RN];
-#pragma unroll
-  for (int r = 0; r < RN; ++r) b[r] = INT_MAX;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    if (lane + k * kWave < m) {
-      int4 f = st.tet[el[k]];
-      int id[4] = {f.x, f.y, f.z, f.w}, q = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (id[j] != x && q < 3) b[4 * k + q++] = id[j];
-    }
-  }
-  sort_lanes_r<RN>(b);
-  int u = put_distinct<RN>(b, st.nn + 3 * (int64_t)off);
-  if (lane == 0) {
-    st.hdr[x] = make_int4(3 * off, u, off, m);
-    st.cap[x] = cap;
-  }
+// Row x's slot for m entries: its own (o, room for cap), else fresh space from
+// one of the stripes. False when that is full.
+__device__ __forceinline__ bool row_slot(int x, int m, int& o, int& cap, int* tops, int64_t base, int64_t per) {
+  if (m <= cap) return true;
+  int need = 2 * m;
+  int sidx = x % kTopStripes;
+  int got = 0;
+  if (__lane_id() == 0) got = atomicAdd(&tops[sidx * kTopStride], need);
+  got = __builtin_amdgcn_readfirstlane(got);
+  if ((int64_t)got + need > base + (int64_t)(sidx + 1) * per) return false;
+  o = got;
+  cap = need;
   return true;
 }
 
-// Row x (slot o, count n, room for capx) from the candidates of put_row3 when
-// every list of them fits the lanes. 1: written; 0: not (more than kWave of
-// something); -1: its stripe is full.
-__device__ __forceinline__ int star_commit(const Store3& st, int x, int o, int n, int capx, const int (&za)[kAbsMax],
-                                           const int (&ca)[kAbsMax], int nab, int* tops, int64_t base, int64_t per,
-                                           StarLds& L) {
+// Row x from the m <= kRowMax element ids in L.w.id, in any order, repeats
+// dropped. False, with nothing written, when its stripe is full.
+__device__ __forceinline__ bool wide_put(const Store3& st, int x, int m, int o, int cap, int* tops, int64_t base,
+                                         int64_t per, RowLds& L) {
+  constexpr int K = kRowMax / kWave;
   int lane = __lane_id();
-  if (n > kWave) return 0;
-  int m = 0;
-  bool fits = true;
-  auto keep = [&](int t, const int4& e, bool alive) {
-    bool k = t >= 0 && alive && has4(e, x);
-    uint64_t b = __ballot(k);
-    int pos = m + __popcll(b & ((1ull << lane) - 1ull));
-    if (k && pos < kWave) {
-      int q[3];
-      others_of(e, x, q);
-      L.kept[pos] = make_int4(t, q[0], q[1], q[2]);
-    }
-    m += __popcll(b);
-  };
-  // NE(x) and the first absorbed row together, then the others
-  int t0 = lane < n ? st.ne[o + lane] : -1, t1 = -1;
-  if (nab > 0) {
-    fits = ca[0] <= kWave;
-    if (fits && lane < ca[0]) t1 = st.ne[za[0] + lane];
-  }
-  int4 e0 = st.tet[max(t0, 0)], e1 = st.tet[max(t1, 0)];
-  bool a0 = st.talive[max(t0, 0)] != 0, a1 = st.talive[max(t1, 0)] != 0;
-  keep(t0, e0, a0);
-  if (nab > 0) keep(t1, e1, a1);
-  for (int j = 1; j < nab; ++j) {
-    if (ca[j] > kWave) {
-      fits = false;
-      break;
-    }
-    int t = lane < ca[j] ? st.ne[za[j] + lane] : -1;
-    int4 e = st.tet[max(t, 0)];
-    keep(t, e, st.talive[max(t, 0)] != 0);
-  }
-  if (!fits || m > kWave) return 0;
+  m = __builtin_amdgcn_readfirstlane(m);
   star_sync();
-  int4 mine = lane < m ? L.kept[lane] : make_int4(INT_MAX, -1, -1, -1);
-  int oth[3] = {mine.y, mine.z, mine.w};
-  int rid, u, val, rnn;
-  if (!star_rows(m, mine.x, oth, L, rid, u, val, rnn)) return 0;
-  int off = o, cap = capx;
-  if (m > capx) {
-    int need = 2 * m;
-    int sidx = x % kTopStripes;
-    int got = 0;
-    if (lane == 0) got = atomicAdd(&tops[sidx * kTopStride], need);
-    got = __shfl(got, 0);
-    if ((int64_t)got + need > base + (int64_t)(sidx + 1) * per) return -1;
-    off = got;
-    cap = need;
+  int a[K], at[K];
+#pragma unroll
+  for (int r = 0; r < K; ++r) {
+    a[r] = r * kWave + lane < m ? L.w.id[r * kWave + lane] : INT_MAX;
+    at[r] = 0;
   }
-  if (lane < m) st.ne[off + rid] = mine.x;
-  if (lane < u) st.nn[3 * (int64_t)off + rnn] = val;
+  for (int k = 0; k < m; ++k) {
+    int q = L.w.id[k];
+#pragma unroll
+    for (int r = 0; r < K; ++r) at[r] |= q == a[r] && k < r * kWave + lane ? 1 : 0;
+  }
+  star_sync();
+  int kept = 0;
+#pragma unroll
+  for (int r = 0; r < K; ++r) {
+    if (a[r] != INT_MAX && at[r]) {
+      a[r] = INT_MAX;
+      L.w.id[r * kWave + lane] = INT_MAX;
+    }
+    at[r] = 0;
+    kept += __popcll(__ballot(a[r] != INT_MAX));
+  }
+  star_sync();
+  for (int k = 0; k < m; ++k) {
+    int q = L.w.id[k];
+#pragma unroll
+    for (int r = 0; r < K; ++r) at[r] += q < a[r] ? 1 : 0;
+  }
+  m = kept;
+  if (!row_slot(x, m, o, cap, tops, base, per)) return false;
+  for (int i = lane; i < 1024; i += kWave) L.w.hash[i] = -1;
+  star_sync();
+  int u = 0;
+#pragma unroll
+  for (int r = 0; r < K; ++r) {
+    bool has = a[r] != INT_MAX;
+    if (has) st.ne[o + at[r]] = a[r];
+    int oth[3];
+    others_of(st.tet[has ? a[r] : 0], x, oth);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      bool fresh = has && hash_in<10>(L.w.hash, oth[q]);
+      uint64_t b = __ballot(fresh);
+      if (fresh) L.w.list[u + __popcll(b & ((1ull << lane) - 1ull))] = oth[q];
+      u += __popcll(b);
+    }
+  }
+  star_sync();
+  u = __builtin_amdgcn_readfirstlane(u);
+  for (int c = lane; c < u; c += kWave) {
+    int val = L.w.list[c], rnn = 0;
+    for (int k = 0; k < u; ++k) rnn += L.w.list[k] < val ? 1 : 0;
+    st.nn[3 * (int64_t)o + rnn] = val;
+  }
   if (lane == 0) {
-    st.hdr[x] = make_int4(3 * off, u, off, m);
+    st.hdr[x] = make_int4(3 * o, u, o, m);
     st.cap[x] = cap;
   }
-  return 1;
+  star_sync();
+  return true;
 }
 
-// one stamped row (every lane of the wavefront)
-__device__ __forceinline__ void commit_row3(const Store3& st, int x, int epoch, const int2* __restrict__ rec,
-                                            int* tops, int64_t base, int64_t per, int* ctr, StarLds& L) {
+// one stamped row (every lane of the wavefront); false: left to a full rebuild
+__device__ __forceinline__ bool commit_row3(const Store3& st, int x, int epoch, const int2* __restrict__ rec, int* tops,
+                                            int64_t base, int64_t per, RowLds& L) {
   int lane = __lane_id();
+  uint64_t below = (1ull << lane) - 1ull;
   int4 h = st.hdr[x];
-  int capx = st.cap[x];
-  if (h.y > 4 * kWave) {
-    if (lane == 0) room3(ctr, epoch);
-    return;
-  }
-  // members collapsed onto x: neighbours whose record names x
-  int w[4];
-  uint64_t bal[4];
-  int nab = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    int j = k * kWave + lane;
-    w[k] = j < h.y ? st.nn[h.x + j] : -1;
-    int2 r = w[k] >= 0 ? rec[w[k]] : make_int2(-1, -1);
-    bal[k] = __ballot(r.x == epoch && r.y == x);
-    nab += __popcll(bal[k]);
-  }
-  int za[kAbsMax], ca[kAbsMax];
-  int tot = h.w;
-  if (nab <= kAbsMax) {
-    int got = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      uint64_t b = bal[k];
-      while (b) {
-        int l = __ffsll((unsigned long long)b) - 1;
-        b &= b - 1;
-        int z = __shfl(w[k], l);
-        int4 hz = st.hdr[z];
-        za[got] = hz.z;
-        ca[got] = hz.w;
-        tot += hz.w;
-        ++got;
+  int cap = __builtin_amdgcn_readfirstlane(st.cap[x]);
+  int nnb = __builtin_amdgcn_readfirstlane(h.x), nn = __builtin_amdgcn_readfirstlane(h.y);
+  int neb = __builtin_amdgcn_readfirstlane(h.z), ne = __builtin_amdgcn_readfirstlane(h.w);
+  if (nn <= kWave && ne <= kWave) {
+    int w = lane < nn ? st.nn[nnb + lane] : -1, t = lane < ne ? st.ne[neb + lane] : -1;
+    int2 rc = rec[max(w, 0)];
+    int4 e = st.tet[max(t, 0)];
+    bool al = st.talive[max(t, 0)] != 0;
+    // members collapsed onto x: neighbours whose record names x
+    uint64_t ab = __ballot(w >= 0 && rc.x == epoch && rc.y == x);
+    bool sorted = ab == 0, fits = true;
+    int m = 0;
+    auto keep = [&]() {
+      bool k = t >= 0 && al && has4(e, x);
+      uint64_t b = __ballot(k);
+      int pos = m + __popcll(b & below);
+      if (k && pos < kWave) {
+        int q[3];
+        others_of(e, x, q);
+        L.s.kept[pos] = make_int4(t, q[0], q[1], q[2]);
+      }
+      m += __popcll(b);
+    };
+    keep();
+    for (; ab; ab &= ab - 1) {
+      int4 hz = st.hdr[__builtin_amdgcn_readlane(w, __ffsll((unsigned long long)ab) - 1)];
+      if (hz.w > kWave) {
+        fits = false;
+        break;
+      }
+      t = lane < hz.w ? st.ne[hz.z + lane] : -1;
+      e = st.tet[max(t, 0)];
+      al = st.talive[max(t, 0)] != 0;
+      keep();
+    }
+    if (fits && m <= kWave) {
+      star_sync();
+      int4 mine = lane < m ? L.s.kept[lane] : make_int4(INT_MAX, -1, -1, -1);
+      int oth[3] = {mine.y, mine.z, mine.w};
+      int rid, u, val, rnn;
+      if (star_rows(m, mine.x, oth, sorted, L.s, rid, u, val, rnn)) {
+        if (!row_slot(x, m, neb, cap, tops, base, per)) return false;
+        if (lane < m) st.ne[neb + rid] = mine.x;
+        if (lane < u) st.nn[3 * (int64_t)neb + rnn] = val;
+        if (lane == 0) {
+          st.hdr[x] = make_int4(3 * neb, u, neb, m);
+          st.cap[x] = cap;
+        }
+        return true;
       }
     }
+    star_sync();
   }
-  // lane counts where they fit; else the smaller network when every candidate
-  // could be kept in it, else the larger
-  bool ok = false;
-  int star = nab <= kAbsMax ? star_commit(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per, L) : 0;
-  if (star != 0)
-    ok = star > 0;
-  else if (nab <= kAbsMax && tot <= 2 * kWave)
-    ok = put_row3<4, 8>(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per);
-  else if (nab <= kAbsMax && tot <= 8 * kWave)
-    ok = put_row3<8, 16>(st, x, h.z, h.w, capx, za, ca, nab, tops, base, per);
-  if (!ok && lane == 0) room3(ctr, epoch);
+  int m = 0;
+  auto gather = [&](int o, int n) {
+    for (int jb = 0; jb < n; jb += kWave) {
+      int t = jb + lane < n ? st.ne[o + jb + lane] : -1;
+      bool k = t >= 0 && st.talive[max(t, 0)] != 0 && has4(st.tet[max(t, 0)], x);
+      uint64_t b = __ballot(k);
+      int pos = m + __popcll(b & below);
+      if (k && pos < kRowMax) L.w.id[pos] = t;
+      m += __popcll(b);
+    }
+  };
+  gather(neb, ne);
+  for (int jb = 0; jb < nn; jb += kWave) {
+    int w = jb + lane < nn ? st.nn[nnb + jb + lane] : -1;
+    int2 rc = rec[max(w, 0)];
+    for (uint64_t ab = __ballot(w >= 0 && rc.x == epoch && rc.y == x); ab; ab &= ab - 1) {
+      int4 hz = st.hdr[__builtin_amdgcn_readlane(w, __ffsll((unsigned long long)ab) - 1)];
+      gather(hz.z, hz.w);
+    }
+  }
+  return m <= kRowMax && wide_put(st, x, m, neb, cap, tops, base, per, L);
 }
 
 // whether the class has rows to commit; the next class's counts start at zero
@@ -761,9 +643,9 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
                                                  const int2* __restrict__ rec, int* tops, int64_t base,
                                                  int64_t per, int* ctr) {
   if (!class_committed(ctr, epoch)) return;
-  __shared__ __align__(16) StarLds L[kB / kWave];
+  __shared__ __align__(16) RowLds L[kB / kWave];
   int lane = __lane_id();
-  int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+  int wid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
   int per_wave = (st.V + nw - 1) / nw;
   int x0 = (int)min((int64_t)wid * per_wave, (int64_t)st.V), x1 = min(st.V, x0 + per_wave);
@@ -773,7 +655,7 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
     while (dm) {
       int l = __ffsll((unsigned long long)dm) - 1;
       dm &= dm - 1;
-      commit_row3(st, c0 + l, epoch, rec, tops, base, per, ctr, L[threadIdx.x / kWave]);
+      if (!commit_row3(st, c0 + l, epoch, rec, tops, base, per, L[threadIdx.x / kWave]) && lane == 0) room3(ctr, epoch);
     }
   }
 }
@@ -782,65 +664,50 @@ __global__ void __launch_bounds__(256) k_commit3_list(Store3 st, int epoch, cons
                                                       const int2* __restrict__ rec, int* tops, int64_t base,
                                                       int64_t per, int* ctr) {
   if (!class_committed(ctr, epoch)) return;
-  __shared__ __align__(16) StarLds L[kB / kWave];
+  __shared__ __align__(16) RowLds L[kB / kWave];
   int n = ctr[K_NROWS + (epoch & 1)];
-  int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+  int wid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
-  for (int i = wid; i < n; i += nw) commit_row3(st, rows[i], epoch, rec, tops, base, per, ctr, L[threadIdx.x / kWave]);
+  for (int i = wid; i < n; i += nw) {
+    int x = __builtin_amdgcn_readfirstlane(rows[i]);
+    if (!commit_row3(st, x, epoch, rec, tops, base, per, L[threadIdx.x / kWave]) && __lane_id() == 0) room3(ctr, epoch);
+  }
 }
 
 // Sorted rows from the element lists gathered in build order: NE(v) sorted;
 // NN(v) = the sorted distinct other vertices of NE(v)'s elements, in a slot
-// of three entries per NE entry. One wavefront per vertex: NE(v) one entry
-// per lane through the lane network; the three other vertices of each
-// element in four slots per lane (the fourth empty) through the
-// four-per-lane network, repeats dropped by comparing each slot with the one
-// before it. Rows of more than kWave elements take the serial form on the
-// wavefront's first lane.
+// of three entries per NE entry. One wavefront per vertex; rows of more than
+// kRowMax elements take the serial form on its first lane.
 __global__ void __launch_bounds__(256) k_rows_finish(Store3 st, const int* __restrict__ off, const int* __restrict__ cnt) {
-  __shared__ __align__(16) StarLds L[kB / kWave];
+  __shared__ __align__(16) RowLds L[kB / kWave];
+  RowLds& mine = L[threadIdx.x / kWave];
   int lane = __lane_id();
-  int wid = (int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave);
+  int wid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
   for (int v = wid; v < st.V; v += nw) {
-    int o = off[v], n = cnt[v];
-    if (n > kWave) {
-      // in place (capacity n), no absorbed rows: the row always fits
-      const int none[kAbsMax] = {};
-      if (n > 8 * kWave || !put_row3<8, 16>(st, v, o, n, n, none, none, 0, nullptr, 0, 0))
-        if (lane == 0) rows_finish_serial(st, v, o, n);
-      continue;
-    }
-    bool has = lane < n;
-    int t = has ? st.ne[o + lane] : INT_MAX;
-    int4 e = st.tet[has ? t : 0];
-    int oth[3], rid, u0, val, rnn;
-    others_of(e, v, oth);
-    if (star_rows(n, t, oth, L[threadIdx.x / kWave], rid, u0, val, rnn)) {
-      if (has) st.ne[o + rid] = t;
-      if (lane < u0) st.nn[3 * (int64_t)o + rnn] = val;
-      if (lane == 0) {
-        st.hdr[v] = make_int4(3 * o, u0, o, n);
-        st.cap[v] = n;
+    int o = __builtin_amdgcn_readfirstlane(off[v]), n = __builtin_amdgcn_readfirstlane(cnt[v]);
+    if (n <= kWave) {
+      bool has = lane < n;
+      int t = has ? st.ne[o + lane] : INT_MAX;
+      int oth[3], rid, u, val, rnn;
+      others_of(st.tet[has ? t : 0], v, oth);
+      if (star_rows(n, t, oth, false, mine.s, rid, u, val, rnn)) {
+        if (has) st.ne[o + rid] = t;
+        if (lane < u) st.nn[3 * (int64_t)o + rnn] = val;
+        if (lane == 0) {
+          st.hdr[v] = make_int4(3 * o, u, o, n);
+          st.cap[v] = n;
+        }
+        continue;
       }
+    }
+    if (n > kRowMax) {
+      if (lane == 0) rows_finish_serial(st, v, o, n);
       continue;
     }
-    int a[4] = {INT_MAX, INT_MAX, INT_MAX, INT_MAX};
-    if (has) {
-      int id[4] = {e.x, e.y, e.z, e.w};
-      int q = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (id[j] != v && q < 3) a[q++] = id[j];
-    }
-    t = sort_lanes(t);
-    if (has) st.ne[o + lane] = t;
-    sort_lanes_r<4>(a);
-    int u = put_distinct<4>(a, st.nn + 3 * o);
-    if (lane == 0) {
-      st.hdr[v] = make_int4(3 * o, u, o, n);
-      st.cap[v] = n;
-    }
+    star_sync();
+    for (int j = lane; j < n; j += kWave) mine.w.id[j] = st.ne[o + j];
+    wide_put(st, v, n, o, n, nullptr, 0, 0, mine);
   }
 }
 
@@ -1783,6 +1650,7 @@ __global__ void __launch_bounds__(kSplitThreads) k_split_write(Store3 st, int T0
 // going along a row in steps of 8, a class of the 11^3 mesh took 47 us; this
 // takes 9 us (and 47 us in place of 77 us on the 29^3 one, with thousands of
 // members).
+
 // the serial loop's minimum over the wavefront (lane 0 holds the first value, a
 // lane without any infinity): a value that is no number counts only as the first
 __device__ __forceinline__ double wave_min(double v) {
@@ -1984,7 +1852,7 @@ struct pm3_mesh {
   int* hctr = nullptr;  // pinned mirror
   pm::Mail mail;        // its block's
   // scratch
-  int *cnt = nullptr, *off = nullptr, *cur = nullptr, *flag = nullptr, *scan = nullptr, *partial = nullptr;
+  int *cnt = nullptr, *off = nullptr, *flag = nullptr, *scan = nullptr, *partial = nullptr;
   int *A = nullptr, *B = nullptr, *cls = nullptr, *col = nullptr, *blk = nullptr, *mark = nullptr,
       *tcnt = nullptr, *tscan = nullptr;
   Rec3* recs = nullptr;  // one-block colourings: predecessor records
@@ -2078,7 +1946,6 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
     T3(dgrow(m, &st.hdr, m->Vcap, nc, true));
     T3(dgrow(m, &m->cnt, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->off, m->Vcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->cur, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->flag, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->scan, m->Vcap + 1, nc + 1, true));
     T3(dgrow(m, &m->A, m->Vcap, nc, true));
@@ -2135,7 +2002,9 @@ pm_status build_rows(pm3_mesh* m) {
   Store3& st = m->st;
   int V = st.V;
   k_fill_int<<<grid(V + 1), kB, 0, m->s>>>(m->cnt, V + 1, 0);
-  k_ne_count<<<grid(st.T), kB, 0, m->s>>>(st, m->cnt);
+  int4* rank = nullptr;
+  T3(dgrow(m, &rank, 0, st.T, false));
+  k_ne_count<<<grid(st.T), kB, 0, m->s>>>(st, m->cnt, rank);
   int total = 0;
   T3(scan_total(m, m->cnt, m->off, V, &total));
   int64_t want = total + (int64_t)(m->headroom * (double)total) + kTopStripes * 64;
@@ -2154,8 +2023,8 @@ pm_status build_rows(pm3_mesh* m) {
     m->mcap = nc;
   }
   if (!m->tops) T3(dgrow(m, &m->tops, 0, kTopStripes * kTopStride, false));
-  k_fill_int<<<grid(V + 1), kB, 0, m->s>>>(m->cur, V + 1, 0);
-  k_ne_fill<<<grid(st.T), kB, 0, m->s>>>(st, m->off, m->cur);
+  k_ne_fill<<<grid(st.T), kB, 0, m->s>>>(st, m->off, rank);
+  dfree3(rank);
   k_rows_finish<<<grid((int64_t)V * kWave), kB, 0, m->s>>>(st, m->off, m->cnt);
   m->top_base = total;
   m->top_per = (m->necap - total) / kTopStripes;
@@ -2383,7 +2252,7 @@ pm_status pm3_mesh_destroy(pm3_mesh* m) {
   dfree3(st.hdr);
   dfree3(st.nn);
   dfree3(st.ne);
-  for (int** p : {&m->cnt, &m->off, &m->cur, &m->flag, &m->scan, &m->partial, &m->A, &m->B, &m->cls, &m->col,
+  for (int** p : {&m->cnt, &m->off, &m->flag, &m->scan, &m->partial, &m->A, &m->B, &m->cls, &m->col,
                   &m->blk, &m->mark, &m->tcnt, &m->tscan, &m->ctr})
     dfree3(*p);
   dfree3(m->recs);
