@@ -217,12 +217,13 @@ __device__ __forceinline__ void zero_colouring(int* ctr) {
   if (threadIdx.x < kStripes) ctr[K_STRIPE + threadIdx.x * kStripeW + S_COLOURED] = 0;
 }
 // the counters (and `more` class sizes behind them) to the host, striped counts
-// summed (256 threads)
-__global__ void k_mail3(const int* ctr, int more, int* dst, int* at, int no) {
+// summed (256 threads); the next selection counts its list from zero
+__global__ void k_mail3(int* ctr, int more, int* dst, int* at, int no) {
   int tid = (int)threadIdx.x;
   for (int i = tid; i < K_COUNT + more; i += (int)blockDim.x) {
     bool striped = i == K_COLOURED || i == K_EVAL || i == K_DEFER || i == K_COMMIT || i == K_EDGES;
     if (!striped) dst[i] = ctr[i];
+    if (i == K_LIST) ctr[i] = 0;
   }
   for (int k = tid / kWave; k < S_SLOTS; k += (int)blockDim.x / kWave) {
     int x = ctr[K_STRIPE + (tid & (kWave - 1)) * kStripeW + k];
@@ -630,7 +631,8 @@ __device__ __forceinline__ bool class_committed(int* ctr, int epoch) {
     ctr[K_CCOMMIT + (~epoch & 1)] = 0;
     ctr[K_NROWS + (~epoch & 1)] = 0;
   }
-  return ctr[K_CCOMMIT + (epoch & 1)] != 0 && ctr[K_ROOM] == 0;
+  int committed = ctr[K_CCOMMIT + (epoch & 1)], room = ctr[K_ROOM];
+  return committed != 0 && room == 0;
 }
 
 // Two launch shapes rebuild the same rows, each once. Vertex order (large
@@ -663,13 +665,15 @@ __global__ void __launch_bounds__(256) k_commit3(Store3 st, int epoch, const int
 __global__ void __launch_bounds__(256) k_commit3_list(Store3 st, int epoch, const int* __restrict__ rows,
                                                       const int2* __restrict__ rec, int* tops, int64_t base,
                                                       int64_t per, int* ctr) {
-  if (!class_committed(ctr, epoch)) return;
   __shared__ __align__(16) RowLds L[kB / kWave];
-  int n = ctr[K_NROWS + (epoch & 1)];
   int wid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
   int nw = (int)((int64_t)gridDim.x * blockDim.x / kWave);
+  // counts and the first row side by side (the list has a slot for every vertex)
+  int n = ctr[K_NROWS + (epoch & 1)];
+  int x = __builtin_amdgcn_readfirstlane(rows[min(wid, st.V - 1)]);
+  if (!class_committed(ctr, epoch)) return;
   for (int i = wid; i < n; i += nw) {
-    int x = __builtin_amdgcn_readfirstlane(rows[i]);
+    if (i != wid) x = __builtin_amdgcn_readfirstlane(rows[i]);
     if (!commit_row3(st, x, epoch, rec, tops, base, per, L[threadIdx.x / kWave]) && __lane_id() == 0) room3(ctr, epoch);
   }
 }
@@ -754,19 +758,6 @@ __global__ void k_colour_start(int* col, uint8_t* act, int V, int* ctr) {
   }
 }
 
-// the same for the list's vertices alone, after its last class (and no list)
-__global__ void k_unlist(const int* __restrict__ A, int n, int* col, uint8_t* act, int* ctr) {
-  zero_colouring(ctr);
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctr[K_LIST] = 0;
-  for (int i = gtid(); i < n; i += gstride()) {
-    col[A[i]] = -1;
-    act[A[i]] = 0;
-  }
-}
-// the colours of a list again from its classes
-__global__ void k_recolour(const int* __restrict__ cls, int n, int c, int* col) {
-  for (int i = gtid(); i < n; i += gstride()) col[cls[i]] = c;
-}
 // a list's length: given, or (colouring ahead of the read-back) the device's,
 // 0 when it is too long for one block
 __device__ __forceinline__ int list_length(int n, const int* n_dev) {
@@ -776,8 +767,7 @@ __device__ __forceinline__ int list_length(int n, const int* n_dev) {
 }
 
 // the list's vertices active, each with its place
-__global__ void k_place(const int* __restrict__ A, int n, const int* n_dev, uint8_t* act, int* blk) {
-  n = list_length(n, n_dev);
+__global__ void k_place(const int* __restrict__ A, int n, uint8_t* act, int* blk) {
   for (int i = gtid(); i < n; i += gstride()) {
     act[A[i]] = 1;
     blk[A[i]] = i;
@@ -1131,11 +1121,18 @@ __device__ __forceinline__ bool has_candidate(const Store3& st, int v, double L_
 // mode 0: live vertices with a candidate; 1: flagged ones (flags cleared);
 // 2: live interior vertices. Their list and its length (ctr[K_LIST], 0 at the
 // start): every pass of a work-group over 256 vertices appends what it selects
-// with one add. After a commit that ran out of room mode 1 selects nothing and
-// leaves the flags for the selection that follows the rebuild.
-__global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_low2, uint8_t* nxt, int* out, int* ctr) {
+// with one add. Mode 1 also ends a round: the old list's vertices lose colour
+// and activity, and the new ones become active, each with its place (in launches
+// of their own over the two lists that took 5 us of a round's 40 besides its
+// classes). After a commit that ran out of room mode 1 does nothing and leaves
+// the flags for the selection that follows the rebuild.
+__global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_low2, uint8_t* nxt, int* out, int* col,
+                                              uint8_t* act, int* blk, int* ctr) {
   __shared__ int wsum[kB / kWave], base, q[kB];
-  if (mode == 1 && ctr[K_ROOM]) return;
+  if (mode == 1) {
+    if (ctr[K_ROOM]) return;
+    zero_colouring(ctr);
+  }
   int tid = (int)threadIdx.x, lane = __lane_id(), wv = tid / kWave;
   uint64_t below = (1ull << lane) - 1ull;
   // the place of a thread that is `on` among those of the work-group
@@ -1159,6 +1156,10 @@ __global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_lo
     if (mode == 1 && v < st.V) {
       on = on && nxt[v];
       nxt[v] = 0;
+      if (act[v]) {
+        act[v] = 0;
+        col[v] = -1;
+      }
     }
     if (mode == 2) on = on && st.tag[v] == 0;
     int at = place(on, total);
@@ -1180,7 +1181,13 @@ __global__ void __launch_bounds__(256) k_select(Store3 st, int mode, double L_lo
     }
     if (tid == 0) base = total ? atomicAdd(&ctr[K_LIST], total) : 0;
     __syncthreads();
-    if (on) out[base + at] = v;
+    if (on) {
+      out[base + at] = v;
+      if (mode == 1) {
+        act[v] = 1;
+        blk[v] = base + at;
+      }
+    }
     __syncthreads();
   }
 }
@@ -1268,16 +1275,21 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
                                                   int2* rec, int* ctr) {
   // an earlier class's row commit ran out of room: the host rebuilds the
   // rows and runs this class again
-  if (ctr[K_ROOM]) return;
+  // (its flag and the member are loaded side by side)
+  int room = ctr[K_ROOM];
   int lane = __lane_id();
   int gid = __builtin_amdgcn_readfirstlane((int)(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave));
-  if (gid >= n) return;
-  int v = __builtin_amdgcn_readfirstlane(list[gid]);
+  int v = __builtin_amdgcn_readfirstlane(list[min(gid, n - 1)]);
+  if (room || gid >= n) return;
   int4 h = st.hdr[v];
   int nn = __builtin_amdgcn_readfirstlane(h.y), ne = __builtin_amdgcn_readfirstlane(h.w);
   uint64_t kv = vkey(sseed, (uint32_t)v);
   // level by level: row entries; neighbours and elements; the elements' vertices
-  int w = lane < nn ? st.nn[h.x + lane] : -1, t = lane < ne ? st.ne[h.z + lane] : -1;
+  // (two candidates side by side where half the lanes hold the elements)
+  bool longer = nn > kWave;  // some candidates are not held by lanes
+  bool pair = ne <= kWave / 2 && !longer, upper = pair && lane >= kWave / 2;
+  int le = upper ? lane - kWave / 2 : lane;
+  int w = lane < nn ? st.nn[h.x + lane] : -1, t = le < ne ? st.ne[h.z + le] : -1;
   int ws = max(w, 0);
   Vtx pv = vtx(st, v), pw = vtx(st, ws);
   int cw = col[ws], tv = st.tag[v], tw = st.tag[ws];
@@ -1303,7 +1315,6 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
     if (l < L_low2) L = l;
   }
   bool cand = L < L_low2;
-  bool longer = nn > kWave;  // some candidates are not held by lanes
   // a held candidate's place in the order
   int rank = 0;
   uint64_t cb = __ballot(cand);
@@ -1327,13 +1338,23 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
   for (;;) {
     // the next candidate: from the lanes, or past pL, pu among all
     Vtx du = pw;
-    int u = -1;
+    int u = -1, u2 = -1;
     if (!longer) {
       if (next >= nc) break;
       int k = __ffsll((unsigned long long)__ballot(cand && rank == next)) - 1;
       ++next;
       u = __builtin_amdgcn_readlane(w, k);
       du = lane_of(pw, k);
+      if (pair && next < nc) {
+        k = __ffsll((unsigned long long)__ballot(cand && rank == next)) - 1;
+        ++next;
+        u2 = __builtin_amdgcn_readlane(w, k);
+        Vtx d2 = lane_of(pw, k);
+        if (upper) {
+          u = u2;
+          du = d2;
+        }
+      }
     } else {
       double bL = 0.0;
       int bu = -1;
@@ -1369,7 +1390,19 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
       Geo3 g = star_geo(u, du, o, p);
       bad = !(vol6(g) > 0.0) || !(qual3(g) >= qmin3);
     }
-    if (__ballot(bad)) continue;
+    uint64_t bb = __ballot(bad);
+    if (pair) {
+      if ((uint32_t)bb == 0) {
+        target = __builtin_amdgcn_readfirstlane(u);
+        break;
+      }
+      if (u2 >= 0 && bb >> 32 == 0) {
+        target = u2;
+        break;
+      }
+      continue;
+    }
+    if (bb) continue;
     for (int k = kWave + lane; k < ne; k += kWave) {
       int4 f = st.tet[st.ne[h.z + k]];
       if (has4(f, u)) continue;
@@ -2036,8 +2069,7 @@ pm_status build_rows(pm3_mesh* m) {
 
 // list of the vertices selected by mode, in m->A; returns its length
 pm_status select_list(pm3_mesh* m, int mode, double L_low2, int* n) {
-  k_unlist<<<1, kB, 0, m->s>>>(nullptr, 0, m->col, m->act, m->ctr);
-  k_select<<<grid(m->st.V), kB, 0, m->s>>>(m->st, mode, L_low2, m->nxt, m->A, m->ctr);
+  k_select<<<grid(m->st.V), kB, 0, m->s>>>(m->st, mode, L_low2, m->nxt, m->A, m->col, m->act, m->blk, m->ctr);
   T3(read_ctr(m));
   *n = m->hctr[K_LIST];
   return PM_OK;
@@ -2067,7 +2099,7 @@ pm_status colour_list(pm3_mesh* m, int n, uint32_t ctx, bool clean, int* ncol, b
   if (!clean) k_colour_start<<<grid(st.V), kB, 0, m->s>>>(m->col, m->act, st.V, m->ctr);
   if (n == 0) return PM_OK;
   int done = 0;
-  k_place<<<grid(n), kB, 0, m->s>>>(m->A, n, nullptr, m->act, m->blk);
+  if (!clean) k_place<<<grid(n), kB, 0, m->s>>>(m->A, n, m->act, m->blk);
   if (n <= kSolve) {
     T3(solve_list(m, m->A, n, nullptr, sseed, true));
     T3(read_ctr(m, kMaxColours));
@@ -2432,11 +2464,9 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
                                                                    m->top_per, m->ctr);
         H3(hipGetLastError());
       }
-      k_unlist<<<grid(n), kB, 0, m->s>>>(m->A, n, m->col, m->act, m->ctr);
-      k_select<<<grid(st.V), kB, 0, m->s>>>(st, 1, o->L_low2, m->nxt, m->B, m->ctr);
+      k_select<<<grid(st.V), kB, 0, m->s>>>(st, 1, o->L_low2, m->nxt, m->B, m->col, m->act, m->blk, m->ctr);
       if (r + 1 < o->coarsen_rounds) {
         const int* len = m->ctr + K_LIST;
-        k_place<<<grid(kSolve), kB, 0, m->s>>>(m->B, kSolve, len, m->act, m->blk);
         T3(solve_list(m, m->B, kSolve, len, stream_seed(m->seed, ctx_of(r + 1)), true));
       }
       T3(read_ctr(m, kMaxColours));
@@ -2450,8 +2480,6 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
       T3(build_rows(m));
       ++sv[13];
       c0 = failed + 1;
-      for (int c = 0; c < ncol; ++c)
-        if (size[c] > 0) k_recolour<<<grid(size[c]), kB, 0, m->s>>>(m->cls + off[c], size[c], c, m->col);
       k_fill_int<<<1, kWave, 0, m->s>>>(m->ctr + K_CCOMMIT, 4, 0);
     }
     std::swap(m->A, m->B);
