@@ -716,10 +716,11 @@ __global__ void __launch_bounds__(256) k_rows_finish(Store3 st, const int* __res
 }
 
 // the stripes' bump pointers after a full row build: stripe s owns
-// [base + s per, base + (s + 1) per)
-__global__ void k_tops_init(int* tops, int64_t base, int64_t per) {
+// [base + s per, base + (s + 1) per). No commit is out of room.
+__global__ void k_tops_init(int* tops, int64_t base, int64_t per, int* ctr) {
   int s = (int)threadIdx.x;
   if (s < kTopStripes) tops[s * kTopStride] = (int)(base + (int64_t)s * per);
+  if (s < 2) ctr[K_ROOM + s] = 0;
 }
 
 // ---- colouring (Sec. 3.2) -----------------------------------------------------------------
@@ -1268,7 +1269,10 @@ __device__ __forceinline__ void star_others(const int4& e, int v, int (&o)[3]) {
 // With 32 lanes a member and the elements' four vertices gathered again for
 // every candidate (21 loads a lane), a class of some hundred members took 30 us,
 // most of it in candidates that fail: late rounds try every short edge of
-// vertices that the quality bound keeps.
+// vertices that the quality bound keeps. Where half the lanes hold the elements
+// (at most 32), the halves try two candidates side by side: the first classes of
+// the 29^3 planar-front coarsening (65 to 116 thousand members) went from 469 to
+// 393 us on average, those of up to four members from 7.9 to 7.2 us.
 __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restrict__ list, int n,
                                                   const int* __restrict__ col, int c, uint64_t sseed, double L_low2,
                                                   double qmin3, uint8_t* nxt, int epoch, int* own, int* rows,
@@ -1459,10 +1463,44 @@ __global__ void __launch_bounds__(256) k_collapse(Store3 st, const int* __restri
   }
 }
 
+// Arrays moved to larger blocks, and the new slots of some set to -1 (src null),
+// a row of the grid each: a copy of its own for each of the 20 arrays took 1.8 us
+// and a gap, 71 times in a cycle of the 11^3 mesh. The blocks start on 256 bytes.
+struct Moves {
+  struct {
+    const void* src;
+    void* dst;
+    int64_t bytes;
+  } e[24];
+  int n;
+};
+__global__ void k_move(Moves mv) {
+  auto e = mv.e[blockIdx.y];
+  int64_t i0 = gtid(), step = (int64_t)gridDim.x * blockDim.x;
+  if (!e.src) {
+    for (int64_t i = i0; i < e.bytes / 4; i += step) ((int*)e.dst)[i] = -1;
+    return;
+  }
+  int64_t full = e.bytes / 16;
+  for (int64_t i = i0; i < full; i += step) ((int4*)e.dst)[i] = ((const int4*)e.src)[i];
+  for (int64_t i = full * 16 + i0; i < e.bytes; i += step) ((uint8_t*)e.dst)[i] = ((const uint8_t*)e.src)[i];
+}
+
 // stable renumbering of live vertices and elements (a monotone map keeps the
 // elements' canonical order)
 __global__ void k_flags(const uint8_t* __restrict__ a, int n, int* f) {
   for (int i = gtid(); i < n; i += gstride()) f[i] = a[i] ? 1 : 0;
+}
+
+// (after a renumbering) every slot is live and no vertex selected
+__global__ void k_all_live(Store3 st, uint8_t* nxt) {
+  for (int i = gtid(); i < max(st.V, st.T); i += gstride()) {
+    if (i < st.V) {
+      st.valive[i] = 1;
+      nxt[i] = 0;
+    }
+    if (i < st.T) st.talive[i] = 1;
+  }
 }
 
 __global__ void k_compact_v(Store3 st, const int* __restrict__ vmap, double4* xyz, Met6* met, uint8_t* tag) {
@@ -1968,44 +2006,79 @@ pm_status zero_ctr(pm3_mesh* m) {
 // capacity for V vertices and T elements (kept contents)
 pm_status reserve(pm3_mesh* m, int V, int T) {
   Store3& st = m->st;
-  if (V > m->Vcap) {
-    int nc = std::max(V, m->Vcap + m->Vcap / 2);
-    T3(dgrow(m, &st.xyz, m->Vcap, nc, true));
-    T3(dgrow(m, &st.met, m->Vcap, nc, true));
-    T3(dgrow(m, &st.tag, m->Vcap, nc, true));
-    T3(dgrow(m, &st.valive, m->Vcap, nc, true));
-    // growth happens in the middle of a refinement pass, whose rows, vertex
-    // scan and element scan must survive it: every array keeps its contents
-    T3(dgrow(m, &st.hdr, m->Vcap, nc, true));
-    T3(dgrow(m, &m->cnt, m->Vcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->off, m->Vcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->flag, m->Vcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->scan, m->Vcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->A, m->Vcap, nc, true));
-    T3(dgrow(m, &m->B, m->Vcap, nc, false));
-    T3(dgrow(m, &m->cls, m->Vcap, nc, true));
-    T3(dgrow(m, &m->col, m->Vcap, nc, true));
-    T3(dgrow(m, &m->blk, m->Vcap, nc, true));
-    T3(dgrow(m, &m->act, m->Vcap, nc, true));
-    T3(dgrow(m, &m->nxt, m->Vcap, nc, true));
-    T3(dgrow(m, &st.cap, m->Vcap, nc, true));
-    T3(dgrow(m, &m->own, m->Vcap, nc, true));
-    T3(dgrow(m, &m->rec, m->Vcap, nc, true));
-    T3(dgrow(m, &m->rows, m->Vcap, nc, false));
-    // new vertex slots carry no class stamp or record
-    k_fill_int<<<grid(nc - m->Vcap), kB, 0, m->s>>>(m->own + m->Vcap, nc - m->Vcap, -1);
-    k_fill_int<<<grid(2 * (int64_t)(nc - m->Vcap)), kB, 0, m->s>>>((int*)(m->rec + m->Vcap), 2 * (nc - m->Vcap), -1);
-    H3(hipGetLastError());
-    m->Vcap = nc;
+  Moves mv{};
+  int64_t most = 0;
+  void* old[24];
+  auto grow = [&](auto** p, int64_t n0, int64_t n1, bool keep) -> pm_status {
+    using E = std::remove_reference_t<decltype(**p)>;
+    E* q = nullptr;
+    T3(dgrow(m, &q, 0, n1, false));
+    if (*p && keep && n0 > 0) {
+      old[mv.n] = *p;
+      mv.e[mv.n++] = {*p, q, (int64_t)sizeof(E) * n0};
+      most = std::max(most, (int64_t)sizeof(E) * n0);
+    } else if (*p) {
+      pm::block_free(*p);
+    }
+    *p = q;
+    return PM_OK;
+  };
+  // new vertex slots carry no class stamp or record
+  auto unset = [&](void* from, int64_t bytes) {
+    old[mv.n] = nullptr;
+    mv.e[mv.n++] = {nullptr, from, bytes};
+    most = std::max(most, bytes);
+  };
+  pm_status rc = PM_OK;
+  auto all = [&]() -> pm_status {
+    if (V > m->Vcap) {
+      int64_t c = m->Vcap, nc = std::max(V, m->Vcap + m->Vcap / 2);
+      T3(grow(&st.xyz, c, nc, true));
+      T3(grow(&st.met, c, nc, true));
+      T3(grow(&st.tag, c, nc, true));
+      T3(grow(&st.valive, c, nc, true));
+      // growth happens in the middle of a refinement pass, whose rows, vertex
+      // scan and element scan must survive it: every array keeps its contents
+      T3(grow(&st.hdr, c, nc, true));
+      T3(grow(&m->cnt, c + 1, nc + 1, true));
+      T3(grow(&m->off, c + 1, nc + 1, true));
+      T3(grow(&m->flag, c + 1, nc + 1, true));
+      T3(grow(&m->scan, c + 1, nc + 1, true));
+      T3(grow(&m->A, c, nc, true));
+      T3(grow(&m->B, c, nc, false));
+      T3(grow(&m->cls, c, nc, true));
+      T3(grow(&m->col, c, nc, true));
+      T3(grow(&m->blk, c, nc, true));
+      T3(grow(&m->act, c, nc, true));
+      T3(grow(&m->nxt, c, nc, true));
+      T3(grow(&st.cap, c, nc, true));
+      T3(grow(&m->own, c, nc, true));
+      T3(grow(&m->rec, c, nc, true));
+      T3(grow(&m->rows, c, nc, false));
+      unset(m->own + c, sizeof(int) * (nc - c));
+      unset(m->rec + c, sizeof(int2) * (nc - c));
+      m->Vcap = (int)nc;
+    }
+    if (T > m->Tcap) {
+      int64_t c = m->Tcap, nc = std::max(T, m->Tcap + m->Tcap / 2);
+      T3(grow(&st.tet, c, nc, true));
+      T3(grow(&st.talive, c, nc, true));
+      T3(grow(&m->tcnt, c + 1, nc + 1, true));
+      T3(grow(&m->tscan, c + 1, nc + 1, true));
+      m->Tcap = (int)nc;
+    }
+    return PM_OK;
+  };
+  rc = all();
+  // (also what was grown before an allocation failed)
+  if (mv.n) {
+    k_move<<<dim3(std::min(grid(most / 16 + 1), 2048), mv.n), kB, 0, m->s>>>(mv);
+    hipError_t e = hipGetLastError();
+    for (int k = 0; k < mv.n; ++k)
+      if (old[k]) pm::block_free(old[k]);
+    if (rc == PM_OK) H3(e);
   }
-  if (T > m->Tcap) {
-    int nc = std::max(T, m->Tcap + m->Tcap / 2);
-    T3(dgrow(m, &st.tet, m->Tcap, nc, true));
-    T3(dgrow(m, &st.talive, m->Tcap, nc, true));
-    T3(dgrow(m, &m->tcnt, m->Tcap + 1, nc + 1, true));
-    T3(dgrow(m, &m->tscan, m->Tcap + 1, nc + 1, true));
-    m->Tcap = nc;
-  }
+  T3(rc);
   int need = pm::scan_partials_needed(std::max(m->Vcap, m->Tcap) + 1);
   if (need > m->pcap) {
     T3(dgrow(m, &m->partial, m->pcap, need, false));
@@ -2061,8 +2134,7 @@ pm_status build_rows(pm3_mesh* m) {
   k_rows_finish<<<grid((int64_t)V * kWave), kB, 0, m->s>>>(st, m->off, m->cnt);
   m->top_base = total;
   m->top_per = (m->necap - total) / kTopStripes;
-  k_tops_init<<<1, kTopStripes, 0, m->s>>>(m->tops, m->top_base, m->top_per);
-  k_fill_int<<<1, kB, 0, m->s>>>(m->ctr + K_ROOM, 2, 0);
+  k_tops_init<<<1, kTopStripes, 0, m->s>>>(m->tops, m->top_base, m->top_per, m->ctr);
   H3(hipGetLastError());
   return PM_OK;
 }
@@ -2187,9 +2259,7 @@ pm_status compact(pm3_mesh* m) {
   st.tet = tet;
   st.V = nv;
   st.T = nt;
-  k_fill_u8<<<grid(nv), kB, 0, m->s>>>(st.valive, nv, 1);
-  k_fill_u8<<<grid(nt), kB, 0, m->s>>>(st.talive, nt, 1);
-  k_fill_u8<<<grid(nv), kB, 0, m->s>>>(m->nxt, nv, 0);
+  k_all_live<<<grid(std::max(nv, nt)), kB, 0, m->s>>>(st, m->nxt);
   H3(hipGetLastError());
   return build_rows(m);
 }
