@@ -492,45 +492,61 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
   TRY(ensure(m, m->vt3, V));
   TRY(ensure(m, m->vt4, V));
   TRY(ensure(m, m->partial, scan_partials_needed(std::max(V, st.T)) + 2));
-  zero_ints(m->vt0.p, V, m->s);
-  build_count(st, m->vt0.p, m->s);
-  build_caps(st, m->vt0.p, m->slack, m->vt1.p, m->vt2.p, m->s);
-  // the slot totals are the pools' new bump pointers
-  scan_excl(m->vt1.p, m->vt3.p, V, m->ctr + C_NN_TOP, m->partial.p, m->s);
-  scan_excl(m->vt2.p, m->vt4.p, V, m->ctr + C_NE_TOP, m->partial.p, m->s);
   // room for rows that outgrow their slot before the next rebuild: the
   // headroom (3 by default) times the used entries. Slot capacities are at
   // most c(1+slack) + slack + 7 for a vertex in c elements, and the c sum to
   // 3T, which bounds both totals; when the pools hold the headroom times that
-  // bound they are large enough without a read-back.
+  // bound they are large enough without a read-back. Small pools are simply
+  // sized by it (about twice what the rows need), which saves the read-back too.
   double bound = 3.0 * st.T * (1.0 + m->slack) + (double)V * (m->slack + 7.0);
   double extra = m->headroom >= 3.0 ? 4096.0 : 64.0;
   double room = m->headroom * bound + extra;
-  if (room <= (double)INT32_MAX && (double)st.nn_pool >= room && (double)st.ne_pool >= room) {
-    set_headers(st, m->vt3.p, m->vt4.p, m->vt1.p, m->vt2.p, m->s);
-    build_fill(st, nullptr, m->s);
-    build_finish(st, m->ctr, m->s);
-    return check ? check_err(m) : PM_OK;
-  }
-  // small pools are simply sized by the bound (about twice what the rows need),
-  // which saves the read-back
+  bool fits = room <= (double)INT32_MAX && (double)st.nn_pool >= room && (double)st.ne_pool >= room;
   bool small = m->headroom >= 3.0 && room <= (double)kSmallPool;
-  if (!small) TRY(read_ctr(m, C_NN_TOP, 2));
-  int64_t nn_used = small ? (int64_t)bound : m->hctr[C_NN_TOP], ne_used = small ? (int64_t)bound : m->hctr[C_NE_TOP];
-  int64_t nn_need = (int64_t)(m->headroom * (double)nn_used + extra);
-  int64_t ne_need = (int64_t)(m->headroom * (double)ne_used + extra);
-  if (nn_need > INT32_MAX || ne_need > INT32_MAX) return fail(m, PM_E_NOMEM, "adjacency pool beyond 2^31 entries");
-  if (st.nn_pool < nn_need || st.ne_pool < ne_need) {
-    dfree(m, st.nn, st.nn_pool);
-    dfree(m, st.ne, st.ne_pool);
-    st.nn_pool = st.ne_pool = 0;
-    TRY(dalloc(m, &st.nn, nn_need));
-    TRY(dalloc(m, &st.ne, ne_need));
-    st.nn_pool = nn_need;
-    st.ne_pool = ne_need;
+  int* place = nullptr;
+  auto pools = [&](int64_t nn_used, int64_t ne_used) -> pm_status {
+    int64_t nn_need = (int64_t)(m->headroom * (double)nn_used + extra);
+    int64_t ne_need = (int64_t)(m->headroom * (double)ne_used + extra);
+    if (nn_need > INT32_MAX || ne_need > INT32_MAX)
+      return fail(m, PM_E_NOMEM, "adjacency pool beyond 2^31 entries");
+    if (st.nn_pool < nn_need || st.ne_pool < ne_need) {
+      dfree(m, st.nn, st.nn_pool);
+      dfree(m, st.ne, st.ne_pool);
+      st.nn_pool = st.ne_pool = 0;
+      place = nullptr;
+      TRY(dalloc(m, &st.nn, nn_need));
+      TRY(dalloc(m, &st.ne, ne_need));
+      st.nn_pool = nn_need;
+      st.ne_pool = ne_need;
+    }
+    return PM_OK;
+  };
+  if (!fits && small) TRY(pools((int64_t)bound, (int64_t)bound));
+  // the incidences' places lie in the NN pool, which the row finish writes last
+  int64_t places = 3 * (int64_t)st.T;
+  place = st.nn_pool >= places ? st.nn : nullptr;
+  zero_ints(m->vt0.p, V, m->s);
+  build_count(st, m->vt0.p, place, m->s);
+  build_caps(st, m->vt0.p, m->slack, m->vt1.p, m->vt2.p, m->s);
+  // the slot totals are the pools' new bump pointers
+  scan_excl(m->vt1.p, m->vt3.p, V, m->ctr + C_NN_TOP, m->partial.p, m->s);
+  scan_excl(m->vt2.p, m->vt4.p, V, m->ctr + C_NE_TOP, m->partial.p, m->s);
+  if (!fits && !small) {
+    TRY(read_ctr(m, C_NN_TOP, 2));
+    TRY(pools(m->hctr[C_NN_TOP], m->hctr[C_NE_TOP]));
   }
-  set_headers(st, m->vt3.p, m->vt4.p, m->vt1.p, m->vt2.p, m->s);
-  build_fill(st, nullptr, m->s);
+  // (the pool was not there yet, was replaced, or is short of a place for every
+  // element slot: counted again)
+  int* own = nullptr;
+  if (!place) {
+    if (st.nn_pool < places) TRY(dalloc(m, &own, places));
+    place = own ? own : st.nn;
+    zero_ints(m->vt0.p, V, m->s);
+    build_count(st, m->vt0.p, place, m->s);
+  }
+  set_headers(st, m->vt3.p, m->vt4.p, m->vt1.p, m->vt2.p, m->vt0.p, m->s);
+  build_fill(st, place, m->s);
+  dfree(m, own, places);
   build_finish(st, m->ctr, m->s);
   return check ? check_err(m) : PM_OK;
 }

@@ -180,11 +180,12 @@ void tags_from_xy(const double2* xy, int V, uint8_t* tag, hipStream_t s);
 void k_validate(const Store& st, int* ctr, hipStream_t s);
 
 // rows from the element list
-void build_count(const Store& st, int* ne_cnt, hipStream_t s);
+// (place: 3 ints an element slot, or null when the places are not wanted)
+void build_count(const Store& st, int* ne_cnt, int* place, hipStream_t s);
 void build_caps(const Store& st, const int* ne_cnt, double slack, int* nn_cap, int* ne_cap, hipStream_t s);
 void set_headers(const Store& st, const int* nn_off, const int* ne_off, const int* nn_cap, const int* ne_cap,
-                 hipStream_t s);
-void build_fill(const Store& st, int* unused, hipStream_t s);
+                 const int* ne_cnt, hipStream_t s);
+void build_fill(const Store& st, const int* place, hipStream_t s);
 void build_finish(const Store& st, int* ctr, hipStream_t s);
 
 // compaction

@@ -169,21 +169,28 @@ void k_validate(const Store& st, int* ctr, hipStream_t s) {
 }
 
 // ---- row build ----------------------------------------------------------------------
-// Element-to-vertex incidence counts and fills. A block takes a contiguous
-// chunk of kIncChunk elements; when the chunk's vertices span at most
-// kIncSpan ids (meshes numbered with locality), it counts in LDS and makes
-// one global atomic per vertex it touches instead of one per incidence.
+// Element-to-vertex incidence counts, and the place of each incidence in its
+// vertex's NE row (rows are sorted by the row finish, so any order does). A block
+// takes a contiguous chunk of kIncChunk elements; when the chunk's vertices span
+// at most kIncSpan ids (meshes numbered with locality), it counts in LDS, where an
+// incidence takes its rank among the chunk's, and makes one global atomic per
+// vertex it touches instead of one per incidence, which reserves the chunk's
+// places. The places go to the fill, which needs no atomics and no chunks:
+// reserving again there, beside loads of the same headers, took @F0@ us of the
+// @F1@ of counting and filling on the 201^2 planar-front mesh; both now take @F2@.
 constexpr int kIncPer = 4;
 constexpr int kIncChunk = kBlock * kIncPer;
 constexpr int kIncSpan = 4096;
-__device__ __forceinline__ void chunk_span(const Elem* __restrict__ tri, int t0, int t1, int& vmin, int& vmax,
-                                           int* red) {
+struct Place3 {
+  int x, y, z;
+};
+__device__ __forceinline__ void chunk_span(const Elem (&e)[kIncPer], int& vmin, int& vmax, int* red) {
   int lo = INT_MAX, hi = -1;
-  for (int t = t0 + (int)threadIdx.x; t < t1; t += kBlock) {
-    Elem e = tri[t];
-    if (!e.w) continue;
-    lo = min(lo, min(e.x, min(e.y, e.z)));
-    hi = max(hi, max(e.x, max(e.y, e.z)));
+#pragma unroll
+  for (int r = 0; r < kIncPer; ++r) {
+    if (!e[r].w) continue;
+    lo = min(lo, min(e[r].x, min(e[r].y, e[r].z)));
+    hi = max(hi, max(e[r].x, max(e[r].y, e[r].z)));
   }
 #pragma unroll
   for (int d = kWave / 2; d > 0; d >>= 1) {
@@ -206,41 +213,64 @@ __device__ __forceinline__ void chunk_span(const Elem* __restrict__ tri, int t0,
   __syncthreads();
 }
 
-__global__ void __launch_bounds__(256) k_ne_count(const Elem* __restrict__ tri, int T, int* __restrict__ cnt) {
+__global__ void __launch_bounds__(256) k_ne_count(const Elem* __restrict__ tri, int T, int* __restrict__ cnt,
+                                                 Place3* __restrict__ place) {
   __shared__ int loc[kIncSpan];
   __shared__ int red[2 * kBlock / kWave];
-  int t0 = blockIdx.x * kIncChunk, t1 = min(T, t0 + kIncChunk);
+  int t0 = blockIdx.x * kIncChunk + (int)threadIdx.x;
+  Elem e[kIncPer];
+#pragma unroll
+  for (int r = 0; r < kIncPer; ++r) e[r] = t0 + r * kBlock < T ? tri[t0 + r * kBlock] : make_int4(0, 0, 0, 0);
   int vmin, vmax;
-  chunk_span(tri, t0, t1, vmin, vmax, red);
+  chunk_span(e, vmin, vmax, red);
   if (vmax < 0) return;
   int span = vmax - vmin + 1;
   if (span > kIncSpan) {
-    for (int t = t0 + (int)threadIdx.x; t < t1; t += kBlock) {
-      Elem e = tri[t];
-      if (!e.w) continue;
-      atomicAdd(&cnt[e.x], 1);
-      atomicAdd(&cnt[e.y], 1);
-      atomicAdd(&cnt[e.z], 1);
-    }
+    Place3 k[kIncPer];
+#pragma unroll
+    for (int r = 0; r < kIncPer; ++r)
+      if (e[r].w) k[r] = Place3{atomicAdd(&cnt[e[r].x], 1), atomicAdd(&cnt[e[r].y], 1), atomicAdd(&cnt[e[r].z], 1)};
+#pragma unroll
+    for (int r = 0; r < kIncPer; ++r)
+      if (e[r].w && place) place[t0 + r * kBlock] = k[r];
     return;
   }
   for (int i = (int)threadIdx.x; i < span; i += kBlock) loc[i] = 0;
   __syncthreads();
-  for (int t = t0 + (int)threadIdx.x; t < t1; t += kBlock) {
-    Elem e = tri[t];
-    if (!e.w) continue;
-    atomicAdd(&loc[e.x - vmin], 1);
-    atomicAdd(&loc[e.y - vmin], 1);
-    atomicAdd(&loc[e.z - vmin], 1);
-  }
+  Place3 k[kIncPer];
+#pragma unroll
+  for (int r = 0; r < kIncPer; ++r)
+    if (e[r].w)
+      k[r] = Place3{atomicAdd(&loc[e[r].x - vmin], 1), atomicAdd(&loc[e[r].y - vmin], 1),
+                    atomicAdd(&loc[e[r].z - vmin], 1)};
   __syncthreads();
-  for (int i = (int)threadIdx.x; i < span; i += kBlock)
-    if (loc[i]) atomicAdd(&cnt[vmin + i], loc[i]);
+  // loc[i] becomes the chunk's first place in row vmin + i; a thread's
+  // reservations are all in flight before it uses one
+  constexpr int R = kIncSpan / kBlock;
+  int at[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    int i = q * kBlock + (int)threadIdx.x;
+    int c = i < span ? loc[i] : 0;
+    at[q] = c ? atomicAdd(&cnt[vmin + i], c) : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    int i = q * kBlock + (int)threadIdx.x;
+    if (i < span) loc[i] = at[q];
+  }
+  if (!place) return;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kIncPer; ++r)
+    if (e[r].w)
+      place[t0 + r * kBlock] =
+          Place3{loc[e[r].x - vmin] + k[r].x, loc[e[r].y - vmin] + k[r].y, loc[e[r].z - vmin] + k[r].z};
 }
 
-void build_count(const Store& st, int* ne_cnt, hipStream_t s) {
+void build_count(const Store& st, int* ne_cnt, int* place, hipStream_t s) {
   int nb = (st.T + kIncChunk - 1) / kIncChunk;
-  if (nb > 0) k_ne_count<<<nb, kBlock, 0, s>>>(st.tri, st.T, ne_cnt);
+  if (nb > 0) k_ne_count<<<nb, kBlock, 0, s>>>(st.tri, st.T, ne_cnt, (Place3*)place);
 }
 
 __device__ __forceinline__ int round4(int x) { return (x + 3) & ~3; }
@@ -267,99 +297,32 @@ void build_caps(const Store& st, const int* ne_cnt, double slack, int* nn_cap, i
 
 __global__ void k_set_headers(Hdr* __restrict__ hdr, int2* __restrict__ cap, int V, const int* __restrict__ nn_off,
                               const int* __restrict__ ne_off, const int* __restrict__ nn_cap,
-                              const int* __restrict__ ne_cap) {
+                              const int* __restrict__ ne_cap, const int* __restrict__ ne_cnt) {
   for (int v = gtid(); v < V; v += gstride()) {
-    hdr[v] = make_int4(nn_off[v], 0, ne_off[v], 0);
+    hdr[v] = make_int4(nn_off[v], 0, ne_off[v], ne_cnt[v]);
     cap[v] = make_int2(nn_cap[v], ne_cap[v]);
   }
 }
 
 void set_headers(const Store& st, const int* nn_off, const int* ne_off, const int* nn_cap, const int* ne_cap,
-                 hipStream_t s) {
-  k_set_headers<<<grid_for(st.V), kBlock, 0, s>>>(st.hdr, st.cap, st.V, nn_off, ne_off, nn_cap, ne_cap);
+                 const int* ne_cnt, hipStream_t s) {
+  k_set_headers<<<grid_for(st.V), kBlock, 0, s>>>(st.hdr, st.cap, st.V, nn_off, ne_off, nn_cap, ne_cap, ne_cnt);
 }
 
-// Fill: each incidence takes a slot of its vertex's NE row (rows are sorted
-// by the row finish, so the order of filling does not matter). In the LDS
-// path an incidence takes its rank among the chunk's incidences of that
-// vertex, and one global atomic per vertex reserves the chunk's slots.
-__global__ void __launch_bounds__(256) k_ne_fill(const Elem* __restrict__ tri, int T, Hdr* hdr, int* __restrict__ ne) {
-  __shared__ int loc[kIncSpan];
-  __shared__ int red[2 * kBlock / kWave];
-  int t0 = blockIdx.x * kIncChunk, t1 = min(T, t0 + kIncChunk);
-  int vmin, vmax;
-  chunk_span(tri, t0, t1, vmin, vmax, red);
-  if (vmax < 0) return;
-  int span = vmax - vmin + 1;
-  if (span > kIncSpan) {
-    for (int t = t0 + (int)threadIdx.x; t < t1; t += kBlock) {
-      Elem e = tri[t];
-      if (!e.w) continue;
-      int vs[3] = {e.x, e.y, e.z};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        int* c = reinterpret_cast<int*>(&hdr[vs[k]]) + 3;
-        int pos = atomicAdd(c, 1);
-        ne[hdr[vs[k]].z + pos] = t;
-      }
-    }
-    return;
-  }
-  for (int i = (int)threadIdx.x; i < span; i += kBlock) loc[i] = 0;
-  __syncthreads();
-  int rank[kIncPer][3];
-#pragma unroll
-  for (int r = 0; r < kIncPer; ++r) {
-    int t = t0 + r * kBlock + (int)threadIdx.x;
-    Elem e = t < t1 ? tri[t] : make_int4(0, 0, 0, 0);
-    rank[r][0] = rank[r][1] = rank[r][2] = -1;
-    if (t < t1 && e.w) {
-      rank[r][0] = atomicAdd(&loc[e.x - vmin], 1);
-      rank[r][1] = atomicAdd(&loc[e.y - vmin], 1);
-      rank[r][2] = atomicAdd(&loc[e.z - vmin], 1);
-    }
-  }
-  __syncthreads();
-  // reserve the chunk's slots: loc[i] becomes the first slot of the chunk in
-  // row vmin + i; a thread's reservations are all in flight before it uses one
-  constexpr int R = kIncSpan / kBlock;
-  int cnt[R], at[R], z[R];
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    int i = q * kBlock + (int)threadIdx.x;
-    cnt[q] = i < span ? loc[i] : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    int i = q * kBlock + (int)threadIdx.x;
-    z[q] = cnt[q] ? hdr[vmin + i].z : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    int i = q * kBlock + (int)threadIdx.x;
-    at[q] = cnt[q] ? atomicAdd(reinterpret_cast<int*>(&hdr[vmin + i]) + 3, cnt[q]) : 0;
-  }
-#pragma unroll
-  for (int q = 0; q < R; ++q) {
-    int i = q * kBlock + (int)threadIdx.x;
-    if (cnt[q]) loc[i] = z[q] + at[q];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kIncPer; ++r) {
-    int t = t0 + r * kBlock + (int)threadIdx.x;
-    if (rank[r][0] < 0) continue;
+__global__ void __launch_bounds__(256) k_ne_fill(const Elem* __restrict__ tri, int T, const Hdr* __restrict__ hdr,
+                                                const Place3* __restrict__ place, int* __restrict__ ne) {
+  for (int t = gtid(); t < T; t += gstride()) {
     Elem e = tri[t];
-    ne[loc[e.x - vmin] + rank[r][0]] = t;
-    ne[loc[e.y - vmin] + rank[r][1]] = t;
-    ne[loc[e.z - vmin] + rank[r][2]] = t;
+    if (!e.w) continue;
+    Place3 k = place[t];
+    ne[hdr[e.x].z + k.x] = t;
+    ne[hdr[e.y].z + k.y] = t;
+    ne[hdr[e.z].z + k.z] = t;
   }
 }
 
-void build_fill(const Store& st, int* fill, hipStream_t s) {
-  (void)fill;
-  int nb = (st.T + kIncChunk - 1) / kIncChunk;
-  if (nb > 0) k_ne_fill<<<nb, kBlock, 0, s>>>(st.tri, st.T, st.hdr, st.ne);
+void build_fill(const Store& st, const int* place, hipStream_t s) {
+  if (st.T > 0) k_ne_fill<<<grid_for(st.T), kBlock, 0, s>>>(st.tri, st.T, st.hdr, (const Place3*)place, st.ne);
 }
 
 __device__ void isort(int* a, int n) {
