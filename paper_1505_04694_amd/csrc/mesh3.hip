@@ -282,17 +282,64 @@ __global__ void k_orient(Store3 st, int* ctr) {
 
 // ---- rows from the element list ----------------------------------------------------------
 
-// how many elements a vertex has; an element's place among its vertices' ones is
-// what the adds return, so that the filling needs none (on
-// average over the builds of the 29^3 planar-front adaptation, up to 3.4 million
-// elements: count 182 and fill 206 us with adds in both, now 197 and 31)
+// how many elements a vertex has, and every element's places in its vertices' rows
+// (in any order: the rows are sorted afterwards), for the filling. A work-group
+// counts its elements' vertices in a hash table in LDS and reserves their places
+// with one add per vertex: the rate of global atomics bounds this. With one per
+// incidence, on average over the builds of the 29^3 planar-front adaptation (up to
+// 3.4 million elements), it took 197 us and takes 58; the filling took 206 us
+// with adds of its own and takes 31.
+constexpr int kCountPer = 2, kCountSlots = 4096;
 __global__ void __launch_bounds__(256) k_ne_count(Store3 st, int* cnt, int4* __restrict__ rank) {
-  for (int t = gtid(); t < st.T; t += gstride()) {
-    if (!st.talive[t]) continue;
-    int4 e = st.tet[t];
-    rank[t] = make_int4(atomicAdd(&cnt[e.x], 1), atomicAdd(&cnt[e.y], 1), atomicAdd(&cnt[e.z], 1),
-                        atomicAdd(&cnt[e.w], 1));
+  __shared__ __align__(16) int key[kCountSlots], num[kCountSlots];
+  int tid = (int)threadIdx.x, t0 = (int)blockIdx.x * kB * kCountPer + tid;
+  for (int i = tid; i < kCountSlots / 4; i += kB) {
+    ((int4*)key)[i] = make_int4(-1, -1, -1, -1);
+    ((int4*)num)[i] = make_int4(0, 0, 0, 0);
   }
+  int4 e[kCountPer];
+  bool on[kCountPer];
+#pragma unroll
+  for (int r = 0; r < kCountPer; ++r) {
+    int t = min(t0 + r * kB, st.T - 1);
+    on[r] = t0 + r * kB < st.T && st.talive[t];
+    e[r] = st.tet[t];
+  }
+  __syncthreads();
+  // (at most 4 kB kCountPer = half the table)
+  int at[kCountPer][4], k[kCountPer][4];
+#pragma unroll
+  for (int r = 0; r < kCountPer; ++r) {
+    if (!on[r]) continue;
+    int v[4] = {e[r].x, e[r].y, e[r].z, e[r].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      int a = (int)(((uint32_t)v[q] * 2654435761u) >> 20);
+      for (;;) {
+        int old = atomicCAS(&key[a], -1, v[q]);
+        if (old == -1 || old == v[q]) break;
+        a = (a + 1) & (kCountSlots - 1);
+      }
+      at[r][q] = a;
+      k[r][q] = atomicAdd(&num[a], 1);
+    }
+  }
+  __syncthreads();
+  constexpr int R = kCountSlots / kB;
+  int base[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    int c = num[q * kB + tid];
+    base[q] = c ? atomicAdd(&cnt[key[q * kB + tid]], c) : 0;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) num[q * kB + tid] = base[q];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kCountPer; ++r)
+    if (on[r])
+      rank[t0 + r * kB] =
+          make_int4(num[at[r][0]] + k[r][0], num[at[r][1]] + k[r][1], num[at[r][2]] + k[r][2], num[at[r][3]] + k[r][3]);
 }
 __global__ void __launch_bounds__(256) k_ne_fill(Store3 st, const int* __restrict__ off, const int4* __restrict__ rank) {
   for (int t = gtid(); t < st.T; t += gstride()) {
@@ -2110,7 +2157,7 @@ pm_status build_rows(pm3_mesh* m) {
   k_fill_int<<<grid(V + 1), kB, 0, m->s>>>(m->cnt, V + 1, 0);
   int4* rank = nullptr;
   T3(dgrow(m, &rank, 0, st.T, false));
-  k_ne_count<<<grid(st.T), kB, 0, m->s>>>(st, m->cnt, rank);
+  k_ne_count<<<(st.T + kB * kCountPer - 1) / (kB * kCountPer), kB, 0, m->s>>>(st, m->cnt, rank);
   int total = 0;
   T3(scan_total(m, m->cnt, m->off, V, &total));
   int64_t want = total + (int64_t)(m->headroom * (double)total) + kTopStripes * 64;
