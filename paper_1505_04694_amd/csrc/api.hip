@@ -65,11 +65,11 @@ struct pm_mesh {
   Mail mail;             // the pinned block's
   hipEvent_t up_ev = nullptr;  // the last staged upload's copy
   // scratch
-  DBuf<int> listA, listB, jpU0, jpU1, cls, vt0, vt1, vt2, vt3, vt4, tt0, tt1, tt2, partial, mid;
+  DBuf<int> listA, listB, jpU0, jpU1, cls, vt0, vt1, vt2, tt0, tt1, tt2, partial, mid;
   DBuf<uint8_t> nxt, u8tmp;
   DBuf<Met> emet;   // smoothing: per-element mean tensors
   DBuf<VRec> vr;    // coarsening and swapping: vertex records
-  DBuf<int> sflag, spos, ctab, ctabs, spart;  // ordered selection and stable class lists
+  DBuf<int> sflag, ctab, ctabs, spart;  // ordered selection and stable class lists
   DBuf<int> stage;       // commit: fallback staging
   DBuf<int> touch, seen; // small rounds: rows rebuilt, selection stamps
   DBuf<int> jpB;         // JP: the neighbour each waiting vertex waits for
@@ -487,11 +487,7 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
   Store& st = m->st;
   int V = st.V;
   TRY(ensure(m, m->vt0, V));
-  TRY(ensure(m, m->vt1, V));
-  TRY(ensure(m, m->vt2, V));
-  TRY(ensure(m, m->vt3, V));
-  TRY(ensure(m, m->vt4, V));
-  TRY(ensure(m, m->partial, scan_partials_needed(std::max(V, st.T)) + 2));
+  TRY(ensure(m, m->partial, scan_partials_needed(V)));
   // room for rows that outgrow their slot before the next rebuild: the
   // headroom (3 by default) times the used entries. Slot capacities are at
   // most c(1+slack) + slack + 7 for a vertex in c elements, and the c sum to
@@ -527,10 +523,7 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
   place = st.nn_pool >= places ? st.nn : nullptr;
   zero_ints(m->vt0.p, V, m->s);
   build_count(st, m->vt0.p, place, m->s);
-  build_caps(st, m->vt0.p, m->slack, m->vt1.p, m->vt2.p, m->s);
-  // the slot totals are the pools' new bump pointers
-  scan_excl(m->vt1.p, m->vt3.p, V, m->ctr + C_NN_TOP, m->partial.p, m->s);
-  scan_excl(m->vt2.p, m->vt4.p, V, m->ctr + C_NE_TOP, m->partial.p, m->s);
+  build_headers(st, m->vt0.p, m->slack, m->ctr, (int2*)m->partial.p, m->s);
   if (!fits && !small) {
     TRY(read_ctr(m, C_NN_TOP, 2));
     TRY(pools(m->hctr[C_NN_TOP], m->hctr[C_NE_TOP]));
@@ -544,7 +537,6 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
     zero_ints(m->vt0.p, V, m->s);
     build_count(st, m->vt0.p, place, m->s);
   }
-  set_headers(st, m->vt3.p, m->vt4.p, m->vt1.p, m->vt2.p, m->vt0.p, m->s);
   build_fill(st, place, m->s);
   dfree(m, own, places);
   build_finish(st, m->ctr, m->s);
@@ -583,7 +575,6 @@ pm_status ensure_phase_scratch(pm_mesh* m) {
   TRY(ensure(m, m->cnt, V, true));
   TRY(ensure(m, m->tgt, V, true));
   TRY(ensure(m, m->sflag, V));
-  TRY(ensure(m, m->spos, V));
   TRY(ensure(m, m->spart, scan_partials_needed(V) + 2));
   // staging for the rows past the wavefront path (more than 64 candidates):
   // 4 ids per candidate; a round that runs out is redone from a row rebuild
@@ -765,11 +756,8 @@ pm_status compact(pm_mesh* m, const std::vector<int>* extra_v = nullptr, const s
   TRY(ensure(m, m->tt1, T));
   TRY(ensure(m, m->tt2, T));
   TRY(ensure(m, m->rtmp, 4 * (size_t)B + 4));
-  TRY(ensure(m, m->partial, scan_partials_needed(std::max(V, T)) + 2));
-  flag_live_vertices(st, m->vt0.p, m->s);
-  scan_excl(m->vt0.p, m->vt1.p, V, m->ctr + C_TOTAL, m->partial.p, m->s);
-  flag_live_elements(st, m->tt0.p, m->s);
-  scan_excl(m->tt0.p, m->tt1.p, T, m->ctr + C_TOTAL2, m->partial.p, m->s);
+  TRY(ensure(m, m->partial, scan_partials_needed(V) + scan_partials_needed(T)));
+  scan_live(st, m->vt0.p, m->vt1.p, m->ctr + C_TOTAL, m->tt0.p, m->tt1.p, m->ctr + C_TOTAL2, m->partial.p, m->s);
   if (B == 1) return compact_one(m);
   range_sums(m->vt1.p, m->vt0.p, st.vbase, st.vused, B, m->rtmp.p, m->s);
   range_sums(m->tt1.p, m->tt0.p, st.tbase, st.tused, B, m->rtmp.p + B, m->s);
@@ -1065,8 +1053,7 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
   double qmin2 = o->q_min * o->q_min;
   stats_zero(m);
   timed(m, PM_K_SELECT, m->st.V,
-        [&] { select_vertices(m->st, mode, o->L_low2, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p,
-                          m->spos.p, m->spart.p, m->s); });
+        [&] { select_vertices(m->st, mode, o->L_low2, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spart.p, m->s); });
   TRY(read_ctr(m, 0, kRoundCtrs));  // pool tops, error bits and the list length at once
   TRY(check_err(m, true));
   int nA = m->hctr[C_LIST_B];
@@ -1126,8 +1113,7 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
         TRY(recover_round(m, kind, dc, dep, rdd, o, n_rr));
       }
       timed(m, PM_K_SELECT, m->st.V, [&] {
-        select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spos.p,
-                        m->spart.p, m->s);
+        select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spart.p, m->s);
       });
       TRY(read_ctr(m, 0, kRoundCtrs));
       TRY(check_err(m, true));
@@ -1180,8 +1166,7 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
     }
     auto select_all = [&]() -> pm_status {
       timed(m, PM_K_SELECT, m->st.V, [&] {
-        select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spos.p,
-                        m->spart.p, m->s);
+        select_vertices(m->st, mode, o->L_low2, nullptr, m->nxt.p, m->listB.p, m->ctr, m->sflag.p, m->spart.p, m->s);
       });
       return read_ctr(m, 0, kRoundCtrs);
     };
@@ -1362,10 +1347,9 @@ pm_status pm_mesh_destroy(pm_mesh* m) {
   dfree(m, s.tmesh, s.Tcap);
   dfree(m, m->ranges, 1);
   dfree(m, m->mdone, 1);
-  DBuf<int>* ib[] = {&m->listA, &m->listB, &m->jpU0, &m->jpU1, &m->cls, &m->vt0, &m->vt1, &m->vt2, &m->vt3,
-                     &m->vt4, &m->tt0, &m->tt1, &m->tt2, &m->partial, &m->mid, &m->stage, &m->touch, &m->seen, &m->jpB, &m->rtmp,
-                     &m->sflag, &m->spos,
-                     &m->ctab, &m->ctabs, &m->spart};
+  DBuf<int>* ib[] = {&m->listA, &m->listB, &m->jpU0, &m->jpU1, &m->cls, &m->vt0, &m->vt1, &m->vt2,
+                     &m->tt0, &m->tt1, &m->tt2, &m->partial, &m->mid, &m->stage, &m->touch, &m->seen, &m->jpB, &m->rtmp,
+                     &m->sflag, &m->ctab, &m->ctabs, &m->spart};
   for (auto* b : ib) dfree(m, b->p, b->n);
   DBuf<uint8_t>* ub[] = {&m->nxt, &m->u8tmp};
   dfree(m, m->emet.p, m->emet.n);
@@ -1547,7 +1531,7 @@ pm_status pm_colour(pm_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* co
                           mem_kind == PM_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice, m->s));
     act_in = m->u8tmp.p;
   }
-  select_vertices(st, 0, 0.0, act_in, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spos.p, m->spart.p,
+  select_vertices(st, 0, 0.0, act_in, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spart.p,
                   m->s);
   TRY(read_ctr(m, C_LIST_B, 1));
   int n = m->hctr[C_LIST_B];
@@ -1596,8 +1580,7 @@ pm_status pm_smooth(pm_mesh* m, const pm_options* o, pm_stats* st) {
   TRY(ensure_phase_scratch(m));
   m->tune = o->tune;
   stats_zero(m);
-  select_vertices(m->st, 3, 0.0, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spos.p,
-                  m->spart.p, m->s);
+  select_vertices(m->st, 3, 0.0, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spart.p, m->s);
   TRY(read_ctr(m, C_LIST_B, 1));
   int n = m->hctr[C_LIST_B];
   Classes cl;
@@ -1674,12 +1657,10 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
     TRY(ensure(m, m->tt0, T0));
     TRY(ensure(m, m->tt1, T0));
     TRY(ensure(m, m->rtmp, 4 * (size_t)B + 4));
-    TRY(ensure(m, m->partial, scan_partials_needed(std::max(V0, T0)) + 2));
+    TRY(ensure(m, m->partial, scan_partials_needed(V0) + scan_partials_needed(T0)));
     stripe_zero(m->ctr, S_EDGES, 1, m->s);
-    refine_mark(s, o->L_up2, m->vt0.p, m->ctr, m->s);
-    scan_excl(m->vt0.p, m->vt1.p, V0, m->ctr + C_TOTAL, m->partial.p, m->s);
-    refine_count(s, o->L_up2, m->tt0.p, m->s);
-    scan_excl(m->tt0.p, m->tt1.p, T0, m->ctr + C_TOTAL2, m->partial.p, m->s);
+    refine_scan(s, o->L_up2, m->vt0.p, m->vt1.p, m->ctr + C_TOTAL, m->tt0.p, m->tt1.p, m->ctr + C_TOTAL2, m->ctr,
+                m->partial.p, m->s);
     std::vector<int> need(2 * B);
     bool aux = 2 * B <= kAuxInts;
     if (B > 1) {

@@ -182,24 +182,22 @@ void k_validate(const Store& st, int* ctr, hipStream_t s);
 // rows from the element list
 // (place: 3 ints an element slot, or null when the places are not wanted)
 void build_count(const Store& st, int* ne_cnt, int* place, hipStream_t s);
-void build_caps(const Store& st, const int* ne_cnt, double slack, int* nn_cap, int* ne_cap, hipStream_t s);
-void set_headers(const Store& st, const int* nn_off, const int* ne_off, const int* nn_cap, const int* ne_cap,
-                 const int* ne_cnt, hipStream_t s);
+void build_headers(const Store& st, const int* ne_cnt, double slack, int* ctr, int2* partial, hipStream_t s);
 void build_fill(const Store& st, const int* place, hipStream_t s);
 void build_finish(const Store& st, int* ctr, hipStream_t s);
 
 // compaction
-void flag_live_vertices(const Store& st, int* flag, hipStream_t s);
-void flag_live_elements(const Store& st, int* flag, hipStream_t s);
+void scan_live(const Store& st, int* vflag, int* vpos, int* vtotal, int* tflag, int* tpos, int* ttotal, int* partial,
+               hipStream_t s);
 void compact_vertices(const Store& st, const int* vmap, double2* xy2, Met* met2, uint8_t* tag2, uint8_t* va2,
                       hipStream_t s);
 void compact_elements(const Store& st, const int* vmap, const int* tmap, Elem* tri2, hipStream_t s);
 
 // refinement
-void refine_mark(const Store& st, double L_up2, int* cnt, int* ctr, hipStream_t s);
+void refine_scan(const Store& store, double L_up2, int* vcnt, int* vscan, int* vtotal, int* ecnt, int* escan,
+                 int* etotal, int* ctr, int* partial, hipStream_t s);
 // new ids inside each mesh's range: base + used + (scan - scan at the range start)
 void refine_mint(const Store& st, double L_up2, const int* vscan, int* mid, hipStream_t s);
-void refine_count(const Store& st, double L_up2, int* ecnt, hipStream_t s);
 void refine_split(const Store& st, double L_up2, const int* mid, const int* escan, hipStream_t s);
 
 // per-mesh sums of a 0/1 (or count) array over the used slots, from its exclusive scan
@@ -276,7 +274,7 @@ void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s)
 // selected vertices in ascending order, their count to ctr[C_LIST_B];
 // flag/pos: V ints, partial: scan scratch
 void select_vertices(const Store& st, int mode, double L_low2, const uint8_t* active, uint8_t* nxt, int* out,
-                     int* ctr, int* flag, int* pos, int* partial, hipStream_t s);
+                     int* ctr, int* flag, int* partial, hipStream_t s);
 // (also clears the counts of waiting vertices)
 void jp_init(const Store& st, const int* A, int n, Round rd, int* ctr, hipStream_t s);
 // round words of the n vertices of the class lists cls (class c starts at

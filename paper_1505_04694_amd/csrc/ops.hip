@@ -13,6 +13,7 @@
 #include <atomic>
 
 #include "kern.hpp"
+#include "scan.hpp"
 
 namespace pm {
 
@@ -64,34 +65,31 @@ __device__ __forceinline__ bool want(const Store& st, int v, int mode, double L_
   }
 }
 
-// flag[v] = 1 for every vertex v with (nxt == null or nxt[v]) and want(v); clears nxt.
+// Every vertex v with (nxt == null or nxt[v]) and want(v); clears nxt.
 // After a commit that ran out of room (the rows are being rebuilt) it selects
 // nothing and leaves the flags for the selection that follows the rebuild.
-__global__ void k_select_flags(Store st, int mode, double L_low2, const uint8_t* __restrict__ active,
-                               uint8_t* __restrict__ nxt, int* __restrict__ flag, const int* ctr) {
-  if (nxt && room_failed(ctr)) {
-    for (int v = xtid(); v < st.V; v += gstride()) flag[v] = 0;
-    return;
-  }
-  for (int v = xtid(); v < st.V; v += gstride()) {
-    bool on = nxt ? nxt[v] != 0 : true;
-    if (nxt && on) nxt[v] = 0;
-    flag[v] = (on && want(st, v, mode, L_low2, active)) ? 1 : 0;
-  }
-}
-__global__ void k_select_scatter(int V, const int* __restrict__ flag, const int* __restrict__ pos,
-                                 int* __restrict__ out) {
-  for (int v = gtid(); v < V; v += gstride())
-    if (flag[v]) out[pos[v]] = v;
-}
-// the selected vertices in ascending id order (an ordered compaction), so
-// that lists and the colour classes cut from them follow the mesh's layout
-void select_vertices(const Store& st, int mode, double L_low2, const uint8_t* active, uint8_t* nxt, int* out,
-                     int* ctr, int* flag, int* pos, int* partial, hipStream_t s) {
-  int* n = ctr + C_LIST_B;
-  k_select_flags<<<grid_for(st.V), kBlock, 0, s>>>(st, mode, L_low2, active, nxt, flag, ctr);
-  scan_excl(flag, pos, st.V, n, partial, s);
-  k_select_scatter<<<grid_for(st.V), kBlock, 0, s>>>(st.V, flag, pos, out);
+// The selected vertices in ascending id order (an ordered compaction), so that
+// lists and the colour classes cut from them follow the mesh's layout.
+void select_vertices(const Store& store, int mode, double L_low2, const uint8_t* active, uint8_t* nxt, int* out,
+                     int* ctr, int* flag, int* partial, hipStream_t s) {
+  Store st = store;
+  scan_fused<int, 1>(
+      [=] __device__(int v, bool on) {
+        if (!on) return 0;
+        int f = 0;
+        if (!nxt || !room_failed(ctr)) {
+          bool sel = nxt ? nxt[v] != 0 : true;
+          if (nxt && sel) nxt[v] = 0;
+          f = sel && want(st, v, mode, L_low2, active) ? 1 : 0;
+        }
+        flag[v] = f;
+        return f;
+      },
+      [=] __device__(int v) { return flag[v]; },
+      [=] __device__(int v, int at, int f) {
+        if (f) out[at] = v;
+      },
+      [=] __device__(int t) { ctr[C_LIST_B] = t; }, st.V, partial, s);
 }
 
 // ---- Jones-Plassmann colouring (Sec. 3.2) ------------------------------------------------

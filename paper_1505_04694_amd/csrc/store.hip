@@ -8,95 +8,13 @@
 #include <algorithm>
 
 #include "kern.hpp"
+#include "scan.hpp"
 
 namespace pm {
 
 // ---- ordered exclusive scan --------------------------------------------------------
-constexpr int SCAN_T = 256;
-constexpr int SCAN_I = 8;
-constexpr int SCAN_B = SCAN_T * SCAN_I;
-
-// exclusive scan over the block; returns the thread's prefix, sets *tot
-__device__ int block_excl(int v, int* lds, int* tot) {
-  int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-  int nw = blockDim.x / kWave;
-  int incl = v;
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int o = __shfl_up(incl, d);
-    if (lane >= d) incl += o;
-  }
-  if (lane == kWave - 1) lds[wid] = incl;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int w = 0; w < nw; ++w) {
-      int t = lds[w];
-      lds[w] = acc;
-      acc += t;
-    }
-    lds[nw] = acc;
-  }
-  __syncthreads();
-  int r = lds[wid] + incl - v;
-  *tot = lds[nw];
-  __syncthreads();
-  return r;
-}
-
-__global__ void k_scan_reduce(const int* __restrict__ in, int n, int* __restrict__ partial) {
-  __shared__ int lds[SCAN_T / kWave + 1];
-  int64_t base = (int64_t)blockIdx.x * SCAN_B;
-  int s = 0;
-  for (int i = threadIdx.x; i < SCAN_B; i += SCAN_T) {
-    int64_t j = base + i;
-    if (j < n) s += in[j];
-  }
-  int tot;
-  block_excl(s, lds, &tot);
-  if (threadIdx.x == 0) partial[blockIdx.x] = tot;
-}
-
-__global__ void k_scan_partials(int* __restrict__ partial, int nb, int* __restrict__ total) {
-  __shared__ int lds[1024 / kWave + 1];
-  int per = (nb + blockDim.x - 1) / blockDim.x;
-  int lo = threadIdx.x * per;
-  int hi = min(nb, lo + per);
-  int s = 0;
-  for (int i = lo; i < hi; ++i) s += partial[i];
-  int tot;
-  int acc = block_excl(s, lds, &tot);
-  for (int i = lo; i < hi; ++i) {
-    int t = partial[i];
-    partial[i] = acc;
-    acc += t;
-  }
-  if (threadIdx.x == 0) *total = tot;
-}
-
-__global__ void k_scan_apply(const int* __restrict__ in, int* __restrict__ out, int n,
-                             const int* __restrict__ partial) {
-  __shared__ int lds[SCAN_T / kWave + 1];
-  int64_t base = (int64_t)blockIdx.x * SCAN_B + (int64_t)threadIdx.x * SCAN_I;
-  int v[SCAN_I];
-  int s = 0;
-#pragma unroll
-  for (int k = 0; k < SCAN_I; ++k) {
-    int64_t j = base + k;
-    v[k] = j < n ? in[j] : 0;
-    s += v[k];
-  }
-  int tot;
-  int acc = block_excl(s, lds, &tot) + partial[blockIdx.x];
-#pragma unroll
-  for (int k = 0; k < SCAN_I; ++k) {
-    int64_t j = base + k;
-    if (j < n) out[j] = acc;
-    acc += v[k];
-  }
-}
-
-int scan_partials_needed(int n) { return (n + SCAN_B - 1) / SCAN_B + 1; }
+// room for the chunk sums of the finest split
+int scan_partials_needed(int n) { return n / kBlock + 4; }
 
 // short arrays: one block of 1024 threads, each scanning a contiguous piece
 // of at most eight entries (its loads are serial, two passes: longer pieces
@@ -105,14 +23,14 @@ int scan_partials_needed(int n) { return (n + SCAN_B - 1) / SCAN_B + 1; }
 constexpr int kScanSingle = 8192;
 __global__ void __launch_bounds__(1024) k_scan_single(const int* __restrict__ in, int* __restrict__ out, int n,
                                                       int* __restrict__ total) {
-  __shared__ int lds[1024 / kWave + 1];
+  __shared__ int lds[1024 / kWave];
   int per = (n + 1023) / 1024;
   int lo = (int)threadIdx.x * per;
   int hi = min(n, lo + per);
   int s = 0;
   for (int i = lo; i < hi; ++i) s += in[i];
   int tot;
-  int acc = block_excl(s, lds, &tot);
+  int acc = block_excl(s, lds, tot);
   for (int i = lo; i < hi; ++i) {
     int t = in[i];
     out[i] = acc;
@@ -126,11 +44,9 @@ void scan_excl(const int* in, int* out, int n, int* total, int* partial, hipStre
     k_scan_single<<<1, 1024, 0, s>>>(in, out, n, total);
     return;
   }
-  int nb = (n + SCAN_B - 1) / SCAN_B;
-  if (nb < 1) nb = 1;
-  k_scan_reduce<<<nb, SCAN_T, 0, s>>>(in, n, partial);
-  k_scan_partials<<<1, 1024, 0, s>>>(partial, nb, total);
-  k_scan_apply<<<nb, SCAN_T, 0, s>>>(in, out, n, partial);
+  scan_fused<int, 8>([=] __device__(int i, bool on) { return on ? in[i] : 0; }, [=] __device__(int i) { return in[i]; },
+                     [=] __device__(int i, int at, int) { out[i] = at; }, [=] __device__(int t) { *total = t; }, n,
+                     partial, s);
 }
 
 // ---- validation ---------------------------------------------------------------------
@@ -277,38 +193,30 @@ void build_count(const Store& st, int* ne_cnt, int* place, hipStream_t s) {
 
 __device__ __forceinline__ int round4(int x) { return (x + 3) & ~3; }
 
-__global__ void k_caps(const int* __restrict__ ne_cnt, int V, double slack, int* __restrict__ nn_cap,
-                       int* __restrict__ ne_cap) {
-  for (int v = gtid(); v < V; v += gstride()) {
-    int c = ne_cnt[v];
-    if (c == 0) {
-      nn_cap[v] = 0;
-      ne_cap[v] = 0;
-      continue;
-    }
-    int a = (int)ceil((double)c * slack);
-    int b = (int)ceil((double)(c + 1) * slack);
-    ne_cap[v] = round4(max(c + 2, a));
-    nn_cap[v] = round4(max(c + 3, b));
-  }
+// a row's slots (NN, NE) for c elements
+__device__ __forceinline__ int2 caps_of(int c, double slack) {
+  if (c == 0) return make_int2(0, 0);
+  int a = (int)ceil((double)c * slack);
+  int b = (int)ceil((double)(c + 1) * slack);
+  return make_int2(round4(max(c + 3, b)), round4(max(c + 2, a)));
 }
 
-void build_caps(const Store& st, const int* ne_cnt, double slack, int* nn_cap, int* ne_cap, hipStream_t s) {
-  k_caps<<<grid_for(st.V), kBlock, 0, s>>>(ne_cnt, st.V, slack, nn_cap, ne_cap);
-}
-
-__global__ void k_set_headers(Hdr* __restrict__ hdr, int2* __restrict__ cap, int V, const int* __restrict__ nn_off,
-                              const int* __restrict__ ne_off, const int* __restrict__ nn_cap,
-                              const int* __restrict__ ne_cap, const int* __restrict__ ne_cnt) {
-  for (int v = gtid(); v < V; v += gstride()) {
-    hdr[v] = make_int4(nn_off[v], 0, ne_off[v], ne_cnt[v]);
-    cap[v] = make_int2(nn_cap[v], ne_cap[v]);
-  }
-}
-
-void set_headers(const Store& st, const int* nn_off, const int* ne_off, const int* nn_cap, const int* ne_cap,
-                 const int* ne_cnt, hipStream_t s) {
-  k_set_headers<<<grid_for(st.V), kBlock, 0, s>>>(st.hdr, st.cap, st.V, nn_off, ne_off, nn_cap, ne_cap, ne_cnt);
+// every row's header and slots, one behind the other in the pools, whose bump
+// pointers the totals become
+void build_headers(const Store& st, const int* ne_cnt, double slack, int* ctr, int2* partial, hipStream_t s) {
+  Hdr* hdr = st.hdr;
+  int2* cap = st.cap;
+  scan_fused<int2, 8>([=] __device__(int v, bool on) { return on ? caps_of(ne_cnt[v], slack) : make_int2(0, 0); },
+                      [=] __device__(int v) { return caps_of(ne_cnt[v], slack); },
+                      [=] __device__(int v, int2 at, int2 c) {
+                        hdr[v] = make_int4(at.x, 0, at.y, ne_cnt[v]);
+                        cap[v] = c;
+                      },
+                      [=] __device__(int2 t) {
+                        ctr[C_NN_TOP] = t.x;
+                        ctr[C_NE_TOP] = t.y;
+                      },
+                      st.V, partial, s);
 }
 
 __global__ void __launch_bounds__(256) k_ne_fill(const Elem* __restrict__ tri, int T, const Hdr* __restrict__ hdr,
@@ -479,17 +387,22 @@ void build_finish(const Store& st, int* ctr, hipStream_t s) {
 }
 
 // ---- compaction --------------------------------------------------------------------------
-__global__ void k_flag_v(const uint8_t* __restrict__ valive, int V, int* __restrict__ f) {
-  for (int v = gtid(); v < V; v += gstride()) f[v] = valive[v] ? 1 : 0;
-}
-__global__ void k_flag_t(const Elem* __restrict__ tri, int T, int* __restrict__ f) {
-  for (int t = gtid(); t < T; t += gstride()) f[t] = tri[t].w ? 1 : 0;
-}
-void flag_live_vertices(const Store& st, int* flag, hipStream_t s) {
-  k_flag_v<<<grid_for(st.V), kBlock, 0, s>>>(st.valive, st.V, flag);
-}
-void flag_live_elements(const Store& st, int* flag, hipStream_t s) {
-  k_flag_t<<<grid_for(st.T), kBlock, 0, s>>>(st.tri, st.T, flag);
+// live flags of vertices and elements, their scans and totals
+void scan_live(const Store& st, int* vflag, int* vpos, int* vtotal, int* tflag, int* tpos, int* ttotal, int* partial,
+               hipStream_t s) {
+  const uint8_t* valive = st.valive;
+  const Elem* tri = st.tri;
+  auto put = [] __device__(int* flag, int i, bool on, int x) {
+    if (on) flag[i] = x;
+    return x;
+  };
+  scan_fused2<int, 8>([=] __device__(int v, bool on) { return put(vflag, v, on, on && valive[v] ? 1 : 0); },
+                      [=] __device__(int v) { return vflag[v]; },
+                      [=] __device__(int v, int at, int) { vpos[v] = at; }, [=] __device__(int t) { *vtotal = t; },
+                      st.V, [=] __device__(int t, bool on) { return put(tflag, t, on, on && tri[t].w ? 1 : 0); },
+                      [=] __device__(int t) { return tflag[t]; },
+                      [=] __device__(int t, int at, int) { tpos[t] = at; }, [=] __device__(int t) { *ttotal = t; },
+                      st.T, partial, s);
 }
 
 __global__ void k_compact_v(const double2* __restrict__ xy, const Met* __restrict__ met,
@@ -570,34 +483,36 @@ __device__ __forceinline__ double elen2(const double2* xy, const Met* met, int i
 
 // count long edges (a, b > a) per vertex; also counts tested edges. Meshes of
 // a batch that have finished refining are skipped.
-__global__ void k_refine_mark(Store st, double L_up2, int* __restrict__ cnt, int* ctr) {
-  const double2* xy = st.xy;
-  const Met* met = st.met;
-  const Hdr* hdr = st.hdr;
-  const int* nn = st.nn;
-  int V = st.V;
-  int stride = gstride();
-  for (int v0 = blockIdx.x * blockDim.x; v0 < V; v0 += stride) {
-    int a = v0 + (int)threadIdx.x;
-    int tested = 0, c = 0;
-    if (a < V) {
-      bool skip = st.mdone && st.mdone[st.vmesh ? st.vmesh[a] : 0];
-      if (st.valive[a] && !skip) {
-        Hdr h = hdr[a];
-        for (int j = 0; j < h.y; ++j) {
-          int b = nn[h.x + j];
-          if (b <= a) continue;
-          ++tested;
-          if (elen2(xy, met, a, b) > L_up2) ++c;
-        }
+// (called by full wavefronts)
+__device__ __forceinline__ int refine_mark(const Store& st, double L_up2, int* cnt, int* ctr, int a, bool on) {
+  int tested = 0, c = 0;
+  if (on) {
+    bool skip = st.mdone && st.mdone[st.vmesh ? st.vmesh[a] : 0];
+    if (st.valive[a] && !skip) {
+      Hdr h = st.hdr[a];
+      for (int j = 0; j < h.y; ++j) {
+        int b = st.nn[h.x + j];
+        if (b <= a) continue;
+        ++tested;
+        if (elen2(st.xy, st.met, a, b) > L_up2) ++c;
       }
-      cnt[a] = c;
     }
-    wave_add_full(stripe_ptr(ctr, S_EDGES), tested);
+    cnt[a] = c;
   }
+  wave_add_full(stripe_ptr(ctr, S_EDGES), tested);
+  return c;
 }
-void refine_mark(const Store& st, double L_up2, int* cnt, int* ctr, hipStream_t s) {
-  k_refine_mark<<<grid_for(st.V), kBlock, 0, s>>>(st, L_up2, cnt, ctr);
+__device__ __forceinline__ int refine_count(const Store& st, double L_up2, int* ecnt, int t, bool on) {
+  if (!on) return 0;
+  Elem e = st.tri[t];
+  int c = 0;
+  if (e.w) {
+    c += elen2(st.xy, st.met, e.x, e.y) > L_up2;
+    c += elen2(st.xy, st.met, e.y, e.z) > L_up2;
+    c += elen2(st.xy, st.met, e.z, e.x) > L_up2;
+  }
+  ecnt[t] = c;
+  return c;
 }
 
 // new vertex ids inside the vertex's mesh range: base + used + (long edges of
@@ -633,21 +548,18 @@ void refine_mint(const Store& st, double L_up2, const int* vscan, int* mid, hipS
   k_refine_mint<<<grid_for(st.V), kBlock, 0, s>>>(st, L_up2, vscan, mid);
 }
 
-__global__ void k_refine_count(const double2* __restrict__ xy, const Met* __restrict__ met,
-                               const Elem* __restrict__ tri, int T, double L_up2, int* __restrict__ ecnt) {
-  for (int t = gtid(); t < T; t += gstride()) {
-    Elem e = tri[t];
-    int c = 0;
-    if (e.w) {
-      c += elen2(xy, met, e.x, e.y) > L_up2;
-      c += elen2(xy, met, e.y, e.z) > L_up2;
-      c += elen2(xy, met, e.z, e.x) > L_up2;
-    }
-    ecnt[t] = c;
-  }
-}
-void refine_count(const Store& st, double L_up2, int* ecnt, hipStream_t s) {
-  k_refine_count<<<grid_for(st.T), kBlock, 0, s>>>(st.xy, st.met, st.tri, st.T, L_up2, ecnt);
+// per vertex the edges to split that it owns (the smaller end), per element its
+// edges to split: counts, scans and totals
+void refine_scan(const Store& store, double L_up2, int* vcnt, int* vscan, int* vtotal, int* ecnt, int* escan,
+                 int* etotal, int* ctr, int* partial, hipStream_t s) {
+  Store st = store;
+  scan_fused2<int, 1>([=] __device__(int a, bool on) { return refine_mark(st, L_up2, vcnt, ctr, a, on); },
+                      [=] __device__(int a) { return vcnt[a]; },
+                      [=] __device__(int a, int at, int) { vscan[a] = at; }, [=] __device__(int t) { *vtotal = t; },
+                      st.V, [=] __device__(int t, bool on) { return refine_count(st, L_up2, ecnt, t, on); },
+                      [=] __device__(int t) { return ecnt[t]; },
+                      [=] __device__(int t, int at, int) { escan[t] = at; }, [=] __device__(int t) { *etotal = t; },
+                      st.T, partial, s);
 }
 
 __device__ int midpoint_of(const Hdr* hdr, const int* nn, const int* mid, int p, int q) {
