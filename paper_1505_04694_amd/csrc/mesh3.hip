@@ -25,6 +25,7 @@
 #include "common.hpp"
 #include "kern.hpp"
 #include "blocks.hpp"
+#include "scan.hpp"
 
 namespace pm3 {
 
@@ -56,7 +57,8 @@ enum {
   K_CCOMMIT = 11,   // 11, 12: 1: the class collapsed something (gates its row commit)
   K_NROWS = 13,     // 13, 14: rows stamped by the class (the length of its row list)
   K_LIST = 15,      // length of the list selected last
-  K_COUNT = 16,
+  K_TOTAL2 = 16,    // the second total of two scans at once
+  K_COUNT = 32,
   K_CLASS = K_COUNT,                    // class sizes, cursors and offsets, kMaxColours each
   K_STRIPE = K_CLASS + 3 * kMaxColours, // kStripes lines of striped counts
   K_ALL = K_STRIPE + 64 * 32
@@ -1539,6 +1541,14 @@ __global__ void k_flags(const uint8_t* __restrict__ a, int n, int* f) {
   for (int i = gtid(); i < n; i += gstride()) f[i] = a[i] ? 1 : 0;
 }
 
+// the live flags of vertices and elements as counts
+__global__ void k_live(Store3 st, int* vf, int* tf) {
+  for (int i = gtid(); i < max(st.V, st.T); i += gstride()) {
+    if (i < st.V) vf[i] = st.valive[i] ? 1 : 0;
+    if (i < st.T) tf[i] = st.talive[i] ? 1 : 0;
+  }
+}
+
 // (after a renumbering) every slot is live and no vertex selected
 __global__ void k_all_live(Store3 st, uint8_t* nxt) {
   for (int i = gtid(); i < max(st.V, st.T); i += gstride()) {
@@ -2126,7 +2136,7 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
     if (rc == PM_OK) H3(e);
   }
   T3(rc);
-  int need = pm::scan_partials_needed(std::max(m->Vcap, m->Tcap) + 1);
+  int need = pm::scan_partials_needed(m->Vcap) + pm::scan_partials_needed(m->Tcap);
   if (need > m->pcap) {
     T3(dgrow(m, &m->partial, m->pcap, need, false));
     m->pcap = need;
@@ -2137,6 +2147,20 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
 // exclusive scan of n ints into out; returns the total
 // the scan's total, with every counter (the host copy is then as current as
 // after read_ctr)
+// a vertex array's and an element array's scans with one read-back
+pm_status scan_both(pm3_mesh* m, const int* v, int* vout, int V, int* nv, const int* t, int* tout, int T, int* nt) {
+  int* ctr = m->ctr;
+  auto load = [](const int* a) { return [=] __device__(int i, bool on) { return on ? a[i] : 0; }; };
+  auto at = [](const int* a) { return [=] __device__(int i) { return a[i]; }; };
+  auto put = [](int* a) { return [=] __device__(int i, int before, int) { a[i] = before; }; };
+  auto total = [](int* a) { return [=] __device__(int x) { *a = x; }; };
+  pm::scan_fused2<int, 8>(load(v), at(v), put(vout), total(ctr + K_TOTAL), V, load(t), at(t), put(tout),
+                          total(ctr + K_TOTAL2), T, m->partial, m->s);
+  T3(read_ctr(m));
+  *nv = m->hctr[K_TOTAL];
+  *nt = m->hctr[K_TOTAL2];
+  return PM_OK;
+}
 pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
   pm::scan_excl(in, out, n, m->ctr + K_TOTAL, m->partial, m->s);
   T3(read_ctr(m));
@@ -2151,15 +2175,26 @@ pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
 // coarsening phase (a row that outgrows its slot moves, with twice the room,
 // and its old slot stays unused until the next full build), split into the
 // stripes' ranges. Clears the room counters.
-pm_status build_rows(pm3_mesh* m) {
+// (all_live: no element slot is dead, so the rows' total is known without a
+// read-back)
+pm_status build_rows(pm3_mesh* m, bool all_live) {
   Store3& st = m->st;
   int V = st.V;
   k_fill_int<<<grid(V + 1), kB, 0, m->s>>>(m->cnt, V + 1, 0);
-  int4* rank = nullptr;
-  T3(dgrow(m, &rank, 0, st.T, false));
-  k_ne_count<<<(st.T + kB * kCountPer - 1) / (kB * kCountPer), kB, 0, m->s>>>(st, m->cnt, rank);
+  struct Temp {
+    int4* p = nullptr;
+    ~Temp() { dfree3(p); }
+  } rank;
+  T3(dgrow(m, &rank.p, 0, st.T, false));
+  k_ne_count<<<(st.T + kB * kCountPer - 1) / (kB * kCountPer), kB, 0, m->s>>>(st, m->cnt, rank.p);
   int total = 0;
-  T3(scan_total(m, m->cnt, m->off, V, &total));
+  if (all_live) {
+    if (4 * (int64_t)st.T > INT32_MAX) return fail3(m, PM_E_NOMEM, "adjacency pool beyond 2^31 entries");
+    total = 4 * st.T;
+    pm::scan_excl(m->cnt, m->off, V, m->ctr + K_TOTAL, m->partial, m->s);
+  } else {
+    T3(scan_total(m, m->cnt, m->off, V, &total));
+  }
   int64_t want = total + (int64_t)(m->headroom * (double)total) + kTopStripes * 64;
   if (want > m->necap) {
     int64_t nc = std::max<int64_t>(want, m->necap + m->necap / 2);
@@ -2176,8 +2211,7 @@ pm_status build_rows(pm3_mesh* m) {
     m->mcap = nc;
   }
   if (!m->tops) T3(dgrow(m, &m->tops, 0, kTopStripes * kTopStride, false));
-  k_ne_fill<<<grid(st.T), kB, 0, m->s>>>(st, m->off, rank);
-  dfree3(rank);
+  k_ne_fill<<<grid(st.T), kB, 0, m->s>>>(st, m->off, rank.p);
   k_rows_finish<<<grid((int64_t)V * kWave), kB, 0, m->s>>>(st, m->off, m->cnt);
   m->top_base = total;
   m->top_per = (m->necap - total) / kTopStripes;
@@ -2280,11 +2314,9 @@ pm_status class_lists(pm3_mesh* m, int n, int ncol, bool listed, std::vector<int
 pm_status compact(pm3_mesh* m) {
   Store3& st = m->st;
   int V = st.V, T = st.T;
-  k_flags<<<grid(V), kB, 0, m->s>>>(st.valive, V, m->flag);
   int nv = 0, nt = 0;
-  T3(scan_total(m, m->flag, m->scan, V, &nv));
-  k_flags<<<grid(T), kB, 0, m->s>>>(st.talive, T, m->tcnt);
-  T3(scan_total(m, m->tcnt, m->tscan, T, &nt));
+  k_live<<<grid(std::max(V, T)), kB, 0, m->s>>>(st, m->flag, m->tcnt);
+  T3(scan_both(m, m->flag, m->scan, V, &nv, m->tcnt, m->tscan, T, &nt));
   double4* xyz = nullptr;
   Met6* met = nullptr;
   uint8_t* tag = nullptr;
@@ -2308,7 +2340,7 @@ pm_status compact(pm3_mesh* m) {
   st.T = nt;
   k_all_live<<<grid(std::max(nv, nt)), kB, 0, m->s>>>(st, m->nxt);
   H3(hipGetLastError());
-  return build_rows(m);
+  return build_rows(m, true);
 }
 
 void put_stats(pm_stats* out, const int64_t* v) {
@@ -2382,7 +2414,7 @@ pm_status pm3_mesh_create(const pm3_mesh_desc* d, const pm_options* o, void* str
     return bail(PM_E_MESH);
   }
   k_fill_u8<<<grid(V), kB, 0, m->s>>>(m->nxt, V, 0);
-  if (build_rows(m) != PM_OK) return bail(PM_E_DEVICE);
+  if (build_rows(m, true) != PM_OK) return bail(PM_E_DEVICE);
   if (hipStreamSynchronize(m->s) != hipSuccess) return bail(PM_E_DEVICE);
   *out = m;
   return PM_OK;
@@ -2594,7 +2626,7 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
       for (int c = 0; c < ncol; ++c)
         if (class_epoch[c] == m->hctr[K_ROOMEP]) failed = c;
       if (failed < c0) return fail3(m, PM_E_DEVICE, "row commit: room counter names no class of this round");
-      T3(build_rows(m));
+      T3(build_rows(m, false));
       ++sv[13];
       c0 = failed + 1;
       k_fill_int<<<1, kWave, 0, m->s>>>(m->ctr + K_CCOMMIT, 4, 0);
@@ -2630,28 +2662,25 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
     int V0 = st.V, T0 = st.T;
     T3(zero_ctr(m));
     k_mark<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, o->L_up2, m->mark, m->cnt, m->ctr);
-    int nv = 0;
-    T3(scan_total(m, m->cnt, m->scan, V0, &nv));
+    k_split_count<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->tcnt, m->ctr);
+    int nv = 0, nt = 0;
+    T3(scan_both(m, m->cnt, m->scan, V0, &nv, m->tcnt, m->tscan, T0, &nt));
     sv[PM_S_EDGES] += m->hctr[K_EDGES];
     if (nv == 0) {
       done = true;
       break;
     }
-    T3(reserve(m, V0 + nv, T0));
-    k_mint<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, V0, m->scan, m->mark);
-    st.V = V0 + nv;
-    k_split_count<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->tcnt, m->ctr);
-    int nt = 0;
-    T3(scan_total(m, m->tcnt, m->tscan, T0, &nt));
     if (m->hctr[K_ERR] & E_LEAVES) return fail3(m, PM_E_DEVICE, "an element split into too many pieces");
     T3(reserve(m, V0 + nv, T0 + nt));
+    k_mint<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, V0, m->scan, m->mark);
+    st.V = V0 + nv;
     k_split_write<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->mark, m->tscan);
     st.T = T0 + nt;
     H3(hipGetLastError());
     sv[PM_S_NEWV] += nv;
     sv[PM_S_NEWT] += nt;
     sv[PM_S_COMMITTED] += nv;
-    T3(build_rows(m));
+    T3(build_rows(m, true));
   }
   H3(hipStreamSynchronize(m->s));
   sv[PM_S_ROUNDS] = p;
