@@ -447,7 +447,7 @@ pm_status upload_ranges(pm_mesh* m) {
   all.insert(all.end(), m->tused.begin(), m->tused.end());
   if (!m->ranges) TRY(dalloc(m, &m->ranges, all.size()));
   if (B == 1) {
-    set_ranges(m->ranges, m->vused[0], m->tused[0], st.V, st.T, m->s);
+    // written by the row build that follows
   } else if (all.size() <= (size_t)kAuxInts / 2) {
     // staged in the upper half of the pinned ints and copied in stream
     // order; the previous upload's copy has finished before the stage is
@@ -521,7 +521,7 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
   // the incidences' places lie in the NN pool, which the row finish writes last
   int64_t places = 3 * (int64_t)st.T;
   place = st.nn_pool >= places ? st.nn : nullptr;
-  zero_ints(m->vt0.p, V, m->s);
+  build_start(m->vt0.p, st.B == 1 ? m->ranges : nullptr, m->vused[0], m->tused[0], V, st.T, m->s);
   build_count(st, m->vt0.p, place, m->s);
   build_headers(st, m->vt0.p, m->slack, m->ctr, (int2*)m->partial.p, m->s);
   if (!fits && !small) {
@@ -1658,7 +1658,6 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
     TRY(ensure(m, m->tt1, T0));
     TRY(ensure(m, m->rtmp, 4 * (size_t)B + 4));
     TRY(ensure(m, m->partial, scan_partials_needed(V0) + scan_partials_needed(T0)));
-    stripe_zero(m->ctr, S_EDGES, 1, m->s);
     refine_scan(s, o->L_up2, m->vt0.p, m->vt1.p, m->ctr + C_TOTAL, m->tt0.p, m->tt1.p, m->ctr + C_TOTAL2, m->ctr,
                 m->partial.p, m->s);
     std::vector<int> need(2 * B);
@@ -1669,8 +1668,10 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
       range_sums(m->tt1.p, m->tt0.p, s.tbase, s.tused, B, m->rtmp.p + B, m->s);
       HIPCHK(hipMemcpyAsync(aux ? m->haux : need.data(), m->rtmp.p, sizeof(int) * 2 * B, hipMemcpyDeviceToHost, m->s));
     }
-    stripe_sum(m->ctr, S_EDGES, 1, C_EDGES, m->s);
-    TRY(read_ctr(m, 0, C_JP));
+    mail_next(m->mail);
+    mail_sum(m->ctr, C_JP, S_EDGES, C_EDGES, m->hctr, m->mail, m->s);
+    HIPCHK(mail_wait(m->mail, m->s));
+    if (m->prof.mask) TRY(sync(m));
     if (B > 1) TRY(sync(m));
     TRY(check_err(m, true));  // also the last row build's
     int nv = m->hctr[C_TOTAL], nt = m->hctr[C_TOTAL2];

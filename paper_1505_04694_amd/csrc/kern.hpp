@@ -71,6 +71,7 @@ void stripe_zero(int* ctr, int slot, int nslots, hipStream_t s);
 void phase_start(int* ctr, hipStream_t s);
 // sums over stripes into pinned host memory, delivered as mail b (numbered by the caller)
 void stripe_mail(const int* ctr, int slot, int nslots, int* dst, const Mail& b, hipStream_t s);
+void mail_sum(int* ctr, int n, int slot, int where, int* dst, const Mail& b, hipStream_t s);
 // ctr[dst + k] = sum over stripes of slot + k, k < nslots
 void stripe_sum(int* ctr, int slot, int nslots, int dst, hipStream_t s);
 constexpr int kMaxColours = 255;  // colour 0xFF marks "uncoloured"
@@ -172,8 +173,9 @@ void copy_vertices(const Store& from, const Store& to, int n, hipStream_t s);
 void copy_elements(const Store& from, Elem* to, int n, hipStream_t s);
 // dead slots from V and T to the capacities
 void clear_tail(const Store& st, int V, int T, hipStream_t s);
-// the ranges of a single mesh
-void set_ranges(int* ranges, int vused, int tused, int V, int T, hipStream_t s);
+// the start of a row build: V counts at zero, and the ranges of a single mesh (null
+// for a batch, whose ranges are uploaded)
+void build_start(int* cnt, int* ranges, int vused, int tused, int V, int T, hipStream_t s);
 void tri_in(const int* tri3, int T, Elem* tri, hipStream_t s);
 void xy_in(const double* xy, int V, double2* out, hipStream_t s);
 void tags_from_xy(const double2* xy, int V, uint8_t* tag, hipStream_t s);

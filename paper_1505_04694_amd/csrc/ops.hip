@@ -355,6 +355,22 @@ __global__ void k_stripe_mail(const int* ctr, int slot, int nslots, int* dst, in
 void stripe_mail(const int* ctr, int slot, int nslots, int* dst, const Mail& b, hipStream_t s) {
   k_stripe_mail<<<1, kStripes, 0, s>>>(ctr, slot, nslots, dst, (int*)b.at, b.no);
 }
+// the first n counters to the host, with a striped count's sum in the place of
+// ctr[where]; the stripes start again at zero
+__global__ void k_mail_sum(int* ctr, int n, int slot, int where, int* dst, int* at, int no) {
+  for (int i = (int)threadIdx.x; i < n; i += (int)blockDim.x)
+    if (i != where) dst[i] = ctr[i];
+  int* mine = &ctr[C_STRIPE + threadIdx.x * kStripeW + slot];
+  int x = *mine;
+  *mine = 0;
+#pragma unroll
+  for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d);
+  if (threadIdx.x == 0) dst[where] = x;
+  mail_post(at, no);
+}
+void mail_sum(int* ctr, int n, int slot, int where, int* dst, const Mail& b, hipStream_t s) {
+  k_mail_sum<<<1, kStripes, 0, s>>>(ctr, n, slot, where, dst, (int*)b.at, b.no);
+}
 void stripe_sum(int* ctr, int slot, int nslots, int dst, hipStream_t s) {
   static_assert(kStripes == kWave, "one lane per stripe");
   k_stripe_sum<<<1, kStripes, 0, s>>>(ctr, slot, nslots, dst);

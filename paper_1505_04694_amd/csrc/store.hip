@@ -747,7 +747,9 @@ __global__ void k_clear_tail(Store st, int V, int T) {
 void clear_tail(const Store& st, int V, int T, hipStream_t s) {
   k_clear_tail<<<grid_for(std::max(st.Vcap - V, st.Tcap - T)), kBlock, 0, s>>>(st, V, T);
 }
-__global__ void k_set_ranges(int* r, int vused, int tused, int V, int T) {
+__global__ void k_build_start(int* __restrict__ cnt, int* r, int vused, int tused, int V, int T) {
+  for (int i = gtid(); i < V; i += gstride()) cnt[i] = 0;
+  if (!r || gtid() != 0) return;
   r[0] = 0;
   r[1] = V;
   r[2] = vused;
@@ -755,8 +757,8 @@ __global__ void k_set_ranges(int* r, int vused, int tused, int V, int T) {
   r[4] = T;
   r[5] = tused;
 }
-void set_ranges(int* ranges, int vused, int tused, int V, int T, hipStream_t s) {
-  k_set_ranges<<<1, 1, 0, s>>>(ranges, vused, tused, V, T);
+void build_start(int* cnt, int* ranges, int vused, int tused, int V, int T, hipStream_t s) {
+  k_build_start<<<grid_for(V, 1024), kBlock, 0, s>>>(cnt, ranges, vused, tused, V, T);
 }
 
 // input triangles (T x 3) to stored elements: rotated smallest-id first, live
