@@ -1285,6 +1285,36 @@ void pinned_give(void* p) {
   g_pinned_free.push_back(p);
 }
 
+static std::vector<void*> g_stage_free;
+constexpr size_t kStageKept = 4;
+void* stage_take() {
+  void* p = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    if (!g_stage_free.empty()) {
+      p = g_stage_free.back();
+      g_stage_free.pop_back();
+      return p;
+    }
+  }
+  if (hipHostMalloc(&p, kStageBytes, hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+void stage_give(void* p) {
+  if (!p) return;
+  {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    if (g_stage_free.size() < kStageKept) {
+      g_stage_free.push_back(p);
+      return;
+    }
+  }
+  (void)hipHostFree(p);
+}
+
 Mail mail_of(void* block) {
   Mail b;
   b.at = (volatile int*)((char*)block + kPinnedBytes - sizeof(int));
@@ -1884,6 +1914,72 @@ pm_status pm_quality_noalloc(pm_mesh* m, double* Q, double* qmin, double* dQdx, 
   return PM_OK;
 }
 
+namespace {
+// host arrays to consecutive places on the device (each padded to 16 bytes),
+// through two pinned blocks in turn
+struct Upload {
+  char* dst;
+  hipStream_t s;
+  char* block[2] = {nullptr, nullptr};
+  hipEvent_t ev[2] = {nullptr, nullptr};
+  bool busy[2] = {false, false};
+  int cur = 0;
+  size_t at = 0;
+  Upload(char* d, hipStream_t stream) : dst(d), s(stream) {}
+  Upload(const Upload&) = delete;
+  ~Upload() { done(); }
+  bool flush() {
+    if (at == 0) return true;
+    if (hipMemcpyAsync(dst, block[cur], at, hipMemcpyHostToDevice, s) != hipSuccess ||
+        hipEventRecord(ev[cur], s) != hipSuccess)
+      return false;
+    busy[cur] = true;
+    dst += at;
+    at = 0;
+    cur ^= 1;
+    return true;
+  }
+  bool put(const void* src, size_t n) {
+    const char* from = (const char*)src;
+    size_t pad = (16 - n % 16) % 16;
+    while (n + pad > 0) {
+      if (at == 0) {
+        if (!block[cur]) {
+          block[cur] = (char*)pm::stage_take();
+          if (!block[cur] || hipEventCreateWithFlags(&ev[cur], hipEventDisableTiming) != hipSuccess) return false;
+        }
+        if (busy[cur] && hipEventSynchronize(ev[cur]) != hipSuccess) return false;
+        busy[cur] = false;
+      }
+      size_t k = std::min(n, pm::kStageBytes - at);
+      memcpy(block[cur] + at, from, k);
+      from += k;
+      n -= k;
+      at += k;
+      if (n == 0) {
+        k = std::min(pad, pm::kStageBytes - at);
+        memset(block[cur] + at, 0, k);
+        pad -= k;
+        at += k;
+      }
+      if (at == pm::kStageBytes && !flush()) return false;
+    }
+    return true;
+  }
+  // once the stream is past the copies
+  void done() {
+    for (int k = 0; k < 2; ++k) {
+      if (busy[k]) (void)hipEventSynchronize(ev[k]);
+      busy[k] = false;
+      if (ev[k]) (void)hipEventDestroy(ev[k]);
+      ev[k] = nullptr;
+      pm::stage_give(block[k]);
+      block[k] = nullptr;
+    }
+  }
+};
+}  // namespace
+
 pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_options* o, void* stream,
                           pm_mesh** out) {
   if (!out) return PM_E_ARG;
@@ -1906,54 +2002,24 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
     tb[i + 1] = tb[i] + (int)ct;
   }
   int nV = vb[count], nT = tb[count];
-  // the concatenated store on the host: unused slots are dead (identity metric)
-  std::vector<double> xy(2 * (size_t)nV, 0.0), met(3 * (size_t)nV, 0.0);
-  std::vector<uint8_t> tag(nV, 0), va(nV, 0);
-  std::vector<Elem> tri(nT, make_int4(0, 0, 0, 0));
-  std::vector<int> vmesh(nV), tmesh(nT);
-  g_create_err.clear();
+  // the caller's arrays go up as they are, one mesh behind the other, a table of
+  // their places first
+  std::vector<BatchIn> in(count);
+  int64_t bytes = 0;
+  auto take = [&](int64_t n) {
+    int64_t at = bytes;
+    bytes += (n + 15) / 16 * 16;
+    return at;
+  };
+  take(sizeof(BatchIn) * count);
   for (int i = 0; i < count; ++i) {
     const pm_mesh_desc& d = meshes[i];
-    for (int v = vb[i]; v < vb[i + 1]; ++v) {
-      vmesh[v] = i;
-      met[3 * (size_t)v] = 1.0;
-      met[3 * (size_t)v + 2] = 1.0;
-    }
-    for (int t = tb[i]; t < tb[i + 1]; ++t) tmesh[t] = i;
-    for (int64_t v = 0; v < d.V; ++v) {
-      size_t g = (size_t)(vb[i] + v);
-      double x = d.xy[2 * v], y = d.xy[2 * v + 1];
-      xy[2 * g] = x;
-      xy[2 * g + 1] = y;
-      for (int k = 0; k < 3; ++k) met[3 * g + k] = d.metric[3 * v + k];
-      va[g] = 1;
-      if (d.tags) {
-        tag[g] = d.tags[v];
-      } else {
-        uint8_t tg = 0;
-        if (x == 0.0) tg |= 1;
-        if (x == 1.0) tg |= 2;
-        if (y == 0.0) tg |= 4;
-        if (y == 1.0) tg |= 8;
-        tag[g] = tg;
-      }
-    }
-    for (int64_t t = 0; t < d.T; ++t) {
-      int a = d.tri[3 * t], b = d.tri[3 * t + 1], c = d.tri[3 * t + 2];
-      if (a < 0 || b < 0 || c < 0 || a >= d.V || b >= d.V || c >= d.V) {
-        g_create_err = "mesh " + std::to_string(i) + ": element id out of range";
-        return PM_E_MESH;
-      }
-      a += vb[i];
-      b += vb[i];
-      c += vb[i];
-      Elem e;
-      if (a < b && a < c) e = make_int4(a, b, c, 1);
-      else if (b < a && b < c) e = make_int4(b, c, a, 1);
-      else e = make_int4(c, a, b, 1);
-      tri[tb[i] + t] = e;
-    }
+    in[i].xy = take(sizeof(double) * 2 * d.V);
+    in[i].met = take(sizeof(double) * 3 * d.V);
+    in[i].tri = take(sizeof(int) * 3 * d.T);
+    in[i].tag = d.tags ? take(d.V) : -1;
   }
+  g_create_err.clear();
   pm_mesh* m = new (std::nothrow) pm_mesh();
   if (!m) return PM_E_NOMEM;
   m->s = (hipStream_t)stream;
@@ -1977,32 +2043,37 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
   st.V = nV;
   st.T = nT;
   if (dalloc(m, &st.vmesh, nV) != PM_OK || dalloc(m, &st.tmesh, nT) != PM_OK) return bail(PM_E_NOMEM);
-  double* xyraw = nullptr;
-  if (dalloc(m, &xyraw, 2 * (size_t)nV) != PM_OK) return bail(PM_E_NOMEM);
-  // the copies below do not wait for the stream: let its queued clears (and
-  // any earlier user of these cached blocks) finish first
-  if (hipStreamSynchronize(m->s) != hipSuccess) return bail(PM_E_DEVICE);
-  bool ok = hipMemcpy(xyraw, xy.data(), sizeof(double) * xy.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.met, met.data(), sizeof(double) * met.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.tag, tag.data(), tag.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.valive, va.data(), va.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.tri, tri.data(), sizeof(Elem) * tri.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.vmesh, vmesh.data(), sizeof(int) * vmesh.size(), hipMemcpyHostToDevice) == hipSuccess &&
-            hipMemcpy(st.tmesh, tmesh.data(), sizeof(int) * tmesh.size(), hipMemcpyHostToDevice) == hipSuccess;
-  if (!ok) {
-    dfree(m, xyraw, 2 * (size_t)nV);
-    return bail(PM_E_DEVICE);
-  }
-  xy_in(xyraw, nV, st.xy, m->s);
-  (void)hipStreamSynchronize(m->s);
-  dfree(m, xyraw, 2 * (size_t)nV);
   m->vbase = vb;
   m->tbase = tb;
   m->vused = vu;
   m->tused = tu;
   if (upload_ranges(m) != PM_OK) return bail(PM_E_DEVICE);
-  k_validate(st, m->ctr, m->s);
-  pm_status r = check_err(m);
+  if (count == 1) build_start(nullptr, m->ranges, vu[0], tu[0], nV, nT, m->s);
+  char* raw = nullptr;
+  if (dalloc(m, &raw, bytes) != PM_OK) return bail(PM_E_NOMEM);
+  Upload up(raw, m->s);
+  bool ok = up.put(in.data(), sizeof(BatchIn) * count);
+  for (int i = 0; i < count && ok; ++i) {
+    const pm_mesh_desc& d = meshes[i];
+    ok = up.put(d.xy, sizeof(double) * 2 * d.V) && up.put(d.metric, sizeof(double) * 3 * d.V) &&
+         up.put(d.tri, sizeof(int) * 3 * d.T) && (!d.tags || up.put(d.tags, d.V));
+  }
+  ok = ok && up.flush();
+  if (ok) {
+    batch_in(raw, count, st, m->ctr, m->s);
+    k_validate(st, m->ctr, m->s);
+  }
+  // (the copies have left the staging blocks)
+  pm_status r = ok ? read_ctr(m, 0, kRoundCtrs) : PM_E_DEVICE;
+  if (r != PM_OK) (void)hipStreamSynchronize(m->s);
+  up.done();
+  dfree(m, raw, bytes);
+  if (r != PM_OK) return bail(PM_E_DEVICE);
+  if (m->hctr[C_FAILEP] != INT_MAX) {
+    m->err = "mesh " + std::to_string(m->hctr[C_FAILEP]) + ": element id out of range";
+    return bail(PM_E_MESH);
+  }
+  r = check_err(m, true);
   if (r != PM_OK) return bail(r);
   r = build_rows(m);
   if (r != PM_OK) return bail(r);
@@ -2028,6 +2099,43 @@ pm_status pm_batch_export(pm_mesh* m, int32_t i, double* xy, int32_t* tri, doubl
   if (!m || i < 0 || i >= m->st.B) return PM_E_ARG;
   Store& st = m->st;
   int v0 = m->vbase[i], nv = m->vused[i], t0 = m->tbase[i], nt = m->tused[i];
+  // one launch that writes what is asked for into pinned memory, local ids and
+  // all, where a block of it holds the mesh: five copies to pageable memory and a
+  // pass over the elements took 94 us a mesh of 250 KB, this takes 33
+  BatchOut bo{};
+  int64_t bytes = 0;
+  auto take = [&](bool on, int64_t n) {
+    if (!on) return (int64_t)-1;
+    int64_t at = bytes;
+    bytes += (n + 15) / 16 * 16;
+    return at;
+  };
+  bo.xy = take(xy, sizeof(double2) * (int64_t)nv);
+  bo.met = take(metric, sizeof(Met) * (int64_t)nv);
+  bo.tri = take(tri, sizeof(int) * 3 * (int64_t)nt);
+  bo.tag = take(tags, nv);
+  bo.valive = take(valive, nv);
+  bo.talive = take(talive, nt);
+  if (bytes <= (int64_t)kStageBytes) {
+    char* b = (char*)stage_take();
+    if (!b) return fail(m, PM_E_NOMEM, "pinned memory");
+    batch_out(st, v0, nv, t0, nt, bo, b, m->s);
+    mail_send(m->mail, m->ctr, 0, m->hctr, m->s);
+    hipError_t e = mail_wait(m->mail, m->s);
+    if (e != hipSuccess) (void)hipStreamSynchronize(m->s);
+    if (e == hipSuccess) {
+      if (xy) memcpy(xy, b + bo.xy, sizeof(double2) * nv);
+      if (metric) memcpy(metric, b + bo.met, sizeof(Met) * nv);
+      if (tri) memcpy(tri, b + bo.tri, sizeof(int) * 3 * nt);
+      if (tags) memcpy(tags, b + bo.tag, nv);
+      if (valive) memcpy(valive, b + bo.valive, nv);
+      if (talive) memcpy(talive, b + bo.talive, nt);
+    }
+    stage_give(b);
+    HIPCHK(e);
+    if (m->prof.mask) TRY(sync(m));
+    return PM_OK;
+  }
   if (xy) HIPCHK(hipMemcpyAsync(xy, st.xy + v0, sizeof(double2) * nv, hipMemcpyDeviceToHost, m->s));
   if (metric) HIPCHK(hipMemcpyAsync(metric, st.met + v0, sizeof(Met) * nv, hipMemcpyDeviceToHost, m->s));
   if (tags) HIPCHK(hipMemcpyAsync(tags, st.tag + v0, nv, hipMemcpyDeviceToHost, m->s));

@@ -18,6 +18,12 @@ constexpr size_t kPinnedBytes = 128 * 1024;
 void* pinned_take();
 void pinned_give(void* p);
 
+// Larger pinned blocks for staging a call's host arrays, taken for the call; a few
+// are kept for the next one (of any handle or thread). null: out of memory.
+constexpr size_t kStageBytes = 2 << 20;
+void* stage_take();
+void stage_give(void* p);
+
 // Mail: a kernel at the end of the stream's work writes a few counters into
 // pinned host memory and then a letter number, which the host polls: about 5 us
 // from the last kernel to the host, where a copy and a stream synchronisation

@@ -174,8 +174,20 @@ void copy_elements(const Store& from, Elem* to, int n, hipStream_t s);
 // dead slots from V and T to the capacities
 void clear_tail(const Store& st, int V, int T, hipStream_t s);
 // the start of a row build: V counts at zero, and the ranges of a single mesh (null
-// for a batch, whose ranges are uploaded)
+// for a batch, whose ranges are uploaded); cnt null: the ranges alone
 void build_start(int* cnt, int* ranges, int vused, int tused, int V, int T, hipStream_t s);
+// byte offsets of a mesh's arrays in the upload of a batch (tag: -1 when it has
+// none), and of the arrays of an export (-1: not wanted)
+struct BatchIn {
+  int64_t xy, met, tri, tag;
+};
+struct BatchOut {
+  int64_t xy, met, tri, tag, valive, talive;
+};
+// the store of a batch from its upload (a table of B entries, then the arrays);
+// ctr[C_FAILEP] becomes the first mesh with an element id out of range
+void batch_in(const char* raw, int B, const Store& st, int* ctr, hipStream_t s);
+void batch_out(const Store& st, int v0, int nv, int t0, int nt, const BatchOut& o, char* dst, hipStream_t s);
 void tri_in(const int* tri3, int T, Elem* tri, hipStream_t s);
 void xy_in(const double* xy, int V, double2* out, hipStream_t s);
 void tags_from_xy(const double2* xy, int V, uint8_t* tag, hipStream_t s);
