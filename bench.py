@@ -52,14 +52,14 @@ BYTES_PER_UNIT = {
 COMMIT_OPS_RANGE = (900, 1600)
 # rocprofv3 kernel names -> the groups above
 GROUPS = [
-    ("jp", r"k_jp_chunk|k_colour_small|k_jp_init"),
-    ("collapse", r"k_collapse|k_class_small<false>|k_round_small<false>"),
-    ("flip", r"k_flip|k_class_small<true>|k_round_small<true>"),
+    ("jp", r"k_jp_|k_colour_small|k_follow|k_solve|k_pred"),
+    ("collapse", r"k_collapse|k_class_small<false|k_rounds_dev<false"),
+    ("flip", r"k_flip|k_class_small<true|k_rounds_dev<true"),
     ("smooth", r"k_smooth"),
     ("commit", r"k_commit"),
     ("adjoint", r"k_adjoint"),
     ("quality", r"k_quality"),
-    ("select", r"k_select"),
+    ("select", r"k_select|select_vertices"),
 ]
 
 
@@ -89,7 +89,7 @@ def sources_sha():
     """Hash of the device code: the kernel sources and the headers they
     include (the host-side api.hip launches kernels but defines none)."""
     h = hashlib.sha256()
-    for name in ("common.hpp", "kern.hpp", "ops.hip", "store.hip"):
+    for name in ("common.hpp", "kern.hpp", "scan.hpp", "blocks.hpp", "ops.hip", "store.hip"):
         h.update(open(os.path.join(ROOT, "paper_1505_04694_amd", "csrc", name), "rb").read())
     return h.hexdigest()
 

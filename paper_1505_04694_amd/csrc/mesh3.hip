@@ -4,13 +4,14 @@
 //
 // Layout: per vertex xyz (double4, w unused), the six metric entries, tag and
 // live bytes, a row header int4 (nn_off, nn_cnt, ne_off, ne_cnt); per element
-// an int4 of vertex ids and a live byte. Rows are rebuilt from the element
-// list after every class that changes the topology (count, scan, fill, sort
-// per vertex): a class's members are pairwise non-adjacent, so the class
-// kernel writes only its members' own elements, and the next class reads the
-// current graph. Every floating-point expression is written in one fixed
-// order and compiled without contraction, so decisions are the ones a serial
-// IEEE-754 program makes from the same inputs.
+// an int4 of vertex ids and a live byte. After every class that changes the
+// topology the rows it touched are rebuilt from their old entries and those of
+// the members collapsed onto them; creation, refinement and renumbering build all
+// rows (count, scan, fill, finish per vertex). A class's members are pairwise
+// non-adjacent, so the class kernel writes only its members' own elements, and
+// the next class reads the current graph. Every floating-point expression is
+// written in one fixed order and compiled without contraction, so decisions are
+// the ones a serial IEEE-754 program makes from the same inputs.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
