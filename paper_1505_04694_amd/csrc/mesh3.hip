@@ -304,7 +304,7 @@ __global__ void __launch_bounds__(256) k_ne_count(Store3 st, int* cnt, int4* __r
   bool on[kCountPer];
 #pragma unroll
   for (int r = 0; r < kCountPer; ++r) {
-    int t = min(t0 + r * kB, st.T - 1);
+    int t = max(0, min(t0 + r * kB, st.T - 1));
     on[r] = t0 + r * kB < st.T && st.talive[t];
     e[r] = st.tet[t];
   }
@@ -2187,7 +2187,7 @@ pm_status build_rows(pm3_mesh* m, bool all_live) {
     ~Temp() { dfree3(p); }
   } rank;
   T3(dgrow(m, &rank.p, 0, st.T, false));
-  k_ne_count<<<(st.T + kB * kCountPer - 1) / (kB * kCountPer), kB, 0, m->s>>>(st, m->cnt, rank.p);
+  k_ne_count<<<std::max(1, (st.T + kB * kCountPer - 1) / (kB * kCountPer)), kB, 0, m->s>>>(st, m->cnt, rank.p);
   int total = 0;
   if (all_live) {
     if (4 * (int64_t)st.T > INT32_MAX) return fail3(m, PM_E_NOMEM, "adjacency pool beyond 2^31 entries");
@@ -2663,7 +2663,7 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
     int V0 = st.V, T0 = st.T;
     T3(zero_ctr(m));
     k_mark<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, o->L_up2, m->mark, m->cnt, m->ctr);
-    k_split_count<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->tcnt, m->ctr);
+    k_split_count<<<std::max(1, (T0 + kSplitThreads - 1) / kSplitThreads), kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->tcnt, m->ctr);
     int nv = 0, nt = 0;
     T3(scan_both(m, m->cnt, m->scan, V0, &nv, m->tcnt, m->tscan, T0, &nt));
     sv[PM_S_EDGES] += m->hctr[K_EDGES];
@@ -2675,7 +2675,7 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
     T3(reserve(m, V0 + nv, T0 + nt));
     k_mint<<<grid(kVL * (int64_t)V0), kB, 0, m->s>>>(st, V0, m->scan, m->mark);
     st.V = V0 + nv;
-    k_split_write<<<(T0 + kSplitThreads - 1) / kSplitThreads, kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->mark, m->tscan);
+    k_split_write<<<std::max(1, (T0 + kSplitThreads - 1) / kSplitThreads), kSplitThreads, 0, m->s>>>(st, T0, o->L_up2, m->mark, m->tscan);
     st.T = T0 + nt;
     H3(hipGetLastError());
     sv[PM_S_NEWV] += nv;

@@ -37,3 +37,15 @@ def test_rows_of_long_stars(n, stacked):
     # short axis: its vertices collapse onto one another, with all they carry
     compare_stats(om.coarsen(0, 0.05, 0.0, 3), gm.coarsen(0, 0.05, 0.0, 3), "coarsen")
     compare(om, gm, "coarsen")
+
+
+def test_collapse_to_nothing():
+    """One tetrahedron whose collapse leaves three vertices and no element."""
+    xyz = np.array([[0.2, 0.2, 0.2], [0.5, 0.2, 0.2], [0.2, 0.5, 0.2], [0.2, 0.2, 0.5]])
+    met = np.tile([1.0, 0.0, 0.0, 1.0, 0.0, 1.0], (4, 1))
+    om, gm = both(inputs.MeshInput3(xyz=xyz, tet=np.array([[0, 1, 2, 3]], np.int32), metric=met,
+                                    tags=np.zeros(4, np.uint8)), 3)
+    compare_stats(om.coarsen(0, 0.5, 0.0, 5), gm.coarsen(0, 0.5, 0.0, 5), "coarsen")
+    compare(om, gm, "coarsen")
+    compare_stats(om.refine(0.01), gm.refine(0.01), "refine")
+    compare(om, gm, "refine")
