@@ -423,8 +423,10 @@ __device__ __forceinline__ void room3(int* ctr, int epoch) {
 // smaller ids, one lane read and compare per element, or its lane where the ids
 // come sorted; the other vertices go through a hash table in LDS, which leaves
 // each once, and are placed the same way. Longer rows, to kRowMax elements, do
-// the same with everything in LDS. The rate of vector instructions bounds these
-// kernels: sorting networks over the 64 lanes with four and eight slots each took
+// the same with everything in LDS. What bounds the kernels now is a row's chain of
+// loads and the memory behind it: two rows side by side on the halves of a
+// wavefront took as long (103 against 101 us a class). Before, it was the rate of
+// vector instructions: sorting networks over the 64 lanes with four and eight slots each took
 // some 700 exchanges a row, whatever its length, and kept for the long rows alone
 // they still cost the others their registers and some 200 spilled scalars. Over
 // the 53 large classes of the 29^3 planar-front coarsening a commit took 135 us
