@@ -1993,8 +1993,9 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
   for (int i = 0; i < count; ++i) {
     const pm_mesh_desc& d = meshes[i];
     if (!d.xy || !d.tri || !d.metric || d.mem_kind != PM_MEM_HOST || d.V < 3 || d.T < 1) return PM_E_ARG;
-    int64_t cv = d.V + headroom((int)std::min<int64_t>(d.V, 1 << 29));
-    int64_t ct = d.T + headroom((int)std::min<int64_t>(d.T, 1 << 29));
+    // (one mesh is packed and grown like any single one)
+    int64_t cv = d.V + (count > 1 ? headroom((int)std::min<int64_t>(d.V, 1 << 29)) : 0);
+    int64_t ct = d.T + (count > 1 ? headroom((int)std::min<int64_t>(d.T, 1 << 29)) : 0);
     if (vb[i] + cv > (1ll << 30) || tb[i] + ct > (1ll << 30)) return PM_E_ARG;
     vu[i] = (int)d.V;
     tu[i] = (int)d.T;
@@ -2042,7 +2043,7 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
   if (grow_vertices(m, nV) != PM_OK || grow_elements(m, nT) != PM_OK) return bail(PM_E_NOMEM);
   st.V = nV;
   st.T = nT;
-  if (dalloc(m, &st.vmesh, nV) != PM_OK || dalloc(m, &st.tmesh, nT) != PM_OK) return bail(PM_E_NOMEM);
+  if (count > 1 && (dalloc(m, &st.vmesh, nV) != PM_OK || dalloc(m, &st.tmesh, nT) != PM_OK)) return bail(PM_E_NOMEM);
   m->vbase = vb;
   m->tbase = tb;
   m->vused = vu;

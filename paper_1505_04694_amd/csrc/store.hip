@@ -790,7 +790,7 @@ __global__ void k_batch_in(const char* __restrict__ raw, int B, Store st, int* c
         if (in[b].tag >= 0) tag = ((const uint8_t*)(raw + in[b].tag))[v];
         else tag = (p.x == 0.0 ? 1 : 0) | (p.x == 1.0 ? 2 : 0) | (p.y == 0.0 ? 4 : 0) | (p.y == 1.0 ? 8 : 0);
       }
-      st.vmesh[i] = b;
+      if (st.vmesh) st.vmesh[i] = b;
       st.xy[i] = p;
       st.met[i] = m;
       st.tag[i] = tag;
@@ -813,7 +813,7 @@ __global__ void k_batch_in(const char* __restrict__ raw, int B, Store st, int* c
           else e = make_int4(z, x, y, 1);
         }
       }
-      st.tmesh[i] = b;
+      if (st.tmesh) st.tmesh[i] = b;
       st.tri[i] = e;
     }
   }

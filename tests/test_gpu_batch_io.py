@@ -31,3 +31,30 @@ def test_error_names_the_first_bad_mesh():
         mis[i].tri[-1, 2] = mis[i].V if i == 1 else -1
     with pytest.raises(pmesh.PMError, match="mesh 1: element id out of range"):
         pmesh.Batch([(mi.xy, mi.tri, mi.metric, mi.tags) for mi in mis])
+
+
+@pytest.mark.parametrize("quality", [pmesh.PM_QUALITY_MEAN_RATIO, pmesh.PM_QUALITY_VASILEVSKII])
+def test_batch_of_one_grows_past_its_first_size(quality):
+    """One mesh in a batch, refined to many times its slots before and after a
+    renumbering, is the mesh that a handle of its own gives."""
+    mi = inputs.refine_start()
+    b = pmesh.Batch.from_inputs([mi], seed=3, quality=quality)
+    m = pmesh.Mesh.from_input(mi, seed=3, quality=quality)
+
+    def same(where):
+        e, g = m.export(), b.export_mesh(0)
+        assert pmesh.pm_batch_sizes(b.h, 0) == m.sizes() == b.sizes(), where
+        for k in ("xy", "tri", "metric", "tags", "valive", "talive"):
+            assert np.array_equal(e[k], g[k]), f"{where}: {k}"
+
+    same("create")
+    for k in range(3):
+        for name in ("refine", "swap", "coarsen", "smooth"):
+            kw = dict(max_passes=2) if name == "refine" else dict(sweep=k)
+            sm, sb = getattr(m, name)(**kw), getattr(b, name)(**kw)
+            assert {k: v for k, v in sm.items() if k != "jp_iterations"} == \
+                {k: v for k, v in sb.items() if k != "jp_iterations"}, f"sweep {k} {name}"
+            same(f"sweep {k} {name}")
+    assert m.sizes()[0] > 4 * mi.V
+    (Q, qmin), (Qb, qb) = m.quality(), b.quality_per_mesh()
+    assert abs(Q - Qb[0]) <= 1e-12 * abs(Q) and qmin == qb[0]
