@@ -94,6 +94,7 @@ struct pm_mesh {
   double headroom = 3.0;  // pool and staging room, a multiple of the live entries
   double stage_scale = 1.0;  // grows when the staging area ran out
   int recoveries = 0;     // row rebuilds after running out of room, in the current phase
+  bool rows_ok = false;   // the rows are those of the element list (false: their last build failed)
   // Algorithm 1's loop state (pm_adapt): outer iteration, next phase, whether
   // the iteration has changed the mesh
   int ad_iter = 0, ad_phase = 1, ad_changed = 0;
@@ -486,6 +487,7 @@ constexpr int64_t kSmallPool = 1 << 24;  // entries: 64 MB a pool
 pm_status build_rows(pm_mesh* m, bool check = true) {
   Store& st = m->st;
   int V = st.V;
+  m->rows_ok = false;
   TRY(ensure(m, m->vt0, V));
   TRY(ensure(m, m->partial, scan_partials_needed(V)));
   // room for rows that outgrow their slot before the next rebuild: the
@@ -540,8 +542,12 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
   build_fill(st, place, m->s);
   dfree(m, own, places);
   build_finish(st, m->ctr, m->s);
+  m->rows_ok = true;
   return check ? check_err(m) : PM_OK;
 }
+// Before a call reads rows: a build that found no memory left them short of the
+// element list, or in blocks that are gone; built now, or the call fails too.
+pm_status rows_ready(pm_mesh* m) { return m->rows_ok ? PM_OK : build_rows(m); }
 
 // free pool space check between rounds: rebuild (repack) when a round could
 // plausibly exhaust it
@@ -880,6 +886,7 @@ pm_status run_rounds_in(pm_mesh* m, const pm_options* o, pm_stats* st, int kind)
 // rounds of colour -> classes -> op + commit (coarsen: kind 0, swap: kind 1);
 // vertices stay fixed through the rounds, so their records are built once
 pm_status run_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind) {
+  TRY(rows_ready(m));
   TRY(ensure(m, m->vr, (size_t)std::max(m->st.V, 1)));
   vertex_records(m->st, m->vr.p, m->s);
   m->st.vr = m->vr.p;
@@ -1511,6 +1518,7 @@ pm_status pm_mesh_export(pm_mesh* m, double* xy, int32_t* tri, double* metric, u
 pm_status pm_mesh_rows(pm_mesh* m, int64_t* nn_total, int64_t* ne_total, int64_t* nn_off, int32_t* nn,
                        int64_t* ne_off, int32_t* ne) {
   if (!m || !nn_total || !ne_total) return PM_E_ARG;
+  TRY(rows_ready(m));
   Store& st = m->st;
   std::vector<Hdr> hdr(st.V);
   std::vector<int2> cap(st.V);
@@ -1552,6 +1560,7 @@ pm_status pm_colour(pm_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* co
                     int32_t mem_kind) {
   if (!m) return PM_E_ARG;
   if (mem_kind != PM_MEM_HOST && mem_kind != PM_MEM_DEVICE) return fail(m, PM_E_ARG, "bad mem_kind");
+  TRY(rows_ready(m));
   TRY(ensure_phase_scratch(m));
   Store& st = m->st;
   const uint8_t* act_in = nullptr;
@@ -1607,6 +1616,7 @@ pm_status pm_smooth(pm_mesh* m, const pm_options* o, pm_stats* st) {
   pm_stats local;
   if (!st) st = &local;
   memset(st, 0, sizeof(*st));
+  TRY(rows_ready(m));
   TRY(ensure_phase_scratch(m));
   m->tune = o->tune;
   stats_zero(m);
@@ -1666,6 +1676,7 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
   pm_stats local;
   if (!st) st = &local;
   memset(st, 0, sizeof(*st));
+  TRY(rows_ready(m));
   stats_zero(m);
   Store& s = m->st;
   int B = s.B;
@@ -1778,6 +1789,7 @@ pm_status pm_refine(pm_mesh* m, const pm_options* o, pm_stats* st) {
 
 pm_status pm_quality(pm_mesh* m, double* Q, double* qmin, double* dQdx, double* dQdM) {
   if (!m) return PM_E_ARG;
+  if (dQdx || dQdM) TRY(rows_ready(m));
   int nparts = quality_parts(m);
   TRY(ensure(m, m->qpart, 2 * (size_t)nparts + 2));
   if (Q || qmin) {
@@ -1902,6 +1914,8 @@ pm_status pm_quality_noalloc(pm_mesh* m, double* Q, double* qmin, double* dQdx, 
   HIPCHK(hipGetDevice(&dev));
   if (!m->scratch || dev != m->dev)
     return fail(m, PM_E_ARG, "pm_quality_noalloc: call it with the handle's device current");
+  if ((dQdx || dQdM) && !m->rows_ok)
+    return fail(m, PM_E_NOMEM, "pm_quality_noalloc: the rows' last build found no memory (pm_quality builds them)");
   double* ps = m->scratch;
   if (Q || qmin) {
     mail_next(m->mail);

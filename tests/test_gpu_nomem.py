@@ -1,0 +1,74 @@
+"""Handles whose device memory runs out in the middle of a call: the call fails,
+and the handle goes on from the mesh it holds."""
+import numpy as np
+import pytest
+
+from paper_1505_04694_amd import inputs, pmesh
+from tests.parity import both, compare_mesh, compare_quality, compare_stats
+
+pytestmark = pytest.mark.gpu
+
+
+class Refusing:
+    """Blocks of torch's allocator; the n-th request from arm(n) on is refused."""
+
+    def __init__(self):
+        inner = pmesh.torch_allocator()
+        self.left, self.live = -1, {}
+
+        def alloc(nbytes, stream, user):
+            self.left -= 1
+            if self.left == 0:
+                return None
+            p = inner.alloc(nbytes, stream, user)
+            self.live[p] = nbytes
+            return p
+
+        def release(p, nbytes, stream, user):
+            assert self.live.pop(p) == nbytes
+            inner.release(p, nbytes, stream, user)
+
+        self.inner = inner
+        self.of = pmesh.Allocator(pmesh.ALLOC_FN(alloc), pmesh.RELEASE_FN(release), None)
+
+    def arm(self, n):
+        self.left = n
+
+
+@pytest.mark.parametrize("headroom", [1.0, 3.0])
+@pytest.mark.parametrize("make", [lambda: inputs.config2(33), lambda: inputs.refine_start(9, 4.0)], ids=["coarsens", "refines"])
+@pytest.mark.parametrize("cycle", [("coarsen", "refine")])
+def test_refused_allocations_leave_a_handle_that_goes_on(make, headroom, cycle):
+    """Every allocation of a cycle refused in turn, each on a fresh handle: what it
+    holds then is a mesh on which it and the oracle do the same from there."""
+    mi, refused = make(), 0
+    phases = ("coarsen", "refine", "swap", "smooth")
+    for n in range(1, 200):
+        a = Refusing()
+        gm = pmesh.Mesh.from_input(mi, seed=2, slack=1.0, pool_headroom=headroom, allocator=a.of)
+        a.arm(n)
+        failed = None
+        for name in cycle:
+            try:
+                getattr(gm, name)()
+            except pmesh.PMError as e:
+                assert e.status == pmesh.PM_E_NOMEM, f"request {n}, {name}: {e}"
+                failed = name
+                break
+        a.arm(-1)
+        if failed is None:
+            gm.close()
+            break
+        refused += 1
+        # (renumbered, where the phase left dead slots)
+        gm.coarsen(max_rounds=0)
+        e = gm.export()
+        assert e["valive"].all() and e["talive"].all()
+        om, _ = both(type(mi)(xy=e["xy"], tri=e["tri"], metric=e["metric"], tags=e["tags"]), 2)
+        compare_mesh(om, gm, f"request {n}, {failed}")
+        compare_quality(om, gm, f"request {n}, {failed}")
+        for name in phases:
+            compare_stats(getattr(om, name)(), getattr(gm, name)(), f"request {n}, {failed}, then {name}")
+        compare_mesh(om, gm, f"request {n}, {failed}, end")
+        gm.close()
+    assert failed is None and refused > 5
