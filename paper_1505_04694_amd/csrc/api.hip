@@ -608,6 +608,14 @@ Commit commit_of(pm_mesh* m) {
   return c;
 }
 
+// A phase that stops early, with status r, may leave vertices selected for its
+// next round, or coloured for it: no other phase sees them.
+pm_status round_left(pm_mesh* m, pm_status r) {
+  if (m->nxt.p) HIPCHK(hipMemsetAsync(m->nxt.p, 0, m->nxt.n, m->s));
+  if (m->rw.p) HIPCHK(hipMemsetAsync(m->rw.p, 0, sizeof(uint64_t) * m->rw.n, m->s));
+  return r;
+}
+
 struct Classes {
   int ncol = 0;
   std::vector<int> size, off;
@@ -892,7 +900,7 @@ pm_status run_rounds(pm_mesh* m, const pm_options* o, pm_stats* st, int kind) {
   m->st.vr = m->vr.p;
   pm_status r = run_rounds_in(m, o, st, kind);
   m->st.vr = nullptr;
-  return r;
+  return r == PM_OK ? r : round_left(m, r);
 }
 
 // One class of a round: the operation over its members, then the commit of
@@ -1575,7 +1583,8 @@ pm_status pm_colour(pm_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* co
   TRY(read_ctr(m, C_LIST_B, 1));
   int n = m->hctr[C_LIST_B];
   Classes cl;
-  TRY(colour_list(m, m->listA.p, n, Round{stream_seed(m->seed, ctx), m->rw.p}, cl));
+  pm_status r = colour_list(m, m->listA.p, n, Round{stream_seed(m->seed, ctx), m->rw.p}, cl);
+  if (r != PM_OK) return round_left(m, r);
   if (ncolours) *ncolours = cl.ncol;
   if (colour_out) {
     TRY(ensure(m, m->vt0, st.V));
@@ -1623,15 +1632,20 @@ pm_status pm_smooth(pm_mesh* m, const pm_options* o, pm_stats* st) {
   select_vertices(m->st, 3, 0.0, nullptr, nullptr, m->listA.p, m->ctr, m->sflag.p, m->spart.p, m->s);
   TRY(read_ctr(m, C_LIST_B, 1));
   int n = m->hctr[C_LIST_B];
+  // (before the colouring, whose round words are cleared at the end)
+  if (m->emet.n < (size_t)std::max(m->st.T, 1)) {
+    m->emet_topo = 0;
+    TRY(ensure(m, m->emet, (size_t)std::max(m->st.T, 1)));
+  }
   Classes cl;
-  TRY(colour_list(m, m->listA.p, n, Round{stream_seed(m->seed, make_ctx(o->sweep, PH_SMOOTH, 0)), m->rw.p}, cl));
+  pm_status rc = colour_list(m, m->listA.p, n, Round{stream_seed(m->seed, make_ctx(o->sweep, PH_SMOOTH, 0)), m->rw.p}, cl);
+  if (rc != PM_OK) return round_left(m, rc);
   st->v[1] = n;
   st->v[5] = cl.ncol;
   st->v[12] = cl.jp_iters;
   // topology and metrics stay fixed while smoothing: element tensors once,
   // and kept while the topology does not change
-  if (m->emet_topo != m->topo || m->emet.n < (size_t)std::max(m->st.T, 1)) {
-    TRY(ensure(m, m->emet, (size_t)std::max(m->st.T, 1)));
+  if (m->emet_topo != m->topo) {
     element_metrics(m->st, m->emet.p, m->s);
     m->emet_topo = m->topo;
   }

@@ -36,8 +36,9 @@ class Refusing:
 
 
 @pytest.mark.parametrize("headroom", [1.0, 3.0])
-@pytest.mark.parametrize("make", [lambda: inputs.config2(33), lambda: inputs.refine_start(9, 4.0)], ids=["coarsens", "refines"])
-@pytest.mark.parametrize("cycle", [("coarsen", "refine")])
+@pytest.mark.parametrize("make", [lambda: inputs.config2(33), lambda: inputs.refine_start(9, 4.0)],
+                         ids=["coarsens", "refines"])
+@pytest.mark.parametrize("cycle", [("coarsen", "refine"), ("coarsen", "refine", "swap", "smooth")])
 def test_refused_allocations_leave_a_handle_that_goes_on(make, headroom, cycle):
     """Every allocation of a cycle refused in turn, each on a fresh handle: what it
     holds then is a mesh on which it and the oracle do the same from there."""
