@@ -1479,9 +1479,10 @@ pm_status pm_mesh_create(const pm_mesh_desc* d, const pm_options* o, void* strea
   // stream is ordered after the conversions that read them
   dfree(m, tri3, 3 * (size_t)T);
   dfree(m, xyraw, 2 * (size_t)V);
-  if (single_ranges(m) != PM_OK) return bail(PM_E_DEVICE);
+  pm_status r = single_ranges(m);
+  if (r != PM_OK) return bail(r);
   k_validate(st, m->ctr, m->s);
-  pm_status r = check_err(m);
+  r = check_err(m);
   if (r != PM_OK) return bail(r);
   r = build_rows(m);
   if (r != PM_OK) return bail(r);
@@ -2076,7 +2077,8 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
   m->tbase = tb;
   m->vused = vu;
   m->tused = tu;
-  if (upload_ranges(m) != PM_OK) return bail(PM_E_DEVICE);
+  pm_status r = upload_ranges(m);
+  if (r != PM_OK) return bail(r);
   if (count == 1) build_start(nullptr, m->ranges, vu[0], tu[0], nV, nT, m->s);
   char* raw = nullptr;
   if (dalloc(m, &raw, bytes) != PM_OK) return bail(PM_E_NOMEM);
@@ -2093,7 +2095,7 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
     k_validate(st, m->ctr, m->s);
   }
   // (the copies have left the staging blocks)
-  pm_status r = ok ? read_ctr(m, 0, kRoundCtrs) : PM_E_DEVICE;
+  r = ok ? read_ctr(m, 0, kRoundCtrs) : PM_E_DEVICE;
   if (r != PM_OK) (void)hipStreamSynchronize(m->s);
   up.done();
   dfree(m, raw, bytes);

@@ -73,3 +73,19 @@ def test_refused_allocations_leave_a_handle_that_goes_on(make, headroom, cycle):
         compare_mesh(om, gm, f"request {n}, {failed}, end")
         gm.close()
     assert failed is None and refused > 5
+
+
+def test_refused_allocations_of_a_creation_fail_as_such():
+    mi, batch, refused = inputs.config2(17), [inputs.make_mesh(k, jitter_seed=k) for k in (9, 5, 7)], 0
+    for make in (lambda a: pmesh.Mesh.from_input(mi, allocator=a), lambda a: pmesh.Batch.from_inputs(batch, allocator=a)):
+        for n in range(1, 60):
+            a = Refusing()
+            a.arm(n)
+            try:
+                make(a.of).close()
+            except pmesh.PMError as e:
+                assert e.status == pmesh.PM_E_NOMEM, f"request {n}: {e}"
+                refused += 1
+            if a.left > 0:
+                break
+    assert refused > 20
