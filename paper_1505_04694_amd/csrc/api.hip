@@ -235,6 +235,16 @@ pm_status dalloc(pm_mesh* m, T** p, size_t n) {
   m->peak_bytes = std::max(m->peak_bytes, m->cur_bytes);
   return PM_OK;
 }
+template <class T>
+void dfree(pm_mesh* m, T*& p, size_t n);
+// arrays of n entries each (null before the call): all of them, or none
+template <class... T>
+pm_status dalloc_all(pm_mesh* m, size_t n, T*&... p) {
+  pm_status r = PM_OK;
+  ((r = r == PM_OK ? dalloc(m, &p, n) : r), ...);
+  if (r != PM_OK) (dfree(m, p, n), ...);
+  return r;
+}
 // the handle's pinned block: the counter mirror, 64 doubles, and kAuxInts ints
 constexpr int kAuxInts = 16384;
 static_assert(C_COUNT * sizeof(int) + 64 * sizeof(double) + kAuxInts * sizeof(int) < kPinnedBytes, "pinned block");
@@ -387,17 +397,12 @@ pm_status grow_vertices(pm_mesh* m, int need) {
   Store& s = m->st;
   if (need <= s.Vcap) return PM_OK;
   int nc = std::max(need, s.Vcap + s.Vcap / 2);
-  double2* xy;
-  Met* met;
-  uint8_t *tag, *va;
-  Hdr* hdr;
-  int2* cap;
-  TRY(dalloc(m, &xy, nc));
-  TRY(dalloc(m, &met, nc));
-  TRY(dalloc(m, &tag, nc));
-  TRY(dalloc(m, &va, nc));
-  TRY(dalloc(m, &hdr, nc));
-  TRY(dalloc(m, &cap, nc));
+  double2* xy = nullptr;
+  Met* met = nullptr;
+  uint8_t *tag = nullptr, *va = nullptr;
+  Hdr* hdr = nullptr;
+  int2* cap = nullptr;
+  TRY(dalloc_all(m, nc, xy, met, tag, va, hdr, cap));
   // one launch; the old blocks go back to this stream's cache, where only later
   // work can take them
   Store to = s;
@@ -733,11 +738,16 @@ pm_status compact_one(pm_mesh* m) {
   int nV = m->hctr[C_TOTAL], nT = m->hctr[C_TOTAL2];
   if (nV == st.V && nT == st.T) return check_err(m, true);
   Store to = st;
-  TRY(dalloc(m, &to.xy, st.Vcap));
-  TRY(dalloc(m, &to.met, st.Vcap));
-  TRY(dalloc(m, &to.tag, st.Vcap));
-  TRY(dalloc(m, &to.valive, st.Vcap));
+  to.xy = nullptr;
+  to.met = nullptr;
+  to.tag = to.valive = nullptr;
+  to.tri = nullptr;
   TRY(dalloc(m, &to.tri, st.Tcap));
+  pm_status r = dalloc_all(m, st.Vcap, to.xy, to.met, to.tag, to.valive);
+  if (r != PM_OK) {
+    dfree(m, to.tri, st.Tcap);
+    return r;
+  }
   compact_vertices(st, m->vt1.p, to.xy, to.met, to.tag, to.valive, m->s);
   compact_elements(st, m->vt1.p, m->tt1.p, to.tri, m->s);
   clear_tail(to, nV, nT, m->s);
@@ -782,8 +792,8 @@ pm_status compact(pm_mesh* m, const std::vector<int>* extra_v = nullptr, const s
   for (int i = 0; i < B; ++i) {
     int lv = live[i], lt = live[B + i];
     int ev = extra_v ? (*extra_v)[i] : 0, et = extra_t ? (*extra_t)[i] : 0;
-    int cv = B == 1 ? lv : lv + ev + headroom(lv + ev);
-    int ct = B == 1 ? lt : lt + et + headroom(lt + et);
+    int cv = lv + ev + headroom(lv + ev);
+    int ct = lt + et + headroom(lt + et);
     if ((int64_t)nvb[i] + cv > (1ll << 30) || (int64_t)ntb[i] + ct > (1ll << 30))
       return fail(m, PM_E_NOMEM, "store beyond 2^30 slots");
     nvb[i + 1] = nvb[i] + cv;
@@ -794,45 +804,44 @@ pm_status compact(pm_mesh* m, const std::vector<int>* extra_v = nullptr, const s
   HIPCHK(hipMemcpyAsync(m->rtmp.p + B + 1, ntb.data(), sizeof(int) * (B + 1), hipMemcpyHostToDevice, m->s));
   mesh_maps(m->vt0.p, m->vt1.p, st.vmesh, st.vbase, m->rtmp.p, V, m->vt2.p, m->s);
   mesh_maps(m->tt0.p, m->tt1.p, st.tmesh, st.tbase, m->rtmp.p + B + 1, T, m->tt2.p, m->s);
-  int vcap = std::max(B == 1 ? st.Vcap : nV, 1), tcap = std::max(B == 1 ? st.Tcap : nT, 1);
-  double2* xy2;
-  Met* met2;
-  uint8_t *tag2, *va2;
-  Elem* tri2;
-  TRY(dalloc(m, &xy2, vcap));
-  TRY(dalloc(m, &met2, vcap));
-  TRY(dalloc(m, &tag2, vcap));
-  TRY(dalloc(m, &va2, vcap));
-  TRY(dalloc(m, &tri2, tcap));
+  int vcap = std::max(nV, 1), tcap = std::max(nT, 1);
+  double2* xy2 = nullptr;
+  Met* met2 = nullptr;
+  uint8_t *tag2 = nullptr, *va2 = nullptr;
+  Elem* tri2 = nullptr;
+  int *vmesh2 = nullptr, *tmesh2 = nullptr;
+  Hdr* hdr2 = nullptr;
+  int2* cap2 = nullptr;
+  TRY(dalloc_all(m, vcap, xy2, met2, tag2, va2, vmesh2, hdr2, cap2));
+  pm_status r = dalloc_all(m, tcap, tri2, tmesh2);
+  if (r != PM_OK) {
+    dfree(m, xy2, vcap);
+    dfree(m, met2, vcap);
+    dfree(m, tag2, vcap);
+    dfree(m, va2, vcap);
+    dfree(m, vmesh2, vcap);
+    dfree(m, hdr2, vcap);
+    dfree(m, cap2, vcap);
+    return r;
+  }
   HIPCHK(hipMemsetAsync(va2, 0, vcap, m->s));
   HIPCHK(hipMemsetAsync(tri2, 0, sizeof(Elem) * (size_t)tcap, m->s));
   compact_vertices(st, m->vt2.p, xy2, met2, tag2, va2, m->s);
   compact_elements(st, m->vt2.p, m->tt2.p, tri2, m->s);
-  int *vmesh2 = nullptr, *tmesh2 = nullptr;
-  if (B > 1) {
-    TRY(dalloc(m, &vmesh2, vcap));
-    TRY(dalloc(m, &tmesh2, tcap));
-    fill_mesh_ids(m->rtmp.p, B, nV, vmesh2, m->s);
-    fill_mesh_ids(m->rtmp.p + B + 1, B, nT, tmesh2, m->s);
-  }
+  fill_mesh_ids(m->rtmp.p, B, nV, vmesh2, m->s);
+  fill_mesh_ids(m->rtmp.p + B + 1, B, nT, tmesh2, m->s);
+  // headers and capacities follow the new slot count
+  HIPCHK(hipMemsetAsync(hdr2, 0, sizeof(Hdr) * (size_t)vcap, m->s));
+  HIPCHK(hipMemsetAsync(cap2, 0, sizeof(int2) * (size_t)vcap, m->s));
   HIPCHK(hipStreamSynchronize(m->s));
-  if (B > 1) {
-    // headers and capacities follow the new slot count
-    Hdr* hdr2;
-    int2* cap2;
-    TRY(dalloc(m, &hdr2, vcap));
-    TRY(dalloc(m, &cap2, vcap));
-    HIPCHK(hipMemsetAsync(hdr2, 0, sizeof(Hdr) * (size_t)vcap, m->s));
-    HIPCHK(hipMemsetAsync(cap2, 0, sizeof(int2) * (size_t)vcap, m->s));
-    dfree(m, st.hdr, st.Vcap);
-    dfree(m, st.cap, st.Vcap);
-    st.hdr = hdr2;
-    st.cap = cap2;
-    dfree(m, st.vmesh, st.Vcap);
-    dfree(m, st.tmesh, st.Tcap);
-    st.vmesh = vmesh2;
-    st.tmesh = tmesh2;
-  }
+  dfree(m, st.hdr, st.Vcap);
+  dfree(m, st.cap, st.Vcap);
+  st.hdr = hdr2;
+  st.cap = cap2;
+  dfree(m, st.vmesh, st.Vcap);
+  dfree(m, st.tmesh, st.Tcap);
+  st.vmesh = vmesh2;
+  st.tmesh = tmesh2;
   dfree(m, st.xy, st.Vcap);
   dfree(m, st.met, st.Vcap);
   dfree(m, st.tag, st.Vcap);
@@ -1460,8 +1469,10 @@ pm_status pm_mesh_create(const pm_mesh_desc* d, const pm_options* o, void* strea
   hipMemcpyKind kind = d->mem_kind == PM_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
   int* tri3 = nullptr;
   double* xyraw = nullptr;
-  if (dalloc(m, &tri3, 3 * (size_t)T) != PM_OK || dalloc(m, &xyraw, 2 * (size_t)V) != PM_OK)
+  if (dalloc(m, &tri3, 3 * (size_t)T) != PM_OK || dalloc(m, &xyraw, 2 * (size_t)V) != PM_OK) {
+    dfree(m, tri3, 3 * (size_t)T);
     return bail(PM_E_NOMEM);
+  }
   bool ok = hipMemcpyAsync(tri3, d->tri, sizeof(int) * 3 * (size_t)T, kind, m->s) == hipSuccess &&
             hipMemcpyAsync(xyraw, d->xy, sizeof(double) * 2 * (size_t)V, kind, m->s) == hipSuccess &&
             hipMemcpyAsync(st.met, d->metric, sizeof(double) * 3 * (size_t)V, kind, m->s) == hipSuccess;

@@ -1,10 +1,11 @@
 """Handles whose device memory runs out in the middle of a call: the call fails,
 and the handle goes on from the mesh it holds."""
-import numpy as np
 import pytest
 
 from paper_1505_04694_amd import inputs, pmesh
+from oracle.orc import OracleMesh
 from tests.parity import both, compare_mesh, compare_quality, compare_stats
+from tests.test_gpu_batch import compare_one
 
 pytestmark = pytest.mark.gpu
 
@@ -59,6 +60,7 @@ def test_refused_allocations_leave_a_handle_that_goes_on(make, headroom, cycle):
         a.arm(-1)
         if failed is None:
             gm.close()
+            assert not a.live
             break
         refused += 1
         # (renumbered, where the phase left dead slots)
@@ -72,10 +74,11 @@ def test_refused_allocations_leave_a_handle_that_goes_on(make, headroom, cycle):
             compare_stats(getattr(om, name)(), getattr(gm, name)(), f"request {n}, {failed}, then {name}")
         compare_mesh(om, gm, f"request {n}, {failed}, end")
         gm.close()
+        assert not a.live, f"request {n}, {failed}: blocks not given back"
     assert failed is None and refused > 5
 
 
-def test_refused_allocations_of_a_creation_fail_as_such():
+def test_refused_allocations_of_a_creation_are_all_given_back():
     mi, batch, refused = inputs.config2(17), [inputs.make_mesh(k, jitter_seed=k) for k in (9, 5, 7)], 0
     for make in (lambda a: pmesh.Mesh.from_input(mi, allocator=a), lambda a: pmesh.Batch.from_inputs(batch, allocator=a)):
         for n in range(1, 60):
@@ -86,6 +89,41 @@ def test_refused_allocations_of_a_creation_fail_as_such():
             except pmesh.PMError as e:
                 assert e.status == pmesh.PM_E_NOMEM, f"request {n}: {e}"
                 refused += 1
+            assert not a.live, f"request {n}: blocks not given back"
             if a.left > 0:
                 break
     assert refused > 20
+
+
+def test_refused_allocations_in_a_batch():
+    """The same with three meshes, which outgrow their ranges and are laid out again."""
+    mis, refused = [inputs.refine_start(k, 4.0) for k in (9, 4, 6)], 0
+    phases = ("coarsen", "refine", "swap", "smooth")
+    for n in range(1, 200):
+        a = Refusing()
+        b = pmesh.Batch.from_inputs(mis, seed=2, allocator=a.of)
+        a.arm(n)
+        failed = None
+        for name in phases:
+            try:
+                getattr(b, name)()
+            except pmesh.PMError as e:
+                assert e.status == pmesh.PM_E_NOMEM, f"request {n}, {name}: {e}"
+                failed = name
+                break
+        a.arm(-1)
+        if failed:
+            refused += 1
+            b.coarsen(max_rounds=0)
+            es = [b.export_mesh(i) for i in range(3)]
+            oms = [OracleMesh(e["xy"], e["tri"], e["metric"], e["tags"], seed=2) for e in es]
+            for name in phases:
+                getattr(b, name)()
+                for i, om in enumerate(oms):
+                    getattr(om, name)()
+                    compare_one(om.export(), b.export_mesh(i), f"request {n}, {failed}, then {name}, mesh {i}")
+        b.close()
+        assert not a.live, f"request {n}, {failed}: blocks not given back"
+        if failed is None:
+            break
+    assert failed is None and refused > 20
