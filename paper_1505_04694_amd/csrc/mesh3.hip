@@ -2003,6 +2003,7 @@ struct pm3_mesh {
   int epoch = 0;
   int64_t top_base = 0, top_per = 0;
   double headroom = 3.0;  // pool_headroom of the creation options
+  bool rows_ok = false;   // the rows are those of the element list (false: their last build failed)
 };
 
 namespace {
@@ -2183,6 +2184,7 @@ pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
 pm_status build_rows(pm3_mesh* m, bool all_live) {
   Store3& st = m->st;
   int V = st.V;
+  m->rows_ok = false;
   k_fill_int<<<grid(V + 1), kB, 0, m->s>>>(m->cnt, V + 1, 0);
   struct Temp {
     int4* p = nullptr;
@@ -2220,8 +2222,12 @@ pm_status build_rows(pm3_mesh* m, bool all_live) {
   m->top_per = (m->necap - total) / kTopStripes;
   k_tops_init<<<1, kTopStripes, 0, m->s>>>(m->tops, m->top_base, m->top_per, m->ctr);
   H3(hipGetLastError());
+  m->rows_ok = true;
   return PM_OK;
 }
+// Before a call reads rows: after a build that found no memory they are not those
+// of the element list; built now, or the call fails too.
+pm_status rows_ready(pm3_mesh* m) { return m->rows_ok ? PM_OK : build_rows(m, false); }
 
 // list of the vertices selected by mode, in m->A; returns its length
 pm_status select_list(pm3_mesh* m, int mode, double L_low2, int* n) {
@@ -2502,6 +2508,7 @@ pm_status pm3_mesh_export(pm3_mesh* m, double* xyz, int32_t* tet, double* metric
 pm_status pm3_mesh_rows(pm3_mesh* m, int64_t* nn_total, int64_t* ne_total, int64_t* nn_off, int32_t* nn,
                         int64_t* ne_off, int32_t* ne) {
   if (!m) return PM_E_ARG;
+  T3(rows_ready(m));
   Store3& st = m->st;
   int V = st.V;
   std::vector<int4> hdr(V);
@@ -2536,6 +2543,7 @@ pm_status pm3_mesh_rows(pm3_mesh* m, int64_t* nn_total, int64_t* ne_total, int64
 
 pm_status pm3_colour(pm3_mesh* m, const uint8_t* active, uint32_t ctx, int32_t* colour_out, int32_t* ncolours) {
   if (!m) return PM_E_ARG;
+  T3(rows_ready(m));
   Store3& st = m->st;
   int n = 0;
   if (active) {
@@ -2575,6 +2583,7 @@ pm_status pm3_coarsen(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   double qmin3 = (o->q_min * o->q_min) * o->q_min;
   int n = 0, ncol = 0;
   bool lists = false;
+  T3(rows_ready(m));
   T3(zero_ctr(m));
   T3(select_list(m, 0, o->L_low2, &n));
   k_fill_u8<<<grid(st.V), kB, 0, m->s>>>(m->nxt, st.V, 0);
@@ -2661,6 +2670,7 @@ pm_status pm3_refine(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   int64_t sv[16] = {};
   int p = 0;
   bool done = false;
+  T3(rows_ready(m));
   for (; p < o->refine_passes; ++p) {
     int V0 = st.V, T0 = st.T;
     T3(zero_ctr(m));
@@ -2698,6 +2708,7 @@ pm_status pm3_smooth(pm3_mesh* m, const pm_options* o, pm_stats* out) {
   Store3& st = m->st;
   int64_t sv[16] = {};
   int n = 0;
+  T3(rows_ready(m));
   T3(select_list(m, 2, 0.0, &n));
   int ncol = 0;
   bool lists;

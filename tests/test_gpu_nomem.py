@@ -1,8 +1,9 @@
 """Handles whose device memory runs out in the middle of a call: the call fails,
 and the handle goes on from the mesh it holds."""
+import numpy as np
 import pytest
 
-from paper_1505_04694_amd import inputs, pmesh
+from paper_1505_04694_amd import inputs, pmesh, pmesh3
 from oracle.orc import OracleMesh
 from tests.parity import both, compare_mesh, compare_quality, compare_stats
 from tests.test_gpu_batch import compare_one
@@ -127,3 +128,29 @@ def test_refused_allocations_in_a_batch():
         if failed is None:
             break
     assert failed is None and refused > 20
+
+
+def test_tetrahedra_whose_rows_do_not_fit_keep_their_mesh():
+    """A refinement to more tetrahedra than the pools' 2^31 entries hold at the
+    largest headroom: it fails, calls that need rows fail after it, and the mesh
+    that it made is there to export."""
+    n = 73
+    xyz, tet = inputs.cube_grid(n)
+    met = np.tile([1.0, 0.0, 0.0, 1.0, 0.0, 1.0], (len(xyz), 1))
+    met[xyz[:, 0] < 0.12] *= 4.0
+    m = pmesh3.Mesh3(xyz, tet, met, inputs.unit_cube_tags(xyz), seed=1, pool_headroom=64.0)
+    L_up2 = 3.5 / (n - 1) ** 2  # every edge in the dense part, none in the rest
+    for call in (lambda: m.refine(L_up2), lambda: m.coarsen(0), lambda: m.smooth(), m.rows, m.colour):
+        with pytest.raises(pmesh.PMError) as e:
+            call()
+        assert e.value.status == pmesh.PM_E_NOMEM
+    V, T = m.sizes()
+    assert 3 * 65 * 4 * T > 2 ** 31 and V > len(xyz)
+    g = m.export()
+    assert g["talive"].all() and g["tet"].max() == V - 1
+    p = g["xyz"][g["tet"]]
+    d = p[:, 1:] - p[:, :1]
+    vol = (d[:, 0] * np.cross(d[:, 1], d[:, 2])).sum(1) / 6.0
+    assert vol.min() > 0.0 and abs(vol.sum() - 1.0) < 1e-9
+    assert np.isfinite(m.quality()[0])
+    m.close()
