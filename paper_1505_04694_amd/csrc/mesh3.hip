@@ -1070,7 +1070,9 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A
   if (n <= kSolveThreads) solve3<1>(st, A, n, recs, act, col, sseed, cl, ctr);
   else solve3<kSolve / kSolveThreads>(st, A, n, recs, act, col, sseed, cl, ctr);
   __syncthreads();
-  for (int i = tid; i < n; i += kSolveThreads) atomicAdd(&hist[cl[i]], 1);
+  // (a place without a colour, 0xFFFF, is an error that the host sees)
+  for (int i = tid; i < n; i += kSolveThreads)
+    if (cl[i] < kMaxColours) atomicAdd(&hist[cl[i]], 1);
   __syncthreads();
   int h = tid < kMaxColours ? hist[tid] : 0, incl = h, lane = __lane_id();
   if (h) atomicMax(&ncol, tid + 1);
@@ -1094,7 +1096,8 @@ __global__ void __launch_bounds__(kSolveThreads) k_solve(Store3 st, const int* A
     cnt[tid] = h;
   }
   __syncthreads();
-  for (int i = tid; i < n; i += kSolveThreads) cls[atomicAdd(&cur[cl[i]], 1)] = A[i];
+  for (int i = tid; i < n; i += kSolveThreads)
+    if (cl[i] < kMaxColours) cls[atomicAdd(&cur[cl[i]], 1)] = A[i];
 }
 
 __global__ void k_fill_int(int* p, int n, int x) {
