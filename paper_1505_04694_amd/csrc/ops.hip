@@ -1332,18 +1332,21 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
   int id = own ? slots[l] : INT_MAX, nx = own ? slots[G + l] : INT_MAX, pv = own ? slots[2 * G + l] : -1;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  int nn_ = fits ? n : 0, rid = 0, rnx = 0;
+  int nn_ = fits ? n : 0, rid = 0, rnx = 0, same = 0;
   bool found = false;
   each_other<G>(id, nn_, [&](int o) { rid += o < id ? 1 : 0; });
   each_other<G>(nx, nn_, [&](int o) {
     rnx += o < nx ? 1 : 0;
+    same += o == nx ? 1 : 0;
     found |= o == pv;
   });
+  // a next vertex that comes twice (a wavefront's lanes also meet themselves)
+  bool twice = gballot(own && same > (G == 64 ? 1 : 0)) != 0;
   uint64_t lone = gballot(own && !found);
   int nextra = __popcll(lone);
   int ex = nextra ? __shfl(pv, gb + __ffsll((unsigned long long)lone) - 1) : INT_MAX;
   int exat = __popcll(gballot(own && nx < ex));
-  bool reg = fits && nextra <= 1;
+  bool reg = fits && nextra <= 1 && !twice;
   int nq = n + nextra;
   if (own && ex < nx) ++rnx;
   // slots: in place when the row fits, else fresh pool space
