@@ -1354,13 +1354,19 @@ void mail_send(Mail& b, const int* src, int n, int* dst, hipStream_t s) {
   mail_next(b);
   k_mail<<<1, kBlock, 0, s>>>(src, n, dst, (int*)b.at, b.no);
 }
+// (like the runtime's own wait for a stream, this polls on a core for as long as the
+// work takes)
 hipError_t mail_wait(const Mail& b, hipStream_t s) {
+  hipError_t launch = hipPeekAtLastError();
   for (int64_t k = 1;; ++k) {
     if (__atomic_load_n(b.at, __ATOMIC_ACQUIRE) == b.no) return hipSuccess;
     __builtin_ia32_pause();
     if (k % 16384 == 0) {  // a fraction of a millisecond: has the stream failed?
       hipError_t e = hipStreamQuery(s);
-      if (e == hipSuccess) return __atomic_load_n(b.at, __ATOMIC_ACQUIRE) == b.no ? hipSuccess : hipErrorUnknown;
+      if (e == hipSuccess) {
+        if (__atomic_load_n(b.at, __ATOMIC_ACQUIRE) == b.no) return hipSuccess;
+        return launch != hipSuccess ? launch : hipErrorUnknown;  // the letter was not launched
+      }
       if (e != hipErrorNotReady) return e;
       (void)hipGetLastError();
       if (k > (1 << 20)) std::this_thread::yield();
