@@ -1992,7 +1992,12 @@ struct Upload {
       if (at == 0) {
         if (!block[cur]) {
           block[cur] = (char*)pm::stage_take();
-          if (!block[cur] || hipEventCreateWithFlags(&ev[cur], hipEventDisableTiming) != hipSuccess) return false;
+          if (!block[cur]) {  // no pinned memory: straight from the caller's, which outlives the copy
+            bool ok = n == 0 || hipMemcpyAsync(dst, from, n, hipMemcpyHostToDevice, s) == hipSuccess;
+            dst += n + pad;
+            return ok;
+          }
+          if (hipEventCreateWithFlags(&ev[cur], hipEventDisableTiming) != hipSuccess) return false;
         }
         if (busy[cur] && hipEventSynchronize(ev[cur]) != hipSuccess) return false;
         busy[cur] = false;
@@ -2112,11 +2117,11 @@ pm_status pm_batch_create(const pm_mesh_desc* meshes, int32_t count, const pm_op
     k_validate(st, m->ctr, m->s);
   }
   // (the copies have left the staging blocks)
-  r = ok ? read_ctr(m, 0, kRoundCtrs) : PM_E_DEVICE;
+  r = ok ? read_ctr(m, 0, kRoundCtrs) : fail(m, PM_E_DEVICE, "upload of the batch");
   if (r != PM_OK) (void)hipStreamSynchronize(m->s);
   up.done();
   dfree(m, raw, bytes);
-  if (r != PM_OK) return bail(PM_E_DEVICE);
+  if (r != PM_OK) return bail(r);
   if (m->hctr[C_FAILEP] != INT_MAX) {
     m->err = "mesh " + std::to_string(m->hctr[C_FAILEP]) + ": element id out of range";
     return bail(PM_E_MESH);
@@ -2164,9 +2169,8 @@ pm_status pm_batch_export(pm_mesh* m, int32_t i, double* xy, int32_t* tri, doubl
   bo.tag = take(tags, nv);
   bo.valive = take(valive, nv);
   bo.talive = take(talive, nt);
-  if (bytes <= (int64_t)kStageBytes) {
-    char* b = (char*)stage_take();
-    if (!b) return fail(m, PM_E_NOMEM, "pinned memory");
+  char* b = bytes <= (int64_t)kStageBytes ? (char*)stage_take() : nullptr;
+  if (b) {
     batch_out(st, v0, nv, t0, nt, bo, b, m->s);
     mail_send(m->mail, m->ctr, 0, m->hctr, m->s);
     hipError_t e = mail_wait(m->mail, m->s);
