@@ -172,7 +172,9 @@ typedef struct {
  * v[8] vertices created, v[9] elements created
  * v[10] deferred-update records committed
  * v[11] adjacency rows relocated by the commit
- * v[12] JP colouring iterations
+ * v[12] JP colouring iterations: launches over the waiting vertices, and where one
+ *       work-group colours (short lists, the end of long ones) the most passes
+ *       that one of its threads made, which may differ between runs
  * v[13] rounds whose rows were rebuilt after the pools or the staging area
  *       ran out of room
  * pm_adapt sums its phases' counters, with v[0] = outer iterations run. */

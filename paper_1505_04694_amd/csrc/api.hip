@@ -690,7 +690,7 @@ pm_status colour_list(pm_mesh* m, const int* A, int n, Round rd, Classes& out) {
     class_lists(A, n, rd.rw, m->ctr, m->cls.p, m->ctab.p, m->ctabs.p, m->spart.p, 256, 0, m->s);
     TRY(read_ctr(m, 0, C_NCOL + 1));
   }
-  out.jp_iters = it;
+  out.jp_iters = it + (finish ? m->hctr[C_JPIT] : 0);
   // the iterations to run before the finish next time: until no more than
   // kFinish wait (the counts of the last seven are there; a further iteration
   // takes 7 us, solving 8,000 vertices 60 and 2,000 vertices 15); without the

@@ -39,6 +39,7 @@ enum Ctr {
   C_ACC_COL = 24,   // vertices coloured, colours and colouring iterations of the rounds run
   C_ACC_NCOL = 25,
   C_ACC_IT = 26,
+  C_JPIT = 27,      // passes of the one-block finish of a colouring
   C_JPN = 31,       // length of the list the one-block finish takes (-1: too many wait)
   C_JPL = 32,       // 32..39: JP vertices left by iteration modulo 8, before the one-block finish
   C_HIST = 64,      // 64..319: colour histogram (class sizes)

@@ -725,6 +725,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_jp_gather(const int* __restri
   constexpr int NT = kSmallThreads;
   __shared__ int offs[NT], wsum[NT / kWave], left;
   int tid = (int)threadIdx.x, lane = __lane_id(), wv = tid / kWave;
+  if (tid == 0) ctr[C_JPIT] = 0;
   // wavefront w adds up what the iterations w modulo 8 left
   if (wv < 8) {
     int x = ctr[C_STRIPE + lane * kStripeW + S_JPL + wv];
@@ -779,7 +780,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_jp_solve(Store st, const int*
   if (n <= 2 * kSmallThreads) solve_items<kSmallThreads, 2>(st, A, n, recs, rd, col, ctr, &its, &visits);
   else solve_items<kSmallThreads, kSmallColour / kSmallThreads>(st, A, n, recs, rd, col, ctr, &its, &visits);
   __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(ctr + C_STRIPE + S_PJP, visits);
+  if (threadIdx.x == 0) {
+    ctr[C_JPIT] = its;
+    atomicAdd(ctr + C_STRIPE + S_PJP, visits);
+  }
 }
 void jp_finish(const Store& st, int n, const int* W, const int* cnt, Round rd, JpRec* recs, int* list, int* ctr, int it,
                hipStream_t s) {

@@ -4,7 +4,7 @@ with more predecessors than a record holds, against the oracle's greedy one."""
 import numpy as np
 import pytest
 
-from paper_1505_04694_amd import inputs
+from paper_1505_04694_amd import inputs, pmesh
 from tests.parity import both
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +36,15 @@ def test_colour_high_degree(k):
     mi = inputs.fan(k, hubs=2, radius=0.3, layers=-1)
     check(mi, (mi.V, mi.V - 5), seed=1)
     check(mi, (mi.V,), seed=4)
+
+
+def test_iterations_count_the_one_block_finish():
+    """A long list's iterations are its launches, and at least one pass in the finish
+    that colours what they leave."""
+    m = pmesh.Mesh.from_input(inputs.make_mesh(257, jitter_seed=4))
+    m.smooth()  # the next call stops iterating where the finish takes over
+    m.profile(1 << pmesh.KERNELS.index("jp"))
+    st = m.smooth(sweep=1)
+    p = m.profile_read(["jp"])["jp"]
+    assert p["launches"] > 1 and st["jp_iterations"] >= p["launches"]
+    m.close()
