@@ -143,7 +143,10 @@ typedef struct {
   double slack;           /* adjacency row capacity factor (>= 1), at creation  */
   double pool_headroom;   /* free room kept in the adjacency pools and the
                              commit's staging area, as a multiple of the live
-                             entries (>= 1), at creation. A round that runs out
+                             entries (>= 1), at creation; pools of less than
+                             64 MB are sized by a bound on the entries, about
+                             twice as many, where memory for that is to be had
+                             (and the headroom is 3 or more). A round that runs out
                              has its rows rebuilt from the element list with
                              twice the room and goes on, so results do not
                              depend on it; less room uses less device memory

@@ -484,7 +484,10 @@ pm_status single_ranges(pm_mesh* m) {
   return upload_ranges(m);
 }
 
-constexpr int64_t kSmallPool = 1 << 24;  // entries: 64 MB a pool
+// Pools of up to so many entries (64 MB each) are sized by a bound on the rows,
+// without a read-back of what they need: 3-5 % of an adaptation of some thousand
+// elements, nothing at half a million.
+constexpr int64_t kSmallPool = 1 << 24;
 
 // (Re)build every adjacency row from the element list into fresh pools.
 // check: read the error bits back at the end (else they stay set for the
@@ -524,7 +527,11 @@ pm_status build_rows(pm_mesh* m, bool check = true) {
     }
     return PM_OK;
   };
-  if (!fits && small) TRY(pools((int64_t)bound, (int64_t)bound));
+  if (!fits && small) {
+    pm_status r = pools((int64_t)bound, (int64_t)bound);
+    if (r != PM_OK && r != PM_E_NOMEM) return r;
+    small = r == PM_OK;  // (no memory for the bound: by the entries)
+  }
   // the incidences' places lie in the NN pool, which the row finish writes last
   int64_t places = 3 * (int64_t)st.T;
   place = st.nn_pool >= places ? st.nn : nullptr;

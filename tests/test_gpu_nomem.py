@@ -12,15 +12,16 @@ pytestmark = pytest.mark.gpu
 
 
 class Refusing:
-    """Blocks of torch's allocator; the n-th request from arm(n) on is refused."""
+    """Blocks of torch's allocator; the n-th request from arm(n) on is refused, and
+    every one of more than `largest` bytes."""
 
-    def __init__(self):
+    def __init__(self, largest=1 << 62):
         inner = pmesh.torch_allocator()
         self.left, self.live = -1, {}
 
         def alloc(nbytes, stream, user):
             self.left -= 1
-            if self.left == 0:
+            if self.left == 0 or nbytes > largest:
                 return None
             p = inner.alloc(nbytes, stream, user)
             self.live[p] = nbytes
@@ -154,3 +155,25 @@ def test_tetrahedra_whose_rows_do_not_fit_keep_their_mesh():
     assert vol.min() > 0.0 and abs(vol.sum() - 1.0) < 1e-9
     assert np.isfinite(m.quality()[0])
     m.close()
+
+
+def test_pools_without_memory_for_their_bound_take_the_rows_size():
+    """The pools of a small mesh have room for a bound on the rows' entries, about twice
+    as many; memory for the headroom times the entries themselves is enough."""
+    mi = inputs.make_mesh(33)
+    ref = pmesh.Mesh.from_input(mi)
+    bound = 4 * (3 * (9 * mi.T + 9 * mi.V) + 4096)  # slack 2: 3 T (1 + 2) + V (2 + 7) entries
+    for largest, fits in ((bound, True), (bound * 3 // 4, True), (bound // 4, False)):
+        a = Refusing(largest)
+        if not fits:
+            with pytest.raises(pmesh.PMError) as e:
+                pmesh.Mesh.from_input(mi, allocator=a.of)
+            assert e.value.status == pmesh.PM_E_NOMEM
+        else:
+            m = pmesh.Mesh.from_input(mi, allocator=a.of)
+            assert (max(a.live.values()) > bound * 9 // 10) == (largest == bound)
+            for x, y in zip(m.rows(), ref.rows()):
+                assert np.array_equal(x, y)
+            assert m.quality() == ref.quality()
+            m.close()
+        assert not a.live
