@@ -36,12 +36,14 @@ constexpr int kWave = 64;
 constexpr double kK4R3 = 6.928203230275509;  // the double nearest 4 sqrt(3)
 constexpr double kK12R3 = 20.784609690826528;  // the double nearest 12 sqrt(3)
 
-// x / 3, rounded as the division rounds it: the quotient by the rounded third
-// is off by less than a unit in the last place, its residual is exact, and one
-// correction then rounds correctly (Markstein 1990). Where the residual is
+// x / 3, rounded as the division rounds it, for every x: the quotient by the
+// rounded third is off by less than a unit in the last place, its residual is a
+// few such units and so exact (also among subnormal numbers, whose unit is the
+// smallest one), and one correction then rounds correctly (Markstein 1990); x / 3
+// lies at least a sixth of a unit from a rounding boundary. Where the residual is
 // zero or no number (zeros, infinities) the quotient stands. Six instructions
 // where the compiler's division takes eleven and a quarter-rate reciprocal.
-__device__ __forceinline__ double third(double x) {
+__host__ __device__ __forceinline__ double third(double x) {
   const double y = 1.0 / 3.0;
   double q = x * y;
   double r = __builtin_fma(-3.0, q, x);
