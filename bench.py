@@ -87,7 +87,7 @@ def op_count(trace):
 
 def sources_sha():
     """Hash of the device code: the kernel sources and the headers they
-    include (the host-side api.hip launches kernels but defines none)."""
+    include (the host-side api.hip defines none but the read-backs' k_mail)."""
     h = hashlib.sha256()
     for name in ("common.hpp", "kern.hpp", "scan.hpp", "blocks.hpp", "ops.hip", "store.hip"):
         h.update(open(os.path.join(ROOT, "paper_1505_04694_amd", "csrc", name), "rb").read())

@@ -30,7 +30,7 @@ enum Ctr {
   C_JP = 16,        // JP: vertices still waiting after the last iteration (summed)
   C_CWIDE = 17,     // class lists: the call number of the last list with a colour past the narrow table
   C_FAILEP = 18,    // smallest commit epoch whose rows ran out of pool or staging room (INT_MAX: none)
-  // device-driven small rounds (the kernels decide, the host reads back every few rounds)
+  // device-driven small rounds (the kernel decides, the host reads back when it stops)
   C_DROUND = 19,    // the round in progress
   C_DEPOCH = 20,    // the next commit epoch
   C_DEPOCH0 = 21,   // the first epoch of the last round run
@@ -282,12 +282,11 @@ struct OpArgs {
   double L_low2, qmin2;
 };
 
-void set_flags(const int* list, int n, uint8_t* flag, uint8_t val, hipStream_t s);
 // zero (or null): an int set to 0
 void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s);
 // mode: 0 colour (active flags or all live), 1 coarsen, 2 swap, 3 smooth
 // selected vertices in ascending order, their count to ctr[C_LIST_B];
-// flag/pos: V ints, partial: scan scratch
+// flag: V ints, partial: scan scratch
 void select_vertices(const Store& st, int mode, double L_low2, const uint8_t* active, uint8_t* nxt, int* out,
                      int* ctr, int* flag, int* partial, hipStream_t s);
 // (also clears the counts of waiting vertices)

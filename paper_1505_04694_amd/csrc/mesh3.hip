@@ -2151,10 +2151,8 @@ pm_status reserve(pm3_mesh* m, int V, int T) {
   return PM_OK;
 }
 
-// exclusive scan of n ints into out; returns the total
-// the scan's total, with every counter (the host copy is then as current as
-// after read_ctr)
-// a vertex array's and an element array's scans with one read-back
+// a vertex array's and an element array's exclusive scans with one read-back, of
+// their totals and every counter
 pm_status scan_both(pm3_mesh* m, const int* v, int* vout, int V, int* nv, const int* t, int* tout, int T, int* nt) {
   int* ctr = m->ctr;
   auto load = [](const int* a) { return [=] __device__(int i, bool on) { return on ? a[i] : 0; }; };
@@ -2168,6 +2166,7 @@ pm_status scan_both(pm3_mesh* m, const int* v, int* vout, int V, int* nv, const 
   *nt = m->hctr[K_TOTAL2];
   return PM_OK;
 }
+// the exclusive scan of n ints and its total, likewise
 pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
   pm::scan_excl(in, out, n, m->ctr + K_TOTAL, m->partial, m->s);
   T3(read_ctr(m));
@@ -2175,8 +2174,6 @@ pm_status scan_total(pm3_mesh* m, const int* in, int* out, int n, int* total) {
   return PM_OK;
 }
 
-// every row from the live elements; sorted rows, or loose ones inside a
-// coarsening phase
 // Every row from the element list, packed and sorted; the pools keep the
 // headroom times the packed size free above it for the row commits of a
 // coarsening phase (a row that outgrows its slot moves, with twice the room,

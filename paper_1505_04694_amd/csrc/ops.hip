@@ -32,14 +32,7 @@ __global__ void k_clear_round(const int* __restrict__ list, int n, uint64_t* __r
 void clear_round(const int* list, int n, uint64_t* rw, int* zero, hipStream_t s) {
   if (n > 0) k_clear_round<<<grid_for(n), kBlock, 0, s>>>(list, n, rw, zero);
 }
-// ---- flags and lists -----------------------------------------------------------------
-__global__ void k_set_flags(const int* __restrict__ list, int n, uint8_t* __restrict__ flag, uint8_t val) {
-  for (int i = gtid(); i < n; i += gstride()) flag[list[i]] = val;
-}
-void set_flags(const int* list, int n, uint8_t* flag, uint8_t val, hipStream_t s) {
-  if (n > 0) k_set_flags<<<grid_for(n), kBlock, 0, s>>>(list, n, flag, val);
-}
-
+// ---- lists -----------------------------------------------------------------------------
 __device__ bool has_candidate(const Store& st, int v, double L_low2) {
   Hdr h = st.hdr[v];
   double2 pv = st.xy[v];
@@ -407,23 +400,19 @@ __global__ void k_class_count(const int* __restrict__ A, int n, const uint64_t* 
 __device__ int block_rank(int c, bool valid, int* wcnt /* 4 waves x 256 */) {
   int lane = __lane_id(), w = threadIdx.x / kWave;
   uint64_t lt = (1ull << lane) - 1ull;
-  int rank = 0, mine = 0;
+  int rank = 0;
   uint64_t left = __ballot(valid);
   while (left) {
     int lead = __ffsll((unsigned long long)left) - 1;
     int cc = __shfl(c, lead);
     uint64_t mask = __ballot(valid && c == cc);
-    if (valid && c == cc) {
-      rank = __popcll(mask & lt);
-      mine = __popcll(mask);
-    }
+    if (valid && c == cc) rank = __popcll(mask & lt);
     if (lane == lead) wcnt[w * 256 + cc] = __popcll(mask);
     left &= ~mask;
   }
   __syncthreads();
   if (valid)
     for (int k = 0; k < w; ++k) rank += wcnt[k * 256 + c];
-  (void)mine;
   return rank;
 }
 
@@ -483,21 +472,20 @@ void class_lists(const int* A, int n, const uint64_t* rw, int* ctr, int* out, in
   }
 }
 
-// Small lists: one block runs the whole colouring (JP iterations separated
-// by block barriers until no vertex waits) and cuts the class lists, in one
-// launch. Classes come out in no particular order; the members of a class
-// are an independent set, so their order does not change any result.
-constexpr int kSmallThreads = 1024;
-// A list of at most kSmallColour vertices is coloured by one block in LDS. Its
-// round words carry each vertex's place in the list (bits 9 ..), one scan of a
-// vertex's row then gives its record: the colours of the neighbours before it
-// that are coloured already, and the places of up to eight that are not. From
-// there on a vertex only follows its predecessors' colours, bytes in LDS.
+// A list of at most kSmallColour vertices is coloured and cut into classes by one
+// block. Classes come out in no particular order; the members of a class are an
+// independent set, so their order does not change any result.
+// The colours lie in LDS. The round words carry each vertex's place in the list
+// (bits 9 ..), one scan of a vertex's row then gives its record: the colours of the
+// neighbours before it that are coloured already, and the places of up to eight
+// that are not. From there on a vertex only follows its predecessors' colours,
+// bytes in LDS, without barriers.
 // Scanning rows is eleven line look-ups a vertex, which one CU does at about
 // one a clock: re-scanning every waiting row per iteration took 31 us for 1,500
-// vertices, this 22 (19 scanned by many blocks). Lists of more than kOneBlock are scanned by as many blocks as they
-// fill (k_jp_pred, into JpRec records), so that only the solving is one
-// block's.
+// vertices, this 22 (19 scanned by many blocks). Lists of more than kOneBlock are
+// scanned by as many blocks as they fill (k_jp_pred, into JpRec records), so that
+// only the solving is one block's.
+constexpr int kSmallThreads = 1024;
 constexpr int kPlaceBit = 9;
 static_assert(kSmallColour <= 1 << 16, "places are 16-bit");
 struct Preds {
