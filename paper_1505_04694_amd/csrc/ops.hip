@@ -1332,7 +1332,10 @@ __device__ __forceinline__ void rebuild_group(const Store& st, const Commit& cm,
     same += o == nx ? 1 : 0;
     found |= o == pv;
   });
-  // a next vertex that comes twice (a wavefront's lanes also meet themselves)
+  // a next vertex that comes twice (a wavefront's lanes also meet themselves): two
+  // lanes with one place. Counted in the loop, 1 us of the 234 of a vertex-order
+  // launch at 2049 x 2049; as the missing rest of the places' sum it cost fewer
+  // registers, but the loads came apart and the launch took 283.
   bool twice = gballot(own && same > (G == 64 ? 1 : 0)) != 0;
   uint64_t lone = gballot(own && !found);
   int nextra = __popcll(lone);
