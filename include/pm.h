@@ -320,7 +320,8 @@ pm_status pm_quality(pm_mesh* m, double* Q, double* qmin, double* dQdx, double* 
  * device current (else PM_E_ARG). Calls that overlap on one device, from any
  * handles or streams, race on that array; serialise them. Outputs as
  * pm_quality: Q and qmin host pointers, dQdx and dQdM device pointers, any
- * may be NULL. */
+ * may be NULL. Gradients need the adjacency rows: PM_E_NOMEM when their last
+ * build found no memory (any phase call, and pm_quality, builds them first). */
 pm_status pm_quality_noalloc(pm_mesh* m, double* Q, double* qmin, double* dQdx, double* dQdM);
 
 /* Diagnostic: computes quot[i] = a[i] / b[i] and root[i] = sqrt(a[i]) in FP64
